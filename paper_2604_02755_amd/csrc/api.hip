@@ -258,6 +258,127 @@ static void build_mesh(Ctx* ctx, const nlth_mesh_desc* d, Mesh& M)
     build_mesh_internal(ctx, &dn, M);
 }
 
+// Element clusters: runs of consecutive storage elements, closed when the next
+// element would bring more than max_elems elements or max_nodes (at most 255)
+// distinct nodes; local node lists in first-use order.
+struct ClusterLists {
+    std::vector<int> off, noff, node;  // elements and rows of each cluster; the node of a row
+    std::vector<uint32_t> lconn;       // local nodes of each element, four 8-bit indices per word
+    std::vector<int4> head;            // per cluster: first element, first row, elements, rows
+    std::vector<int> nodes;            // per cluster, node_stride apart: the nodes of its rows
+    std::vector<uint16_t> lists, lptr; // incidences of each row in groups of four; first group of each row
+    int max_elems = 0, max_nodes = 0, node_stride = 0, list_stride = 0;
+    std::vector<int> cn_ptr, cn_row;   // node -> rows, ascending; a boundary node's dashpot row last
+};
+
+static void build_clusters(const nlth_mesh_desc* d, const Mesh& M, int max_elems, int max_nodes, ClusterLists& L)
+{
+    const int nn = d->n_nodes, ne = d->n_tets;
+    L.off.assign(1, 0);
+    L.noff.assign(1, 0);
+    L.lconn.assign(4L * ne, 0u);
+    std::vector<int> loc(nn, -1), cur;  // cur: the open cluster's nodes
+    int start = 0;
+    auto close = [&](int end) {
+        for (int g : cur) loc[g] = -1;
+        L.node.insert(L.node.end(), cur.begin(), cur.end());
+        L.noff.push_back((int)L.node.size());
+        L.off.push_back(end);
+        cur.clear();
+        start = end;
+    };
+    for (int pos = 0; pos < ne; ++pos) {
+        const int* t = d->tet10 + 10L * M.order[pos];
+        int add = 0;
+        for (int a = 0; a < 10; ++a) {
+            bool seen = loc[t[a]] >= 0;
+            for (int b = 0; b < a && !seen; ++b) seen = t[b] == t[a];
+            add += !seen;
+        }
+        if (pos > start && (pos - start >= max_elems || (int)cur.size() + add > max_nodes)) close(pos);
+        for (int a = 0; a < 10; ++a) {
+            if (loc[t[a]] < 0) {
+                loc[t[a]] = (int)cur.size();
+                cur.push_back(t[a]);
+            }
+            L.lconn[4L * pos + a / 4] |= (uint32_t)loc[t[a]] << (8 * (a % 4));
+        }
+    }
+    close(ne);
+    const int ncl = (int)L.off.size() - 1;
+    // tables at fixed strides; incidences of each row by element, in groups of
+    // four padded with the entry of a row of zeros (local node 10)
+    constexpr uint16_t kZeroRow = 10 * 64;
+    L.head.resize(ncl);
+    std::vector<uint16_t> cnt(256);
+    for (int pass = 0; pass < 2; ++pass) {  // sizes, then the tables
+        if (pass == 1) {
+            L.node_stride = (L.max_nodes + 1 + 15) / 16 * 16;
+            L.nodes.assign((size_t)ncl * L.node_stride, 0);
+            L.lptr.assign((size_t)ncl * L.node_stride, 0);
+            L.lists.assign((size_t)ncl * L.list_stride * 4, kZeroRow);
+        }
+        for (int c = 0; c < ncl; ++c) {
+            const int e0 = L.off[c], nec = L.off[c + 1] - e0, r0 = L.noff[c], ncn = L.noff[c + 1] - r0;
+            auto local = [&](int el, int a) { return (L.lconn[4L * (e0 + el) + a / 4] >> (8 * (a % 4))) & 0xFFu; };
+            std::fill(cnt.begin(), cnt.end(), 0);
+            for (int el = 0; el < nec; ++el)
+                for (int a = 0; a < 10; ++a) cnt[local(el, a)]++;
+            if (pass == 0) {
+                int ng = 0;
+                for (int k = 0; k < ncn; ++k) ng += (cnt[k] + 3) / 4;
+                L.list_stride = std::max(L.list_stride, (ng + 1) / 2 * 2);
+                L.max_elems = std::max(L.max_elems, nec);
+                L.max_nodes = std::max(L.max_nodes, ncn);
+                continue;
+            }
+            L.head[c] = int4{e0, r0, nec, ncn};
+            uint16_t* lp = &L.lptr[(size_t)c * L.node_stride];
+            for (int k = 0; k < ncn; ++k) {
+                L.nodes[(size_t)c * L.node_stride + k] = L.node[r0 + k];
+                lp[k + 1] = (uint16_t)(lp[k] + (cnt[k] + 3) / 4);
+                cnt[k] = (uint16_t)(lp[k] * 4);  // next entry of the row
+            }
+            uint16_t* ls = &L.lists[(size_t)c * L.list_stride * 4];
+            for (int el = 0; el < nec; ++el)
+                for (int a = 0; a < 10; ++a) ls[cnt[local(el, a)]++] = (uint16_t)(a * 64 + el);
+        }
+    }
+    // node -> rows, ascending (the dashpot rows are appended once the boundary is known)
+    L.cn_ptr.assign(nn + 1, 0);
+    for (int g : L.node) L.cn_ptr[g + 1]++;
+}
+
+// node -> rows of the clusters, then the node's dashpot row (rows + its place
+// in the ascending list of boundary nodes)
+static void finish_clusters(int nn, const std::vector<int>& bn_node, ClusterLists& L)
+{
+    const int rows = (int)L.node.size();
+    for (int g : bn_node) L.cn_ptr[g + 1]++;
+    for (int i = 0; i < nn; ++i) L.cn_ptr[i + 1] += L.cn_ptr[i];
+    L.cn_row.resize(L.cn_ptr[nn]);
+    std::vector<int> fill(L.cn_ptr.begin(), L.cn_ptr.end() - 1);
+    for (int r = 0; r < rows; ++r) L.cn_row[fill[L.node[r]]++] = r;
+    for (size_t i = 0; i < bn_node.size(); ++i) L.cn_row[fill[bn_node[i]]++] = rows + (int)i;
+}
+
+static void upload_clusters(Budget* b, const ClusterLists& L, Mesh::Clusters& C)
+{
+    upload(b, C.off, L.off);
+    upload(b, C.noff, L.noff);
+    upload(b, C.lconn, L.lconn);
+    upload(b, C.nodes, L.nodes);
+    upload(b, C.head, L.head);
+    upload(b, C.lists, L.lists);
+    upload(b, C.lptr, L.lptr);
+    C.max_elems = L.max_elems;
+    C.max_nodes = L.max_nodes;
+    C.node_stride = L.node_stride;
+    C.list_stride = L.list_stride;
+    upload(b, C.cn_ptr, L.cn_ptr);
+    upload(b, C.cn_row, L.cn_row);
+}
+
 static void build_mesh_internal(Ctx* ctx, const nlth_mesh_desc* d, Mesh& M)
 {
     const int nn = d->n_nodes, ne = d->n_tets;
@@ -366,64 +487,14 @@ static void build_mesh_internal(Ctx* ctx, const nlth_mesh_desc* d, Mesh& M)
         std::vector<int> fill(M.color_off.begin(), M.color_off.end() - 1);
         for (int pos = 0; pos < ne; ++pos) M.color_elems[fill[color[pos]]++] = pos;
     }
-    // node -> (element, local node) incidences in storage order, for the
-    // deterministic gather of element outputs
-    std::vector<int> inc_ptr(nn + 1, 0), inc(10L * ne);
-    for (int pos = 0; pos < ne; ++pos)
-        for (int a = 0; a < 10; ++a) inc_ptr[d->tet10[10L * M.order[pos] + a] + 1]++;
-    for (int i = 0; i < nn; ++i) inc_ptr[i + 1] += inc_ptr[i];
-    {
-        std::vector<int> fill(inc_ptr.begin(), inc_ptr.end() - 1);
-        for (int pos = 0; pos < ne; ++pos)
-            for (int a = 0; a < 10; ++a) inc[fill[d->tet10[10L * M.order[pos] + a]]++] = pos * 10 + a;
-    }
     if (10L * ne > INT32_MAX) throw Error{NLTH_EINVAL, "mesh: more than 214,748,364 tets"};
-    // element clusters: runs of consecutive storage elements, closed when the
-    // next element would bring more than kClusterElems elements or
-    // kClusterNodes distinct nodes; local node lists in first-use order
-    std::vector<int> cl_off(1, 0), cl_noff(1, 0), cl_node;
-    std::vector<uint32_t> cl_lconn(4L * ne, 0u);
-    {
-        std::vector<int> loc(nn, -1);
-        std::vector<int> cur;  // the open cluster's nodes
-        int start = 0;
-        auto close = [&](int end) {
-            for (int g : cur) loc[g] = -1;
-            cl_node.insert(cl_node.end(), cur.begin(), cur.end());
-            cl_noff.push_back((int)cl_node.size());
-            cl_off.push_back(end);
-            cur.clear();
-            start = end;
-        };
-        for (int pos = 0; pos < ne; ++pos) {
-            const int* t = d->tet10 + 10L * M.order[pos];
-            int add = 0;
-            for (int a = 0; a < 10; ++a) {
-                bool seen = loc[t[a]] >= 0;
-                for (int b = 0; b < a && !seen; ++b) seen = t[b] == t[a];
-                add += !seen;
-            }
-            if (pos > start && (pos - start >= kClusterElems || (int)cur.size() + add > kClusterNodes)) close(pos);
-            for (int a = 0; a < 10; ++a) {
-                if (loc[t[a]] < 0) {
-                    loc[t[a]] = (int)cur.size();
-                    cur.push_back(t[a]);
-                }
-                cl_lconn[4L * pos + a / 4] |= (uint32_t)loc[t[a]] << (8 * (a % 4));
-            }
-        }
-        close(ne);
-    }
-    M.ncl = (int)cl_off.size() - 1;
-    // node -> cluster rows, ascending
-    std::vector<int> cn_ptr(nn + 1, 0), cn_row(cl_node.size());
-    for (int g : cl_node) cn_ptr[g + 1]++;
-    for (int i = 0; i < nn; ++i) cn_ptr[i + 1] += cn_ptr[i];
-    {
-        std::vector<int> fill(cn_ptr.begin(), cn_ptr.end() - 1);
-        for (int r = 0; r < (int)cl_node.size(); ++r) cn_row[fill[cl_node[r]]++] = r;
-    }
-    M.cl_rows = (long)cl_node.size();
+    ClusterLists cl, wide;
+    build_clusters(d, M, kClusterElems, kClusterNodes, cl);
+    build_clusters(d, M, kWideElems, kWideNodes, wide);
+    M.cl.n = (int)cl.off.size() - 1;
+    M.cl.rows = (long)cl.node.size();
+    M.wide.n = (int)wide.off.size() - 1;
+    M.wide.rows = (long)wide.node.size();
     // sorted SoA arrays
     std::vector<int> conn(10L * ne), lay(ne);
     std::vector<double> g64(13L * ne);
@@ -540,20 +611,29 @@ static void build_mesh_internal(Ctx* ctx, const nlth_mesh_desc* d, Mesh& M)
     upload(b, M.f_layer, flayer);
     upload(b, M.f_kind, fkind);
     upload(b, M.recv_d, M.recv);
-    upload(b, M.inc_ptr, inc_ptr);
-    upload(b, M.inc, inc);
     upload(b, M.celem, M.color_elems);
     upload(b, M.bn_of, bn_of_node);
-    upload(b, M.cl_off_d, cl_off);
-    upload(b, M.cl_noff_d, cl_noff);
-    upload(b, M.cl_lconn_d, cl_lconn);
-    upload(b, M.cn_ptr_d, cn_ptr);
-    upload(b, M.cn_row_d, cn_row);
+    finish_clusters(nn, bn_node, cl);
+    finish_clusters(nn, bn_node, wide);
+    upload_clusters(b, cl, M.cl);
+    upload_clusters(b, wide, M.wide);
     upload(b, M.order_d, M.order);
-    upload(b, M.node_new_d, M.node_new);
+    std::vector<int> node_in(nn), list;
+    for (int i = 0; i < nn; ++i) node_in[M.node_new[i]] = i;
+    upload(b, M.node_in, node_in);
+    auto upload_in = [&](DevBuf& dst, const std::vector<int>& src) {
+        list.resize(src.size());
+        for (size_t i = 0; i < src.size(); ++i) list[i] = node_in[src[i]];
+        upload(b, dst, list);
+    };
+    upload_in(M.wide_node_in, wide.nodes);
+    upload_in(M.f_node_in, fnode);
+    upload_in(M.bn_node_in, bn_node);
 }
 
-DevMesh Mesh::dev() const
+const Mesh::Clusters& Mesh::clusters(int MB) const { return MB <= kWideSlots ? wide : cl; }
+
+DevMesh Mesh::dev(int MB) const
 {
     DevMesh d{};
     d.ne = ne;
@@ -572,16 +652,33 @@ DevMesh Mesh::dev() const
     d.f_n = f_n.as<double>();
     d.f_layer = f_layer.as<int>();
     d.f_kind = f_kind.as<uint8_t>();
-    d.inc_ptr = inc_ptr.as<int>();
-    d.inc = inc.as<int>();
     d.celem = celem.as<int>();
     d.bn_of_node = bn_of.as<int>();
-    d.ncl = ncl;
-    d.cl_off = cl_off_d.as<int>();
-    d.cl_noff = cl_noff_d.as<int>();
-    d.cl_lconn = cl_lconn_d.as<uint32_t>();
-    d.cn_ptr = cn_ptr_d.as<int>();
-    d.cn_row = cn_row_d.as<int>();
+    const Clusters& c = clusters(MB);
+    d.ncl = c.n;
+    d.cl_off = c.off.as<int>();
+    d.cl_noff = c.noff.as<int>();
+    d.cl_lconn = c.lconn.as<uint32_t>();
+    d.cl_rows = c.rows;
+    d.cl_max_elems = c.max_elems;
+    d.cl_max_nodes = c.max_nodes;
+    d.cl_node_stride = c.node_stride;
+    d.cl_list_stride = c.list_stride;
+    d.cl_nodes = c.nodes.as<int>();
+    d.cl_head = c.head.as<int4>();
+    d.cl_lists = c.lists.as<uint2>();
+    d.cl_lptr = c.lptr.as<uint16_t>();
+    d.cn_ptr = c.cn_ptr.as<int>();
+    d.cn_row = c.cn_row.as<int>();
+    return d;
+}
+
+DevMesh Mesh::dev_input() const
+{
+    DevMesh d = dev(1);
+    d.cl_nodes = wide_node_in.as<int>();
+    d.f_node = f_node_in.as<int>();
+    d.bn_node = bn_node_in.as<int>();
     return d;
 }
 
@@ -693,8 +790,7 @@ int64_t ensemble_bytes(const Mesh& m, const Problem& p, int MB, bool paged)
         bytes += (int64_t)m.ne * 4 *
                  (p.inner_dtype == NLTH_INNER_FP32 ? 84 : (p.inner_dtype == NLTH_INNER_BF16_MEAN ? 11 : 44)) * MB;
     bytes += (int64_t)m.ne * MB * 8;                        // h
-    if (MB >= 64 && MB <= 256) bytes += (int64_t)m.cl_rows * 3 * MB * 8;  // cluster rows
-    else if (MB < 64) bytes += (int64_t)m.ne * 30 * MB * 8;             // element outputs
+    if (MB <= 256) bytes += (m.clusters(MB).rows + m.nbn) * 3 * MB * 8;  // cluster and dashpot rows
     bytes += (int64_t)p.n_steps * std::max(1, m.nrecv) * 3 * MB * 8;  // receiver history
     bytes += (int64_t)p.n_steps * 3 * MB * 8 * 2;           // acc, vI
     if (!paged) bytes += (int64_t)m.ne * 4 * p.ns * MB * theta_bytes(p.depth);
@@ -769,6 +865,7 @@ void Ens::create(Ctx* c, const Mesh* m, const Problem& prob, int member_pad)
     sc.h0 = P.h0;
     if (P.damping_mode == NLTH_DAMPING_NONE) sc.ahat = sc.bhat = 0.0;
     else rayleigh_fit(P.f_lo, P.f_hi, &sc.ahat, &sc.bhat);
+    sc.quotients();
 
     // per-member material table (padded members copy member 0)
     std::vector<double> mt((size_t)P.nl * MAT_N * MB, 0.0);
@@ -834,19 +931,12 @@ void Ens::create(Ctx* c, const Mesh* m, const Problem& prob, int member_pad)
     d16_mean = P.inner_dtype == NLTH_INNER_BF16_MEAN;
     tail_max = MB >= 64 && MB <= 256 && (P.precision == NLTH_FP64 || d16_mean) ? 32 : 0;
     h.alloc(bg, (size_t)m->ne * MB * 8);
-    // operator path: element clusters (64-member groups) when MB is a multiple
-    // of 64, element outputs below that, colours above 256 member slots (the
+    // operator path: clusters in 64-member groups when MB is a multiple of 64,
+    // the few-slot kernels below that, colours above 256 member slots (the
     // node gather covers at most 256 slots per block)
-    if (MB > 256) {
-        scatter = 1;
-    } else if (MB >= 64) {
-        scatter = 2;
-        cbuf.alloc(bg, (size_t)m->cl_rows * 3 * MB * 8);
-    } else {
-        scatter = 0;
-        fbuf.alloc(bg, (size_t)ne_pad * 30 * MB * 8);
-    }
-    const DevMesh dm = m->dev();
+    scatter = MB > 256 ? 1 : (MB >= 64 ? 2 : 0);
+    if (MB <= 256) cbuf.alloc(bg, (size_t)(m->clusters(MB).rows + m->nbn) * 3 * MB * 8);
+    const DevMesh dm = m->dev(MB);
     launch_law_init(s, dm, MB, MB, mat.as<double>(), P.nl, P.ns, dirs.as<double>(), w.as<double>(),
                     D64.as<double>(), D32.as<float>(), D16.as<uint32_t>(), h.as<double>(), -1, d16_mean);
 
@@ -909,7 +999,10 @@ void Ens::create(Ctx* c, const Mesh* m, const Problem& prob, int member_pad)
     launch_fill(s, vmax.as<double>(), 0.0, (long)MB * std::max(1, m->nrecv));
     iters_dev.alloc(bg, (size_t)MB * ns_steps * 2 * 4);
     NLTH_HIP(hipMemsetAsync(iters_dev.p, 0, iters_dev.bytes, s));
-    partial.alloc(bg, (size_t)kPartialRows * MB * 8);
+    // with the few-slot operator a row per cluster and boundary block
+    const size_t op_rows = MB < 64 ? (size_t)m->clusters(MB).n + 8 + kDashpotBlocks : 0;
+    partial.alloc(bg, (std::max<size_t>(kPartialRows, op_rows) + 3 * kFoldBlocks) * MB * 8);
+    fold = partial.as<double>() + std::max<size_t>(kPartialRows, op_rows) * MB;
     // CG scalars: 12 double arrays and 9 int arrays of MB
     scal.alloc(bg, (size_t)MB * (12 * 8 + 9 * 4) + 64);
     NLTH_HIP(hipMemsetAsync(scal.p, 0, scal.bytes, s));
@@ -980,30 +1073,32 @@ void Ens::destroy()
 // y = operator of `mode` applied to x1 (and x2 for the right-hand side)
 //     + bscale * base + the boundary dashpot dcoef * C_abs x1 (+ 2 C_base vI),
 // and with nblk the per-member block partials of x1 . y in `partial`.
-// Gather path: one launch writes every element's nodal forces, a second sums
-// them per node with the base, the dashpot and the dot fused in.  Colour
-// path: one launch per colour adds the forces into y, then the dashpot and
-// the dot as launches of their own.
+// Gather paths: a launch writes cluster rows (the few-slot kernels the
+// dashpot rows and the dot as well), a second sums them per node with the
+// base.  Colour path: one launch per colour adds the forces into y, then the
+// dashpot and the dot as launches of their own.
 void Ens::ebe(OpMode mode, const double* x1, const double* x2, double* y, const int* act, const double* base,
               double bscale, double dcoef, const double* vI, int* nblk)
 {
-    const DevMesh dm = mesh->dev();
+    const DevMesh dm = mesh->dev(MB);
     set_ebe_block(ebe_block);
     set_cluster_blocks(cluster_blocks);
     if (scatter != 1) {
         hipEvent_t t0;
         tstart(t0);
         double* pd = nblk ? partial.as<double>() : nullptr;
+        double* rows = cbuf.as<double>();
         if (scatter == 2) {
             launch_ebe_cluster64(s, mode, dm, MB, nm, D64.as<double>(), h.as<double>(), mat.as<double>(), sc, x1, x2,
-                                 cbuf.as<double>(), act);
-            launch_gather<double>(s, dm, MB, nm, cbuf.as<double>(), base, bscale, y, act, x1, pd, nblk, true);
+                                 rows, act);
+            launch_gather<double>(s, dm, MB, nm, rows, false, base, bscale, y, act, x1, pd, nblk);
+            if (dcoef != 0.0)
+                launch_dashpot<double>(s, dm, MB, nm, mat.as<double>(), P.nl, dcoef, x1, y, vI, act, pd, nblk);
         } else {
-            launch_ebe<double>(s, mode, dm, MB, nm, 0, mesh->ne, D64.as<double>(), h.as<double>(), mat.as<double>(),
-                               P.nl, sc, x1, x2, fbuf.as<double>(), act, true);
-            launch_gather<double>(s, dm, MB, nm, fbuf.as<double>(), base, bscale, y, act, x1, pd, nblk, false);
+            launch_op_slots64(s, mode, dm, MB, nm, D64.as<double>(), h.as<double>(), mat.as<double>(), sc, x1, x2,
+                              rows, act, dcoef, vI, pd, nblk);
+            launch_gather<double>(s, dm, MB, nm, rows, dcoef != 0.0, base, bscale, y, act, nullptr, nullptr, nullptr);
         }
-        if (dcoef != 0.0) launch_dashpot<double>(s, dm, MB, nm, mat.as<double>(), P.nl, dcoef, x1, y, vI, act, pd, nblk);
         tstop(t0, &pc_ebe64, (int64_t)mesh->ne * nm);
         return;
     }
@@ -1015,7 +1110,7 @@ void Ens::ebe(OpMode mode, const double* x1, const double* x2, double* y, const 
         hipEvent_t t0;
         tstart(t0);
         launch_ebe<double>(s, mode, dm, MB, nm, e0, e1, D64.as<double>(), h.as<double>(), mat.as<double>(), P.nl, sc,
-                           x1, x2, y, act, false);
+                           x1, x2, y, act);
         tstop(t0, &pc_ebe64, (int64_t)(e1 - e0) * nm);
     }
     if (dcoef != 0.0) launch_dashpot<double>(s, dm, MB, nm, mat.as<double>(), P.nl, dcoef, x1, y, vI, act);
@@ -1026,27 +1121,30 @@ void Ens::ebe(OpMode mode, const double* x1, const double* x2, double* y, const 
 // dashpot included; with nblk the per-member block partials of x . y
 void Ens::ebe32(const float* x, float* y, const int* act, int* nblk)
 {
-    const DevMesh dm = mesh->dev();
+    const DevMesh dm = mesh->dev(MB);
     set_ebe_block(ebe_block);
     set_cluster_blocks(cluster_blocks);
     const double dc = 2.0 / P.dt;
     if (scatter != 1) {
-        const bool cl = scatter == 2;
-        float* f = cl ? (float*)cbuf.p : (float*)fbuf.p;
+        float* rows = (float*)cbuf.p;
+        double* pd = nblk ? partial.as<double>() : nullptr;
         hipEvent_t t0;
         tstart(t0);
-        if (cl)
+        if (scatter == 2)
             launch_ebe_cluster32(s, dm, MB, nm, D32.as<float>(), D16.as<uint32_t>(), h.as<double>(), mat.as<double>(),
-                                 sc, x, f, act, d16_mean);
+                                 sc, x, rows, act, d16_mean);
         else
-            launch_ebe32(s, dm, MB, nm, 0, mesh->ne, D32.as<float>(), D16.as<uint32_t>(), h.as<double>(),
-                         mat.as<double>(), sc, x, f, act, true, d16_mean);
+            launch_op_slots32(s, dm, MB, nm, D32.as<float>(), D16.as<uint32_t>(), d16_mean, h.as<double>(),
+                              mat.as<double>(), sc, x, rows, act, dc, pd, nblk);
         tstop(t0, &pc_ebe32, (int64_t)mesh->ne * nm);
         tstart(t0);
-        double* pd = nblk ? partial.as<double>() : nullptr;
-        launch_gather<float>(s, dm, MB, nm, f, nullptr, 0.0f, y, act, x, pd, nblk, cl);
+        if (scatter == 2)
+            launch_gather<float>(s, dm, MB, nm, rows, false, nullptr, 0.0f, y, act, x, pd, nblk);
+        else
+            launch_gather<float>(s, dm, MB, nm, rows, true, nullptr, 0.0f, y, act, nullptr, nullptr, nullptr);
         tstop(t0, &pc_gather32, (int64_t)mesh->nn * nm);
-        launch_dashpot<float>(s, dm, MB, nm, mat.as<double>(), P.nl, (float)dc, x, y, nullptr, act, pd, nblk);
+        if (scatter == 2)
+            launch_dashpot<float>(s, dm, MB, nm, mat.as<double>(), P.nl, (float)dc, x, y, nullptr, act, pd, nblk);
         return;
     }
     launch_fill32(s, y, 0.0f, (long)ndof * MB);
@@ -1055,7 +1153,7 @@ void Ens::ebe32(const float* x, float* y, const int* act, int* nblk)
         hipEvent_t t0;
         tstart(t0);
         launch_ebe32(s, dm, MB, nm, e0, e1, D32.as<float>(), D16.as<uint32_t>(), h.as<double>(), mat.as<double>(),
-                     sc, x, y, act, false, d16_mean);
+                     sc, x, y, act, d16_mean);
         tstop(t0, &pc_ebe32, (int64_t)(e1 - e0) * nm);
     }
     launch_dashpot<float>(s, dm, MB, nm, mat.as<double>(), P.nl, (float)dc, x, y, nullptr, act);
@@ -1077,7 +1175,7 @@ void Ens::build_rhs()
 // FP64 iteration of the mixed path does not use the diagonal.
 void Ens::build_diag()
 {
-    const DevMesh dm = mesh->dev();
+    const DevMesh dm = mesh->dev(MB);
     const bool mean = P.precision == NLTH_MIXED && d16_mean;
     launch_fill(s, diag.as<double>(), 0.0, (long)mesh->nn * 6 * MB);
     for (int c = 0; c < mesh->ncolor; ++c) {
@@ -1119,7 +1217,7 @@ int Ens::read_any_active(const int* flags)
 
 void Ens::fin(FinalizeStage st, int nd, int nblk, double tol2, int maxit)
 {
-    launch_finalize(s, st, nd, MB, nm, partial.as<double>(), nblk, cs, tol2, maxit);
+    launch_finalize(s, st, nd, MB, nm, partial.as<double>(), nblk, fold, cs, tol2, maxit);
 }
 
 void Ens::apply_A64(const double* x, double* y, const int* act, int* nblk)
@@ -1174,7 +1272,7 @@ bool Ens::enter_tail64()
     launch_copy_i32(s, d_mail + 4 * MB, tlist.as<int>(), 1 + na);
     tail64_g = na <= 16 ? 16 : 32;
     const int* tl = tlist.as<int>();
-    launch_tail_pack64(s, mesh->dev(), MB, tail64_g, P.nl, tl, D64.as<double>(), h.as<double>(), mat.as<double>(),
+    launch_tail_pack64(s, mesh->dev(MB), MB, tail64_g, P.nl, tl, D64.as<double>(), h.as<double>(), mat.as<double>(),
                        pinv.as<double>(), tc.D, tc.h, tc.mat, tc.pinv);
     launch_tail_rows64(s, ndof, MB, tail64_g, tl, du.as<double>(), tc.x, false);
     launch_tail_rows64(s, ndof, MB, tail64_g, tl, r.as<double>(), tc.r, false);
@@ -1224,7 +1322,7 @@ bool Ens::enter_outer_tail()
         return false;
     }
     const int* tl = tlist.as<int>();
-    launch_tail_pack64(s, mesh->dev(), MB, tail_g, P.nl, tl, D64.as<double>(), h.as<double>(), mat.as<double>(),
+    launch_tail_pack64(s, mesh->dev(MB), MB, tail_g, P.nl, tl, D64.as<double>(), h.as<double>(), mat.as<double>(),
                        pinv.as<double>(), tc.D, tc.h, tc.mat, tc.pinv);
     launch_tail_rows64(s, ndof, MB, tail_g, tl, du.as<double>(), tc.x, false);
     launch_tail_rows64(s, ndof, MB, tail_g, tl, r.as<double>(), tc.r, false);
@@ -1244,7 +1342,7 @@ void Ens::leave_tail64()
 // stage logic of the full path
 void Ens::tail64_iter()
 {
-    const DevMesh dm = mesh->dev();
+    const DevMesh dm = mesh->dev(MB);
     const int* tl = tlist.as<int>();
     const int* act = cs.active;
     const double tol2 = P.cg_tol * P.cg_tol;
@@ -1253,7 +1351,7 @@ void Ens::tail64_iter()
     hipEvent_t t0;
     tstart(t0);
     launch_ebe64_ctail(s, dm, tail64_g, tl, tc.D, tc.h, tc.mat, sc, tc.p, tc.f);
-    launch_gather_tail<double>(s, dm, MB, nm, tail64_g, tl, tc.f, tc.Ap, act, tc.p, pd, &nblk, true);
+    launch_gather_tail<double>(s, dm, MB, nm, tail64_g, tl, tc.f, tc.Ap, act, tc.p, pd, &nblk);
     launch_dashpot_tail<double>(s, dm, MB, nm, tail64_g, tl, tc.mat, 2.0 / P.dt, tc.p, tc.Ap, act, pd, &nblk);
     tstop(t0, &pc_tail32, (int64_t)mesh->ne * tail_count);
     fin(FIN_ALPHA, 1, nblk, tol2, P.cg_maxit);
@@ -1344,7 +1442,7 @@ void Ens::update_tail()
     // the previous list copy has completed: the caller synchronised to read h_flags
     launch_copy_i32(s, d_mail + 4 * MB, tlist.as<int>(), 1 + na);
     tail_g = na <= 16 ? 16 : 32;
-    launch_tail_pack(s, mesh->dev(), MB, tail_g, P.nl, tlist.as<int>(), D16.as<uint32_t>(), h.as<double>(),
+    launch_tail_pack(s, mesh->dev(MB), MB, tail_g, P.nl, tlist.as<int>(), D16.as<uint32_t>(), h.as<double>(),
                      mat.as<double>(), pinv32.as<float>(), tb.D, tb.h, tb.mat, tb.pinv);
 }
 
@@ -1353,7 +1451,7 @@ void Ens::update_tail()
 // full path with the same per-member stage logic
 void Ens::tail_iter()
 {
-    const DevMesh dm = mesh->dev();
+    const DevMesh dm = mesh->dev(MB);
     const int* tl = tlist.as<int>();
     const int* iact = cs.inner_active;
     const double tol2 = P.inner_tol * P.inner_tol;
@@ -1362,7 +1460,7 @@ void Ens::tail_iter()
     hipEvent_t t0;
     tstart(t0);
     launch_ebe32_ctail(s, dm, tail_g, tl, tb.D, tb.h, tb.mat, sc, tb.ip, tb.f);
-    launch_gather_tail(s, dm, MB, nm, tail_g, tl, tb.f, tb.Ap, iact, tb.ip, pd, &nblk, true);
+    launch_gather_tail(s, dm, MB, nm, tail_g, tl, tb.f, tb.Ap, iact, tb.ip, pd, &nblk);
     launch_dashpot_tail(s, dm, MB, nm, tail_g, tl, tb.mat, (float)(2.0 / P.dt), tb.ip, tb.Ap, iact, pd, &nblk);
     tstop(t0, &pc_tail32, (int64_t)mesh->ne * tail_count);
     fin(FIN_IN_ALPHA, 1, nblk, tol2, P.inner_maxit);
@@ -1378,7 +1476,7 @@ void Ens::cheb_body()
 {
     const int n = std::min(P.inner_maxit, kChebMax);
     const int* act = cs.active;
-    const DevMesh dm = mesh->dev();
+    const DevMesh dm = mesh->dev(MB);
     const float* cheb = chebc.as<float>();
     const float* pv = pinv32.as<float>();
     launch_cheb_start(s, mesh->nn, MB, nm, r.as<double>(), pv, cheb, ir.as<float>(), iz.as<float>(), ip.as<float>(),
@@ -1407,7 +1505,7 @@ void Ens::cheb_body()
         }
         std::swap(d, dn);
     }
-    launch_finalize(s, FIN_CHEB_COUNT, 0, MB, nm, partial.as<double>(), 0, cs, 0.0, n);
+    launch_finalize(s, FIN_CHEB_COUNT, 0, MB, nm, partial.as<double>(), 0, fold, cs, 0.0, n);
 }
 
 // Largest eigenvalue of the block-Jacobi preconditioned inner operator, from
@@ -1588,14 +1686,14 @@ void Ens::solve_fcg()
     fin(FIN_FCG_RZ, 2, nblk, tol2, P.cg_maxit);
     launch_p_update<double>(s, n, MB, nm, z.as<double>(), p.as<double>(), nullptr, act, nullptr);
     outer_compact = false;
-    const DevMesh dm = mesh->dev();
+    const DevMesh dm = mesh->dev(MB);
     for (;;) {
         if (outer_compact) {
             const int* tl = tlist.as<int>();
             hipEvent_t t0;
             tstart(t0);
             launch_ebe64_ctail(s, dm, tail_g, tl, tc.D, tc.h, tc.mat, sc, tc.p, tc.f);
-            launch_gather_tail<double>(s, dm, MB, nm, tail_g, tl, tc.f, tc.Ap, act, tc.p, pd, &nblk, true);
+            launch_gather_tail<double>(s, dm, MB, nm, tail_g, tl, tc.f, tc.Ap, act, tc.p, pd, &nblk);
             launch_dashpot_tail<double>(s, dm, MB, nm, tail_g, tl, tc.mat, 2.0 / P.dt, tc.p, tc.Ap, act, pd, &nblk);
             tstop(t0, &pc_ebe64, (int64_t)mesh->ne * tail_count);  // an FP64 operator application
             fin(FIN_ALPHA, 1, nblk, tol2, P.cg_maxit);
@@ -1635,7 +1733,7 @@ void Ens::solve_fcg()
 
 void Ens::law_phase()
 {
-    const DevMesh dm = mesh->dev();
+    const DevMesh dm = mesh->dev(MB);
     const size_t per_elem = (size_t)4 * P.ns * MB * theta_bytes(P.depth);
     if (!paged) {
         hipEvent_t t0;
@@ -1735,7 +1833,7 @@ void Ens::read_status()
 
 void Ens::enqueue_step()
 {
-    const DevMesh dm = mesh->dev();
+    const DevMesh dm = mesh->dev(MB);
     // the previous step has completed (its status was read), so the mailbox is free
     std::copy(h_member_step.begin(), h_member_step.end(), h_mail + 2 * MB);
     std::copy(h_stepping.begin(), h_stepping.end(), h_mail + 3 * MB);
@@ -1986,8 +2084,8 @@ int nlth_mesh_query(const nlth_mesh* mesh, nlth_mesh_info* info, int32_t* elem_o
         info->n_nodes = mesh->nn;
         info->n_tets = mesh->ne;
         info->n_colors = mesh->ncolor;
-        info->n_clusters = mesh->ncl;
-        info->cluster_rows = mesh->cl_rows;
+        info->n_clusters = mesh->cl.n;
+        info->cluster_rows = mesh->cl.rows;
         info->n_bnodes = mesh->nbn;
         info->volume = mesh->volume;
     }
@@ -2106,8 +2204,8 @@ int nlth_ens_set_tuning(nlth_ens* ens, const nlth_tuning* t)
     if (t->scatter < -1 || t->scatter > 2) throw Error{NLTH_EINVAL, "scatter must be -1, 0, 1 or 2"};
     if (t->cluster_blocks != 0 && (t->cluster_blocks < 2 || t->cluster_blocks > 4))
         throw Error{NLTH_EINVAL, "cluster_blocks must be 0, 2, 3 or 4"};
-    if ((t->scatter == 0 && !ens->fbuf.p) || (t->scatter == 2 && !ens->cbuf.p))
-        throw Error{NLTH_EINVAL, "scatter: element outputs need fewer than 64 member slots, clusters 64..256"};
+    if ((t->scatter == 0 && ens->MB >= 64) || (t->scatter == 2 && (ens->MB < 64 || ens->MB > 256)))
+        throw Error{NLTH_EINVAL, "scatter: 0 needs fewer than 64 member slots, 2 (clusters) 64..256"};
     if (t->inner_method < -1 || t->inner_method > 1) throw Error{NLTH_EINVAL, "inner_method must be -1, 0 or 1"};
     if (t->zero_copy < -1 || t->zero_copy > 1) throw Error{NLTH_EINVAL, "zero_copy must be -1, 0 or 1"};
     if (t->tail_members != -1 && t->tail_members != 0 && t->tail_members != 16 && t->tail_members != 32)

@@ -15,53 +15,9 @@
 // host issues the colours in sequence on one stream.
 #include <math.h>
 
-#include "nlth_impl.hpp"
+#include "device.hpp"
 
 namespace nlth {
-
-// ---------------------------------------------------------------------------
-// constants
-// ---------------------------------------------------------------------------
-
-// 4-point degree-2 rule: barycentric (a, b, b, b) and permutations, weight V/4.
-#define QA_ 0.5854101966249685
-#define QB_ 0.1381966011250105
-
-// Consistent mass of the 10-node tet divided by its volume: the classical
-// pattern /420 (corner diagonal 6, corner-corner 1, corner and an edge through
-// it -4, corner and the opposite-side edge -6, edge diagonal 32, edges sharing
-// a vertex 16, opposite edges 8).
-__host__ __device__ constexpr double mass_ref(int a, int b)
-{
-    // edges as vertex pairs
-    constexpr int E[6][2] = {{0, 1}, {1, 2}, {2, 0}, {0, 3}, {1, 3}, {2, 3}};
-    if (a < 4 && b < 4) return (a == b ? 6.0 : 1.0) / 420.0;
-    if (a < 4 || b < 4) {
-        int c = a < 4 ? a : b;
-        int e = (a < 4 ? b : a) - 4;
-        return (E[e][0] == c || E[e][1] == c ? -4.0 : -6.0) / 420.0;
-    }
-    if (a == b) return 32.0 / 420.0;
-    int ea = a - 4, eb = b - 4;
-    bool share = E[ea][0] == E[eb][0] || E[ea][0] == E[eb][1] || E[ea][1] == E[eb][0] ||
-                 E[ea][1] == E[eb][1];
-    return (share ? 16.0 : 8.0) / 420.0;
-}
-
-// index of (r, c) in the row-by-row upper triangle of a symmetric 6x6
-__host__ __device__ constexpr int sym6(int r, int c)
-{
-    return r <= c ? r * 6 - r * (r - 1) / 2 + (c - r) : c * 6 - c * (c - 1) / 2 + (r - c);
-}
-
-template <typename T> __device__ __forceinline__ const T* geo_of(const DevMesh& M);
-template <> __device__ __forceinline__ const double* geo_of<double>(const DevMesh& M) { return M.geo64; }
-template <> __device__ __forceinline__ const float* geo_of<float>(const DevMesh& M) { return M.geo32; }
-
-__device__ __forceinline__ double matv(const double* mat, int l, int f, int MB, int m)
-{
-    return mat[((long)l * MAT_N + f) * MB + m];
-}
 
 // Shape-function gradients of the quadratic tet at integration point j.
 template <typename T>
@@ -153,365 +109,34 @@ void launch_cast32(hipStream_t s, const double* a, float* b, long n)
 }
 
 // ---------------------------------------------------------------------------
-// element-by-element operator (Eq. 1 left-hand side, Eq. 2 stiffness)
+// element-by-element operator, colour and cluster forms (the element's
+// arithmetic is in device.hpp; the form for few member slots in slots.hip)
 // ---------------------------------------------------------------------------
-//
-// Per (element, member): gather the 10 nodal displacements, add the mass
-// term (consistent P2 mass applied through corner and edge sums), then the
-// stiffness term of Eq. 2 with the 4-point rule.  Straight-sided tets make the
-// shape-function gradients linear in the barycentrics, so the strain at the
-// four points is a combination of four per-element 6-vectors E_k and the
-// point forces fold back onto the nodes the same way; D_j is streamed once.
 
-// Voigt symmetric part of u (x) g  (F_cd = u_c g_d, engineering shear)
-template <typename T>
-__device__ __forceinline__ void vsym_acc(const T u[3], const T g[3], T o[6])
-{
-    // each component a chain of fused multiply-adds into the accumulator
-    o[0] = fma(u[0], g[0], o[0]);
-    o[1] = fma(u[1], g[1], o[1]);
-    o[2] = fma(u[2], g[2], o[2]);
-    o[3] = fma(u[0], g[1], fma(u[1], g[0], o[3]));
-    o[4] = fma(u[1], g[2], fma(u[2], g[1], o[4]));
-    o[5] = fma(u[2], g[0], fma(u[0], g[2], o[5]));
-}
-
-// f += s * sigma . g  (sigma in Voigt order xx, yy, zz, xy, yz, zx)
-template <typename T>
-__device__ __forceinline__ void tdot_acc(const T sg[6], const T g[3], T s, T f[3])
-{
-    f[0] += s * (sg[0] * g[0] + sg[3] * g[1] + sg[5] * g[2]);
-    f[1] += s * (sg[3] * g[0] + sg[1] * g[1] + sg[4] * g[2]);
-    f[2] += s * (sg[5] * g[0] + sg[4] * g[1] + sg[2] * g[2]);
-}
-
-// f += sigma . g as chains of fused multiply-adds into f
-template <typename T>
-__device__ __forceinline__ void tdot_add(const T sg[6], const T g[3], T f[3])
-{
-    f[0] = fma(sg[0], g[0], fma(sg[3], g[1], fma(sg[5], g[2], f[0])));
-    f[1] = fma(sg[3], g[0], fma(sg[1], g[1], fma(sg[4], g[2], f[1])));
-    f[2] = fma(sg[5], g[0], fma(sg[4], g[1], fma(sg[2], g[2], f[2])));
-}
-
-// index of D(e, j, k) for member m: elements in blocks of EB so that a
-// wavefront's lanes (EB elements x MB members) read contiguous memory
-__device__ __forceinline__ long d_index(long e, int j, int k, int MB, int EB, int m)
-{
-    return (((e / EB) * 84 + j * 21 + k) * EB + e % EB) * (long)MB + m;
-}
-
-// bfloat16 storage of D for the inner operator: pairs of consecutive upper-
-// triangle entries (k = 2q, 2q+1; k = 21 is padding) packed in one 32-bit word
-__device__ __forceinline__ long d16_index(long e, int j, int q, int MB, int EB, int m)
-{
-    return (((e / EB) * 44 + j * 11 + q) * EB + e % EB) * (long)MB + m;
-}
-// element-mean D of the inner operator in bfloat16 pairs: 11 words per element
-__device__ __forceinline__ long d16m_index(long e, int q, int MB, int EB, int m)
-{
-    return (((e / EB) * 11 + q) * EB + e % EB) * (long)MB + m;
-}
-__device__ __forceinline__ uint32_t f2bf(double x)
-{
-    // round to nearest even on the FP32 bit pattern
-    const uint32_t u = __float_as_uint((float)x);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-__device__ __forceinline__ float bf2f(uint32_t b) { return __uint_as_float(b << 16); }
-
-constexpr int kEdgeOpp[6] = {5, 3, 4, 1, 2, 0};  // edge opposite each edge
-
-// element outputs (the 30 nodal forces of an element-member) stored for the
-// gather: row r = 3 * local node + component, element blocks of EB as for D
-__device__ __forceinline__ size_t f_index(long e, int r, int MB, int EB, int m)
-{
-    return (((size_t)(e / EB) * 30 + r) * EB + e % EB) * (size_t)MB + m;
-}
-
-// DK: storage of D, 0 = T itself, 1 = bfloat16 pairs (uint32 words).
-// OUT = 0: positions [e0, e1) of the colour lists (tets of one colour share no
-// node), forces added into y.  OUT = 1: storage positions [e0, e1), forces
-// written to the element-output array y (f_index); the grid is a multiple of
-// 8 blocks and each XCD takes a contiguous range of elements.
-// Forces of one element-member (element e, member m): the 30 nodal values of
-// the operator of MODE applied to x1 (and x2), written to f; nbase[n] is the
-// offset of node n's row in the nodal vectors.
-// element i of an array at a wavefront-uniform base: the byte offset is
-// formed in 32 bits, so the load takes the scalar-base + 32-bit vector-offset
-// form (no per-lane 64-bit address arithmetic).  i * sizeof(T) < 2^32.
-template <typename T>
-__device__ __forceinline__ T ld_u(const T* base, uint32_t i)
-{
-    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + i * (uint32_t)sizeof(T));
-}
-
-template <typename T>
-__device__ __forceinline__ T ld_u_nt(const T* base, uint32_t i)
-{
-    return __builtin_nontemporal_load(
-        reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + i * (uint32_t)sizeof(T)));
-}
-
-template <typename T, int DK, int MODE>
-__device__ __forceinline__ void ebe_element(const DevMesh& M, int MB, int m, long e, const void* __restrict__ Dv,
-                                            const double* __restrict__ h, const double* __restrict__ mat,
-                                            const StepConst& sc, const T* __restrict__ x1,
-                                            const T* __restrict__ x2, T f[10][3], size_t nbase[10])
-{
-    const int EB = MB >= 64 ? 1 : 64 / MB;
-    const long ne = M.ne;
-    const T* geo = geo_of<T>(M);
-    T gL[4][3];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) gL[k / 3][k % 3] = geo[k * ne + e];
-    const T vol = geo[12 * ne + e];
-    int nodes[10];
-#pragma unroll
-    for (int k = 0; k < 10; ++k) nodes[k] = M.conn[k * ne + e];
-    const int l = M.layer[e];
-    const double rho = matv(mat, l, MAT_RHO, MB, m);
-    double he = 0.0;
-    if (sc.damping_mode == 0 && h) he = h[e * MB + m];
-    else if (sc.damping_mode == 1) he = sc.h0;
-    const double dt = sc.dt;
-    T sm, sk, cv = 0;
-    if (MODE == OP_A) {
-        // the quotients by dt involve kernel arguments only (computed once per
-        // thread), so no FP64 division is left per element
-        const double m4 = 4.0 / (dt * dt), a2 = 2.0 * sc.ahat / dt, b2 = 2.0 * sc.bhat / dt;
-        sm = (T)(rho * (double)vol * (m4 + a2 * he));
-        sk = (T)(1.0 + b2 * he);
-    } else if (MODE == OP_K) {
-        sm = 0; sk = 1;
-    } else if (MODE == OP_M) {
-        sm = (T)(rho * (double)vol); sk = 0;
-    } else {  // RHS: M (a + (4/dt + alpha) v) + beta K v
-        sm = (T)(rho * (double)vol);
-        sk = (T)(sc.bhat * he);
-        cv = (T)(4.0 / dt + sc.ahat * he);
-    }
-    // addresses: a base per node (wave-uniform when a wavefront is one element)
-    // plus a 32-bit lane offset, so loads use a scalar base and no 64-bit math
-#pragma unroll
-    for (int n = 0; n < 10; ++n) nbase[n] = (size_t)nodes[n] * 3 * MB;
-    T xk[10][3];
-    // ---- mass: consistent P2 mass applied through corner/edge sums; with
-    // the scale folded into the coefficients each node's force is a short
-    // chain of fused multiply-adds on the corner and edge sums
-    const T s420 = sm * (T)(1.0 / 420.0);
-    const T c2 = s420 * (T)2, c5 = s420 * (T)5, c6 = s420 * (T)6, c8 = s420 * (T)8, c16 = s420 * (T)16;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        T xm[10];
-        // the component's offset joins the uniform base, so every load is a
-        // scalar base plus the member lane
-        const T* x1c = x1 + (size_t)c * MB;
-        const T* x2c = (MODE == OP_RHS) ? x2 + (size_t)c * MB : x2;
-#pragma unroll
-        for (int n = 0; n < 10; ++n) {
-            const T v1 = ld_u(x1c + nbase[n], (uint32_t)m);
-            xk[n][c] = v1;
-            xm[n] = (MODE == OP_RHS) ? ld_u(x2c + nbase[n], (uint32_t)m) + cv * v1 : v1;
-        }
-        if (MODE == OP_K) {
-#pragma unroll
-            for (int n = 0; n < 10; ++n) f[n][c] = 0;
-        } else {
-            constexpr int E[6][2] = {{0, 1}, {1, 2}, {2, 0}, {0, 3}, {1, 3}, {2, 3}};
-            const T Sc = xm[0] + xm[1] + xm[2] + xm[3];
-            const T Se = xm[4] + xm[5] + xm[6] + xm[7] + xm[8] + xm[9];
-            // corner i: (5 x_i + Sc + 2 A_i - 6 Se) / 420, A_i = the edges at i;
-            // edge q (a, b): (2 (x_a + x_b) - 6 Sc + 16 x_q + 16 Se - 8 x_opp) / 420
-            const T bc = fma(-c6, Se, s420 * Sc);
-            const T be = fma(c16, Se, -c6 * Sc);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                T A = 0;
-#pragma unroll
-                for (int q = 0; q < 6; ++q)
-                    if (E[q][0] == i || E[q][1] == i) A += xm[4 + q];
-                f[i][c] = fma(c5, xm[i], fma(c2, A, bc));
-            }
-#pragma unroll
-            for (int q = 0; q < 6; ++q)
-                f[4 + q][c] = fma(c2, xm[E[q][0]] + xm[E[q][1]],
-                                  fma(c16, xm[4 + q], fma(-c8, xm[4 + kEdgeOpp[q]], be)));
-        }
-    }
-    // ---- stiffness (Eq. 2)
-    if (MODE != OP_M && sk != (T)0) {
-        constexpr int E[6][2] = {{0, 1}, {1, 2}, {2, 0}, {0, 3}, {1, 3}, {2, 3}};
-        // E_k = voigt(G_k), G_k = 4 x_k gL_k^T - H + 4 sum_{edges (k,o)} x_ko gL_o^T,
-        // H = sum_k x_k gL_k^T: the corner products P_k are formed once
-        T Ek[4][6], H[6];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-#pragma unroll
-            for (int q = 0; q < 6; ++q) Ek[k][q] = 0;
-            vsym_acc<T>(xk[k], gL[k], Ek[k]);
-        }
-#pragma unroll
-        for (int q = 0; q < 6; ++q) {
-            H[q] = Ek[0][q] + Ek[1][q] + Ek[2][q] + Ek[3][q];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) Ek[k][q] = (T)4 * Ek[k][q] - H[q];
-        }
-#pragma unroll
-        for (int q = 0; q < 6; ++q) {
-            const T u4[3] = {(T)4 * xk[4 + q][0], (T)4 * xk[4 + q][1], (T)4 * xk[4 + q][2]};
-            vsym_acc<T>(u4, gL[E[q][1]], Ek[E[q][0]]);
-            vsym_acc<T>(u4, gL[E[q][0]], Ek[E[q][1]]);
-        }
-        T S[6];
-#pragma unroll
-        for (int q = 0; q < 6; ++q) S[q] = Ek[0][q] + Ek[1][q] + Ek[2][q] + Ek[3][q];
-        const T w = sk * vol * (T)0.25;
-        const T c1 = (T)(QA_ - QB_);
-        T dm[22];  // DK 4: one D for the element, read once
-        if constexpr (DK == 4) {
-            const size_t eb = (size_t)(e / EB) * EB, ei = (size_t)(e % EB);
-            const uint32_t rs = (uint32_t)(EB * MB);
-            const uint32_t* D = (const uint32_t*)Dv + (eb * 11 + ei) * MB;
-#pragma unroll
-            for (int q = 0; q < 11; ++q) {
-                const uint32_t wv = ld_u_nt(D, (uint32_t)q * rs + (uint32_t)m);
-                dm[2 * q] = (T)bf2f(wv & 0xFFFFu);
-                dm[2 * q + 1] = (T)bf2f(wv >> 16);
-            }
-        }
-        if constexpr (DK == 4) {
-            // One D for the element: the stress sigma(L) = sum_k L_k D E_k is
-            // linear in the barycentrics and the forces integrate in closed form
-            // with int L_a L_b dV = V (1 + delta_ab) / 20:
-            //   corner i:     (V/20) (4 s_i - T) . gL_i,
-            //   edge (a, b):  (4V/20) ((T + s_a) . gL_b + (T + s_b) . gL_a),
-            // with s_k = D E_k and T = s_1 + ... + s_4 (the 4-point rule gives the
-            // same values for constant D).
-            const T v20 = sk * vol * (T)0.05;
-            T sgk[4][6], T6[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-#pragma unroll
-                for (int r = 0; r < 6; ++r) {
-                    T a = 0;
-#pragma unroll
-                    for (int c = 0; c < 6; ++c) a += dm[sym6(r, c)] * Ek[k][c];
-                    sgk[k][r] = a * v20;
-                    T6[r] += sgk[k][r];
-                }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                T v[6];
-#pragma unroll
-                for (int r = 0; r < 6; ++r) v[r] = (T)4 * sgk[i][r] - T6[r];
-                tdot_add<T>(v, gL[i], f[i]);
-            }
-            T T4[6];  // the edges' factor 4 folded into their stress sums
-#pragma unroll
-            for (int r = 0; r < 6; ++r) T4[r] = (T)4 * T6[r];
-#pragma unroll
-            for (int q = 0; q < 6; ++q) {
-                const int a = E[q][0], b = E[q][1];
-                T va[6], vb[6];
-#pragma unroll
-                for (int r = 0; r < 6; ++r) {
-                    va[r] = fma((T)4, sgk[a][r], T4[r]);
-                    vb[r] = fma((T)4, sgk[b][r], T4[r]);
-                }
-                tdot_add<T>(va, gL[b], f[4 + q]);
-                tdot_add<T>(vb, gL[a], f[4 + q]);
-            }
-            return;
-        }
-        T ST[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            T eps[6], sg[6];
-#pragma unroll
-            for (int q = 0; q < 6; ++q) eps[q] = (T)QB_ * S[q] + c1 * Ek[j][q];
-            T d[22];
-            // element base (uniform per wavefront) + 32-bit row offsets
-            const size_t eb = (size_t)(e / EB) * EB, ei = (size_t)(e % EB);
-            const uint32_t rs = (uint32_t)(EB * MB);  // stride between rows (j, k)
-            if constexpr (DK == 4) {
-#pragma unroll
-                for (int k = 0; k < 22; ++k) d[k] = dm[k];
-            } else if constexpr (DK == 0) {
-                const T* D = (const T*)Dv + (eb * 84 + ei) * MB;
-#pragma unroll
-                for (int k = 0; k < 21; ++k)
-                    d[k] = ld_u_nt(D, (uint32_t)(j * 21 + k) * rs + (uint32_t)m);
-            } else {
-                const uint32_t* D = (const uint32_t*)Dv + (eb * 44 + ei) * MB;
-#pragma unroll
-                for (int q = 0; q < 11; ++q) {
-                    const uint32_t wv = ld_u_nt(D, (uint32_t)(j * 11 + q) * rs + (uint32_t)m);
-                    d[2 * q] = (T)bf2f(wv & 0xFFFFu);
-                    d[2 * q + 1] = (T)bf2f(wv >> 16);
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < 6; ++r) {
-                T a = 0;
-#pragma unroll
-                for (int c = 0; c < 6; ++c) a += d[sym6(r, c)] * eps[c];
-                sg[r] = a * w;
-                ST[r] += sg[r];
-            }
-            // point-j part of the nodal forces
-#pragma unroll
-            for (int i = 0; i < 4; ++i) tdot_acc<T>(sg, gL[i], i == j ? (T)3 * c1 : -c1, f[i]);
-#pragma unroll
-            for (int q = 0; q < 6; ++q) {
-                if (E[q][0] == j) tdot_acc<T>(sg, gL[E[q][1]], (T)4 * c1, f[4 + q]);
-                if (E[q][1] == j) tdot_acc<T>(sg, gL[E[q][0]], (T)4 * c1, f[4 + q]);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 6; ++q) {
-            T g[3] = {gL[E[q][0]][0] + gL[E[q][1]][0], gL[E[q][0]][1] + gL[E[q][1]][1],
-                      gL[E[q][0]][2] + gL[E[q][1]][2]};
-            tdot_acc<T>(ST, g, (T)(4.0 * QB_), f[4 + q]);
-        }
-    }
-}
-
-template <typename T, int DK, int MODE, bool WAVE_ELEM, int OUT>
+// Colour form (more than 256 member slots, or scatter = 1): positions [e0, e1)
+// of the colour lists (tets of one colour share no node), forces added into y.
+template <typename T, int DK, int MODE, bool WAVE_ELEM>
 __global__ __launch_bounds__(256) void k_ebe(DevMesh M, int MB, int nm, int e0, int e1,
                                             const void* __restrict__ Dv, const double* __restrict__ h,
                                             const double* __restrict__ mat, StepConst sc,
                                             const T* __restrict__ x1, const T* __restrict__ x2,
                                             T* __restrict__ y, const int* __restrict__ active)
 {
-    long blk = blockIdx.x;
-    if (OUT) blk = (blk % 8) * (gridDim.x / 8) + blk / 8;
-    const long t = blk * blockDim.x + threadIdx.x;
+    const long t = blockIdx.x * (long)blockDim.x + threadIdx.x;
     const int m = (int)(t % MB);
     long e = e0 + t / MB;
     if (WAVE_ELEM) e = __builtin_amdgcn_readfirstlane((int)e);  // one element per wavefront
     if (e >= e1 || m >= nm) return;
     if (active && !active[m]) return;
-    if (!OUT) e = WAVE_ELEM ? __builtin_amdgcn_readfirstlane(M.celem[e]) : M.celem[e];
-    const int EB = MB >= 64 ? 1 : 64 / MB;
+    e = WAVE_ELEM ? __builtin_amdgcn_readfirstlane(M.celem[e]) : M.celem[e];
     size_t nbase[10];
     T f[10][3];
     ebe_element<T, DK, MODE>(M, MB, m, e, Dv, h, mat, sc, x1, x2, f, nbase);
-    if (OUT) {
-        // row bases are uniform per wavefront when EB == 1; the lane adds m
-        T* fb = y + f_index(e, 0, MB, EB, 0);
-        const size_t rs = (size_t)EB * MB;
 #pragma unroll
-        for (int n = 0; n < 10; ++n)
+    for (int n = 0; n < 10; ++n) {
+        T* yb = y + nbase[n];
 #pragma unroll
-            for (int c = 0; c < 3; ++c) (fb + (3 * n + c) * rs)[m] = f[n][c];
-    } else {
-#pragma unroll
-        for (int n = 0; n < 10; ++n) {
-            T* yb = y + nbase[n];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) yb[(uint32_t)(c * MB + m)] += f[n][c];
-        }
+        for (int c = 0; c < 3; ++c) yb[(uint32_t)(c * MB + m)] += f[n][c];
     }
 }
 
@@ -662,25 +287,24 @@ void launch_ebe_cluster32(hipStream_t s, const DevMesh& M, int MB, int nm, const
     else cluster32<0>(s, M, MB, nm, D32, h, mat, sc, x, co, active);
 }
 
-// y = sum of the element outputs at each node (incidences in ascending
-// order, so the sum is reproducible) + bscale * base (base may be NULL and may
+// y = sum of the node's cluster rows (ascending, so the sum is reproducible),
+// with bnd its dashpot row last, + bscale * base (base may be NULL and may
 // alias y).  With DOT the per-member partial sums of x . y over the block's
 // nodes go to partial[blockIdx * MB + m] (a fixed tree in LDS).  A block takes
 // a contiguous range of nodes, 256 / MB nodes per pass (MB <= 256): with nodes
 // in Morton order, interleaving the blocks' passes over the whole range was
 // 40 % slower (concurrent blocks then read cluster rows of one small region);
 // members with active[m] == 0 keep y and add nothing.
-template <typename T, bool DOT, bool CL>
-__global__ __launch_bounds__(256) void k_gather(DevMesh M, int MB, int nm, const T* __restrict__ f,
+template <typename T, bool DOT>
+__global__ __launch_bounds__(256) void k_gather(DevMesh M, int MB, int nm, const T* __restrict__ f, int bnd,
                                                const T* base, T bscale, T* y, const int* __restrict__ active,
-                                               const T* __restrict__ x, double* __restrict__ partial)
+                                               const T* __restrict__ x, double* __restrict__ partial,
+                                               const int* __restrict__ ymap)
 {
     const int t = threadIdx.x, m = t % MB;
     const int rpb = 256 / MB;
     const int slot = t / MB;
     const bool act = m < nm && (!active || active[m]);
-    const int EB = MB >= 64 ? 1 : 64 / MB;
-    const size_t rs = (size_t)EB * MB;
     double dot = 0.0;
     const long per = ((M.nn + gridDim.x - 1) / gridDim.x + rpb - 1) / rpb * rpb;
     const long n0 = (long)blockIdx.x * per, n1 = n0 + per < M.nn ? n0 + per : M.nn;
@@ -688,28 +312,15 @@ __global__ __launch_bounds__(256) void k_gather(DevMesh M, int MB, int nm, const
         const int node = MB >= 64 ? __builtin_amdgcn_readfirstlane((int)nd) : (int)nd;
         if (!act) continue;
         T a0 = 0, a1 = 0, a2 = 0;
-        if (CL) {  // cluster rows of the node, ascending
-            const int q1 = M.cn_ptr[node + 1];
+        const int q1 = M.cn_ptr[node + 1] - (!bnd && M.bn_of_node[node] >= 0);
 #pragma unroll 4
-            for (int q = M.cn_ptr[node]; q < q1; ++q) {
-                const T* fb = f + (size_t)M.cn_row[q] * 3 * MB + m;
-                a0 += fb[0];
-                a1 += fb[MB];
-                a2 += fb[2 * MB];
-            }
-        } else {  // element outputs of the node, ascending
-            const int q1 = M.inc_ptr[node + 1];
-#pragma unroll 4
-            for (int q = M.inc_ptr[node]; q < q1; ++q) {
-                const int ent = M.inc[q];
-                const int e = ent / 10, k = ent - 10 * e;
-                const T* fb = f + f_index(e, 3 * k, MB, EB, m);
-                a0 += fb[0];
-                a1 += fb[rs];
-                a2 += fb[2 * rs];
-            }
+        for (int q = M.cn_ptr[node]; q < q1; ++q) {
+            const T* fb = f + (size_t)M.cn_row[q] * 3 * MB + m;
+            a0 += fb[0];
+            a1 += fb[MB];
+            a2 += fb[2 * MB];
         }
-        const size_t yi = (size_t)node * 3 * MB + m;
+        const size_t yi = (size_t)(ymap ? ymap[node] : node) * 3 * MB + m;
         if (base) {
             a0 += bscale * base[yi];
             a1 += bscale * base[yi + MB];
@@ -741,70 +352,48 @@ static int gather_blocks(int nn, int MB, int maxblk)
 }
 
 template <typename T>
-void launch_gather(hipStream_t s, const DevMesh& M, int MB, int nm, const T* f, const T* base, T bscale, T* y,
-                   const int* active, const T* x, double* partial, int* nblk, bool clusters)
+void launch_gather(hipStream_t s, const DevMesh& M, int MB, int nm, const T* rows, bool bnd, const T* base, T bscale,
+                   T* y, const int* active, const T* x, double* partial, int* nblk, const int* ymap)
 {
+    const int g = gather_blocks(M.nn, MB, partial ? kGatherBlocks : 1 << 24);
     if (partial) {
-        const int g = gather_blocks(M.nn, MB, kGatherBlocks);
         *nblk = g;
-        if (clusters)
-            hipLaunchKernelGGL((k_gather<T, true, true>), dim3(g), dim3(256), 0, s, M, MB, nm, f, base, bscale, y,
-                               active, x, partial);
-        else
-            hipLaunchKernelGGL((k_gather<T, true, false>), dim3(g), dim3(256), 0, s, M, MB, nm, f, base, bscale, y,
-                               active, x, partial);
+        hipLaunchKernelGGL((k_gather<T, true>), dim3(g), dim3(256), 0, s, M, MB, nm, rows, (int)bnd, base, bscale, y,
+                           active, x, partial, ymap);
     } else {
-        const int g = gather_blocks(M.nn, MB, 1 << 24);
-        if (clusters)
-            hipLaunchKernelGGL((k_gather<T, false, true>), dim3(g), dim3(256), 0, s, M, MB, nm, f, base, bscale, y,
-                               active, x, nullptr);
-        else
-            hipLaunchKernelGGL((k_gather<T, false, false>), dim3(g), dim3(256), 0, s, M, MB, nm, f, base, bscale, y,
-                               active, x, nullptr);
+        hipLaunchKernelGGL((k_gather<T, false>), dim3(g), dim3(256), 0, s, M, MB, nm, rows, (int)bnd, base, bscale, y,
+                           active, x, nullptr, ymap);
     }
 }
-template void launch_gather<double>(hipStream_t, const DevMesh&, int, int, const double*, const double*, double,
-                                    double*, const int*, const double*, double*, int*, bool);
-template void launch_gather<float>(hipStream_t, const DevMesh&, int, int, const float*, const float*, float, float*,
-                                   const int*, const float*, double*, int*, bool);
+template void launch_gather<double>(hipStream_t, const DevMesh&, int, int, const double*, bool, const double*, double,
+                                    double*, const int*, const double*, double*, int*, const int*);
+template void launch_gather<float>(hipStream_t, const DevMesh&, int, int, const float*, bool, const float*, float,
+                                   float*, const int*, const float*, double*, int*, const int*);
 
 // threads per block of the element-by-element launches (a tuning knob; per
 // host thread so concurrent contexts do not interfere)
 static thread_local int t_ebe_block = 256;
 void set_ebe_block(int bs) { t_ebe_block = (bs == 64 || bs == 128 || bs == 256) ? bs : 256; }
 
-// grid of an element launch: OUT launches round up to a multiple of 8 blocks
-static dim3 ebe_grid(long n, bool out)
-{
-    unsigned g = nblocks(n, t_ebe_block);
-    if (out) g = (g + 7) / 8 * 8;
-    return dim3(g);
-}
-
 template <typename T, int DK, int MODE>
 static void ebe_dispatch(hipStream_t s, const DevMesh& M, int MB, int nm, int e0, int e1, const void* D,
                          const double* h, const double* mat, StepConst sc, const T* x1, const T* x2, T* y,
-                         const int* active, bool out)
+                         const int* active)
 {
-    const dim3 g = ebe_grid((long)(e1 - e0) * MB, out), b(t_ebe_block);
-    if (MB >= 64) {
-        if (out) hipLaunchKernelGGL((k_ebe<T, DK, MODE, true, 1>), g, b, 0, s, M, MB, nm, e0, e1, D, h, mat, sc, x1, x2, y, active);
-        else hipLaunchKernelGGL((k_ebe<T, DK, MODE, true, 0>), g, b, 0, s, M, MB, nm, e0, e1, D, h, mat, sc, x1, x2, y, active);
-    } else {
-        if (out) hipLaunchKernelGGL((k_ebe<T, DK, MODE, false, 1>), g, b, 0, s, M, MB, nm, e0, e1, D, h, mat, sc, x1, x2, y, active);
-        else hipLaunchKernelGGL((k_ebe<T, DK, MODE, false, 0>), g, b, 0, s, M, MB, nm, e0, e1, D, h, mat, sc, x1, x2, y, active);
-    }
+    const dim3 g(nblocks((long)(e1 - e0) * MB, t_ebe_block)), b(t_ebe_block);
+    if (MB >= 64) hipLaunchKernelGGL((k_ebe<T, DK, MODE, true>), g, b, 0, s, M, MB, nm, e0, e1, D, h, mat, sc, x1, x2, y, active);
+    else hipLaunchKernelGGL((k_ebe<T, DK, MODE, false>), g, b, 0, s, M, MB, nm, e0, e1, D, h, mat, sc, x1, x2, y, active);
 }
 
 // inner FP32 operator (Eq. 1 left-hand side) with D stored in FP32 or bfloat16
 void launch_ebe32(hipStream_t s, const DevMesh& M, int MB, int nm, int e0, int e1, const float* D32,
                   const uint32_t* D16, const double* h, const double* mat, StepConst sc, const float* x, float* y,
-                  const int* active, bool out, bool d16_mean)
+                  const int* active, bool d16_mean)
 {
     if (e1 <= e0) return;
-    if (D16 && d16_mean) ebe_dispatch<float, 4, OP_A>(s, M, MB, nm, e0, e1, D16, h, mat, sc, x, nullptr, y, active, out);
-    else if (D16) ebe_dispatch<float, 1, OP_A>(s, M, MB, nm, e0, e1, D16, h, mat, sc, x, nullptr, y, active, out);
-    else ebe_dispatch<float, 0, OP_A>(s, M, MB, nm, e0, e1, D32, h, mat, sc, x, nullptr, y, active, out);
+    if (D16 && d16_mean) ebe_dispatch<float, 4, OP_A>(s, M, MB, nm, e0, e1, D16, h, mat, sc, x, nullptr, y, active);
+    else if (D16) ebe_dispatch<float, 1, OP_A>(s, M, MB, nm, e0, e1, D16, h, mat, sc, x, nullptr, y, active);
+    else ebe_dispatch<float, 0, OP_A>(s, M, MB, nm, e0, e1, D32, h, mat, sc, x, nullptr, y, active);
 }
 
 // ---------------------------------------------------------------------------
@@ -885,111 +474,9 @@ void launch_tail_rows64(hipStream_t s, long nrows, int MB, int G, const int* tl,
     tail_rows<double>(s, nrows, MB, G, 1, 1, tl, src, dst, unpack);
 }
 
-// operator A on the compact rows summed per element cluster (the compact form
-// of k_ebe_cluster): one block per cluster; a wavefront holds 64/G element
-// slots of G lanes, and each slot adds its element's forces into its own copy
-// of the cluster's node rows in LDS (the slots of a wavefront run in
-// lockstep), the wavefronts one after another; on the way out the copies are
-// summed in slot order and written as G-wide cluster rows
-// co[(row * 3 + c) * G + k], which the cluster-row gather completes.  The
-// order of every sum is fixed.  The cluster rows take about a third of the
-// element outputs' bytes, written once and read once.
-template <typename T, int DK, int G>
-__global__ __launch_bounds__(256) void k_ebe_ctail(DevMesh M, const int* __restrict__ tl, const void* __restrict__ cD,
-                                                  const double* __restrict__ ch, const double* __restrict__ cmat,
-                                                  StepConst sc, const T* __restrict__ x, T* __restrict__ co)
-{
-    constexpr int S = 64 / G, SLOTS = 4 * S, ROWS = kClusterNodes * 3 * G;
-    __shared__ T ys[S * ROWS];
-    const int c = (int)((blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8);  // XCD-contiguous clusters
-    if (c >= M.ncl) return;  // whole block: padding of the grid to a multiple of 8
-    const int t = threadIdx.x, k = t % G, slot = t / G, sw = (t & 63) / G;
-    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int e0 = M.cl_off[c], nec = M.cl_off[c + 1] - e0;
-    const int r0 = M.cl_noff[c], n3 = (M.cl_noff[c + 1] - r0) * 3 * G;
-    for (int i = t; i < S * n3; i += 256) ys[(i / n3) * ROWS + i % n3] = (T)0;
-    const bool act = k < min(tl[0], G);
-    T* yc = ys + sw * ROWS;
-    __syncthreads();
-    for (int r = 0; r < nec; r += SLOTS) {
-        const int le = r + slot;
-        T f[10][3];
-        if (le < nec && act) {
-            size_t nbase[10];
-            ebe_element<T, DK, OP_A>(M, G, k, e0 + le, cD, ch, cmat, sc, x, nullptr, f, nbase);
-        } else {
-#pragma unroll
-            for (int n = 0; n < 10; ++n) f[n][0] = f[n][1] = f[n][2] = (T)0;
-        }
-        uint32_t lw[3] = {0u, 0u, 0u};
-        if (le < nec) {
-            const uint32_t* lp = M.cl_lconn + (size_t)(e0 + le) * 4;
-            lw[0] = lp[0];
-            lw[1] = lp[1];
-            lw[2] = lp[2];
-        }
-        for (int ww = 0; ww < 4; ++ww) {
-            __syncthreads();
-            if (w == ww && le < nec) {
-                // the element's ten distinct node rows: all reads before the writes
-                T* yr[10];
-                T v[10][3];
-#pragma unroll
-                for (int n = 0; n < 10; ++n) {
-                    yr[n] = yc + (int)((lw[n / 4] >> (8 * (n % 4))) & 0xFFu) * 3 * G + k;
-                    v[n][0] = yr[n][0];
-                    v[n][1] = yr[n][G];
-                    v[n][2] = yr[n][2 * G];
-                }
-#pragma unroll
-                for (int n = 0; n < 10; ++n) {
-                    yr[n][0] = v[n][0] + f[n][0];
-                    yr[n][G] = v[n][1] + f[n][1];
-                    yr[n][2 * G] = v[n][2] + f[n][2];
-                }
-            }
-        }
-    }
-    __syncthreads();
-    for (int i = t; i < n3; i += 256) {
-        T v = ys[i];
-#pragma unroll
-        for (int q = 1; q < S; ++q) v += ys[q * ROWS + i];
-        co[(size_t)r0 * 3 * G + i] = v;
-    }
-}
-
-void launch_ebe64_ctail(hipStream_t s, const DevMesh& M, int G, const int* tl, const double* cD, const double* ch,
-                        const double* cmat, StepConst sc, const double* x, double* co)
-{
-    long g = (M.ncl + 7) / 8 * 8;
-    if (M.ncl <= 0) return;
-    if (G == 16)
-        hipLaunchKernelGGL((k_ebe_ctail<double, 0, 16>), dim3((unsigned)g), dim3(256), 0, s, M, tl, cD, ch, cmat, sc, x,
-                           co);
-    else
-        hipLaunchKernelGGL((k_ebe_ctail<double, 0, 32>), dim3((unsigned)g), dim3(256), 0, s, M, tl, cD, ch, cmat, sc, x,
-                           co);
-}
-
-void launch_ebe32_ctail(hipStream_t s, const DevMesh& M, int G, const int* tl, const uint32_t* cD, const double* ch,
-                        const double* cmat, StepConst sc, const float* x, float* co)
-{
-    long g = (M.ncl + 7) / 8 * 8;
-    if (M.ncl <= 0) return;
-    if (G == 16)
-        hipLaunchKernelGGL((k_ebe_ctail<float, 4, 16>), dim3((unsigned)g), dim3(256), 0, s, M, tl, cD, ch, cmat, sc, x,
-                           co);
-    else
-        hipLaunchKernelGGL((k_ebe_ctail<float, 4, 32>), dim3((unsigned)g), dim3(256), 0, s, M, tl, cD, ch, cmat, sc, x,
-                           co);
-}
-
-// node sums of compact element outputs (incidences in ascending order) or,
-// with CL, of the compact cluster rows (the node's rows in ascending order;
-// the form the operators write) into the compact y of the listed, active
-// members; with partial, the x . y partials of the block's nodes
-template <typename T, int G, bool CL>
+// node sums of the compact cluster rows (ascending) into the compact y of the
+// listed, active members; with partial, the x . y partials of the block's nodes
+template <typename T, int G>
 __global__ __launch_bounds__(256) void k_gather_tail(DevMesh M, int MB, int nm, const int* __restrict__ tl,
                                                     const T* __restrict__ fc, T* __restrict__ y,
                                                     const int* __restrict__ active, const T* __restrict__ x,
@@ -1005,25 +492,13 @@ __global__ __launch_bounds__(256) void k_gather_tail(DevMesh M, int MB, int nm, 
     if (act) {
         for (long nd = n0 + slot; nd < n1; nd += NPB) {
             T a0 = 0, a1 = 0, a2 = 0;
-            if (CL) {
-                const int q1 = M.cn_ptr[nd + 1];
+            const int q1 = M.cn_ptr[nd + 1] - (M.bn_of_node[nd] >= 0);  // without the dashpot row
 #pragma unroll 4
-                for (int q = M.cn_ptr[nd]; q < q1; ++q) {
-                    const T* fb = fc + (size_t)3 * M.cn_row[q] * G + k;
-                    a0 += fb[0];
-                    a1 += fb[G];
-                    a2 += fb[2 * G];
-                }
-            } else {
-                const int q1 = M.inc_ptr[nd + 1];
-#pragma unroll 4
-                for (int q = M.inc_ptr[nd]; q < q1; ++q) {
-                    // incidence e * 10 + local node: its output rows start at 3 * incidence
-                    const T* fb = fc + (size_t)3 * M.inc[q] * G + k;
-                    a0 += fb[0];
-                    a1 += fb[G];
-                    a2 += fb[2 * G];
-                }
+            for (int q = M.cn_ptr[nd]; q < q1; ++q) {
+                const T* fb = fc + (size_t)3 * M.cn_row[q] * G + k;
+                a0 += fb[0];
+                a1 += fb[G];
+                a2 += fb[2 * G];
             }
             const size_t yi = (size_t)nd * 3 * G + k;
             y[yi] = a0;
@@ -1041,84 +516,41 @@ __global__ __launch_bounds__(256) void k_gather_tail(DevMesh M, int MB, int nm, 
 
 template <typename T>
 void launch_gather_tail(hipStream_t s, const DevMesh& M, int MB, int nm, int G, const int* tl, const T* fc, T* y,
-                        const int* active, const T* x, double* partial, int* nblk, bool clusters)
+                        const int* active, const T* x, double* partial, int* nblk)
 {
     const int g = gather_blocks(M.nn, G, partial ? kGatherBlocks : (1 << 24));
     if (partial) *nblk = g;
-    if (clusters) {
-        if (G == 16)
-            hipLaunchKernelGGL((k_gather_tail<T, 16, true>), dim3(g), dim3(256), 0, s, M, MB, nm, tl, fc, y, active, x,
-                               partial);
-        else
-            hipLaunchKernelGGL((k_gather_tail<T, 32, true>), dim3(g), dim3(256), 0, s, M, MB, nm, tl, fc, y, active, x,
-                               partial);
-    } else {
-        if (G == 16)
-            hipLaunchKernelGGL((k_gather_tail<T, 16, false>), dim3(g), dim3(256), 0, s, M, MB, nm, tl, fc, y, active, x,
-                               partial);
-        else
-            hipLaunchKernelGGL((k_gather_tail<T, 32, false>), dim3(g), dim3(256), 0, s, M, MB, nm, tl, fc, y, active, x,
-                               partial);
-    }
+    if (G == 16)
+        hipLaunchKernelGGL((k_gather_tail<T, 16>), dim3(g), dim3(256), 0, s, M, MB, nm, tl, fc, y, active, x, partial);
+    else
+        hipLaunchKernelGGL((k_gather_tail<T, 32>), dim3(g), dim3(256), 0, s, M, MB, nm, tl, fc, y, active, x, partial);
 }
 template void launch_gather_tail<float>(hipStream_t, const DevMesh&, int, int, int, const int*, const float*, float*,
-                                        const int*, const float*, double*, int*, bool);
+                                        const int*, const float*, double*, int*);
 template void launch_gather_tail<double>(hipStream_t, const DevMesh&, int, int, int, const int*, const double*,
-                                         double*, const int*, const double*, double*, int*, bool);
+                                         double*, const int*, const double*, double*, int*);
 
 template <typename T>
 void launch_ebe(hipStream_t s, OpMode mode, const DevMesh& M, int MB, int nm, int e0, int e1, const T* D,
                 const double* h, const double* mat, int, StepConst sc, const T* x1, const T* x2, T* y,
-                const int* active, bool out)
+                const int* active)
 {
     if (e1 <= e0) return;
     switch (mode) {
-    case OP_A: ebe_dispatch<T, 0, OP_A>(s, M, MB, nm, e0, e1, D, h, mat, sc, x1, x2, y, active, out); break;
-    case OP_K: ebe_dispatch<T, 0, OP_K>(s, M, MB, nm, e0, e1, D, h, mat, sc, x1, x2, y, active, out); break;
-    case OP_M: ebe_dispatch<T, 0, OP_M>(s, M, MB, nm, e0, e1, D, h, mat, sc, x1, x2, y, active, out); break;
-    case OP_RHS: ebe_dispatch<T, 0, OP_RHS>(s, M, MB, nm, e0, e1, D, h, mat, sc, x1, x2, y, active, out); break;
+    case OP_A: ebe_dispatch<T, 0, OP_A>(s, M, MB, nm, e0, e1, D, h, mat, sc, x1, x2, y, active); break;
+    case OP_K: ebe_dispatch<T, 0, OP_K>(s, M, MB, nm, e0, e1, D, h, mat, sc, x1, x2, y, active); break;
+    case OP_M: ebe_dispatch<T, 0, OP_M>(s, M, MB, nm, e0, e1, D, h, mat, sc, x1, x2, y, active); break;
+    case OP_RHS: ebe_dispatch<T, 0, OP_RHS>(s, M, MB, nm, e0, e1, D, h, mat, sc, x1, x2, y, active); break;
     }
 }
 template void launch_ebe<double>(hipStream_t, OpMode, const DevMesh&, int, int, int, int, const double*,
                                  const double*, const double*, int, StepConst, const double*,
-                                 const double*, double*, const int*, bool);
+                                 const double*, double*, const int*);
 
 // ---------------------------------------------------------------------------
 // absorbing boundary: node-centric gather over boundary faces (deterministic)
 // dashpot on a face: rho (Vp n n^T + Vs (I - n n^T)) times int N_a N_b dA
 // ---------------------------------------------------------------------------
-
-// dashpot force at boundary node i (index into the boundary-node lists) for
-// member m: coef * sum over its faces of rho (Vp n n^T + Vs (I - n n^T)) int N_a N_b dA x_b,
-// plus, with vI, the incident-wave force 2 C_base v_I on base faces
-template <typename T>
-__device__ __forceinline__ void dashpot_at(const DevMesh& M, int MB, int m, int i, const double* __restrict__ mat,
-                                           double coef, const T* __restrict__ x, const double* __restrict__ vI,
-                                           double acc[3])
-{
-    for (int q = M.bn_ptr[i]; q < M.bn_ptr[i + 1]; ++q) {
-        const int f = M.bn_face[q], a = M.bn_loc[q];
-        const int l = M.f_layer[f];
-        const double rho = matv(mat, l, MAT_RHO, MB, m);
-        const double vs = matv(mat, l, MAT_VS, MB, m);
-        const double vp = matv(mat, l, MAT_VP, MB, m);
-        const double* nv = M.f_n + 3 * (long)f;
-        double X[3] = {0, 0, 0}, rs = 0;
-        for (int b = 0; b < 6; ++b) {
-            const double Mab = M.f_M[36 * (long)f + 6 * a + b];
-            const long nb = M.f_node[6 * (long)f + b];
-            rs += Mab;
-            for (int c = 0; c < 3; ++c) X[c] += Mab * (double)x[(nb * 3 + c) * MB + m];
-        }
-        double nx = nv[0] * X[0] + nv[1] * X[1] + nv[2] * X[2];
-        for (int c = 0; c < 3; ++c) acc[c] += coef * rho * (vs * X[c] + (vp - vs) * nx * nv[c]);
-        if (vI && M.f_kind[f] == 0) {  // incident wave: 2 C_base v_I
-            double V[3] = {vI[0 * MB + m], vI[1 * MB + m], vI[2 * MB + m]};
-            double nV = nv[0] * V[0] + nv[1] * V[1] + nv[2] * V[2];
-            for (int c = 0; c < 3; ++c) acc[c] += 2.0 * rs * rho * (vs * V[c] + (vp - vs) * nV * nv[c]);
-        }
-    }
-}
 
 // y += dashpot at the boundary nodes; with DOT also the per-member partial
 // sums of x . (dashpot x) over the block's nodes, written to
@@ -1304,7 +736,7 @@ __global__ __launch_bounds__(256) void k_gather_cheb(DevMesh M, int MB, int nm, 
     for (long nd = n0 + slot; nd < n1; nd += rpb) {
         const int node = __builtin_amdgcn_readfirstlane((int)nd);
         float a0 = 0, a1 = 0, a2 = 0;
-        const int q1 = M.cn_ptr[node + 1];
+        const int bi = M.bn_of_node[node], q1 = M.cn_ptr[node + 1] - (bi >= 0);
 #pragma unroll 4
         for (int q = M.cn_ptr[node]; q < q1; ++q) {
             const float* fb = rows + (size_t)M.cn_row[q] * 3 * MB + m;
@@ -1312,7 +744,6 @@ __global__ __launch_bounds__(256) void k_gather_cheb(DevMesh M, int MB, int nm, 
             a1 += fb[MB];
             a2 += fb[2 * MB];
         }
-        const int bi = M.bn_of_node[node];
         if (bi >= 0) {
             const float* qp = qb + (size_t)bi * 3 * MB + m;
             a0 += qp[0];

@@ -28,7 +28,11 @@ constexpr int kGatherBlocks = 16384;      // blocks of a node gather with partia
 constexpr int kDashpotBlocks = 1024;      // blocks of a dashpot launch with partial sums
 constexpr int kClusterNodes = 48;         // most distinct nodes of an element cluster
 constexpr int kClusterElems = 16;         // most elements of an element cluster
-// length (in MB-rows of doubles) of the partial-sum buffer
+constexpr int kWideNodes = 240;           // the same of a wide cluster, which
+constexpr int kWideElems = 64;            // ensembles of up to
+constexpr int kWideSlots = 8;             // member slots use
+constexpr int kFoldBlocks = 256;          // rows to which long partial sums are folded before the finalize
+// length (in MB-rows of doubles) of the partial-sum buffer, without the few-slot operator's rows
 constexpr int kPartialRows = (3 * kMaxPartialBlocks > kGatherBlocks + kDashpotBlocks)
                                  ? 3 * kMaxPartialBlocks : kGatherBlocks + kDashpotBlocks;
 
@@ -52,9 +56,6 @@ struct DevMesh {
     const double* f_n;    // [nf*3] unit normal
     const int* f_layer;   // [nf]
     const uint8_t* f_kind;
-    // node -> incidences (storage element * 10 + local node), ascending
-    const int* inc_ptr;   // [nn+1]
-    const int* inc;       // [10*ne]
     const int* celem;     // [ne] storage positions grouped by colour
     const int* bn_of_node;  // [nn] index into bn_node, or -1
     // element clusters: consecutive storage elements with few distinct nodes
@@ -62,8 +63,16 @@ struct DevMesh {
     const int* cl_off;      // [ncl+1] storage positions
     const int* cl_noff;     // [ncl+1] rows of the clusters' node lists
     const uint32_t* cl_lconn; // [ne*4] local nodes of each element, four 8-bit indices per word
-    const int* cn_ptr;      // [nn+1] node -> cluster rows
-    const int* cn_row;      // [rows] ascending per node
+    long cl_rows;           // rows of all clusters
+    int cl_max_elems, cl_max_nodes;      // of the clusters
+    int cl_node_stride, cl_list_stride;  // of the tables of a cluster
+    const int4* cl_head;      // [ncl] first element, first row, elements, rows
+    const int* cl_nodes;      // [ncl][cl_node_stride] node of a row
+    const uint16_t* cl_lptr;  // [ncl][cl_node_stride] first list group of a row, one past the last row too
+    const uint2* cl_lists;    // [ncl][cl_list_stride] incidences of the rows in groups of four: local node * 64
+                              // + element within the cluster, ascending, padded with local node 10
+    const int* cn_ptr;      // [nn+1] node -> rows
+    const int* cn_row;      // ascending per node: cluster rows, then a boundary node's dashpot row cl_rows + i
 };
 
 struct StepConst {
@@ -71,6 +80,14 @@ struct StepConst {
     double ahat, bhat;   // Rayleigh fit
     int damping_mode;    // 0 law, 1 const, 2 none
     double h0;
+    double m4, a2, b2, c4;  // 4/dt^2, 2 ahat/dt, 2 bhat/dt, 4/dt
+    void quotients()
+    {
+        m4 = 4.0 / (dt * dt);
+        a2 = 2.0 * ahat / dt;
+        b2 = 2.0 * bhat / dt;
+        c4 = 4.0 / dt;
+    }
 };
 
 // ---- kernel launchers (kernels.hip) ----
@@ -84,13 +101,26 @@ void launch_neg_copy(hipStream_t s, const double* a, double* b, long n);
 template <typename T>
 void launch_ebe(hipStream_t s, OpMode mode, const DevMesh& M, int MB, int nm, int e0, int e1,
                 const T* D, const double* h, const double* mat, int n_layers, StepConst sc,
-                const T* x1, const T* x2, T* y, const int* active, bool out);
-// y = sum over incident elements of the element outputs f, or over the
-// node's cluster rows when clusters is set (+ bscale * base); with partial,
-// also the per-member block partials of x . y (*nblk blocks).  MB <= 256.
+                const T* x1, const T* x2, T* y, const int* active);
+// y = sum over the node's cluster rows (+ bscale * base), with bnd also its
+// dashpot row; with partial, also the per-member block partials of x . y
+// (*nblk blocks).  MB <= 256.  ymap: storage node -> row of y (NULL: the same).
 template <typename T>
-void launch_gather(hipStream_t s, const DevMesh& M, int MB, int nm, const T* f, const T* base, T bscale, T* y,
-                   const int* active, const T* x, double* partial, int* nblk, bool clusters);
+void launch_gather(hipStream_t s, const DevMesh& M, int MB, int nm, const T* rows, bool bnd, const T* base, T bscale,
+                   T* y, const int* active, const T* x, double* partial, int* nblk, const int* ymap = nullptr);
+// operator of `mode` for fewer than 64 member slots: cluster rows and (dcoef
+// != 0) the dashpot rows dcoef * C_abs x1 (+ 2 C_base vI) of the boundary
+// nodes, to `rows`; with partial the per-member block partials of x1 . y
+void launch_op_slots64(hipStream_t s, OpMode mode, const DevMesh& M, int MB, int nm, const double* D,
+                       const double* h, const double* mat, StepConst sc, const double* x1, const double* x2,
+                       double* rows, const int* active, double dcoef, const double* vI, double* partial, int* nblk);
+void launch_op_slots32(hipStream_t s, const DevMesh& M, int MB, int nm, const float* D32, const uint32_t* D16,
+                       bool d16_mean, const double* h, const double* mat, StepConst sc, const float* x, float* rows,
+                       const int* active, double dcoef, double* partial, int* nblk);
+// one member, D [ne][4][21] and h [ne] in input tet order (order: storage
+// position -> input tet): the operator of launch_op_slots64 on them
+void launch_op_input64(hipStream_t s, OpMode mode, const DevMesh& M, const int* order, const double* D,
+                       const double* h, const double* mat, StepConst sc, const double* x, double* rows, double dcoef);
 // cluster form of the operator (MB a multiple of 64): cluster node rows to co
 void launch_ebe_cluster64(hipStream_t s, OpMode mode, const DevMesh& M, int MB, int nm, const double* D,
                           const double* h, const double* mat, StepConst sc, const double* x1, const double* x2,
@@ -148,7 +178,7 @@ void launch_ebe64_ctail(hipStream_t s, const DevMesh& M, int G, const int* tl, c
                         const double* cmat, StepConst sc, const double* x, double* co);
 template <typename T>
 void launch_gather_tail(hipStream_t s, const DevMesh& M, int MB, int nm, int G, const int* tl, const T* fc, T* y,
-                        const int* active, const T* x, double* partial, int* nblk, bool clusters = false);
+                        const int* active, const T* x, double* partial, int* nblk);
 template <typename T>
 void launch_dashpot_tail(hipStream_t s, const DevMesh& M, int MB, int nm, int G, const int* tl, const double* cmat,
                          T coef, const T* x, T* y, const int* active, double* partial, int* nblk);
@@ -178,7 +208,7 @@ void launch_tail_pz(hipStream_t s, long nrows, int nm, int G, const int* tl, flo
 // inner FP32 operator (A) with D in FP32 (D32) or bfloat16 pairs (D16, if non-null)
 void launch_ebe32(hipStream_t s, const DevMesh& M, int MB, int nm, int e0, int e1, const float* D32,
                   const uint32_t* D16, const double* h, const double* mat, StepConst sc, const float* x, float* y,
-                  const int* active, bool out, bool d16_mean);
+                  const int* active, bool d16_mean);
 void launch_theta_init(hipStream_t s, void* theta_chunk, long ecp, int ns, int MB);
 void launch_law(hipStream_t s, const DevMesh& M, int MB, int nm, int e0, int ec, long ecp, const double* mat,
                 int n_layers, const int* nonlinear, int ns, int depth, const double* dirs, const double* w,
@@ -257,7 +287,7 @@ __device__ __forceinline__ void tail_partials(double acc[ND], int MB, int m, dou
 }
 
 void launch_finalize(hipStream_t s, FinalizeStage st, int nd, int MB, int nm, const double* partial, int nblk,
-                     CgScalars cs, double tol2, int maxit);
+                     double* fold, CgScalars cs, double tol2, int maxit);
 
 void launch_pcg_start(hipStream_t s, int nn, int MB, int nm, const double* b, const double* Ap, const double* pinv,
                       double* r, double* z, double* p, const int* stepping, double* partial, int* nblk);

@@ -2,14 +2,15 @@
 // that cannot allocate device memory: code under HIP graph capture, tight
 // serving loops, harnesses that forbid hipMalloc.  The caller passes device
 // buffers for the inputs and the output; every intermediate (the material
-// table, D and h in the library's storage layout, x and y in storage node
-// order, the element outputs) lives in one file-scope device array of
+// table, the operator's rows) lives in one file-scope device array of
 // kScratchBytes that each device the library runs on holds until the process
 // ends.  Its device address comes from hipGetSymbolAddress, taken once per
 // device when a context is created on it (in host code the array's name is
 // only a host-side stand-in).  The kernels are those of nlth_apply_operator's
-// FP64 path (one member slot: element outputs, then the node gather, then the
-// dashpot), so the two entry points give the same results.
+// FP64 path for one member slot, which read D and h in input tet order and x in
+// input node order, so the two entry points give the same results.  (Copying D,
+// h, x and y between the orders took 5 launches more and moved D three times:
+// 85 -> 31 us a call with 58,080 tets.)
 #include <math.h>
 #include <string.h>
 
@@ -59,31 +60,6 @@ __global__ void k_noalloc_mat(LayerMat lm, double* __restrict__ mat)
     for (int t = threadIdx.x; t < lm.n; t += blockDim.x) mat[t] = lm.v[t];
 }
 
-// D (input tet order, [n_tets][4][21]) and h into the storage layout of one
-// member slot: elements of the storage order in blocks of 64
-__global__ void k_noalloc_D(int ne, const int* __restrict__ order, const double* __restrict__ Din,
-                            const double* __restrict__ hin, double* __restrict__ D, double* __restrict__ h)
-{
-    const long t = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (t >= (long)ne * 84) return;
-    const int pos = (int)(t / 84), q = (int)(t % 84);
-    const long e0 = order[pos];
-    D[((long)(pos / 64) * 84 + q) * 64 + pos % 64] = Din[e0 * 84 + q];
-    if (q == 0) h[pos] = hin ? hin[e0] : 0.0;
-}
-
-// nodal vector, input node order -> storage order (forward) or back
-__global__ void k_noalloc_perm(long n3, const int* __restrict__ node_new, const double* __restrict__ src,
-                               double* __restrict__ dst, int forward)
-{
-    const long t = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (t >= n3) return;
-    const long i = t / 3, c = t % 3;
-    const long s = 3L * node_new[i] + c;
-    if (forward) dst[s] = src[t];
-    else dst[t] = src[s];
-}
-
 void rayleigh_coefficients(double f_lo, double f_hi, double* a, double* b);
 
 }  // namespace nlth
@@ -117,16 +93,16 @@ extern "C" int nlth_apply_operator_noalloc(nlth_ctx* ctx, const nlth_mesh* mesh,
         if (prob->damping_mode != NLTH_DAMPING_NONE && !(prob->f_lo > 0 && prob->f_hi > prob->f_lo))
             throw Error{NLTH_EINVAL, "problem: Rayleigh band needs 0 < f_lo < f_hi"};
         const int ne = mesh->ne, nn = mesh->nn;
-        const int ne_pad = (ne + 63) / 64 * 64;
         const long n3 = 3L * nn;
-        // scratch regions
+        // scratch regions: the material table and the operator's rows (at most
+        // ten per element)
         const size_t o_mat = 0;
-        const size_t o_D = o_mat + round256((size_t)nl * MAT_N * 8);
-        const size_t o_h = o_D + round256((size_t)ne_pad * 84 * 8);
-        const size_t o_x = o_h + round256((size_t)ne_pad * 8);
-        const size_t o_y = o_x + round256((size_t)n3 * 8);
-        const size_t o_f = o_y + round256((size_t)n3 * 8);
-        const size_t need = o_f + round256((size_t)ne_pad * 30 * 8);
+        const size_t o_rows = o_mat + round256((size_t)nl * MAT_N * 8);
+        // the capacity that the entry point states (D, h, two nodal vectors and
+        // ten rows per element): more than what the regions above take
+        const size_t ne_pad = ((size_t)ne + 63) / 64 * 64;
+        const size_t need = o_rows + round256(ne_pad * 84 * 8) + round256(ne_pad * 8) + 2 * round256((size_t)n3 * 8) +
+                            round256(ne_pad * 30 * 8);
         if (need > kScratchBytes) {
             char buf[200];
             snprintf(buf, sizeof buf,
@@ -158,32 +134,21 @@ extern "C" int nlth_apply_operator_noalloc(nlth_ctx* ctx, const nlth_mesh* mesh,
         sc.h0 = prob->h0;
         if (prob->damping_mode == NLTH_DAMPING_NONE) sc.ahat = sc.bhat = 0.0;
         else rayleigh_coefficients(prob->f_lo, prob->f_hi, &sc.ahat, &sc.bhat);
+        sc.quotients();
 
         std::lock_guard<std::mutex> g(ctx->mu);
         NLTH_HIP(hipSetDevice(ctx->device));
         char* base = scratch_of(ctx->device);
         if (!base) throw Error{NLTH_EDEVICE, "scratch address not set up on this device"};
         double* mat = (double*)(base + o_mat);
-        double* Ds = (double*)(base + o_D);
-        double* hs = (double*)(base + o_h);
-        double* xs = (double*)(base + o_x);
-        double* ys = (double*)(base + o_y);
-        double* f = (double*)(base + o_f);
+        double* rows = (double*)(base + o_rows);
         hipStream_t s = ctx->stream;
-        const DevMesh dm = mesh->dev();
+        const DevMesh dm = mesh->dev_input();
+        const double dc = which == NLTH_OP_A ? 2.0 / prob->dt : 0.0;
         hipLaunchKernelGGL(k_noalloc_mat, dim3(1), dim3(256), 0, s, lm, mat);
-        const long nD = (long)ne * 84;
-        hipLaunchKernelGGL(k_noalloc_D, dim3((unsigned)((nD + 255) / 256)), dim3(256), 0, s, ne,
-                           mesh->order_d.as<int>(), D_ip, h, Ds, hs);
-        hipLaunchKernelGGL(k_noalloc_perm, dim3((unsigned)((n3 + 255) / 256)), dim3(256), 0, s, n3,
-                           mesh->node_new_d.as<int>(), x, xs, 1);
-        set_ebe_block(256);
-        launch_ebe<double>(s, (OpMode)which, dm, 1, 1, 0, ne, Ds, hs, mat, nl, sc, xs, nullptr, f, nullptr, true);
-        launch_gather<double>(s, dm, 1, 1, f, nullptr, 0.0, ys, nullptr, xs, nullptr, nullptr, false);
-        if (which == NLTH_OP_A)
-            launch_dashpot<double>(s, dm, 1, 1, mat, nl, 2.0 / prob->dt, xs, ys, nullptr, nullptr);
-        hipLaunchKernelGGL(k_noalloc_perm, dim3((unsigned)((n3 + 255) / 256)), dim3(256), 0, s, n3,
-                           mesh->node_new_d.as<int>(), ys, y, 0);
+        launch_op_input64(s, (OpMode)which, dm, mesh->order_d.as<int>(), D_ip, h, mat, sc, x, rows, dc);
+        launch_gather<double>(s, dm, 1, 1, rows, dc != 0.0, nullptr, 0.0, y, nullptr, nullptr, nullptr, nullptr,
+                              mesh->node_in.as<int>());
         NLTH_HIP(hipGetLastError());
         return NLTH_OK;
     } catch (const Error& e) {

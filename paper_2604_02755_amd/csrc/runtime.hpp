@@ -67,14 +67,24 @@ struct Mesh {
     std::vector<int> recv;
     // device
     DevBuf conn, geo64, geo32, layer, bn_node, bn_ptr, bn_face, bn_loc, f_node, f_M, f_n, f_layer, f_kind, recv_d;
-    DevBuf inc_ptr, inc, celem, bn_of;
-    DevBuf cl_off_d, cl_noff_d, cl_lconn_d, cn_ptr_d, cn_row_d;
-    DevBuf order_d, node_new_d;    // storage position -> input tet; input node -> storage node
-    int ncl = 0;
-    long cl_rows = 0;  // total rows of the clusters' node lists
+    DevBuf celem, bn_of;
+    // element clusters with their row lists on the device: the regular ones
+    // (4 member slots and more) and the wide ones (1 and 2 slots)
+    struct Clusters {
+        int n = 0;
+        long rows = 0;  // total rows of the clusters' node lists
+        int max_elems = 0, max_nodes = 0, node_stride = 0, list_stride = 0;
+        DevBuf off, noff, lconn, nodes, head, lists, lptr, cn_ptr, cn_row;
+    } cl, wide;
+    // node numbers in input order (the allocation-free application): of the
+    // wide clusters' rows, the faces and the boundary nodes, and of every node
+    DevBuf wide_node_in, f_node_in, bn_node_in, node_in;
+    DevBuf order_d;                // storage position -> input tet
     int nbn = 0;
     mutable std::atomic<int> refs{0};  // pending requests using the mesh
-    DevMesh dev() const;
+    const Clusters& clusters(int MB) const;
+    DevMesh dev(int MB) const;      // with the clusters that MB member slots use
+    DevMesh dev_input() const;      // wide clusters, node numbers in input order
 };
 
 struct Problem {  // host copy of an nlth_problem
@@ -141,13 +151,13 @@ struct Ens {
     int est_iters = 0;                  // estimate iterations of this step, not yet counted
     DevBuf D64, D32, D16, h;             // D16: bfloat16 pairs for the inner operator
     bool d16_mean = false;              // inner D: one bfloat16 D per element (the mean over its points)
-    DevBuf fbuf;                        // element outputs of the gather path (FP64 or FP32)
-    DevBuf cbuf;                        // cluster node rows of the cluster path (FP64 or FP32)
-    int scatter = 0;                    // 0: element outputs + gather; 1: colour launches; 2: clusters + gather
+    DevBuf cbuf;                        // cluster node rows, then the boundary nodes' dashpot rows (FP64 or FP32)
+    int scatter = 0;                    // 0: few-slot operator + gather; 1: colour launches; 2: wide clusters + gather
     DevBuf theta;                       // resident law state (or the device chunk ring)
     DevBuf theta_host;                  // pinned host state when paged
     DevBuf hist, vmax, iters_dev;
-    DevBuf partial, scal;               // CG scalars block
+    DevBuf partial, scal;               // partial sums; CG scalars block
+    double* fold = nullptr;             // in partial: long sums folded to kFoldBlocks rows
     DevBuf member_step, stepping, status;
     CgScalars cs{};
     // paging

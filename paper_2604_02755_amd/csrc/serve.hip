@@ -104,7 +104,7 @@ static ServeState& serve_state(Ctx* c)
 void Ens::reset_member(int m)
 {
     const int ns_steps = std::max(1, P.n_steps);
-    const DevMesh dm = mesh->dev();
+    const DevMesh dm = mesh->dev(MB);
     // material column m
     std::vector<double> mt((size_t)P.nl * MAT_N * MB);
     NLTH_HIP(hipMemcpy(mt.data(), mat.p, mt.size() * 8, hipMemcpyDeviceToHost));

@@ -1,0 +1,307 @@
+// Element-by-element operator of ensembles with few member slots (fewer than
+// 64), of the compact rows of the convergence tail, and of the single-member
+// application: Section 2.2, Eq. 1 and 2.
+//
+// A wavefront of the wide kernels (kernels.hip) covers one element and 64
+// members.  With fewer slots its lanes hold different elements, so nothing is
+// wave-uniform, the nodal loads scatter, and a small mesh leaves the chip
+// nearly empty: what counts then is the number of round trips to memory in a
+// block's chain and the number of launches, and on a large mesh the bytes of
+// the intermediate sums.
+#include "device.hpp"
+
+namespace nlth {
+
+// Sums of a cluster row's incidences: its list groups p0..p1 in LDS,
+// out[(3 * node + component) * OS + pair].  Lists are padded to groups of four
+// with the entry of rows of zeros, so all loads of a group are issued together:
+// an entry at a time, with a test, was a chain of 48 LDS round trips at a vertex.
+template <typename T>
+__device__ __forceinline__ void row_sums(const uint2* __restrict__ lists, int p0, int p1, const T* __restrict__ out,
+                                         int OS, int lg, int mm, T s[3])
+{
+    s[0] = s[1] = s[2] = 0;
+    uint2 w = lists[p0];
+    for (int p = p0; p < p1; ++p) {
+        const uint2 wn = lists[p + 1];  // (one group past the row: the next row's, or the rows' pointers)
+        const uint32_t en[4] = {w.x & 0xFFFFu, w.x >> 16, w.y & 0xFFFFu, w.y >> 16};
+        T v[4][3];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[q][c] = out[((en[q] >> 6) * 3 + c) * OS + ((en[q] & 63u) << lg) + mm];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) s[c] += v[q][c];
+        w = wn;
+    }
+}
+
+// per-member sums of the threads' values (a thread's are all of member t % MB)
+// to partial[m], in a fixed order: the lanes of a wavefront by
+// exchanges, then the wavefronts one after another (a tree over the block with
+// a barrier a level took 0.9 us of a block's 8)
+__device__ __forceinline__ void slot_partials(double dot, int MB, double* __restrict__ sh, double* __restrict__ partial)
+{
+    const int t = threadIdx.x, nw = blockDim.x >> 6;
+    for (int o = 32; o >= MB; o >>= 1) dot += __shfl_xor(dot, o);
+    __syncthreads();
+    if ((t & 63) < MB) sh[(t >> 6) * MB + (t & 63)] = dot;
+    __syncthreads();
+    if (t < MB) {
+        double a = 0.0;
+        for (int w = 0; w < nw; ++w) a += sh[w * MB + t];
+        partial[t] = a;
+    }
+}
+
+// Shape of the kernel for 1 << LG member lanes: up to 8 slots the wide clusters
+// (64 elements: a block then has 64 to 512 lanes of work and 2.6 rows go out per
+// element), the regular ones (12 elements, 3.75 rows) with 16 and 32, whose
+// nodal values would not fit the LDS otherwise.
+template <typename T, int LG>
+struct SlotShape {
+    static constexpr bool WIDE = (1 << LG) <= kWideSlots;
+    static constexpr int ELEMS = WIDE ? kWideElems : kClusterElems, NODES = WIDE ? kWideNodes : kClusterNodes;
+    static constexpr int PAIRS = ELEMS << LG, OS = PAIRS + 4;  // element-members; stride of the LDS rows
+    static constexpr int XS = NODES << LG;                      // staged values of a component
+    // nodal values staged in LDS, where a wavefront's lanes read 32 or 64
+    // scattered addresses otherwise (1 slot 19.7 -> 16.1 us below; from 4 slots on
+    // the staging cost more than it saved)
+    static constexpr bool STAGE = LG <= 1;
+    // least threads: a wavefront or two more than the pairs fill, for the row sums
+    // (331,776 elements, FP32, 1 slot: 64 threads 39 us, 128 33, 256 46;
+    // 98,304 elements, 16 slots: 192 threads 92 us, 256 86, 320 146)
+    static constexpr int THREADS = LG == 0 ? 128 : (LG < 4 ? 64 << LG : 16 << LG);
+};
+
+// One block per element cluster, one lane per element-member: forces of all its
+// element-members to LDS, summed there per node row over the cluster's
+// incidence lists (a fixed order), the rows out for the gather.  Blocks after
+// the clusters write the dashpot rows of the boundary nodes.  MB / L groups
+// of L = 1 << LG members.  tl (may be NULL): compact
+// rows, lane k is member tl[1 + k].  partial (may be NULL): the per-member sums
+// of x1 . (operator x1) over the block's rows.  The tables of a cluster (nodes,
+// lists) lie at fixed strides, so a block's chain of dependent loads is
+// tables -> values and element data -> LDS -> rows; one trip is about 0.9 us
+// (2200 cycles: what another kernel has just written comes from beyond the L2).
+// Bound: instruction issue (about 1200 a wavefront) on large meshes, that chain
+// on small ones.  Operator with its node sums and the dashpot on 98,304
+// elements, against element outputs to memory, a gather of ten per element and
+// a dashpot kernel: FP32 with bfloat16 element-mean D 1 slot 45 -> 23 us, 8 slots
+// 89 -> 60, 32 slots 250 -> 197; FP64 1 slot 59 -> 38, 8 slots 226 -> 183, 32 slots
+// 808 -> 675.  Four lanes per element-member, one per integration point, had a
+// shorter chain but 1.5 times the instructions: no faster on small meshes, 124
+// against 45 us (FP32, without the sums) at 8 slots.
+template <typename T, int DK, int MODE, int LG>
+__global__ __launch_bounds__(512) void k_op_slots(DevMesh M, int MB, int nm, int ncb, int nbb, const int* __restrict__ tl,
+                                                 const void* __restrict__ Dv, const int* __restrict__ order,
+                                                 const double* __restrict__ h, const double* __restrict__ mat,
+                                                 StepConst sc, const T* __restrict__ x1, const T* __restrict__ x2,
+                                                 T* __restrict__ rows, const int* __restrict__ active, double dcoef,
+                                                 const double* __restrict__ vI, double* __restrict__ partial)
+{
+    using S = SlotShape<T, LG>;
+    constexpr int L = 1 << LG, OS = S::OS, XS = S::XS;
+    constexpr bool STAGE = S::STAGE && MODE != OP_RHS;
+    extern __shared__ __align__(16) char smem[];
+    const int t = threadIdx.x, NT = blockDim.x;
+    if (tl) nm = min(tl[0], MB);
+    double dot = 0.0;
+    const int blk = (int)blockIdx.x, g = blk / ncb * L, cb = blk % ncb;  // first member of the group; cluster block
+    const int c = (cb % 8) * (ncb / 8) + cb / 8;                        // XCD-contiguous clusters
+    const int ncl_blocks = ncb * (MB / L);
+    if (blk >= ncl_blocks) {
+        dot = boundary_rows<T>(M, MB, nm, mat, dcoef, x1, vI, active, rows + (size_t)M.cl_rows * 3 * MB,
+                               blk - ncl_blocks, nbb, NT);
+        if (partial) slot_partials(dot, MB, (double*)smem, partial + (size_t)(ncb + blk - ncl_blocks) * MB);
+        return;
+    }
+    if (c < M.ncl) {
+        T* out = (T*)smem;  // [33][OS], the last three rows zeros
+        T* xs = out + 33 * OS;  // [3][XS]
+        uint2* lists = (uint2*)(xs + (STAGE ? 3 * XS : 0));
+        uint16_t* lptr = (uint16_t*)(lists + M.cl_list_stride);
+        int* nds = (int*)(lptr + 256);
+        const int4 ch = M.cl_head[c];
+        const int e0 = ch.x, r0 = ch.y, nec = ch.z, ncn = ch.w;
+        const int slot = t >> LG, lane = t & (L - 1), m = g + lane;
+        if constexpr (STAGE) {
+            // the member lanes of a row read its node's three values
+            for (int lr = slot; lr < ncn; lr += NT >> LG) {
+                const size_t x0 = (size_t)M.cl_nodes[(size_t)c * M.cl_node_stride + lr] * 3 * MB + m;
+#pragma unroll
+                for (int cc = 0; cc < 3; ++cc) xs[cc * XS + (lr << LG) + lane] = x1[x0 + (size_t)cc * MB];
+            }
+        } else {
+            for (int i = t; i < ncn; i += NT) nds[i] = M.cl_nodes[(size_t)c * M.cl_node_stride + i];
+        }
+        const uint4* lsrc = (const uint4*)(M.cl_lists + (size_t)c * M.cl_list_stride);
+        for (int i = t; 2 * i < M.cl_list_stride; i += NT) ((uint4*)lists)[i] = lsrc[i];
+        for (int i = t; i < M.cl_node_stride; i += NT) lptr[i] = M.cl_lptr[(size_t)c * M.cl_node_stride + i];
+        for (int i = t; i < 3 * OS; i += NT) out[30 * OS + i] = (T)0;
+        const bool act = m < nm && (!active || active[m]), on = slot < nec && act;
+        const int e = e0 + (slot < nec ? slot : 0);
+        const T* geo = geo_of<T>(M);
+        T gL[4][3];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) gL[k / 3][k % 3] = geo[(size_t)k * M.ne + e];
+        const T vol = geo[(size_t)12 * M.ne + e];
+        const double rho = MODE == OP_K ? 0.0 : matv(mat, M.layer[e], MAT_RHO, MB, m);
+        double he = 0.0;
+        if (sc.damping_mode == 0 && h) he = h[DK == 2 ? (size_t)order[e] : (size_t)e * MB + m];
+        else if (sc.damping_mode == 1) he = sc.h0;
+        T sm, sk, cv = 0;
+        op_scales<T, MODE>(sc, rho, (double)vol, he, sm, sk, cv);
+        // D in blocks of 64 (element, member) pairs; DK 2: FP64 rows of an element
+        // contiguous, in input order
+        constexpr int W = DK == 4 ? 11 : (DK == 1 ? 44 : 84);
+        constexpr size_t B = DK == 0 || DK == 2 ? sizeof(T) : 4;
+        const size_t pe = (size_t)e * MB;
+        const char* Dp = DK == 2 ? (const char*)Dv + (size_t)order[e] * 84 * B
+                                 : (const char*)Dv + ((pe >> 6) * W * 64 + (pe & 63) + m) * B;
+        constexpr uint32_t rs = DK == 2 ? 1 : 64;
+        T f[10][3];
+        if constexpr (STAGE) {
+            const uint4 lw = ((const uint4*)M.cl_lconn)[e];
+            const uint32_t w[3] = {lw.x, lw.y, lw.z};
+            __syncthreads();
+            if (on)
+                element_forces<T, DK == 2 ? 0 : DK, MODE>(
+                    gL, vol, sm, sk, cv, Dp, rs, 0u,
+                    [&](int n, int cc, int) { return xs[cc * XS + (int)(((w[n / 4] >> (8 * (n % 4))) & 0xFFu) << LG) + lane]; },
+                    f);
+        } else if (on) {
+            size_t nb[10];
+#pragma unroll
+            for (int n = 0; n < 10; ++n) nb[n] = (size_t)M.conn[(size_t)n * M.ne + e] * 3 * MB + m;
+            element_forces<T, DK == 2 ? 0 : DK, MODE>(
+                gL, vol, sm, sk, cv, Dp, rs, 0u,
+                [&](int n, int cc, int v) { return (v ? x2 : x1)[nb[n] + (size_t)cc * MB]; }, f);
+        }
+        if (on) {
+#pragma unroll
+            for (int n = 0; n < 10; ++n)
+#pragma unroll
+                for (int cc = 0; cc < 3; ++cc) out[(3 * n + cc) * OS + t] = f[n][cc];
+        }
+        __syncthreads();
+        for (int lr = slot; act && lr < ncn; lr += NT >> LG) {
+            T s[3];
+            row_sums<T>(lists, lptr[lr], lptr[lr + 1], out, OS, LG, lane, s);
+            T* rp = rows + ((size_t)r0 + lr) * 3 * MB + m;
+#pragma unroll
+            for (int cc = 0; cc < 3; ++cc) {
+                rp[(size_t)cc * MB] = s[cc];
+                if (partial) {
+                    T xv;
+                    if constexpr (STAGE) xv = xs[cc * XS + (lr << LG) + lane];
+                    else xv = x1[((size_t)nds[lr] * 3 + cc) * MB + m];
+                    dot += (double)xv * (double)s[cc];
+                }
+            }
+        }
+    }
+    if (partial) slot_partials(dot, L, (double*)smem, partial + (size_t)cb * MB + g);
+}
+
+template <typename T, int DK, int MODE, int LG>
+static void op_launch(hipStream_t s, const DevMesh& M, int MB, int nm, const int* tl, const void* D, const int* order,
+                      const double* h, const double* mat, StepConst sc, const T* x1, const T* x2, T* rows,
+                      const int* active, double dcoef, const double* vI, double* partial, int* nblk)
+{
+    using S = SlotShape<T, LG>;
+    const int NT = std::max(S::THREADS, ((M.cl_max_elems << LG) + 63) / 64 * 64);
+    const int ncb = (M.ncl + 7) / 8 * 8;
+    // boundary nodes per block: up to 8 lanes of a wavefront share a node
+    const int parts = 64 / MB < 8 ? 64 / MB : 8, npb = NT / (MB * parts);
+    const long nb = dcoef != 0.0 ? ((long)M.nbn + npb - 1) / npb : 0;
+    const int nbb = (int)(nb < kDashpotBlocks ? nb : kDashpotBlocks);
+    if (nblk) *nblk = ncb + nbb;
+    size_t lds = ((size_t)33 * S::OS + (S::STAGE && MODE != OP_RHS ? 3 * S::XS : 0)) * sizeof(T);
+    lds += (size_t)M.cl_list_stride * 8 + 512 + (size_t)M.cl_node_stride * 4;
+    hipLaunchKernelGGL((k_op_slots<T, DK, MODE, LG>), dim3(ncb * (MB >> LG) + nbb), dim3(NT), lds, s, M, MB, nm, ncb,
+                       nbb, tl, D, order, h, mat, sc, x1, x2, rows, active, dcoef, vI, partial);
+}
+
+template <typename T, int DK, int MODE>
+static void op_slots(hipStream_t s, const DevMesh& M, int MB, int nm, const int* tl, const void* D, const double* h,
+                     const double* mat, StepConst sc, const T* x1, const T* x2, T* rows, const int* active,
+                     double dcoef, const double* vI, double* partial, int* nblk)
+{
+#define NLTH_LG(LG) \
+    op_launch<T, DK, MODE, LG>(s, M, MB, nm, tl, D, nullptr, h, mat, sc, x1, x2, rows, active, dcoef, vI, partial, nblk)
+    switch (MB) {
+    case 1: NLTH_LG(0); break;
+    case 2: NLTH_LG(1); break;
+    case 4: NLTH_LG(2); break;
+    case 8: NLTH_LG(3); break;
+    case 16: NLTH_LG(4); break;
+    case 32:
+        // FP64: two groups of 16 lanes (a block of 12 x 32 lanes fills the registers
+        // of a CU alone, with nothing to run across its barriers)
+        if constexpr (sizeof(T) == 8) NLTH_LG(4);
+        else NLTH_LG(5);
+        break;
+    }
+#undef NLTH_LG
+}
+
+void launch_op_slots64(hipStream_t s, OpMode mode, const DevMesh& M, int MB, int nm, const double* D,
+                       const double* h, const double* mat, StepConst sc, const double* x1, const double* x2,
+                       double* rows, const int* active, double dcoef, const double* vI, double* partial, int* nblk)
+{
+    switch (mode) {
+    case OP_A: op_slots<double, 0, OP_A>(s, M, MB, nm, nullptr, D, h, mat, sc, x1, x2, rows, active, dcoef, vI, partial, nblk); break;
+    case OP_K: op_slots<double, 0, OP_K>(s, M, MB, nm, nullptr, D, h, mat, sc, x1, x2, rows, active, dcoef, vI, partial, nblk); break;
+    case OP_M: op_slots<double, 0, OP_M>(s, M, MB, nm, nullptr, D, h, mat, sc, x1, x2, rows, active, dcoef, vI, partial, nblk); break;
+    case OP_RHS: op_slots<double, 0, OP_RHS>(s, M, MB, nm, nullptr, D, h, mat, sc, x1, x2, rows, active, dcoef, vI, partial, nblk); break;
+    }
+}
+
+void launch_op_slots32(hipStream_t s, const DevMesh& M, int MB, int nm, const float* D32, const uint32_t* D16,
+                       bool d16_mean, const double* h, const double* mat, StepConst sc, const float* x, float* rows,
+                       const int* active, double dcoef, double* partial, int* nblk)
+{
+    const float* none = nullptr;
+    if (D16 && d16_mean)
+        op_slots<float, 4, OP_A>(s, M, MB, nm, nullptr, D16, h, mat, sc, x, none, rows, active, dcoef, nullptr, partial, nblk);
+    else if (D16)
+        op_slots<float, 1, OP_A>(s, M, MB, nm, nullptr, D16, h, mat, sc, x, none, rows, active, dcoef, nullptr, partial, nblk);
+    else
+        op_slots<float, 0, OP_A>(s, M, MB, nm, nullptr, D32, h, mat, sc, x, none, rows, active, dcoef, nullptr, partial, nblk);
+}
+
+void launch_op_input64(hipStream_t s, OpMode mode, const DevMesh& M, const int* order, const double* D,
+                       const double* h, const double* mat, StepConst sc, const double* x, double* rows, double dcoef)
+{
+    const double* none = nullptr;
+    switch (mode) {
+    case OP_A: op_launch<double, 2, OP_A, 0>(s, M, 1, 1, nullptr, D, order, h, mat, sc, x, none, rows, nullptr, dcoef, nullptr, nullptr, nullptr); break;
+    case OP_K: op_launch<double, 2, OP_K, 0>(s, M, 1, 1, nullptr, D, order, h, mat, sc, x, none, rows, nullptr, dcoef, nullptr, nullptr, nullptr); break;
+    default: op_launch<double, 2, OP_M, 0>(s, M, 1, 1, nullptr, D, order, h, mat, sc, x, none, rows, nullptr, dcoef, nullptr, nullptr, nullptr); break;
+    }
+}
+
+// operator A on the compact rows of the convergence tail (G = 16 or 32 lanes)
+template <typename T, int DK>
+static void op_tail(hipStream_t s, const DevMesh& M, int G, const int* tl, const void* cD, const double* ch,
+                    const double* cmat, StepConst sc, const T* x, T* co)
+{
+    const T* none = nullptr;
+    op_slots<T, DK, OP_A>(s, M, G, G, tl, cD, ch, cmat, sc, x, none, co, nullptr, 0.0, nullptr, nullptr, nullptr);
+}
+void launch_ebe64_ctail(hipStream_t s, const DevMesh& M, int G, const int* tl, const double* cD, const double* ch,
+                        const double* cmat, StepConst sc, const double* x, double* co)
+{
+    op_tail<double, 0>(s, M, G, tl, cD, ch, cmat, sc, x, co);
+}
+
+void launch_ebe32_ctail(hipStream_t s, const DevMesh& M, int G, const int* tl, const uint32_t* cD, const double* ch,
+                        const double* cmat, StepConst sc, const float* x, float* co)
+{
+    op_tail<float, 4>(s, M, G, tl, cD, ch, cmat, sc, x, co);
+}
+
+}  // namespace nlth

@@ -1259,9 +1259,41 @@ __global__ __launch_bounds__(256) void k_finalize(int stage, int nd, int MB, int
     }
 }
 
-void launch_finalize(hipStream_t s, FinalizeStage st, int nd, int MB, int nm, const double* partial, int nblk,
-                     CgScalars cs, double tol2, int maxit)
+// Sums of nd x nblk partial rows over runs of consecutive rows, coalesced:
+// fold[(k * kFoldBlocks + b) * MB + m].  One block per member reading a column
+// of thousands of rows (8 bytes of every row) took 24 us at 16,384 rows of 64.
+__global__ __launch_bounds__(256) void k_fold(int MB, const double* __restrict__ partial, int nblk,
+                                             double* __restrict__ fold)
 {
+    const int k = blockIdx.y, t = threadIdx.x;
+    const int per = (nblk + kFoldBlocks - 1) / kFoldBlocks;
+    const int b0 = blockIdx.x * per, b1 = b0 + per < nblk ? b0 + per : nblk;
+    const double* p = partial + (size_t)k * nblk * MB;
+    __shared__ double sh[256];
+    // thread t takes member t % MB of every (256 / MB)-th row (MB <= 256 here)
+    const int m = t % MB, rl = t / MB, rpb = 256 / MB;
+    double a = 0.0;
+#pragma unroll 4
+    for (int b = b0 + rl; b < b1; b += rpb) a += p[(size_t)b * MB + m];
+    sh[t] = a;
+    __syncthreads();
+    for (int s = 128; s >= MB; s >>= 1) {
+        if (t < s) sh[t] += sh[t + s];
+        __syncthreads();
+    }
+    if (t < MB) fold[((size_t)k * kFoldBlocks + blockIdx.x) * MB + t] = sh[t];
+}
+
+void launch_finalize(hipStream_t s, FinalizeStage st, int nd, int MB, int nm, const double* partial, int nblk,
+                     double* fold, CgScalars cs, double tol2, int maxit)
+{
+    // the fold is a launch more (about 3 us): it pays once a column takes
+    // longer than that to read
+    if (nd > 0 && nblk > 2048 && MB <= 256) {
+        hipLaunchKernelGGL(k_fold, dim3(kFoldBlocks, nd), dim3(256), 0, s, MB, partial, nblk, fold);
+        partial = fold;
+        nblk = kFoldBlocks;
+    }
     hipLaunchKernelGGL(k_finalize, dim3(nm), dim3(256), 0, s, (int)st, nd, MB, nm, partial, nblk, cs, tol2, maxit);
 }
 
