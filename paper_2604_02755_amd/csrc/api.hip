@@ -783,7 +783,6 @@ int64_t ensemble_bytes(const Mesh& m, const Problem& p, int MB, bool paged)
     if (p.precision == NLTH_MIXED) {
         bytes += 5 * ndof * MB * 4;
         bytes += (int64_t)(2 * kLanczosMax * 8 + (2 * kChebMax + 1) * 4 + 16) * MB;  // Lanczos, Chebyshev tables
-        if (MB >= 64 && MB <= 256) bytes += (int64_t)m.nbn * 3 * MB * 4;           // dashpot rows
     }
     bytes += (int64_t)m.ne * 4 * 21 * MB * 8;               // D64
     if (p.precision == NLTH_MIXED)
@@ -919,7 +918,6 @@ void Ens::create(Ctx* c, const Mesh* m, const Problem& prob, int member_pad)
         launch_fill32(s, chebc.as<float>(), 0.0f, (long)(2 * kChebMax + 1) * MB);
         cheb_bounds.alloc(bg, (size_t)(2 * MB + 1) * 8);  // per-member lo, hi; the running upper bound
         launch_fill(s, cheb_bounds.as<double>(), 0.0, (long)2 * MB + 1);
-        if (MB >= 64 && MB <= 256 && m->nbn > 0) qb.alloc(bg, (size_t)m->nbn * 3 * MB * 4);
     }
     EB = MB >= 64 ? 1 : 64 / MB;
     ne_pad = (m->ne + EB - 1) / EB * EB;
@@ -999,10 +997,11 @@ void Ens::create(Ctx* c, const Mesh* m, const Problem& prob, int member_pad)
     launch_fill(s, vmax.as<double>(), 0.0, (long)MB * std::max(1, m->nrecv));
     iters_dev.alloc(bg, (size_t)MB * ns_steps * 2 * 4);
     NLTH_HIP(hipMemsetAsync(iters_dev.p, 0, iters_dev.bytes, s));
-    // with the few-slot operator a row per cluster and boundary block
-    const size_t op_rows = MB < 64 ? (size_t)m->clusters(MB).n + 8 + kDashpotBlocks : 0;
-    partial.alloc(bg, (std::max<size_t>(kPartialRows, op_rows) + 3 * kFoldBlocks) * MB * 8);
-    fold = partial.as<double>() + std::max<size_t>(kPartialRows, op_rows) * MB;
+    // partial sums: of the vector kernels, or of the operator (a row per cluster
+    // and boundary block, the latter rounded up to a multiple of 8); then the fold
+    const size_t prows = std::max<size_t>(kPartialRows, MB <= 256 ? (size_t)m->clusters(MB).n + 16 + kDashpotBlocks : 0);
+    partial.alloc(bg, (prows + 3 * kFoldBlocks) * MB * 8);
+    fold = partial.as<double>() + prows * MB;
     // CG scalars: 12 double arrays and 9 int arrays of MB
     scal.alloc(bg, (size_t)MB * (12 * 8 + 9 * 4) + 64);
     NLTH_HIP(hipMemsetAsync(scal.p, 0, scal.bytes, s));
@@ -1070,35 +1069,51 @@ void Ens::destroy()
     own_s = nullptr;
 }
 
+// Rows of the operator of `mode` applied to x1 (and x2 for the right-hand
+// side), with dcoef != 0 the dashpot rows of dcoef * C_abs x1 (+ 2 C_base vI),
+// and with nblk the per-member block partials of x1 . y (gather paths).
+void Ens::op_rows(OpMode mode, const double* x1, const double* x2, const int* act, double dcoef, const double* vI,
+                  int* nblk)
+{
+    const DevMesh dm = mesh->dev(MB);
+    double* pd = nblk ? partial.as<double>() : nullptr;
+    if (scatter == 2)
+        launch_ebe_cluster64(s, mode, dm, MB, nm, D64.as<double>(), h.as<double>(), mat.as<double>(), sc, x1, x2,
+                             cbuf.as<double>(), act, dcoef, vI, pd, nblk);
+    else
+        launch_op_slots64(s, mode, dm, MB, nm, D64.as<double>(), h.as<double>(), mat.as<double>(), sc, x1, x2,
+                          cbuf.as<double>(), act, dcoef, vI, pd, nblk);
+}
+
+// the same with the inner operator's arithmetic (FP32, D in FP32 or bfloat16), A only
+void Ens::op_rows32(const float* x, const int* act, int* nblk)
+{
+    const DevMesh dm = mesh->dev(MB);
+    double* pd = nblk ? partial.as<double>() : nullptr;
+    set_cluster_blocks(cluster_blocks);
+    if (scatter == 2)
+        launch_ebe_cluster32(s, dm, MB, nm, D32.as<float>(), D16.as<uint32_t>(), d16_mean, h.as<double>(),
+                             mat.as<double>(), sc, x, (float*)cbuf.p, act, 2.0 / P.dt, pd, nblk);
+    else
+        launch_op_slots32(s, dm, MB, nm, D32.as<float>(), D16.as<uint32_t>(), d16_mean, h.as<double>(),
+                          mat.as<double>(), sc, x, (float*)cbuf.p, act, 2.0 / P.dt, pd, nblk);
+}
+
 // y = operator of `mode` applied to x1 (and x2 for the right-hand side)
-//     + bscale * base + the boundary dashpot dcoef * C_abs x1 (+ 2 C_base vI),
-// and with nblk the per-member block partials of x1 . y in `partial`.
-// Gather paths: a launch writes cluster rows (the few-slot kernels the
-// dashpot rows and the dot as well), a second sums them per node with the
+//     + bscale * base + the boundary dashpot dcoef * C_abs x1 (+ 2 C_base vI).
+// Gather paths: a launch writes the rows, a second sums them per node with the
 // base.  Colour path: one launch per colour adds the forces into y, then the
-// dashpot and the dot as launches of their own.
+// dashpot as a launch of its own.
 void Ens::ebe(OpMode mode, const double* x1, const double* x2, double* y, const int* act, const double* base,
-              double bscale, double dcoef, const double* vI, int* nblk)
+              double bscale, double dcoef, const double* vI)
 {
     const DevMesh dm = mesh->dev(MB);
     set_ebe_block(ebe_block);
-    set_cluster_blocks(cluster_blocks);
     if (scatter != 1) {
         hipEvent_t t0;
         tstart(t0);
-        double* pd = nblk ? partial.as<double>() : nullptr;
-        double* rows = cbuf.as<double>();
-        if (scatter == 2) {
-            launch_ebe_cluster64(s, mode, dm, MB, nm, D64.as<double>(), h.as<double>(), mat.as<double>(), sc, x1, x2,
-                                 rows, act);
-            launch_gather<double>(s, dm, MB, nm, rows, false, base, bscale, y, act, x1, pd, nblk);
-            if (dcoef != 0.0)
-                launch_dashpot<double>(s, dm, MB, nm, mat.as<double>(), P.nl, dcoef, x1, y, vI, act, pd, nblk);
-        } else {
-            launch_op_slots64(s, mode, dm, MB, nm, D64.as<double>(), h.as<double>(), mat.as<double>(), sc, x1, x2,
-                              rows, act, dcoef, vI, pd, nblk);
-            launch_gather<double>(s, dm, MB, nm, rows, dcoef != 0.0, base, bscale, y, act, nullptr, nullptr, nullptr);
-        }
+        op_rows(mode, x1, x2, act, dcoef, vI, nullptr);
+        launch_gather<double>(s, dm, MB, nm, cbuf.as<double>(), dcoef != 0.0, base, bscale, y, act);
         tstop(t0, &pc_ebe64, (int64_t)mesh->ne * nm);
         return;
     }
@@ -1113,38 +1128,23 @@ void Ens::ebe(OpMode mode, const double* x1, const double* x2, double* y, const 
                            x1, x2, y, act);
         tstop(t0, &pc_ebe64, (int64_t)(e1 - e0) * nm);
     }
-    if (dcoef != 0.0) launch_dashpot<double>(s, dm, MB, nm, mat.as<double>(), P.nl, dcoef, x1, y, vI, act);
-    if (nblk) dots(1, x1, y, nullptr, nullptr, nullptr, nullptr, *nblk);
+    if (dcoef != 0.0) launch_dashpot<double>(s, dm, MB, nm, mat.as<double>(), dcoef, x1, y, vI, act);
 }
 
 // y = A x with the inner operator's arithmetic (FP32, D in FP32 or bfloat16),
-// dashpot included; with nblk the per-member block partials of x . y
-void Ens::ebe32(const float* x, float* y, const int* act, int* nblk)
+// dashpot included
+void Ens::ebe32(const float* x, float* y, const int* act)
 {
     const DevMesh dm = mesh->dev(MB);
     set_ebe_block(ebe_block);
-    set_cluster_blocks(cluster_blocks);
-    const double dc = 2.0 / P.dt;
     if (scatter != 1) {
-        float* rows = (float*)cbuf.p;
-        double* pd = nblk ? partial.as<double>() : nullptr;
         hipEvent_t t0;
         tstart(t0);
-        if (scatter == 2)
-            launch_ebe_cluster32(s, dm, MB, nm, D32.as<float>(), D16.as<uint32_t>(), h.as<double>(), mat.as<double>(),
-                                 sc, x, rows, act, d16_mean);
-        else
-            launch_op_slots32(s, dm, MB, nm, D32.as<float>(), D16.as<uint32_t>(), d16_mean, h.as<double>(),
-                              mat.as<double>(), sc, x, rows, act, dc, pd, nblk);
+        op_rows32(x, act, nullptr);
         tstop(t0, &pc_ebe32, (int64_t)mesh->ne * nm);
         tstart(t0);
-        if (scatter == 2)
-            launch_gather<float>(s, dm, MB, nm, rows, false, nullptr, 0.0f, y, act, x, pd, nblk);
-        else
-            launch_gather<float>(s, dm, MB, nm, rows, true, nullptr, 0.0f, y, act, nullptr, nullptr, nullptr);
+        launch_gather<float>(s, dm, MB, nm, (const float*)cbuf.p, true, nullptr, 0.0f, y, act);
         tstop(t0, &pc_gather32, (int64_t)mesh->nn * nm);
-        if (scatter == 2)
-            launch_dashpot<float>(s, dm, MB, nm, mat.as<double>(), P.nl, (float)dc, x, y, nullptr, act, pd, nblk);
         return;
     }
     launch_fill32(s, y, 0.0f, (long)ndof * MB);
@@ -1156,17 +1156,14 @@ void Ens::ebe32(const float* x, float* y, const int* act, int* nblk)
                      sc, x, y, act, d16_mean);
         tstop(t0, &pc_ebe32, (int64_t)(e1 - e0) * nm);
     }
-    launch_dashpot<float>(s, dm, MB, nm, mat.as<double>(), P.nl, (float)dc, x, y, nullptr, act);
-    if (nblk)
-        launch_dotsv<float>(s, 1, x, y, nullptr, nullptr, nullptr, nullptr, ndof, MB, nm, act, partial.as<double>(),
-                            nblk);
+    launch_dashpot<float>(s, dm, MB, nm, mat.as<double>(), (float)(2.0 / P.dt), x, y, nullptr, act);
 }
 
 void Ens::build_rhs()
 {
     // b = f - q + C v + M (a + 4/dt v), f = 2 C_base v_I
     ebe(OP_RHS, v.as<double>(), a.as<double>(), b.as<double>(), stepping.as<int>(), q.as<double>(), -1.0, 1.0,
-        vI_cur.as<double>(), nullptr);
+        vI_cur.as<double>());
 }
 
 // Block-Jacobi diagonal: from D per point (FP64), or, for the mixed path with
@@ -1215,14 +1212,15 @@ int Ens::read_any_active(const int* flags)
     return 0;
 }
 
-void Ens::fin(FinalizeStage st, int nd, int nblk, double tol2, int maxit)
+// tl: the partials are rows of G lanes, the listed members'
+void Ens::fin(FinalizeStage st, int nd, int nblk, double tol2, int maxit, const int* tl, int G)
 {
-    launch_finalize(s, st, nd, MB, nm, partial.as<double>(), nblk, fold, cs, tol2, maxit);
+    launch_finalize(s, st, nd, MB, nm, partial.as<double>(), nblk, fold, tl, G, cs, tol2, maxit);
 }
 
-void Ens::apply_A64(const double* x, double* y, const int* act, int* nblk)
+void Ens::apply_A64(const double* x, double* y, const int* act)
 {
-    ebe(OP_A, x, nullptr, y, act, nullptr, 0.0, 2.0 / P.dt, nullptr, nblk);
+    ebe(OP_A, x, nullptr, y, act, nullptr, 0.0, 2.0 / P.dt, nullptr);
 }
 
 // FP64 block-Jacobi PCG (Section 2.2): x0 = previous increment
@@ -1240,7 +1238,6 @@ void Ens::solve_pcg()
                      z.as<double>(), p.as<double>(), st, pd, &nblk);
     fin(FIN_START, 3, nblk, tol2, P.cg_maxit);
     launch_zero_if_b0(s, n, MB, nm, x, cs.bb, st);
-    launch_p_update<double>(s, n, MB, nm, z.as<double>(), p.as<double>(), nullptr, nullptr, nullptr);
     if (!read_any_active(act)) return;
     for (;;) {
         if (!tail64_g) enter_tail64();  // with few members left: compact rows
@@ -1282,15 +1279,14 @@ bool Ens::enter_tail64()
 }
 
 // FP64 compact rows of 32 lanes: D per point (elements padded to blocks of
-// 4), h, material, inverse blocks, five CG vectors, the operator's cluster
-// rows (at most 10 per element: sized as element outputs)
+// 4), h, material, inverse blocks, five CG vectors, the operator's rows
 bool Ens::alloc_tail64()
 {
     if (tail64_mem.p) return true;
     const size_t ne4 = ((size_t)mesh->ne + 3) / 4 * 4, nn = mesh->nn, L = 32;
     const size_t nv = 3 * nn * L * 8;
     const size_t sz[10] = {ne4 * 84 * L * 8, (size_t)mesh->ne * L * 8, (size_t)P.nl * MAT_N * L * 8,
-                           nn * 6 * L * 8, nv, nv, nv, nv, nv, (size_t)mesh->ne * 30 * L * 8};
+                           nn * 6 * L * 8, nv, nv, nv, nv, nv, (size_t)(mesh->cl.rows + mesh->nbn) * 3 * L * 8};
     size_t off[10], tot = 0;
     for (int i = 0; i < 10; ++i) {
         off[i] = tot;
@@ -1350,15 +1346,13 @@ void Ens::tail64_iter()
     int nblk;
     hipEvent_t t0;
     tstart(t0);
-    launch_ebe64_ctail(s, dm, tail64_g, tl, tc.D, tc.h, tc.mat, sc, tc.p, tc.f);
-    launch_gather_tail<double>(s, dm, MB, nm, tail64_g, tl, tc.f, tc.Ap, act, tc.p, pd, &nblk);
-    launch_dashpot_tail<double>(s, dm, MB, nm, tail64_g, tl, tc.mat, 2.0 / P.dt, tc.p, tc.Ap, act, pd, &nblk);
+    launch_ebe64_ctail(s, dm, tail64_g, tl, tc.D, tc.h, tc.mat, sc, tc.p, tc.f, 2.0 / P.dt, pd, &nblk);
     tstop(t0, &pc_tail32, (int64_t)mesh->ne * tail_count);
-    fin(FIN_ALPHA, 1, nblk, tol2, P.cg_maxit);
-    launch_tail_pcg_update(s, mesh->nn, MB, nm, tail64_g, tl, tc.x, tc.r, tc.z, tc.p, tc.Ap, tc.pinv, cs.alpha, act,
-                           pd, &nblk);
+    fin(FIN_ALPHA, 1, nblk, tol2, P.cg_maxit, tl, tail64_g);
+    launch_rows_update<double>(s, UPD_PZ, dm, MB, nm, tail64_g, tl, tc.f, tc.r, tc.z, tc.pinv, nullptr, nullptr,
+                               cs.alpha, act, pd, &nblk);
     fin(FIN_BETA, 2, nblk, tol2, P.cg_maxit);
-    launch_tail_p_update(s, ndof, nm, tail64_g, tl, tc.z, tc.p, cs.beta, act);
+    launch_tail_pz<double>(s, ndof, nm, tail64_g, tl, tc.x, tc.p, tc.z, cs.alpha, cs.beta, cs.inner_upd);
 }
 
 // inner FP32 block-Jacobi PCG: z ~ A^-1 r to inner_tol relative (preconditioner)
@@ -1402,12 +1396,11 @@ void Ens::update_tail()
     if (na == 0 || na > tail_max) return;
     if (!tail_mem.p) {
         // compact rows of 32 lanes: D (elements padded to blocks of 4), h,
-        // material, inverse blocks, five CG vectors, the operator's cluster
-        // rows (at most 10 per element: sized as element outputs)
+        // material, inverse blocks, five CG vectors, the operator's rows
         const size_t ne4 = ((size_t)mesh->ne + 3) / 4 * 4, nn = mesh->nn, L = 32;
         const size_t sz[10] = {ne4 * 11 * L * 4, (size_t)mesh->ne * L * 8, (size_t)P.nl * MAT_N * L * 8,
                                nn * 6 * L * 4, nn * 3 * L * 4, nn * 3 * L * 4, nn * 3 * L * 4, nn * 3 * L * 4,
-                               nn * 3 * L * 4, (size_t)mesh->ne * 30 * L * 4};
+                               nn * 3 * L * 4, (size_t)(mesh->cl.rows + mesh->nbn) * 3 * L * 4};
         size_t off[10], tot = 0;
         for (int i = 0; i < 10; ++i) {
             off[i] = tot;
@@ -1459,14 +1452,13 @@ void Ens::tail_iter()
     int nblk;
     hipEvent_t t0;
     tstart(t0);
-    launch_ebe32_ctail(s, dm, tail_g, tl, tb.D, tb.h, tb.mat, sc, tb.ip, tb.f);
-    launch_gather_tail(s, dm, MB, nm, tail_g, tl, tb.f, tb.Ap, iact, tb.ip, pd, &nblk);
-    launch_dashpot_tail(s, dm, MB, nm, tail_g, tl, tb.mat, (float)(2.0 / P.dt), tb.ip, tb.Ap, iact, pd, &nblk);
+    launch_ebe32_ctail(s, dm, tail_g, tl, tb.D, tb.h, tb.mat, sc, tb.ip, tb.f, 2.0 / P.dt, pd, &nblk);
     tstop(t0, &pc_tail32, (int64_t)mesh->ne * tail_count);
-    fin(FIN_IN_ALPHA, 1, nblk, tol2, P.inner_maxit);
-    launch_tail_update(s, mesh->nn, MB, nm, tail_g, tl, tb.ir, tb.w, tb.Ap, tb.pinv, cs.ialpha, iact, pd, &nblk);
+    fin(FIN_IN_ALPHA, 1, nblk, tol2, P.inner_maxit, tl, tail_g);
+    launch_rows_update<float>(s, UPD_PZ, dm, MB, nm, tail_g, tl, tb.f, tb.ir, tb.w, tb.pinv, nullptr, nullptr,
+                              cs.ialpha, iact, pd, &nblk);
     fin(FIN_IN_BETA, 2, nblk, tol2, P.inner_maxit);
-    launch_tail_pz(s, ndof, nm, tail_g, tl, tb.iz, tb.ip, tb.w, cs.ialpha, cs.ibeta, cs.inner_upd);
+    launch_tail_pz<float>(s, ndof, nm, tail_g, tl, tb.iz, tb.ip, tb.w, cs.ialpha, cs.ibeta, cs.inner_upd);
 }
 
 // Chebyshev inner solve of degree inner_maxit for the outer-active members,
@@ -1483,29 +1475,26 @@ void Ens::cheb_body()
                       act);
     float* d = ip.as<float>();
     float* dn = iw.as<float>();
-    const bool fused = scatter == 2 && (qb.p || dm.nbn == 0);
+    const bool fused = scatter != 1;
     for (int k = 0; k < n; ++k) {
         const bool last = k + 1 == n;
         if (fused) {
-            set_cluster_blocks(cluster_blocks);
             hipEvent_t t0;
             tstart(t0);
-            launch_ebe_cluster32(s, dm, MB, nm, D32.as<float>(), D16.as<uint32_t>(), h.as<double>(),
-                                 mat.as<double>(), sc, d, (float*)cbuf.p, act, d16_mean);
+            op_rows32(d, act, nullptr);
             tstop(t0, &pc_ebe32, (int64_t)mesh->ne * nm);
-            launch_dashpot_rows(s, dm, MB, nm, mat.as<double>(), (float)(2.0 / P.dt), d, qb.as<float>(), act);
             tstart(t0);
-            launch_gather_cheb(s, dm, MB, nm, k, last, (const float*)cbuf.p, qb.as<float>(), iz.as<float>(),
-                               ir.as<float>(), d, dn, pv, cheb, act);
+            launch_gather_cheb(s, dm, MB, nm, k, last, (const float*)cbuf.p, iz.as<float>(), ir.as<float>(), d, dn, pv,
+                               cheb, act);
             tstop(t0, &pc_gather32, (int64_t)mesh->nn * nm);
         } else {
-            ebe32(d, iAp.as<float>(), act, nullptr);
+            ebe32(d, iAp.as<float>(), act);
             launch_cheb_update(s, mesh->nn, MB, nm, k, last, iz.as<float>(), ir.as<float>(), d, iAp.as<float>(), dn,
                                pv, cheb, act);
         }
         std::swap(d, dn);
     }
-    launch_finalize(s, FIN_CHEB_COUNT, 0, MB, nm, partial.as<double>(), 0, fold, cs, 0.0, n);
+    launch_finalize(s, FIN_CHEB_COUNT, 0, MB, nm, partial.as<double>(), 0, fold, nullptr, 0, cs, 0.0, n);
 }
 
 // Largest eigenvalue of the block-Jacobi preconditioned inner operator, from
@@ -1580,12 +1569,35 @@ void Ens::inner_iter()
     const int* iact = cs.inner_active;
     const double tol2 = P.inner_tol * P.inner_tol;
     double* pd = partial.as<double>();
-    ebe32(ip.as<float>(), iAp.as<float>(), iact, &nblk);
-    fin(FIN_IN_ALPHA, 1, nblk, tol2, P.inner_maxit);
-    launch_inner_update(s, mesh->nn, MB, nm, ir.as<float>(), iw.as<float>(), iAp.as<float>(), pinv32.as<float>(),
-                        cs.ialpha, iact, pd, &nblk);
+    hipEvent_t t0;
+    tstart(t0);
+    if (scatter == 0) {
+        op_rows32(ip.as<float>(), iact, &nblk);
+        tstop(t0, &pc_ebe32, (int64_t)mesh->ne * nm);
+        fin(FIN_IN_ALPHA, 1, nblk, tol2, P.inner_maxit);
+        tstart(t0);
+        launch_rows_update<float>(s, UPD_PZ, mesh->dev(MB), MB, nm, 0, nullptr, (const float*)cbuf.p, ir.as<float>(),
+                                  iw.as<float>(), pinv32.as<float>(), nullptr, nullptr, cs.ialpha, iact, pd, &nblk);
+        tstop(t0, &pc_gather32, (int64_t)mesh->nn * nm);
+    } else {
+        if (scatter == 2) {
+            op_rows32(ip.as<float>(), iact, nullptr);
+            tstop(t0, &pc_ebe32, (int64_t)mesh->ne * nm);
+            tstart(t0);
+            launch_gather_dot(s, mesh->dev(MB), MB, nm, (const float*)cbuf.p, iAp.as<float>(), iact, ip.as<float>(), pd,
+                              &nblk);
+            tstop(t0, &pc_gather32, (int64_t)mesh->nn * nm);
+        } else {
+            ebe32(ip.as<float>(), iAp.as<float>(), iact);
+            launch_dotsv<float>(s, 1, ip.as<float>(), iAp.as<float>(), nullptr, nullptr, nullptr, nullptr, ndof, MB,
+                                nm, iact, pd, &nblk);
+        }
+        fin(FIN_IN_ALPHA, 1, nblk, tol2, P.inner_maxit);
+        launch_inner_update(s, mesh->nn, MB, nm, ir.as<float>(), iw.as<float>(), iAp.as<float>(), pinv32.as<float>(),
+                            cs.ialpha, iact, pd, &nblk);
+    }
     fin(FIN_IN_BETA, 2, nblk, tol2, P.inner_maxit);
-    launch_inner_pz(s, n, MB, nm, iz.as<float>(), ip.as<float>(), iw.as<float>(), cs.ialpha, cs.ibeta, cs.inner_upd);
+    launch_pz<float>(s, n, MB, nm, iz.as<float>(), ip.as<float>(), iw.as<float>(), cs.ialpha, cs.ibeta, cs.inner_upd);
 }
 
 // one FP64 block-Jacobi PCG iteration
@@ -1601,12 +1613,35 @@ void Ens::pcg_iter()
     const int* act = cs.active;
     const double tol2 = P.cg_tol * P.cg_tol;
     double* pd = partial.as<double>();
-    apply_A64(p.as<double>(), Ap.as<double>(), act, &nblk);
-    fin(FIN_ALPHA, 1, nblk, tol2, P.cg_maxit);
+    op_alpha(FIN_ALPHA, tol2, act);
+    if (scatter != 1) {
+        launch_rows_update<double>(s, UPD_PZ, mesh->dev(MB), MB, nm, 0, nullptr, cbuf.as<double>(), r.as<double>(),
+                                   z.as<double>(), pinv.as<double>(), nullptr, nullptr, cs.alpha, act, pd, &nblk);
+        fin(FIN_BETA, 2, nblk, tol2, P.cg_maxit);
+        launch_pz<double>(s, n, MB, nm, x, p.as<double>(), z.as<double>(), cs.alpha, cs.beta, cs.inner_upd);
+        return;
+    }
     launch_pcg_update(s, mesh->nn, MB, nm, x, r.as<double>(), z.as<double>(), p.as<double>(), Ap.as<double>(),
                       pinv.as<double>(), cs.alpha, act, pd, &nblk);
     fin(FIN_BETA, 2, nblk, tol2, P.cg_maxit);
     launch_p_update<double>(s, n, MB, nm, z.as<double>(), p.as<double>(), cs.beta, act, nullptr);
+}
+
+// A p and alpha of the outer CG: the operator's rows (colour path: Ap itself),
+// p . A p, the stage
+void Ens::op_alpha(FinalizeStage stage, double tol2, const int* act)
+{
+    int nblk;
+    if (scatter != 1) {
+        hipEvent_t t0;
+        tstart(t0);
+        op_rows(OP_A, p.as<double>(), nullptr, act, 2.0 / P.dt, nullptr, &nblk);
+        tstop(t0, &pc_ebe64, (int64_t)mesh->ne * nm);
+    } else {
+        apply_A64(p.as<double>(), Ap.as<double>(), act);
+        dots(1, p.as<double>(), Ap.as<double>(), nullptr, nullptr, nullptr, nullptr, nblk);
+    }
+    fin(stage, 1, nblk, tol2, P.cg_maxit);
 }
 
 void Ens::clear_graphs()
@@ -1692,17 +1727,19 @@ void Ens::solve_fcg()
             const int* tl = tlist.as<int>();
             hipEvent_t t0;
             tstart(t0);
-            launch_ebe64_ctail(s, dm, tail_g, tl, tc.D, tc.h, tc.mat, sc, tc.p, tc.f);
-            launch_gather_tail<double>(s, dm, MB, nm, tail_g, tl, tc.f, tc.Ap, act, tc.p, pd, &nblk);
-            launch_dashpot_tail<double>(s, dm, MB, nm, tail_g, tl, tc.mat, 2.0 / P.dt, tc.p, tc.Ap, act, pd, &nblk);
+            launch_ebe64_ctail(s, dm, tail_g, tl, tc.D, tc.h, tc.mat, sc, tc.p, tc.f, 2.0 / P.dt, pd, &nblk);
             tstop(t0, &pc_ebe64, (int64_t)mesh->ne * tail_count);  // an FP64 operator application
-            fin(FIN_ALPHA, 1, nblk, tol2, P.cg_maxit);
-            launch_tail_xr_update(s, n, MB, nm, tail_g, tl, tc.x, tc.r, tc.p, tc.Ap, cs.alpha, act, pd, &nblk);
+            fin(FIN_ALPHA, 1, nblk, tol2, P.cg_maxit, tl, tail_g);
+            launch_rows_update<double>(s, UPD_XR, dm, MB, nm, tail_g, tl, tc.f, tc.r, tc.Ap, nullptr, tc.x, tc.p,
+                                       cs.alpha, act, pd, &nblk);
         } else {
-            apply_A64(p.as<double>(), Ap.as<double>(), act, &nblk);
-            fin(FIN_ALPHA, 1, nblk, tol2, P.cg_maxit);
-            launch_xr_update(s, n, MB, nm, x, r.as<double>(), p.as<double>(), Ap.as<double>(), cs.alpha, act, pd,
-                             &nblk);
+            op_alpha(FIN_ALPHA, tol2, act);
+            if (scatter != 1)
+                launch_rows_update<double>(s, UPD_XR, dm, MB, nm, 0, nullptr, cbuf.as<double>(), r.as<double>(),
+                                           Ap.as<double>(), nullptr, x, p.as<double>(), cs.alpha, act, pd, &nblk);
+            else
+                launch_xr_update(s, n, MB, nm, x, r.as<double>(), p.as<double>(), Ap.as<double>(), cs.alpha, act, pd,
+                                 &nblk);
         }
         fin(FIN_FCG_RR, 1, nblk, tol2, P.cg_maxit);
         if (!read_any_active(act)) break;
@@ -1858,8 +1895,7 @@ void Ens::enqueue_step()
     if (P.precision == NLTH_FP64) solve_pcg();
     else solve_fcg();
     tstart(t0);
-    ebe(OP_K, du.as<double>(), nullptr, q.as<double>(), stepping.as<int>(), q.as<double>(), 1.0, 0.0, nullptr,
-        nullptr);
+    ebe(OP_K, du.as<double>(), nullptr, q.as<double>(), stepping.as<int>(), q.as<double>(), 1.0, 0.0, nullptr);
     launch_newmark(s, ndof, MB, nm, du.as<double>(), u.as<double>(), v.as<double>(), a.as<double>(), P.dt,
                    stepping.as<int>());
     tstop(t0, &pc_other, 0);
@@ -2457,7 +2493,7 @@ int nlth_apply_operator(nlth_ctx* ctx, const nlth_mesh* mesh, const nlth_problem
         NLTH_HIP(hipMemcpy(e->p.p, x, n * 8, hipMemcpyHostToDevice));
         launch_fill(s, e->Ap.as<double>(), 0.0, n);
         e->ebe((OpMode)which, e->p.as<double>(), nullptr, e->Ap.as<double>(), e->stepping.as<int>(), nullptr, 0.0,
-               which == NLTH_OP_A ? 2.0 / P.dt : 0.0, nullptr, nullptr);
+               which == NLTH_OP_A ? 2.0 / P.dt : 0.0, nullptr);
         NLTH_HIP(hipStreamSynchronize(s));
         NLTH_HIP(hipMemcpy(y, e->Ap.p, n * 8, hipMemcpyDeviceToHost));
     } else {

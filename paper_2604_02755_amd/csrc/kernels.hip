@@ -147,7 +147,12 @@ __global__ __launch_bounds__(256) void k_ebe(DevMesh M, int MB, int nm, int e0, 
 // the cluster's node rows in LDS, wavefront after wavefront, so the order of
 // the sums is fixed.  The cluster's node rows are then written to
 // co[(row * 3 + c) * MB + m] (row = the cluster's first row + local node) and
-// a gather over the node -> rows lists finishes the sum.
+// a gather over the node -> rows lists finishes the sum.  nbb blocks spread
+// over the grid write the dashpot rows of the boundary nodes (first in the grid
+// they held every CU for 30 us; a kernel of their own took 57 us of 1.2 ms with
+// 221,184 elements and 64 members).  With partial, the per-member sums of x1 .
+// (operator x1) over a block's rows go to partial[block * MB + m] (nbb + clusters
+// rows), so the node sums need not read x for a dot product.
 // LDS of a cluster block: the node rows, padded so that NB blocks share a CU
 // (160 KB of LDS per CU, allocated in 8 KB steps).  With one bfloat16 D per
 // element four FP32 blocks per CU run fastest; with D per point four thrash
@@ -162,16 +167,36 @@ constexpr int cluster_lds_elems()
 }
 
 template <typename T, int DK, int MODE, int NB>
-__global__ __launch_bounds__(256) void k_ebe_cluster(DevMesh M, int MB, int nm, int ngroups, int ncl,
+__global__ __launch_bounds__(256) void k_ebe_cluster(DevMesh M, int MB, int nm, int ngroups, int nbb,
                                                     const void* __restrict__ Dv, const double* __restrict__ h,
                                                     const double* __restrict__ mat, StepConst sc,
                                                     const T* __restrict__ x1, const T* __restrict__ x2,
-                                                    T* __restrict__ co, const int* __restrict__ active)
+                                                    T* __restrict__ co, const int* __restrict__ active, double dcoef,
+                                                    const double* __restrict__ vI, double* __restrict__ partial)
 {
     __shared__ T ys[cluster_lds_elems<T, NB>()];
-    const long blk = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;  // XCD-contiguous clusters
+    // groups of eight blocks, one per XCD; every gs-th group is a boundary group
+    const int gi = blockIdx.x >> 3, nb8 = nbb >> 3, gs = nb8 ? (int)(gridDim.x >> 3) / nb8 : 1;
+    const int gb = nb8 ? (gi / gs < nb8 ? gi / gs : nb8) : 0;  // boundary groups before this one
+    if (nb8 && gi % gs == gs - 1 && gi / gs < nb8) {
+        const int bb = gb * 8 + (blockIdx.x & 7);
+        const double d = boundary_rows<T>(M, MB, nm, mat, dcoef, x1, vI, active, co + (size_t)M.cl_rows * 3 * MB, bb,
+                                          nbb, 256);
+        if (!partial) return;
+        double* sh = (double*)ys;
+        sh[threadIdx.x] = d;  // all of member t % MB
+        __syncthreads();
+        if ((int)threadIdx.x < MB) {
+            double a = d;
+            for (int o = MB; o < 256; o += MB) a += sh[threadIdx.x + o];
+            partial[(size_t)bb * MB + threadIdx.x] = a;
+        }
+        return;
+    }
+    // XCD-contiguous clusters
+    const long blk = (long)(blockIdx.x & 7) * ((gridDim.x - nbb) >> 3) + (gi - gb);
     const int c = (int)(blk / ngroups), g = (int)(blk % ngroups);
-    if (c >= ncl) return;  // whole block: padding of the grid to a multiple of 8
+    if (c >= M.ncl) return;  // whole block: padding of the grid to a multiple of 8
     // the wavefront index is uniform: saying so keeps the element's
     // connectivity and row bases in scalar registers (scalar loads and
     // address arithmetic instead of per-lane 64-bit adds)
@@ -226,80 +251,137 @@ __global__ __launch_bounds__(256) void k_ebe_cluster(DevMesh M, int MB, int nm, 
         }
     }
     __syncthreads();
-    for (int i = t; i < ncn * 3 * 64; i += 256) {
-        const int q = i >> 6;  // row * 3 + component within the cluster
-        co[((size_t)r0 * 3 + q) * MB + g * 64 + (i & 63)] = ys[i];
+    if (!partial) {
+        for (int i = t; i < ncn * 3 * 64; i += 256) {
+            const int q = i >> 6;  // row * 3 + component within the cluster
+            co[((size_t)r0 * 3 + q) * MB + g * 64 + (i & 63)] = ys[i];
+        }
+        return;
     }
+    // with the dot: a wavefront writes a row's three components, every fourth row,
+    // the loads of x four rows at a time (one at a time their latency showed:
+    // FP64 1141 us a launch against 1110, FP32 794 against 727)
+    double dot = 0.0;
+    const int* nodes = M.cl_nodes + (size_t)c * M.cl_node_stride;
+    for (int q0 = w; q0 < ncn; q0 += 16) {
+        T xv[4][3];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int q = q0 + 4 * u < ncn ? q0 + 4 * u : q0;
+            const T* xp = x1 + (size_t)nodes[q] * 3 * MB + m;
+#pragma unroll
+            for (int cc = 0; cc < 3; ++cc) xv[u][cc] = xp[cc * MB];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int q = q0 + 4 * u;
+            if (q < ncn) {
+                T* p = co + ((size_t)r0 + q) * 3 * MB + m;
+#pragma unroll
+                for (int cc = 0; cc < 3; ++cc) {
+                    const T y = ys[(q * 3 + cc) * 64 + lane];
+                    p[cc * MB] = y;
+                    dot += (double)xv[u][cc] * (double)y;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    double* sh = (double*)ys;  // the four wavefronts one after another
+    sh[t] = act ? dot : 0.0;
+    __syncthreads();
+    if (t < 64) partial[((size_t)nbb + c) * MB + m] = sh[t] + sh[t + 64] + sh[t + 128] + sh[t + 192];
+}
+
+// boundary blocks of a cluster launch (a multiple of 8, so that the clusters
+// keep their XCDs) and its rows of partial sums
+static int cluster_bnd_blocks(const DevMesh& M, int MB, double dcoef)
+{
+    if (dcoef == 0.0 || M.nbn <= 0) return 0;
+    const long npb = 256 / MB, n = (M.nbn + npb - 1) / npb;
+    return (int)((n < kDashpotBlocks ? n : kDashpotBlocks) + 7) / 8 * 8;
 }
 
 // blocks of the FP32 cluster launches per CU (a tuning knob, per host thread)
 static thread_local int t_cluster_blocks = 3;
 void set_cluster_blocks(int b) { t_cluster_blocks = (b == 2 || b == 3 || b == 4) ? b : 3; }
 
-template <typename T, int DK, int NB>
-static void cluster_dispatch(hipStream_t s, OpMode mode, const DevMesh& M, int MB, int nm, const void* D,
-                             const double* h, const double* mat, StepConst sc, const T* x1, const T* x2, T* co,
-                             const int* active)
+template <typename T, int DK, int MODE, int NB>
+static void cluster_launch(hipStream_t s, const DevMesh& M, int MB, int nm, const void* D, const double* h,
+                           const double* mat, StepConst sc, const T* x1, const T* x2, T* co, const int* active,
+                           double dcoef, const double* vI, double* partial, int* nblk)
 {
-    const int ngroups = MB / 64;
-    long g = (long)M.ncl * ngroups;
-    g = (g + 7) / 8 * 8;
-    const dim3 grid((unsigned)g), b(256);
-    switch (mode) {
-    case OP_A: hipLaunchKernelGGL((k_ebe_cluster<T, DK, OP_A, NB>), grid, b, 0, s, M, MB, nm, ngroups, M.ncl, D, h, mat, sc, x1, x2, co, active); break;
-    case OP_K: hipLaunchKernelGGL((k_ebe_cluster<T, DK, OP_K, NB>), grid, b, 0, s, M, MB, nm, ngroups, M.ncl, D, h, mat, sc, x1, x2, co, active); break;
-    case OP_M: hipLaunchKernelGGL((k_ebe_cluster<T, DK, OP_M, NB>), grid, b, 0, s, M, MB, nm, ngroups, M.ncl, D, h, mat, sc, x1, x2, co, active); break;
-    case OP_RHS: hipLaunchKernelGGL((k_ebe_cluster<T, DK, OP_RHS, NB>), grid, b, 0, s, M, MB, nm, ngroups, M.ncl, D, h, mat, sc, x1, x2, co, active); break;
-    }
+    const int ngroups = MB / 64, nbb = cluster_bnd_blocks(M, MB, dcoef);
+    const long g = ((long)M.ncl * ngroups + 7) / 8 * 8;
+    if (nblk) *nblk = nbb + M.ncl;
+    hipLaunchKernelGGL((k_ebe_cluster<T, DK, MODE, NB>), dim3((unsigned)(nbb + g)), dim3(256), 0, s, M, MB, nm, ngroups,
+                       nbb, D, h, mat, sc, x1, x2, co, active, dcoef, vI, partial);
 }
 
 // FP32 operator (A) with D storage DK, NB blocks per CU
 template <int DK>
 static void cluster32(hipStream_t s, const DevMesh& M, int MB, int nm, const void* D, const double* h,
-                      const double* mat, StepConst sc, const float* x, float* co, const int* active)
+                      const double* mat, StepConst sc, const float* x, float* co, const int* active, double dcoef,
+                      double* partial, int* nblk)
 {
-    const int ngroups = MB / 64;
-    long g = (long)M.ncl * ngroups;
-    g = (g + 7) / 8 * 8;
-    const dim3 grid((unsigned)g), b(256);
     const float* none = nullptr;
     switch (t_cluster_blocks) {
-    case 2: hipLaunchKernelGGL((k_ebe_cluster<float, DK, OP_A, 2>), grid, b, 0, s, M, MB, nm, ngroups, M.ncl, D, h, mat, sc, x, none, co, active); break;
-    case 4: hipLaunchKernelGGL((k_ebe_cluster<float, DK, OP_A, 4>), grid, b, 0, s, M, MB, nm, ngroups, M.ncl, D, h, mat, sc, x, none, co, active); break;
-    default: hipLaunchKernelGGL((k_ebe_cluster<float, DK, OP_A, 3>), grid, b, 0, s, M, MB, nm, ngroups, M.ncl, D, h, mat, sc, x, none, co, active); break;
+    case 2: cluster_launch<float, DK, OP_A, 2>(s, M, MB, nm, D, h, mat, sc, x, none, co, active, dcoef, nullptr, partial, nblk); break;
+    case 4: cluster_launch<float, DK, OP_A, 4>(s, M, MB, nm, D, h, mat, sc, x, none, co, active, dcoef, nullptr, partial, nblk); break;
+    default: cluster_launch<float, DK, OP_A, 3>(s, M, MB, nm, D, h, mat, sc, x, none, co, active, dcoef, nullptr, partial, nblk); break;
     }
 }
 
 void launch_ebe_cluster64(hipStream_t s, OpMode mode, const DevMesh& M, int MB, int nm, const double* D,
                           const double* h, const double* mat, StepConst sc, const double* x1, const double* x2,
-                          double* co, const int* active)
+                          double* co, const int* active, double dcoef, const double* vI, double* partial, int* nblk)
 {
     // FP64 rows take 72 KB: two blocks per CU
-    cluster_dispatch<double, 0, 2>(s, mode, M, MB, nm, D, h, mat, sc, x1, x2, co, active);
+    switch (mode) {
+    case OP_A: cluster_launch<double, 0, OP_A, 2>(s, M, MB, nm, D, h, mat, sc, x1, x2, co, active, dcoef, vI, partial, nblk); break;
+    case OP_K: cluster_launch<double, 0, OP_K, 2>(s, M, MB, nm, D, h, mat, sc, x1, x2, co, active, dcoef, vI, partial, nblk); break;
+    case OP_M: cluster_launch<double, 0, OP_M, 2>(s, M, MB, nm, D, h, mat, sc, x1, x2, co, active, dcoef, vI, partial, nblk); break;
+    case OP_RHS: cluster_launch<double, 0, OP_RHS, 2>(s, M, MB, nm, D, h, mat, sc, x1, x2, co, active, dcoef, vI, partial, nblk); break;
+    }
 }
 
 void launch_ebe_cluster32(hipStream_t s, const DevMesh& M, int MB, int nm, const float* D32, const uint32_t* D16,
-                          const double* h, const double* mat, StepConst sc, const float* x, float* co,
-                          const int* active, bool d16_mean)
+                          bool d16_mean, const double* h, const double* mat, StepConst sc, const float* x, float* co,
+                          const int* active, double dcoef, double* partial, int* nblk)
 {
-    if (D16 && d16_mean) cluster32<4>(s, M, MB, nm, D16, h, mat, sc, x, co, active);
-    else if (D16) cluster32<1>(s, M, MB, nm, D16, h, mat, sc, x, co, active);
-    else cluster32<0>(s, M, MB, nm, D32, h, mat, sc, x, co, active);
+    if (D16 && d16_mean) cluster32<4>(s, M, MB, nm, D16, h, mat, sc, x, co, active, dcoef, partial, nblk);
+    else if (D16) cluster32<1>(s, M, MB, nm, D16, h, mat, sc, x, co, active, dcoef, partial, nblk);
+    else cluster32<0>(s, M, MB, nm, D32, h, mat, sc, x, co, active, dcoef, partial, nblk);
 }
 
-// y = sum of the node's cluster rows (ascending, so the sum is reproducible),
-// with bnd its dashpot row last, + bscale * base (base may be NULL and may
-// alias y).  With DOT the per-member partial sums of x . y over the block's
-// nodes go to partial[blockIdx * MB + m] (a fixed tree in LDS).  A block takes
-// a contiguous range of nodes, 256 / MB nodes per pass (MB <= 256): with nodes
-// in Morton order, interleaving the blocks' passes over the whole range was
-// 40 % slower (concurrent blocks then read cluster rows of one small region);
-// members with active[m] == 0 keep y and add nothing.
+// sum of a node's rows: cluster rows ascending, then (bnd) its dashpot row, so
+// the sum is reproducible; W lanes per row
+template <typename T>
+__device__ __forceinline__ void node_rows(const DevMesh& M, long node, const T* __restrict__ f, int W, int m, bool bnd,
+                                          T a[3])
+{
+    a[0] = a[1] = a[2] = 0;
+    const int q1 = M.cn_ptr[node + 1] - (!bnd && M.bn_of_node[node] >= 0);
+#pragma unroll 4
+    for (int q = M.cn_ptr[node]; q < q1; ++q) {
+        const T* fb = f + (size_t)M.cn_row[q] * 3 * W + m;
+        a[0] += fb[0];
+        a[1] += fb[W];
+        a[2] += fb[2 * W];
+    }
+}
+
+// y = the node's rows + bscale * base (base may be NULL and may alias y);
+// members with active[m] == 0 keep y and add nothing.  With DOT the per-member
+// partial sums of x . y over the block's nodes (a fixed tree in LDS).  A block takes a contiguous range of
+// nodes, 256 / MB per pass (MB <= 256): with nodes in Morton order,
+// interleaving the blocks' passes over the whole range was 40 % slower
+// (concurrent blocks then read cluster rows of one small region).
 template <typename T, bool DOT>
 __global__ __launch_bounds__(256) void k_gather(DevMesh M, int MB, int nm, const T* __restrict__ f, int bnd,
                                                const T* base, T bscale, T* y, const int* __restrict__ active,
-                                               const T* __restrict__ x, double* __restrict__ partial,
-                                               const int* __restrict__ ymap)
+                                               const int* __restrict__ ymap, const T* __restrict__ x,
+                                               double* __restrict__ partial)
 {
     const int t = threadIdx.x, m = t % MB;
     const int rpb = 256 / MB;
@@ -308,28 +390,17 @@ __global__ __launch_bounds__(256) void k_gather(DevMesh M, int MB, int nm, const
     double dot = 0.0;
     const long per = ((M.nn + gridDim.x - 1) / gridDim.x + rpb - 1) / rpb * rpb;
     const long n0 = (long)blockIdx.x * per, n1 = n0 + per < M.nn ? n0 + per : M.nn;
-    for (long nd = n0 + slot; nd < n1; nd += rpb) {
+    for (long nd = n0 + slot; act && nd < n1; nd += rpb) {
         const int node = MB >= 64 ? __builtin_amdgcn_readfirstlane((int)nd) : (int)nd;
-        if (!act) continue;
-        T a0 = 0, a1 = 0, a2 = 0;
-        const int q1 = M.cn_ptr[node + 1] - (!bnd && M.bn_of_node[node] >= 0);
-#pragma unroll 4
-        for (int q = M.cn_ptr[node]; q < q1; ++q) {
-            const T* fb = f + (size_t)M.cn_row[q] * 3 * MB + m;
-            a0 += fb[0];
-            a1 += fb[MB];
-            a2 += fb[2 * MB];
-        }
+        T a[3];
+        node_rows<T>(M, node, f, MB, m, bnd, a);
         const size_t yi = (size_t)(ymap ? ymap[node] : node) * 3 * MB + m;
-        if (base) {
-            a0 += bscale * base[yi];
-            a1 += bscale * base[yi + MB];
-            a2 += bscale * base[yi + 2 * MB];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            if (base) a[c] += bscale * base[yi + (size_t)c * MB];
+            y[yi + (size_t)c * MB] = a[c];
+            if (DOT) dot += (double)x[yi + (size_t)c * MB] * (double)a[c];
         }
-        y[yi] = a0;
-        y[yi + MB] = a1;
-        y[yi + 2 * MB] = a2;
-        if (DOT) dot += (double)x[yi] * (double)a0 + (double)x[yi + MB] * (double)a1 + (double)x[yi + 2 * MB] * (double)a2;
     }
     if (DOT) {
         __shared__ double sh[256];
@@ -353,22 +424,142 @@ static int gather_blocks(int nn, int MB, int maxblk)
 
 template <typename T>
 void launch_gather(hipStream_t s, const DevMesh& M, int MB, int nm, const T* rows, bool bnd, const T* base, T bscale,
-                   T* y, const int* active, const T* x, double* partial, int* nblk, const int* ymap)
+                   T* y, const int* active, const int* ymap)
 {
-    const int g = gather_blocks(M.nn, MB, partial ? kGatherBlocks : 1 << 24);
-    if (partial) {
-        *nblk = g;
-        hipLaunchKernelGGL((k_gather<T, true>), dim3(g), dim3(256), 0, s, M, MB, nm, rows, (int)bnd, base, bscale, y,
-                           active, x, partial, ymap);
-    } else {
-        hipLaunchKernelGGL((k_gather<T, false>), dim3(g), dim3(256), 0, s, M, MB, nm, rows, (int)bnd, base, bscale, y,
-                           active, x, nullptr, ymap);
-    }
+    hipLaunchKernelGGL((k_gather<T, false>), dim3(gather_blocks(M.nn, MB, 1 << 24)), dim3(256), 0, s, M, MB, nm, rows,
+                       (int)bnd, base, bscale, y, active, ymap, nullptr, nullptr);
+}
+void launch_gather_dot(hipStream_t s, const DevMesh& M, int MB, int nm, const float* rows, float* y, const int* active,
+                       const float* x, double* partial, int* nblk)
+{
+    const int g = gather_blocks(M.nn, MB, kGatherBlocks);
+    const float* none = nullptr;
+    *nblk = g;
+    hipLaunchKernelGGL((k_gather<float, true>), dim3(g), dim3(256), 0, s, M, MB, nm, rows, 1, none, 0.0f, y, active,
+                       nullptr, x, partial);
 }
 template void launch_gather<double>(hipStream_t, const DevMesh&, int, int, const double*, bool, const double*, double,
-                                    double*, const int*, const double*, double*, int*, const int*);
+                                    double*, const int*, const int*);
 template void launch_gather<float>(hipStream_t, const DevMesh&, int, int, const float*, bool, const float*, float,
-                                   float*, const int*, const float*, double*, int*, const int*);
+                                   float*, const int*, const int*);
+
+// The node sums of a CG iteration's operator application with the update that
+// needs them, so q = A p is not written and read back: with alpha from p . q
+// (taken on the rows by the operator; the FP32 operator of 64 and more slots is
+// not bound by memory and pays more for the dot than this saves: 727 + 509 us
+// against 610 + 300 + 262 for the gather and k_inner_update, 221,184 elements and
+// 64 members; the FP64 one 1100 + 357 + 203 against 1040 + 270 + 362 + 128 with
+// the x update in the p update),
+//   UPD_PZ: r -= alpha q, z = P r; partials (r.r, r.z)       (the PCGs)
+//   UPD_XR: r -= alpha q, x += alpha p, Ap = q; partial r.r  (the outer flexible
+//           CG, whose beta reads Ap)
+// for the active members.  G = 0: full rows of MB lanes; 16 or 32: the compact
+// rows of the listed members, partials in the full layout.  Bound by HBM: per
+// DOF-member of the FP32 inner CG on 64 members the rows (2.7 per node) 11 B, r
+// read and written and z written 12 B, the inverse 8 B.
+template <typename T, int KIND, int G>
+__global__ __launch_bounds__(256) void k_rows_update(DevMesh M, int MB, int nm, const int* __restrict__ tl,
+                                                    const T* __restrict__ f, T* __restrict__ r, T* __restrict__ z,
+                                                    const T* __restrict__ pinv, T* __restrict__ x,
+                                                    const T* __restrict__ p, const double* __restrict__ alpha,
+                                                    const int* __restrict__ active, double* __restrict__ partial)
+{
+    const int W = G ? G : MB, t = threadIdx.x, k = t % W, slot = t / W;
+    const int npb = 256 / W;
+    const int m = !G ? k : (k < min(tl[0], W) ? tl[1 + k] : -1);
+    const bool act = m >= 0 && m < nm && active[m];
+    double d0 = 0.0, d1 = 0.0;
+    if (act) {
+        const T al = (T)alpha[m];
+        const long per = ((M.nn + gridDim.x - 1) / gridDim.x + npb - 1) / npb * npb;
+        const long n0 = (long)blockIdx.x * per, n1 = n0 + per < M.nn ? n0 + per : M.nn;
+        for (long nd = n0 + slot; nd < n1; nd += npb) {
+            const long node = !G && MB >= 64 ? (long)__builtin_amdgcn_readfirstlane((int)nd) : nd;
+            T q[3];
+            const size_t i = (size_t)node * 3 * W + k;
+            T R[3] = {r[i], r[i + W], r[i + 2 * W]};
+            T P[6];
+            if (KIND == UPD_PZ) {
+                const T* pv = pinv + (size_t)node * 6 * W + k;
+#pragma unroll
+                for (int c = 0; c < 6; ++c) P[c] = pv[(size_t)c * W];
+            }
+            node_rows<T>(M, node, f, W, k, true, q);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                R[c] -= al * q[c];
+                r[i + (size_t)c * W] = R[c];
+                d0 += (double)R[c] * (double)R[c];
+            }
+            if (KIND == UPD_PZ) {
+                const T Z[3] = {P[0] * R[0] + P[1] * R[1] + P[2] * R[2], P[1] * R[0] + P[3] * R[1] + P[4] * R[2],
+                                P[2] * R[0] + P[4] * R[1] + P[5] * R[2]};
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    z[i + (size_t)c * W] = Z[c];
+                    d1 += (double)R[c] * (double)Z[c];
+                }
+            } else {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    z[i + (size_t)c * W] = q[c];
+                    x[i + (size_t)c * W] += al * p[i + (size_t)c * W];
+                }
+            }
+        }
+    }
+    constexpr int ND = KIND == UPD_PZ ? 2 : 1;
+    if constexpr (G != 0) {
+        double acc[ND];
+        acc[0] = d0;
+        if constexpr (ND > 1) acc[1] = d1;
+        tail_partials<ND, G>(acc, MB, m, partial, 0, gridDim.x);
+    } else {
+        __shared__ double sh[ND][256];
+        sh[0][t] = d0;
+        if constexpr (ND > 1) sh[ND - 1][t] = d1;
+        __syncthreads();
+        for (int s = 128; s >= MB; s >>= 1) {
+            if (t < s)
+#pragma unroll
+                for (int j = 0; j < ND; ++j) sh[j][t] += sh[j][t + s];
+            __syncthreads();
+        }
+        if (t < MB)
+#pragma unroll
+            for (int j = 0; j < ND; ++j) partial[((size_t)j * gridDim.x + blockIdx.x) * MB + t] = sh[j][t];
+    }
+}
+
+template <typename T>
+void launch_rows_update(hipStream_t s, int kind, const DevMesh& M, int MB, int nm, int G, const int* tl, const T* rows,
+                        T* r, T* z, const T* pinv, T* x, const T* p, const double* alpha, const int* active,
+                        double* partial, int* nblk)
+{
+    const int g = gather_blocks(M.nn, G ? G : MB, kMaxPartialBlocks);
+    *nblk = g;
+#define NLTH_UPD(KIND, GG)                                                                                          \
+    hipLaunchKernelGGL((k_rows_update<T, KIND, GG>), dim3(g), dim3(256), 0, s, M, MB, nm, tl, rows, r, z, pinv, x, p, \
+                       alpha, active, partial)
+    if constexpr (sizeof(T) == 8) {
+        if (kind == UPD_XR) {
+            if (G == 0) NLTH_UPD(UPD_XR, 0);
+            else if (G == 16) NLTH_UPD(UPD_XR, 16);
+            else NLTH_UPD(UPD_XR, 32);
+            return;
+        }
+    }
+    if (G == 0) NLTH_UPD(UPD_PZ, 0);
+    else if (G == 16) NLTH_UPD(UPD_PZ, 16);
+    else NLTH_UPD(UPD_PZ, 32);
+#undef NLTH_UPD
+}
+template void launch_rows_update<double>(hipStream_t, int, const DevMesh&, int, int, int, const int*, const double*,
+                                         double*, double*, const double*, double*, const double*, const double*,
+                                         const int*, double*, int*);
+template void launch_rows_update<float>(hipStream_t, int, const DevMesh&, int, int, int, const int*, const float*,
+                                        float*, float*, const float*, float*, const float*, const double*, const int*,
+                                        double*, int*);
 
 // threads per block of the element-by-element launches (a tuning knob; per
 // host thread so concurrent contexts do not interfere)
@@ -474,62 +665,6 @@ void launch_tail_rows64(hipStream_t s, long nrows, int MB, int G, const int* tl,
     tail_rows<double>(s, nrows, MB, G, 1, 1, tl, src, dst, unpack);
 }
 
-// node sums of the compact cluster rows (ascending) into the compact y of the
-// listed, active members; with partial, the x . y partials of the block's nodes
-template <typename T, int G>
-__global__ __launch_bounds__(256) void k_gather_tail(DevMesh M, int MB, int nm, const int* __restrict__ tl,
-                                                    const T* __restrict__ fc, T* __restrict__ y,
-                                                    const int* __restrict__ active, const T* __restrict__ x,
-                                                    double* __restrict__ partial)
-{
-    constexpr int NPB = 256 / G;  // nodes per block pass
-    const int t = threadIdx.x, k = t % G, slot = t / G;
-    const int m = k < min(tl[0], G) ? tl[1 + k] : -1;
-    const bool act = m >= 0 && m < nm && (!active || active[m]);
-    double dot = 0.0;
-    const long per = ((M.nn + gridDim.x - 1) / gridDim.x + NPB - 1) / NPB * NPB;
-    const long n0 = (long)blockIdx.x * per, n1 = n0 + per < M.nn ? n0 + per : M.nn;
-    if (act) {
-        for (long nd = n0 + slot; nd < n1; nd += NPB) {
-            T a0 = 0, a1 = 0, a2 = 0;
-            const int q1 = M.cn_ptr[nd + 1] - (M.bn_of_node[nd] >= 0);  // without the dashpot row
-#pragma unroll 4
-            for (int q = M.cn_ptr[nd]; q < q1; ++q) {
-                const T* fb = fc + (size_t)3 * M.cn_row[q] * G + k;
-                a0 += fb[0];
-                a1 += fb[G];
-                a2 += fb[2 * G];
-            }
-            const size_t yi = (size_t)nd * 3 * G + k;
-            y[yi] = a0;
-            y[yi + G] = a1;
-            y[yi + 2 * G] = a2;
-            if (partial)
-                dot += (double)x[yi] * (double)a0 + (double)x[yi + G] * (double)a1 + (double)x[yi + 2 * G] * (double)a2;
-        }
-    }
-    if (partial) {
-        double acc[1] = {dot};
-        tail_partials<1, G>(acc, MB, m, partial, 0, gridDim.x);
-    }
-}
-
-template <typename T>
-void launch_gather_tail(hipStream_t s, const DevMesh& M, int MB, int nm, int G, const int* tl, const T* fc, T* y,
-                        const int* active, const T* x, double* partial, int* nblk)
-{
-    const int g = gather_blocks(M.nn, G, partial ? kGatherBlocks : (1 << 24));
-    if (partial) *nblk = g;
-    if (G == 16)
-        hipLaunchKernelGGL((k_gather_tail<T, 16>), dim3(g), dim3(256), 0, s, M, MB, nm, tl, fc, y, active, x, partial);
-    else
-        hipLaunchKernelGGL((k_gather_tail<T, 32>), dim3(g), dim3(256), 0, s, M, MB, nm, tl, fc, y, active, x, partial);
-}
-template void launch_gather_tail<float>(hipStream_t, const DevMesh&, int, int, int, const int*, const float*, float*,
-                                        const int*, const float*, double*, int*);
-template void launch_gather_tail<double>(hipStream_t, const DevMesh&, int, int, int, const int*, const double*,
-                                         double*, const int*, const double*, double*, int*);
-
 template <typename T>
 void launch_ebe(hipStream_t s, OpMode mode, const DevMesh& M, int MB, int nm, int e0, int e1, const T* D,
                 const double* h, const double* mat, int, StepConst sc, const T* x1, const T* x2, T* y,
@@ -552,170 +687,45 @@ template void launch_ebe<double>(hipStream_t, OpMode, const DevMesh&, int, int, 
 // dashpot on a face: rho (Vp n n^T + Vs (I - n n^T)) times int N_a N_b dA
 // ---------------------------------------------------------------------------
 
-// y += dashpot at the boundary nodes; with DOT also the per-member partial
-// sums of x . (dashpot x) over the block's nodes, written to
-// partial[(boff + blockIdx) * MB + m] (a fixed tree in LDS).  Lane t of a
-// block takes member t % MB of boundary node (block pass) * (256 / MB) + t / MB
-// when MB <= 256 (a grid-stride loop over the nodes); wider ensembles (no DOT)
-// map one (node, member) pair per thread.
-template <typename T, bool DOT>
+// y += dashpot at the boundary nodes (the colour form of the operator; the
+// others write dashpot rows), one (node, member) pair per thread
+template <typename T>
 __global__ __launch_bounds__(256) void k_dashpot(DevMesh M, int MB, int nm, const double* __restrict__ mat, double coef,
                                                 const T* __restrict__ x, T* __restrict__ y,
-                                                const double* __restrict__ vI, const int* __restrict__ active,
-                                                double* __restrict__ partial, int boff)
+                                                const double* __restrict__ vI, const int* __restrict__ active)
 {
-    const int t = threadIdx.x;
-    int m;
-    long first, stride;
-    if (MB <= 256) {
-        m = t % MB;
-        first = (long)blockIdx.x * (256 / MB) + t / MB;
-        stride = (long)gridDim.x * (256 / MB);
-    } else {
-        const long g = (long)blockIdx.x * 256 + t;
-        m = (int)(g % MB);
-        first = g / MB;
-        stride = M.nbn;  // one pair per thread
-    }
-    const bool act = m < nm && (!active || active[m]);
-    double dot = 0.0;
-    for (long i = first; i < M.nbn; i += stride) {
-        if (!act) continue;
-        const int node = M.bn_node[i];
-        double acc[3] = {0, 0, 0};
-        dashpot_at<T>(M, MB, m, (int)i, mat, coef, x, vI, acc);
-        for (int c = 0; c < 3; ++c) {
-            const size_t yi = ((size_t)node * 3 + c) * MB + m;
-            y[yi] += (T)acc[c];
-            if (DOT) dot += (double)x[yi] * (double)(T)acc[c];
-        }
-    }
-    if (DOT) {
-        __shared__ double sh[256];
-        sh[t] = dot;
-        __syncthreads();
-        for (int s = 128; s >= MB; s >>= 1) {
-            if (t < s) sh[t] += sh[t + s];
-            __syncthreads();
-        }
-        if (t < MB) partial[((size_t)boff + blockIdx.x) * MB + t] = sh[t];
-    }
-}
-
-template <typename T>
-void launch_dashpot(hipStream_t s, const DevMesh& M, int MB, int nm, const double* mat, int, T coef, const T* x,
-                    T* y, const double* vI, const int* active, double* partial, int* nblk)
-{
-    if (M.nbn <= 0) return;
-    if (partial && MB <= 256) {
-        // appended to the *nblk partials already written (same layout)
-        const long rpb = 256 / MB;
-        long g = ((long)M.nbn + rpb - 1) / rpb;
-        g = g < kDashpotBlocks ? g : kDashpotBlocks;
-        hipLaunchKernelGGL((k_dashpot<T, true>), dim3(g), dim3(256), 0, s, M, MB, nm, mat, (double)coef, x, y, vI,
-                           active, partial, *nblk);
-        *nblk += (int)g;
-        return;
-    }
-    const long g = MB <= 256 ? ((long)M.nbn + 256 / MB - 1) / (256 / MB) : ((long)M.nbn * MB + 255) / 256;
-    hipLaunchKernelGGL((k_dashpot<T, false>), dim3(g), dim3(256), 0, s, M, MB, nm, mat, (double)coef, x, y, vI,
-                       active, nullptr, 0);
-}
-template void launch_dashpot<double>(hipStream_t, const DevMesh&, int, int, const double*, int, double,
-                                     const double*, double*, const double*, const int*, double*, int*);
-template void launch_dashpot<float>(hipStream_t, const DevMesh&, int, int, const double*, int, float,
-                                    const float*, float*, const double*, const int*, double*, int*);
-
-// dashpot of the compact rows (material rows packed, lane k = member tl[1 + k]):
-// y += coef C x at the boundary nodes for the listed, active members; partials
-// of x . (C x) appended after the boff blocks already written
-template <typename T, int G>
-__global__ __launch_bounds__(256) void k_dashpot_tail(DevMesh M, int MB, int nm, const int* __restrict__ tl,
-                                                     const double* __restrict__ cmat, double coef,
-                                                     const T* __restrict__ x, T* __restrict__ y,
-                                                     const int* __restrict__ active, double* __restrict__ partial,
-                                                     int boff, int nblk)
-{
-    constexpr int NPB = 256 / G;
-    const int t = threadIdx.x, k = t % G;
-    const int m = k < min(tl[0], G) ? tl[1 + k] : -1;
-    const bool act = m >= 0 && m < nm && (!active || active[m]);
-    double dot = 0.0;
-    if (act) {
-        for (long i = (long)blockIdx.x * NPB + t / G; i < M.nbn; i += (long)gridDim.x * NPB) {
-            const int node = M.bn_node[i];
-            double acc[3] = {0, 0, 0};
-            dashpot_at<T>(M, G, k, (int)i, cmat, coef, x, nullptr, acc);
-            for (int c = 0; c < 3; ++c) {
-                const size_t yi = ((size_t)node * 3 + c) * G + k;
-                y[yi] += (T)acc[c];
-                if (partial) dot += (double)x[yi] * (double)(T)acc[c];
-            }
-        }
-    }
-    if (partial) {
-        double a1[1] = {dot};
-        tail_partials<1, G>(a1, MB, m, partial, boff, nblk);
-    }
-}
-
-template <typename T>
-void launch_dashpot_tail(hipStream_t s, const DevMesh& M, int MB, int nm, int G, const int* tl, const double* cmat,
-                         T coef, const T* x, T* y, const int* active, double* partial, int* nblk)
-{
-    if (M.nbn <= 0) return;
-    const long rpb = 256 / G;
-    long g = ((long)M.nbn + rpb - 1) / rpb;
-    g = g < kDashpotBlocks ? g : kDashpotBlocks;
-    const int boff = partial ? *nblk : 0;
-    // the partials of one part: rows boff .. boff + g of the gather's layout,
-    // so the row count passed as nblk is irrelevant for part 0
-    if (G == 16)
-        hipLaunchKernelGGL((k_dashpot_tail<T, 16>), dim3(g), dim3(256), 0, s, M, MB, nm, tl, cmat, (double)coef, x, y,
-                           active, partial, boff, 0);
-    else
-        hipLaunchKernelGGL((k_dashpot_tail<T, 32>), dim3(g), dim3(256), 0, s, M, MB, nm, tl, cmat, (double)coef, x, y,
-                           active, partial, boff, 0);
-    if (partial) *nblk += (int)g;
-}
-template void launch_dashpot_tail<float>(hipStream_t, const DevMesh&, int, int, int, const int*, const double*, float,
-                                         const float*, float*, const int*, double*, int*);
-template void launch_dashpot_tail<double>(hipStream_t, const DevMesh&, int, int, int, const int*, const double*,
-                                          double, const double*, double*, const int*, double*, int*);
-
-// dashpot rows of the boundary nodes for the fused Chebyshev gather:
-// qb[(i * 3 + c) * MB + m] = (dashpot x)(boundary node i), active members only
-__global__ __launch_bounds__(256) void k_dashpot_rows(DevMesh M, int MB, int nm, const double* __restrict__ mat,
-                                                     double coef, const float* __restrict__ x,
-                                                     float* __restrict__ qb, const int* __restrict__ active)
-{
-    const int t = threadIdx.x, m = t % MB;
-    const long first = (long)blockIdx.x * (256 / MB) + t / MB, stride = (long)gridDim.x * (256 / MB);
-    if (m >= nm || (active && !active[m])) return;
-    for (long i = first; i < M.nbn; i += stride) {
-        double acc[3] = {0, 0, 0};
-        dashpot_at<float>(M, MB, m, (int)i, mat, coef, x, nullptr, acc);
+    const long g = (long)blockIdx.x * 256 + threadIdx.x;
+    const int m = (int)(g % MB);
+    const long i = g / MB;
+    if (i >= M.nbn || m >= nm || (active && !active[m])) return;
+    double acc[3] = {0, 0, 0};
+    dashpot_at<T>(M, MB, m, (int)i, mat, coef, x, vI, acc);
+    const size_t yi = (size_t)M.bn_node[i] * 3 * MB + m;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) qb[((size_t)i * 3 + c) * MB + m] = (float)acc[c];
-    }
+    for (int c = 0; c < 3; ++c) y[yi + (size_t)c * MB] += (T)acc[c];
 }
 
-void launch_dashpot_rows(hipStream_t s, const DevMesh& M, int MB, int nm, const double* mat, float coef,
-                         const float* x, float* qb, const int* active)
+template <typename T>
+void launch_dashpot(hipStream_t s, const DevMesh& M, int MB, int nm, const double* mat, T coef, const T* x, T* y,
+                    const double* vI, const int* active)
 {
-    if (M.nbn <= 0) return;
-    const long g = ((long)M.nbn + 256 / MB - 1) / (256 / MB);  // MB <= 256 on the cluster path
-    hipLaunchKernelGGL(k_dashpot_rows, dim3(g), dim3(256), 0, s, M, MB, nm, mat, (double)coef, x, qb, active);
+    const long n = (long)M.nbn * MB;
+    if (n > 0)
+        hipLaunchKernelGGL((k_dashpot<T>), dim3(nblocks(n)), dim3(256), 0, s, M, MB, nm, mat, (double)coef, x, y, vI,
+                           active);
 }
+template void launch_dashpot<double>(hipStream_t, const DevMesh&, int, int, const double*, double, const double*,
+                                     double*, const double*, const int*);
+template void launch_dashpot<float>(hipStream_t, const DevMesh&, int, int, const double*, float, const float*, float*,
+                                    const double*, const int*);
 
-// One fused Chebyshev iteration on the cluster path (MB = 64..256): per node
-// the cluster rows are summed in ascending order (as the gather does), the
-// boundary nodes add their dashpot row, and with q = that sum
+// One fused Chebyshev iteration on the gather paths (MB <= 256): per node the
+// rows are summed as the gather does, and with q = that sum
 //   iz += id,  ir -= q,  id_next = c1_k id + c2_k P ir   (no id_next on the last)
 // so the operator result never goes to memory.  Node ranges per block as in
 // the gather.
 __global__ __launch_bounds__(256) void k_gather_cheb(DevMesh M, int MB, int nm, int k, int last,
-                                                    const float* __restrict__ rows, const float* __restrict__ qb,
+                                                    const float* __restrict__ rows,
                                                     float* __restrict__ iz, float* __restrict__ ir,
                                                     const float* __restrict__ id, float* __restrict__ id_next,
                                                     const float* __restrict__ pinv32, const float* __restrict__ cheb,
@@ -734,28 +744,15 @@ __global__ __launch_bounds__(256) void k_gather_cheb(DevMesh M, int MB, int nm, 
     const long per = ((M.nn + gridDim.x - 1) / gridDim.x + rpb - 1) / rpb * rpb;
     const long n0 = (long)blockIdx.x * per, n1 = n0 + per < M.nn ? n0 + per : M.nn;
     for (long nd = n0 + slot; nd < n1; nd += rpb) {
-        const int node = __builtin_amdgcn_readfirstlane((int)nd);
-        float a0 = 0, a1 = 0, a2 = 0;
-        const int bi = M.bn_of_node[node], q1 = M.cn_ptr[node + 1] - (bi >= 0);
-#pragma unroll 4
-        for (int q = M.cn_ptr[node]; q < q1; ++q) {
-            const float* fb = rows + (size_t)M.cn_row[q] * 3 * MB + m;
-            a0 += fb[0];
-            a1 += fb[MB];
-            a2 += fb[2 * MB];
-        }
-        if (bi >= 0) {
-            const float* qp = qb + (size_t)bi * 3 * MB + m;
-            a0 += qp[0];
-            a1 += qp[MB];
-            a2 += qp[2 * MB];
-        }
+        const int node = MB >= 64 ? __builtin_amdgcn_readfirstlane((int)nd) : (int)nd;
+        float a[3];
+        node_rows<float>(M, node, rows, MB, m, true, a);
         const size_t yi = (size_t)node * 3 * MB + m;
         const float d0 = id[yi], d1 = id[yi + MB], d2 = id[yi + 2 * MB];
         iz[yi] += d0;
         iz[yi + MB] += d1;
         iz[yi + 2 * MB] += d2;
-        const float r0 = ir[yi] - a0, r1 = ir[yi + MB] - a1, r2 = ir[yi + 2 * MB] - a2;
+        const float r0 = ir[yi] - a[0], r1 = ir[yi + MB] - a[1], r2 = ir[yi + 2 * MB] - a[2];
         ir[yi] = r0;
         ir[yi + MB] = r1;
         ir[yi + 2 * MB] = r2;
@@ -772,11 +769,11 @@ __global__ __launch_bounds__(256) void k_gather_cheb(DevMesh M, int MB, int nm, 
 }
 
 void launch_gather_cheb(hipStream_t s, const DevMesh& M, int MB, int nm, int k, bool last, const float* rows,
-                        const float* qb, float* iz, float* ir, const float* id, float* id_next, const float* pinv32,
+                        float* iz, float* ir, const float* id, float* id_next, const float* pinv32,
                         const float* cheb, const int* active)
 {
     const int g = gather_blocks(M.nn, MB, 1 << 24);
-    hipLaunchKernelGGL(k_gather_cheb, dim3(g), dim3(256), 0, s, M, MB, nm, k, (int)last, rows, qb, iz, ir, id, id_next,
+    hipLaunchKernelGGL(k_gather_cheb, dim3(g), dim3(256), 0, s, M, MB, nm, k, (int)last, rows, iz, ir, id, id_next,
                        pinv32, cheb, active);
 }
 

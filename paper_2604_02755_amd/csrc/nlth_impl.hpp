@@ -25,16 +25,15 @@ enum OpMode { OP_A = 0, OP_K = 1, OP_M = 2, OP_RHS = 3 };
 
 constexpr int kMaxPartialBlocks = 2048;   // blocks of a fused vector kernel's partial sums
 constexpr int kGatherBlocks = 16384;      // blocks of a node gather with partial sums
-constexpr int kDashpotBlocks = 1024;      // blocks of a dashpot launch with partial sums
+constexpr int kDashpotBlocks = 1024;      // most boundary blocks of an operator launch
 constexpr int kClusterNodes = 48;         // most distinct nodes of an element cluster
 constexpr int kClusterElems = 16;         // most elements of an element cluster
 constexpr int kWideNodes = 240;           // the same of a wide cluster, which
 constexpr int kWideElems = 64;            // ensembles of up to
 constexpr int kWideSlots = 8;             // member slots use
 constexpr int kFoldBlocks = 256;          // rows to which long partial sums are folded before the finalize
-// length (in MB-rows of doubles) of the partial-sum buffer, without the few-slot operator's rows
-constexpr int kPartialRows = (3 * kMaxPartialBlocks > kGatherBlocks + kDashpotBlocks)
-                                 ? 3 * kMaxPartialBlocks : kGatherBlocks + kDashpotBlocks;
+// length (in MB-rows of doubles) of the partial-sum buffer, without the operator's rows
+constexpr int kPartialRows = 3 * kMaxPartialBlocks > kGatherBlocks ? 3 * kMaxPartialBlocks : kGatherBlocks;
 
 // Per-member material of one layer, member-innermost: mat[(l*MAT_N + field)*MB + m]
 enum MatField { MAT_RHO = 0, MAT_G0, MAT_KB, MAT_VS, MAT_VP, MAT_GREF, MAT_HMAX, MAT_BETA, MAT_N };
@@ -102,12 +101,22 @@ template <typename T>
 void launch_ebe(hipStream_t s, OpMode mode, const DevMesh& M, int MB, int nm, int e0, int e1,
                 const T* D, const double* h, const double* mat, int n_layers, StepConst sc,
                 const T* x1, const T* x2, T* y, const int* active);
-// y = sum over the node's cluster rows (+ bscale * base), with bnd also its
-// dashpot row; with partial, also the per-member block partials of x . y
-// (*nblk blocks).  MB <= 256.  ymap: storage node -> row of y (NULL: the same).
+// y = sum of the node's cluster rows, with bnd also its dashpot row, + bscale *
+// base.  MB <= 256.  ymap: storage node -> row of y (NULL: the same).
 template <typename T>
 void launch_gather(hipStream_t s, const DevMesh& M, int MB, int nm, const T* rows, bool bnd, const T* base, T bscale,
-                   T* y, const int* active, const T* x, double* partial, int* nblk, const int* ymap = nullptr);
+                   T* y, const int* active, const int* ymap = nullptr);
+// the same of FP32 rows with the dashpot rows, and the per-member block partials of x . y
+void launch_gather_dot(hipStream_t s, const DevMesh& M, int MB, int nm, const float* rows, float* y, const int* active,
+                       const float* x, double* partial, int* nblk);
+// the node sums q of an operator application with the CG update that needs
+// them (UPD_PZ: r -= alpha q, z = P r, partials (r.r, r.z); UPD_XR: r -= alpha q,
+// x += alpha p, z = q, partial r.r); G = 0 full rows, 16 or 32 compact rows
+enum { UPD_PZ = 0, UPD_XR = 1 };
+template <typename T>
+void launch_rows_update(hipStream_t s, int kind, const DevMesh& M, int MB, int nm, int G, const int* tl, const T* rows,
+                        T* r, T* z, const T* pinv, T* x, const T* p, const double* alpha, const int* active,
+                        double* partial, int* nblk);
 // operator of `mode` for fewer than 64 member slots: cluster rows and (dcoef
 // != 0) the dashpot rows dcoef * C_abs x1 (+ 2 C_base vI) of the boundary
 // nodes, to `rows`; with partial the per-member block partials of x1 . y
@@ -121,20 +130,17 @@ void launch_op_slots32(hipStream_t s, const DevMesh& M, int MB, int nm, const fl
 // position -> input tet): the operator of launch_op_slots64 on them
 void launch_op_input64(hipStream_t s, OpMode mode, const DevMesh& M, const int* order, const double* D,
                        const double* h, const double* mat, StepConst sc, const double* x, double* rows, double dcoef);
-// cluster form of the operator (MB a multiple of 64): cluster node rows to co
+// the same for a multiple of 64 slots (up to 256), co the rows
 void launch_ebe_cluster64(hipStream_t s, OpMode mode, const DevMesh& M, int MB, int nm, const double* D,
                           const double* h, const double* mat, StepConst sc, const double* x1, const double* x2,
-                          double* co, const int* active);
+                          double* co, const int* active, double dcoef, const double* vI, double* partial, int* nblk);
 void launch_ebe_cluster32(hipStream_t s, const DevMesh& M, int MB, int nm, const float* D32, const uint32_t* D16,
-                          const double* h, const double* mat, StepConst sc, const float* x, float* co,
-                          const int* active, bool d16_mean);
-// node-centric absorbing-boundary dashpot: y += coef * C_abs x (+ 2 C_base vI for
-// the right-hand side); with partial (MB <= 256), the per-member block partials
-// of x . (C_abs x) are appended after the *nblk already written, *nblk grows
+                          bool d16_mean, const double* h, const double* mat, StepConst sc, const float* x, float* co,
+                          const int* active, double dcoef, double* partial, int* nblk);
+// absorbing-boundary dashpot of the colour form: y += coef * C_abs x (+ 2 C_base vI)
 template <typename T>
-void launch_dashpot(hipStream_t s, const DevMesh& M, int MB, int nm, const double* mat, int n_layers,
-                    T coef, const T* x, T* y, const double* vI, const int* active, double* partial = nullptr,
-                    int* nblk = nullptr);
+void launch_dashpot(hipStream_t s, const DevMesh& M, int MB, int nm, const double* mat, T coef, const T* x, T* y,
+                    const double* vI, const int* active);
 // diagonal 3x3 blocks of A (sym, 6 entries per node) over elements [e0, e1)
 void launch_diag(hipStream_t s, const DevMesh& M, int MB, int nm, int e0, int e1, const double* D,
                  const double* h, const double* mat, int n_layers, StepConst sc, double* diag);
@@ -169,24 +175,16 @@ void launch_tail_pack64(hipStream_t s, const DevMesh& M, int MB, int G, int n_la
 // nrows member-innermost FP64 rows, full <-> compact
 void launch_tail_rows64(hipStream_t s, long nrows, int MB, int G, const int* tl, const double* src, double* dst,
                         bool unpack);
-// operator A on the compact rows summed per element cluster (the mixed path's
-// inner operator, or the FP64 one with D per point): G-wide cluster rows
-// co[(row * 3 + c) * G + k] for the gather with clusters = true
+// operator A on the compact rows (the mixed path's inner operator, or the FP64
+// one with D per point): G-wide rows, dashpot rows included, and partials of
+// x . (A x) as G-wide rows of the listed members
 void launch_ebe32_ctail(hipStream_t s, const DevMesh& M, int G, const int* tl, const uint32_t* cD, const double* ch,
-                        const double* cmat, StepConst sc, const float* x, float* co);
+                        const double* cmat, StepConst sc, const float* x, float* co, double dcoef, double* partial,
+                        int* nblk);
 void launch_ebe64_ctail(hipStream_t s, const DevMesh& M, int G, const int* tl, const double* cD, const double* ch,
-                        const double* cmat, StepConst sc, const double* x, double* co);
-template <typename T>
-void launch_gather_tail(hipStream_t s, const DevMesh& M, int MB, int nm, int G, const int* tl, const T* fc, T* y,
-                        const int* active, const T* x, double* partial, int* nblk);
-template <typename T>
-void launch_dashpot_tail(hipStream_t s, const DevMesh& M, int MB, int nm, int G, const int* tl, const double* cmat,
-                         T coef, const T* x, T* y, const int* active, double* partial, int* nblk);
-// FP64 PCG on the compact rows: x += a p, r -= a Ap, z = P r with partials
-// (r.r, r.z); then p = z + beta p
-void launch_tail_pcg_update(hipStream_t s, int nn, int MB, int nm, int G, const int* tl, double* cx, double* cr,
-                            double* cz, const double* cp, const double* cAp, const double* cpinv,
-                            const double* alpha, const int* active, double* partial, int* nblk);
+                        const double* cmat, StepConst sc, const double* x, double* co, double dcoef, double* partial,
+                        int* nblk);
+// p = z + beta p on the compact rows
 void launch_tail_p_update(hipStream_t s, long nrows, int nm, int G, const int* tl, const double* cz, double* cp,
                           const double* beta, const int* active);
 // r_compact: r in the compact rows (the outer CG on compact rows), else full
@@ -194,17 +192,13 @@ void launch_tail_start(hipStream_t s, int nn, int MB, int nm, int G, const int* 
                        const float* cpinv, float* cir, float* ciz, float* cip, const int* active, double* partial,
                        int* nblk);
 // the mixed path's outer flexible CG on the compact rows
-void launch_tail_xr_update(hipStream_t s, long nrows, int MB, int nm, int G, const int* tl, double* cx, double* cr,
-                           const double* cp, const double* cAp, const double* alpha, const int* active,
-                           double* partial, int* nblk);
 void launch_tail_inner_out(hipStream_t s, long nrows, int MB, int nm, int G, const int* tl, const float* ciz,
                            double* cz, const double* cAp, const double* cr, const int* active, double* partial,
                            int* nblk);
-void launch_tail_update(hipStream_t s, int nn, int MB, int nm, int G, const int* tl, float* cir, float* cw,
-                        const float* ciAp, const float* cpinv, const double* ialpha, const int* iactive,
-                        double* partial, int* nblk);
-void launch_tail_pz(hipStream_t s, long nrows, int nm, int G, const int* tl, float* ciz, float* cip, const float* cw,
-                    const double* ialpha, const double* ibeta, const int* upd);
+// x += alpha p, then p = z + beta p, for the members of upd
+template <typename T>
+void launch_tail_pz(hipStream_t s, long nrows, int nm, int G, const int* tl, T* cx, T* cp, const T* cz,
+                    const double* alpha, const double* beta, const int* upd);
 // inner FP32 operator (A) with D in FP32 (D32) or bfloat16 pairs (D16, if non-null)
 void launch_ebe32(hipStream_t s, const DevMesh& M, int MB, int nm, int e0, int e1, const float* D32,
                   const uint32_t* D16, const double* h, const double* mat, StepConst sc, const float* x, float* y,
@@ -224,7 +218,7 @@ struct CgScalars {  // per member [MB] device arrays
     double *bb, *rr, *rz, *alpha, *beta, *pAp, *r0;
     int *active, *iters, *status, *stepping;  // stepping: member takes part in this step
     int *inner_active, *inner_iters, *inner_total;
-    int* inner_upd;  // members whose inner alpha was formed this iteration (their iz, ip still update)
+    int* inner_upd;  // members whose alpha was formed this iteration (their x, p still update)
     double *irr, *irz, *ialpha, *ibeta, *ir0;
     double* lz;  // inner CG coefficients: alpha_k at [k * MB + m], beta_k at [(kLanczosMax + k) * MB + m]
 };
@@ -287,7 +281,7 @@ __device__ __forceinline__ void tail_partials(double acc[ND], int MB, int m, dou
 }
 
 void launch_finalize(hipStream_t s, FinalizeStage st, int nd, int MB, int nm, const double* partial, int nblk,
-                     double* fold, CgScalars cs, double tol2, int maxit);
+                     double* fold, const int* tl, int G, CgScalars cs, double tol2, int maxit);
 
 void launch_pcg_start(hipStream_t s, int nn, int MB, int nm, const double* b, const double* Ap, const double* pinv,
                       double* r, double* z, double* p, const int* stepping, double* partial, int* nblk);
@@ -303,8 +297,10 @@ void launch_inner_start(hipStream_t s, int nn, int MB, int nm, const double* r, 
                         float* iz, float* ip, float* w, float* iAp, const int* active, double* partial, int* nblk);
 void launch_inner_update(hipStream_t s, int nn, int MB, int nm, float* ir, float* w, const float* iAp,
                          const float* pinv32, const double* ialpha, const int* iactive, double* partial, int* nblk);
-void launch_inner_pz(hipStream_t s, long nrows, int MB, int nm, float* iz, float* ip, const float* w,
-                     const double* ialpha, const double* ibeta, const int* upd);
+// x += alpha p, then p = z + beta p, for the members of upd
+template <typename T>
+void launch_pz(hipStream_t s, long nrows, int MB, int nm, T* x, T* p, const T* z, const double* alpha,
+               const double* beta, const int* upd);
 void launch_inner_out(hipStream_t s, long nrows, int MB, int nm, const float* iz, double* z, const double* Ap,
                       const double* r, const int* active, double* partial, int* nblk);
 void launch_zero_if_b0(hipStream_t s, long nrows, int MB, int nm, double* x, const double* bb, const int* stepping);
@@ -319,10 +315,8 @@ void launch_cheb_start(hipStream_t s, int nn, int MB, int nm, const double* r, c
 void launch_cheb_update(hipStream_t s, int nn, int MB, int nm, int k, bool last, float* iz, float* ir,
                         const float* id, const float* iAp, float* id_next, const float* pinv32, const float* cheb,
                         const int* active);
-void launch_dashpot_rows(hipStream_t s, const DevMesh& M, int MB, int nm, const double* mat, float coef,
-                         const float* x, float* qb, const int* active);
 void launch_gather_cheb(hipStream_t s, const DevMesh& M, int MB, int nm, int k, bool last, const float* rows,
-                        const float* qb, float* iz, float* ir, const float* id, float* id_next, const float* pinv32,
+                        float* iz, float* ir, const float* id, float* id_next, const float* pinv32,
                         const float* cheb, const int* active);
 
 // Newmark state updates (Section 2.1) and receivers

@@ -147,8 +147,7 @@ extern "C" int nlth_apply_operator_noalloc(nlth_ctx* ctx, const nlth_mesh* mesh,
         const double dc = which == NLTH_OP_A ? 2.0 / prob->dt : 0.0;
         hipLaunchKernelGGL(k_noalloc_mat, dim3(1), dim3(256), 0, s, lm, mat);
         launch_op_input64(s, (OpMode)which, dm, mesh->order_d.as<int>(), D_ip, h, mat, sc, x, rows, dc);
-        launch_gather<double>(s, dm, 1, 1, rows, dc != 0.0, nullptr, 0.0, y, nullptr, nullptr, nullptr, nullptr,
-                              mesh->node_in.as<int>());
+        launch_gather<double>(s, dm, 1, 1, rows, dc != 0.0, nullptr, 0.0, y, nullptr, mesh->node_in.as<int>());
         NLTH_HIP(hipGetLastError());
         return NLTH_OK;
     } catch (const Error& e) {

@@ -113,7 +113,7 @@ struct Ens {
     DevBuf du2, du3;                    // increments of the two steps before the last (CG initial guess)
     int predictor = 0;                  // degree of the extrapolation of the increments giving x0 (0..2)
     DevBuf ir, iz, ip, iw, iAp;
-    DevBuf lz, chebc, cheb_bounds, qb;  // inner CG coefficients, Chebyshev table and bounds, dashpot rows
+    DevBuf lz, chebc, cheb_bounds;      // inner CG coefficients, Chebyshev table and bounds
     int inner_method = 0;               // 0: inner CG; 1: Chebyshev after one inner CG per step
     // convergence tail: with at most tail_max (16 or 32; 0 off) members still
     // active, the inner operator runs on their list only (tail_g lanes per element)
@@ -209,8 +209,12 @@ struct Ens {
     void read(nlth_result* res) const;
     // pieces
     void ebe(OpMode mode, const double* x1, const double* x2, double* y, const int* active, const double* base,
-             double bscale, double dcoef, const double* vI, int* nblk);
-    void ebe32(const float* x, float* y, const int* active, int* nblk = nullptr);
+             double bscale, double dcoef, const double* vI);
+    void ebe32(const float* x, float* y, const int* active);
+    void op_rows(OpMode mode, const double* x1, const double* x2, const int* active, double dcoef, const double* vI,
+                 int* nblk);
+    void op_rows32(const float* x, const int* active, int* nblk);
+    void op_alpha(FinalizeStage stage, double tol2, const int* active);
     void build_rhs();
     void build_diag();
     void solve_pcg();
@@ -235,8 +239,8 @@ struct Ens {
     void clear_graphs();
     int ebe_block = 256;
     int cluster_blocks = 3;             // co-resident cluster blocks per CU
-    void fin(FinalizeStage st, int nd, int nblk, double tol2, int maxit);
-    void apply_A64(const double* x, double* y, const int* act, int* nblk = nullptr);
+    void fin(FinalizeStage st, int nd, int nblk, double tol2, int maxit, const int* tl = nullptr, int G = 0);
+    void apply_A64(const double* x, double* y, const int* act);
     // Host mailbox: pinned, device-mapped and coherent, written and read by
     // small copy kernels on the compute stream (not by the copy engines, which
     // a paged member set keeps busy with large transfers): per-member flags,

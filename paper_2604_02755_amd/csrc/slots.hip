@@ -285,23 +285,20 @@ void launch_op_input64(hipStream_t s, OpMode mode, const DevMesh& M, const int* 
 }
 
 // operator A on the compact rows of the convergence tail (G = 16 or 32 lanes)
-template <typename T, int DK>
-static void op_tail(hipStream_t s, const DevMesh& M, int G, const int* tl, const void* cD, const double* ch,
-                    const double* cmat, StepConst sc, const T* x, T* co)
-{
-    const T* none = nullptr;
-    op_slots<T, DK, OP_A>(s, M, G, G, tl, cD, ch, cmat, sc, x, none, co, nullptr, 0.0, nullptr, nullptr, nullptr);
-}
 void launch_ebe64_ctail(hipStream_t s, const DevMesh& M, int G, const int* tl, const double* cD, const double* ch,
-                        const double* cmat, StepConst sc, const double* x, double* co)
+                        const double* cmat, StepConst sc, const double* x, double* co, double dcoef, double* partial,
+                        int* nblk)
 {
-    op_tail<double, 0>(s, M, G, tl, cD, ch, cmat, sc, x, co);
+    const double* none = nullptr;
+    op_slots<double, 0, OP_A>(s, M, G, G, tl, cD, ch, cmat, sc, x, none, co, nullptr, dcoef, nullptr, partial, nblk);
 }
 
 void launch_ebe32_ctail(hipStream_t s, const DevMesh& M, int G, const int* tl, const uint32_t* cD, const double* ch,
-                        const double* cmat, StepConst sc, const float* x, float* co)
+                        const double* cmat, StepConst sc, const float* x, float* co, double dcoef, double* partial,
+                        int* nblk)
 {
-    op_tail<float, 4>(s, M, G, tl, cD, ch, cmat, sc, x, co);
+    const float* none = nullptr;
+    op_slots<float, 4, OP_A>(s, M, G, G, tl, cD, ch, cmat, sc, x, none, co, nullptr, dcoef, nullptr, partial, nblk);
 }
 
 }  // namespace nlth

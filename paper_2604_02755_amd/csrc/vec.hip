@@ -501,48 +501,53 @@ void launch_inner_update(hipStream_t s, int nn, int MB, int nm, float* ir, float
     else hipLaunchKernelGGL((k_inner_update<1>), dim3(g), dim3(256), 0, s, nn, MB, nm, ir, w, iAp, pinv32, ialpha, iactive, partial);
 }
 
-// inner: iz += a ip (with this iteration's ip), then ip = w + b ip, for the
-// members whose alpha was formed this iteration (upd); a member that has just
-// converged takes its last iz update, and its ip is not used again
-template <int VEC>
-__global__ __launch_bounds__(256) void k_inner_pz(long nrows, int MB, int nm, float* __restrict__ iz,
-                                                 float* __restrict__ ip, const float* __restrict__ w,
-                                                 const double* __restrict__ ialpha, const double* __restrict__ ibeta,
+// CG: x += a p (with this iteration's p), then p = z + b p, for the members
+// whose alpha was formed this iteration (upd); a member that has just converged
+// takes its last x update, and its p is not used again
+template <typename T, int VEC>
+__global__ __launch_bounds__(256) void k_pz(long nrows, int MB, int nm, T* __restrict__ x,
+                                           T* __restrict__ p, const T* __restrict__ z,
+                                                 const double* __restrict__ alpha, const double* __restrict__ beta,
                                                  const int* __restrict__ upd)
 {
     const int QB = MB / VEC, rpb = 256 / QB;
     const int t = threadIdx.x, q = t % QB, m0 = q * VEC;
     bool act[4];
     if (!member_mask(upd, m0, VEC, nm, act)) return;
-    float al[VEC], be[VEC];
+    T al[VEC], be[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) {
-        al[v] = act[v] ? (float)ialpha[m0 + v] : 0.0f;
-        be[v] = act[v] ? (float)ibeta[m0 + v] : 0.0f;
+        al[v] = act[v] ? (T)alpha[m0 + v] : (T)0;
+        be[v] = act[v] ? (T)beta[m0 + v] : (T)0;
     }
     for (long row = (long)blockIdx.x * rpb + t / QB; row < nrows; row += (long)gridDim.x * rpb) {
         const long i = row * MB + m0;
-        Pk<float, VEC> Z = ld<float, VEC>(iz + i), P = ld<float, VEC>(ip + i);
-        const Pk<float, VEC> W = ld<float, VEC>(w + i);
+        Pk<T, VEC> X = ld<T, VEC>(x + i), P = ld<T, VEC>(p + i);
+        const Pk<T, VEC> Z = ld<T, VEC>(z + i);
 #pragma unroll
         for (int v = 0; v < VEC; ++v)
             if (act[v]) {
-                Z.a[v] += al[v] * P.a[v];
-                P.a[v] = W.a[v] + be[v] * P.a[v];
+                X.a[v] += al[v] * P.a[v];
+                P.a[v] = Z.a[v] + be[v] * P.a[v];
             }
-        st<float, VEC>(iz + i, Z);
-        st<float, VEC>(ip + i, P);
+        st<T, VEC>(x + i, X);
+        st<T, VEC>(p + i, P);
     }
 }
 
-void launch_inner_pz(hipStream_t s, long nrows, int MB, int nm, float* iz, float* ip, const float* w,
-                     const double* ialpha, const double* ibeta, const int* upd)
+template <typename T>
+void launch_pz(hipStream_t s, long nrows, int MB, int nm, T* x, T* p, const T* z, const double* alpha,
+               const double* beta, const int* upd)
 {
     const int VEC = vec_of(MB), QB = MB / VEC;
     const int g = grid_for(nrows, 256 / QB);
-    if (VEC == 4) hipLaunchKernelGGL((k_inner_pz<4>), dim3(g), dim3(256), 0, s, nrows, MB, nm, iz, ip, w, ialpha, ibeta, upd);
-    else hipLaunchKernelGGL((k_inner_pz<1>), dim3(g), dim3(256), 0, s, nrows, MB, nm, iz, ip, w, ialpha, ibeta, upd);
+    if (VEC == 4) hipLaunchKernelGGL((k_pz<T, 4>), dim3(g), dim3(256), 0, s, nrows, MB, nm, x, p, z, alpha, beta, upd);
+    else hipLaunchKernelGGL((k_pz<T, 1>), dim3(g), dim3(256), 0, s, nrows, MB, nm, x, p, z, alpha, beta, upd);
 }
+template void launch_pz<float>(hipStream_t, long, int, int, float*, float*, const float*, const double*, const double*,
+                               const int*);
+template void launch_pz<double>(hipStream_t, long, int, int, double*, double*, const double*, const double*,
+                                const double*, const int*);
 
 // preconditioner output z = iz (FP64) for outer-active members (0 for the
 // others, whose z is not used again in the step); partials (z.Ap, z.r)
@@ -589,9 +594,9 @@ void launch_inner_out(hipStream_t s, long nrows, int MB, int nm, const float* iz
 }
 
 // ---------------------------------------------------------------------------
-// inner CG of the convergence tail on compact rows (lane k = member tl[1 + k],
-// G lanes per row): the start, update and p/z steps above, partials in the
-// full [block][MB] layout
+// CG of the convergence tail on compact rows (lane k = member tl[1 + k], G lanes
+// per row): the start and p/z steps above, partials in the full [block][MB]
+// layout
 // ---------------------------------------------------------------------------
 
 __device__ __forceinline__ int tail_member(const int* __restrict__ tl, int k, int G)
@@ -630,96 +635,26 @@ __global__ __launch_bounds__(256) void k_tail_start(int nn, int MB, int nm, cons
     tail_partials<2, G>(acc, MB, m, partial, 0, gridDim.x);
 }
 
-template <int G>
-__global__ __launch_bounds__(256) void k_tail_update(int nn, int MB, int nm, const int* __restrict__ tl,
-                                                    float* __restrict__ cir, float* __restrict__ cw,
-                                                    const float* __restrict__ ciAp, const float* __restrict__ cpinv,
-                                                    const double* __restrict__ ialpha,
-                                                    const int* __restrict__ iactive, double* __restrict__ partial)
-{
-    constexpr int NPB = 256 / G;
-    const int t = threadIdx.x, k = t % G;
-    const int m = tail_member(tl, k, G);
-    double acc[2] = {0.0, 0.0};
-    if (m >= 0 && m < nm && iactive[m]) {
-        const float al = (float)ialpha[m];
-        for (long node = (long)blockIdx.x * NPB + t / G; node < nn; node += (long)gridDim.x * NPB) {
-            Pk<float, 1> R[3], W[3];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const long i = (node * 3 + c) * G + k;
-                R[c].a[0] = cir[i] - al * ciAp[i];
-                cir[i] = R[c].a[0];
-            }
-            pinv_apply<float, 1>(cpinv, node, G, k, R, W);
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                cw[(node * 3 + c) * G + k] = W[c].a[0];
-                acc[0] += (double)R[c].a[0] * (double)R[c].a[0];
-                acc[1] += (double)R[c].a[0] * (double)W[c].a[0];
-            }
-        }
-    }
-    tail_partials<2, G>(acc, MB, m, partial, 0, gridDim.x);
-}
-
-template <int G>
-__global__ __launch_bounds__(256) void k_tail_pz(long nrows, int nm, const int* __restrict__ tl,
-                                                float* __restrict__ ciz, float* __restrict__ cip,
-                                                const float* __restrict__ cw, const double* __restrict__ ialpha,
-                                                const double* __restrict__ ibeta, const int* __restrict__ upd)
+template <typename T, int G>
+__global__ __launch_bounds__(256) void k_tail_pz(long nrows, int nm, const int* __restrict__ tl, T* __restrict__ cx,
+                                                T* __restrict__ cp, const T* __restrict__ cz,
+                                                const double* __restrict__ alpha, const double* __restrict__ beta,
+                                                const int* __restrict__ upd)
 {
     constexpr int NPB = 256 / G;
     const int t = threadIdx.x, k = t % G;
     const int m = tail_member(tl, k, G);
     if (m < 0 || m >= nm || !upd[m]) return;
-    const float al = (float)ialpha[m], be = (float)ibeta[m];
+    const T al = (T)alpha[m], be = (T)beta[m];
     for (long row = (long)blockIdx.x * NPB + t / G; row < nrows; row += (long)gridDim.x * NPB) {
         const long i = row * G + k;
-        const float P = cip[i];
-        ciz[i] += al * P;
-        cip[i] = cw[i] + be * P;
+        const T P = cp[i];
+        cx[i] += al * P;
+        cp[i] = cz[i] + be * P;
     }
 }
 
-// FP64 PCG on the compact rows (the tail of the plain FP64 path): the update
-// of k_pcg_update and the p step of k_p_update for the listed members
-template <int G>
-__global__ __launch_bounds__(256) void k_tail_pcg_update(int nn, int MB, int nm, const int* __restrict__ tl,
-                                                        double* __restrict__ cx, double* __restrict__ cr,
-                                                        double* __restrict__ cz, const double* __restrict__ cp,
-                                                        const double* __restrict__ cAp,
-                                                        const double* __restrict__ cpinv,
-                                                        const double* __restrict__ alpha,
-                                                        const int* __restrict__ active, double* __restrict__ partial)
-{
-    constexpr int NPB = 256 / G;
-    const int t = threadIdx.x, k = t % G;
-    const int m = tail_member(tl, k, G);
-    double acc[2] = {0.0, 0.0};
-    if (m >= 0 && m < nm && active[m]) {
-        const double al = alpha[m];
-        for (long node = (long)blockIdx.x * NPB + t / G; node < nn; node += (long)gridDim.x * NPB) {
-            Pk<double, 1> R[3], Z[3];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const long i = (node * 3 + c) * G + k;
-                cx[i] += al * cp[i];
-                R[c].a[0] = cr[i] - al * cAp[i];
-                cr[i] = R[c].a[0];
-            }
-            pinv_apply<double, 1>(cpinv, node, G, k, R, Z);
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                cz[(node * 3 + c) * G + k] = Z[c].a[0];
-                acc[0] += R[c].a[0] * R[c].a[0];
-                acc[1] += R[c].a[0] * Z[c].a[0];
-            }
-        }
-    }
-    tail_partials<2, G>(acc, MB, m, partial, 0, gridDim.x);
-}
-
+// p = z + beta p on the compact rows (the outer flexible CG)
 template <int G>
 __global__ __launch_bounds__(256) void k_tail_p_update(long nrows, int nm, const int* __restrict__ tl,
                                                       const double* __restrict__ cz, double* __restrict__ cp,
@@ -735,20 +670,6 @@ __global__ __launch_bounds__(256) void k_tail_p_update(long nrows, int nm, const
         const long i = row * G + k;
         cp[i] = cz[i] + be * cp[i];
     }
-}
-
-void launch_tail_pcg_update(hipStream_t s, int nn, int MB, int nm, int G, const int* tl, double* cx, double* cr,
-                            double* cz, const double* cp, const double* cAp, const double* cpinv,
-                            const double* alpha, const int* active, double* partial, int* nblk)
-{
-    const int g = grid_for(nn, 256 / G);
-    *nblk = g;
-    if (G == 16)
-        hipLaunchKernelGGL((k_tail_pcg_update<16>), dim3(g), dim3(256), 0, s, nn, MB, nm, tl, cx, cr, cz, cp, cAp, cpinv,
-                           alpha, active, partial);
-    else
-        hipLaunchKernelGGL((k_tail_pcg_update<32>), dim3(g), dim3(256), 0, s, nn, MB, nm, tl, cx, cr, cz, cp, cAp, cpinv,
-                           alpha, active, partial);
 }
 
 void launch_tail_p_update(hipStream_t s, long nrows, int nm, int G, const int* tl, const double* cz, double* cp,
@@ -775,33 +696,8 @@ void launch_tail_start(hipStream_t s, int nn, int MB, int nm, int G, const int* 
         hipLaunchKernelGGL((k_tail_start<32, false>), dim3(g), dim3(256), 0, s, nn, MB, nm, tl, r, cpinv, cir, ciz, cip, active, partial);
 }
 
-// outer flexible CG of the mixed path on the compact rows: x += a p, r -= a Ap
-// with the partial r.r (k_xr_update), and z = iz for the outer-active members
-// with the partials (z.Ap, z.r) (k_inner_out)
-template <int G>
-__global__ __launch_bounds__(256) void k_tail_xr_update(long nrows, int MB, int nm, const int* __restrict__ tl,
-                                                       double* __restrict__ cx, double* __restrict__ cr,
-                                                       const double* __restrict__ cp, const double* __restrict__ cAp,
-                                                       const double* __restrict__ alpha,
-                                                       const int* __restrict__ active, double* __restrict__ partial)
-{
-    constexpr int NPB = 256 / G;
-    const int t = threadIdx.x, k = t % G;
-    const int m = tail_member(tl, k, G);
-    double acc[1] = {0.0};
-    if (m >= 0 && m < nm && active[m]) {
-        const double al = alpha[m];
-        for (long row = (long)blockIdx.x * NPB + t / G; row < nrows; row += (long)gridDim.x * NPB) {
-            const long i = row * G + k;
-            cx[i] += al * cp[i];
-            const double R = cr[i] - al * cAp[i];
-            cr[i] = R;
-            acc[0] += R * R;
-        }
-    }
-    tail_partials<1, G>(acc, MB, m, partial, 0, gridDim.x);
-}
-
+// outer flexible CG of the mixed path on the compact rows: z = iz for the
+// outer-active members with the partials (z.Ap, z.r) (k_inner_out)
 template <int G>
 __global__ __launch_bounds__(256) void k_tail_inner_out(long nrows, int MB, int nm, const int* __restrict__ tl,
                                                        const float* __restrict__ ciz, double* __restrict__ cz,
@@ -825,18 +721,6 @@ __global__ __launch_bounds__(256) void k_tail_inner_out(long nrows, int MB, int 
     tail_partials<2, G>(acc, MB, m, partial, 0, gridDim.x);
 }
 
-void launch_tail_xr_update(hipStream_t s, long nrows, int MB, int nm, int G, const int* tl, double* cx, double* cr,
-                           const double* cp, const double* cAp, const double* alpha, const int* active,
-                           double* partial, int* nblk)
-{
-    const int g = grid_for(nrows, 256 / G);
-    *nblk = g;
-    if (G == 16)
-        hipLaunchKernelGGL((k_tail_xr_update<16>), dim3(g), dim3(256), 0, s, nrows, MB, nm, tl, cx, cr, cp, cAp, alpha, active, partial);
-    else
-        hipLaunchKernelGGL((k_tail_xr_update<32>), dim3(g), dim3(256), 0, s, nrows, MB, nm, tl, cx, cr, cp, cAp, alpha, active, partial);
-}
-
 void launch_tail_inner_out(hipStream_t s, long nrows, int MB, int nm, int G, const int* tl, const float* ciz,
                            double* cz, const double* cAp, const double* cr, const int* active, double* partial,
                            int* nblk)
@@ -849,23 +733,18 @@ void launch_tail_inner_out(hipStream_t s, long nrows, int MB, int nm, int G, con
         hipLaunchKernelGGL((k_tail_inner_out<32>), dim3(g), dim3(256), 0, s, nrows, MB, nm, tl, ciz, cz, cAp, cr, active, partial);
 }
 
-void launch_tail_update(hipStream_t s, int nn, int MB, int nm, int G, const int* tl, float* cir, float* cw,
-                        const float* ciAp, const float* cpinv, const double* ialpha, const int* iactive,
-                        double* partial, int* nblk)
-{
-    const int g = grid_for(nn, 256 / G);
-    *nblk = g;
-    if (G == 16) hipLaunchKernelGGL((k_tail_update<16>), dim3(g), dim3(256), 0, s, nn, MB, nm, tl, cir, cw, ciAp, cpinv, ialpha, iactive, partial);
-    else hipLaunchKernelGGL((k_tail_update<32>), dim3(g), dim3(256), 0, s, nn, MB, nm, tl, cir, cw, ciAp, cpinv, ialpha, iactive, partial);
-}
-
-void launch_tail_pz(hipStream_t s, long nrows, int nm, int G, const int* tl, float* ciz, float* cip, const float* cw,
-                    const double* ialpha, const double* ibeta, const int* upd)
+template <typename T>
+void launch_tail_pz(hipStream_t s, long nrows, int nm, int G, const int* tl, T* cx, T* cp, const T* cz,
+                    const double* alpha, const double* beta, const int* upd)
 {
     const int g = grid_for(nrows, 256 / G);
-    if (G == 16) hipLaunchKernelGGL((k_tail_pz<16>), dim3(g), dim3(256), 0, s, nrows, nm, tl, ciz, cip, cw, ialpha, ibeta, upd);
-    else hipLaunchKernelGGL((k_tail_pz<32>), dim3(g), dim3(256), 0, s, nrows, nm, tl, ciz, cip, cw, ialpha, ibeta, upd);
+    if (G == 16) hipLaunchKernelGGL((k_tail_pz<T, 16>), dim3(g), dim3(256), 0, s, nrows, nm, tl, cx, cp, cz, alpha, beta, upd);
+    else hipLaunchKernelGGL((k_tail_pz<T, 32>), dim3(g), dim3(256), 0, s, nrows, nm, tl, cx, cp, cz, alpha, beta, upd);
 }
+template void launch_tail_pz<float>(hipStream_t, long, int, int, const int*, float*, float*, const float*,
+                                    const double*, const double*, const int*);
+template void launch_tail_pz<double>(hipStream_t, long, int, int, const int*, double*, double*, const double*,
+                                     const double*, const double*, const int*);
 
 // ---------------------------------------------------------------------------
 // Chebyshev inner solve: A z = r by the Chebyshev iteration on the block-
@@ -1156,6 +1035,7 @@ __device__ void stage_logic(int stage, int m, int MB, const double S[3], CgScala
     case FIN_ALPHA:  // S = (p.Ap)
         cs.pAp[m] = S[0];
         cs.alpha[m] = cs.active[m] ? cs.rz[m] / S[0] : 0.0;
+        cs.inner_upd[m] = cs.active[m];
         break;
     case FIN_BETA:  // S = (r.r, r.z)
         if (cs.active[m]) {
@@ -1235,16 +1115,26 @@ __device__ void stage_logic(int stage, int m, int MB, const double S[3], CgScala
 }
 
 __global__ __launch_bounds__(256) void k_finalize(int stage, int nd, int MB, int nm, const double* __restrict__ partial,
-                                                 int nblk, CgScalars cs, double tol2, int maxit)
+                                                 int nblk, const int* __restrict__ tl, int G, CgScalars cs,
+                                                 double tol2, int maxit)
 {
     const int m = blockIdx.x;
     if (m >= nm) return;
+    // column and width of the member's partials; with tl (compact rows of G
+    // lanes) the listed members' only, the others are not iterating
+    int col = m, W = MB;
+    if (tl) {
+        W = G;
+        col = -1;
+        for (int k = 0; k < min(tl[0], G); ++k)
+            if (tl[1 + k] == m) col = k;
+    }
     __shared__ double sh[3][256];
     const int t = threadIdx.x;
     for (int k = 0; k < 3; ++k) {
         double a = 0.0;
         if (k < nd)
-            for (int b = t; b < nblk; b += 256) a += partial[((long)k * nblk + b) * MB + m];
+            for (int b = t; col >= 0 && b < nblk; b += 256) a += partial[((long)k * nblk + b) * W + col];
         sh[k][t] = a;
     }
     __syncthreads();
@@ -1285,16 +1175,18 @@ __global__ __launch_bounds__(256) void k_fold(int MB, const double* __restrict__
 }
 
 void launch_finalize(hipStream_t s, FinalizeStage st, int nd, int MB, int nm, const double* partial, int nblk,
-                     double* fold, CgScalars cs, double tol2, int maxit)
+                     double* fold, const int* tl, int G, CgScalars cs, double tol2, int maxit)
 {
-    // the fold is a launch more (about 3 us): it pays once a column takes
-    // longer than that to read
-    if (nd > 0 && nblk > 2048 && MB <= 256) {
-        hipLaunchKernelGGL(k_fold, dim3(kFoldBlocks, nd), dim3(256), 0, s, MB, partial, nblk, fold);
+    // the fold is a launch more (about 3 us): it pays once a column takes longer
+    // than that to read
+    const int W = tl ? G : MB;
+    if (nd > 0 && W <= 256 && nblk > (W >= 16 ? 512 : 2048)) {
+        hipLaunchKernelGGL(k_fold, dim3(kFoldBlocks, nd), dim3(256), 0, s, W, partial, nblk, fold);
         partial = fold;
         nblk = kFoldBlocks;
     }
-    hipLaunchKernelGGL(k_finalize, dim3(nm), dim3(256), 0, s, (int)st, nd, MB, nm, partial, nblk, cs, tol2, maxit);
+    hipLaunchKernelGGL(k_finalize, dim3(nm), dim3(256), 0, s, (int)st, nd, MB, nm, partial, nblk, tl, G, cs, tol2,
+                       maxit);
 }
 
 }  // namespace nlth
