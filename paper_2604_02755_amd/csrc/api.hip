@@ -1174,6 +1174,16 @@ void Ens::build_diag()
 {
     const DevMesh dm = mesh->dev(MB);
     const bool mean = P.precision == NLTH_MIXED && d16_mean;
+    float* inv32 = P.precision == NLTH_MIXED ? pinv32.as<float>() : nullptr;
+    if (scatter != 1) {
+        for (int half = 0; half < 2; ++half) {
+            launch_diag_slots(s, dm, MB, nm, half, D64.as<double>(), mean ? D16.as<uint32_t>() : nullptr,
+                              h.as<double>(), mat.as<double>(), sc, cbuf.as<double>());
+            launch_diag_rows(s, dm, MB, nm, half, cbuf.as<double>(), mat.as<double>(), 2.0 / P.dt, diag.as<double>(),
+                             pinv.as<double>(), inv32);
+        }
+        return;
+    }
     launch_fill(s, diag.as<double>(), 0.0, (long)mesh->nn * 6 * MB);
     for (int c = 0; c < mesh->ncolor; ++c) {
         if (mean)
@@ -1184,8 +1194,7 @@ void Ens::build_diag()
                         mat.as<double>(), P.nl, sc, diag.as<double>());
     }
     launch_diag_dashpot(s, dm, MB, nm, mat.as<double>(), P.nl, 2.0 / P.dt, diag.as<double>());
-    launch_invert_diag(s, mesh->nn, MB, nm, diag.as<double>(), pinv.as<double>(),
-                       P.precision == NLTH_MIXED ? pinv32.as<float>() : nullptr);
+    launch_invert_diag(s, mesh->nn, MB, nm, diag.as<double>(), pinv.as<double>(), inv32);
 }
 
 void Ens::dots(int nd, const double* a0, const double* b0, const double* a1, const double* b1, const double* a2,

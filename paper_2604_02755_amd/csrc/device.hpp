@@ -464,4 +464,81 @@ __device__ __forceinline__ double boundary_rows(const DevMesh& M, int MB, int nm
     return dot;
 }
 
+// Diagonal 3x3 block of node n of one element:
+//   c_M rho V Mref(n, n) I + c_K (V/4) sum_j B_n(j)^T D_j B_n(j)
+// with B_n^T D B_n [c][d] = sum_{p,q} g_p g_q D[v(c, p)][v(d, q)], g = grad N_n
+// at point j and v(c, p) the Voigt index of du_c/dx_p.  Per point the
+// coefficients of the quadratic forms in (gx^2, gy^2, gz^2, gx gy, gy gz, gz gx)
+// are formed once and shared by the nodes.
+__device__ __forceinline__ constexpr int voigt_of(int c, int p)
+{
+    return c == p ? c : ((c + p == 1) ? 3 : ((c + p == 3) ? 4 : 5));
+}
+
+// those of the block's entries C0 .. C0 + NC - 1 in the order 00 01 02 11 12 22
+template <int C0, int NC>
+__device__ __forceinline__ void diag_coef(const double* __restrict__ d, double C[NC][6])
+{
+    constexpr int PQ[6][2] = {{0, 0}, {1, 1}, {2, 2}, {0, 1}, {1, 2}, {2, 0}};
+    constexpr int CD[6][2] = {{0, 0}, {0, 1}, {0, 2}, {1, 1}, {1, 2}, {2, 2}};
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+#pragma unroll
+        for (int pq = 0; pq < 6; ++pq) {
+            const int c = CD[C0 + i][0], dd = CD[C0 + i][1], p = PQ[pq][0], q = PQ[pq][1];
+            double v = d[sym6(voigt_of(c, p), voigt_of(dd, q))];
+            if (p != q) v += d[sym6(voigt_of(c, q), voigt_of(dd, p))];
+            C[i][pq] = v;
+        }
+}
+
+// adds w g^T C g (NC entries of the symmetric 3x3 block) for node n (a
+// compile-time index after unrolling) with g = grad N_n at barycentrics L
+template <int NC>
+__device__ __forceinline__ void diag_node_add(int n, const double L[4], const double gL[4][3], const double C[NC][6],
+                                              double w, double acc[NC])
+{
+    constexpr int E[6][2] = {{0, 1}, {1, 2}, {2, 0}, {0, 3}, {1, 3}, {2, 3}};
+    double g[3];
+    if (n < 4) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) g[a] = (4.0 * L[n] - 1.0) * gL[n][a];
+    } else {
+        const int ea = E[n - 4][0], eb = E[n - 4][1];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) g[a] = 4.0 * (L[ea] * gL[eb][a] + L[eb] * gL[ea][a]);
+    }
+    const double gg[6] = {g[0] * g[0], g[1] * g[1], g[2] * g[2], g[0] * g[1], g[1] * g[2], g[2] * g[0]};
+#pragma unroll
+    for (int cd = 0; cd < NC; ++cd) {
+        double a = 0.0;
+#pragma unroll
+        for (int pq = 0; pq < 6; ++pq) a += gg[pq] * C[cd][pq];
+        acc[cd] += w * a;
+    }
+}
+
+// With D constant over the element (the inner operator's bfloat16 element
+// mean) the stiffness block of node n is C : int grad N_n grad N_n^T dV, and
+// that integral has a closed form in the barycentric gradients g (int L_a^2 =
+// V/10, int L_a L_b = V/20, int L_a = V/4): corner a 0.6 V g_a g_a^T; edge
+// (a, b) 1.6 V (g_a g_a^T + g_b g_b^T) + 0.8 V (g_a g_b^T + g_b g_a^T).
+// G = int d_p N_n d_q N_n dV / V in the order 00 11 22 01 12 20.
+__device__ __forceinline__ void mean_grad_products(int n, const double gL[4][3], double G[6])
+{
+    constexpr int PQ[6][2] = {{0, 0}, {1, 1}, {2, 2}, {0, 1}, {1, 2}, {2, 0}};
+    constexpr int E[6][2] = {{0, 1}, {1, 2}, {2, 0}, {0, 3}, {1, 3}, {2, 3}};
+#pragma unroll
+    for (int pq = 0; pq < 6; ++pq) {
+        const int p = PQ[pq][0], q = PQ[pq][1];
+        if (n < 4) {
+            G[pq] = 0.6 * gL[n][p] * gL[n][q];
+        } else {
+            const int a = E[n - 4][0], b = E[n - 4][1];
+            G[pq] = 1.6 * (gL[a][p] * gL[a][q] + gL[b][p] * gL[b][q]) +
+                    0.8 * (gL[a][p] * gL[b][q] + gL[b][p] * gL[a][q]);
+        }
+    }
+}
+
 }  // namespace nlth

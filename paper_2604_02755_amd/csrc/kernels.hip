@@ -781,45 +781,11 @@ void launch_gather_cheb(hipStream_t s, const DevMesh& M, int MB, int nm, int k, 
 // 3x3 block-Jacobi preconditioner (Section 2.2): diagonal blocks of A
 // ---------------------------------------------------------------------------
 
-// Diagonal 3x3 block of node n of one element:
-//   c_M rho V Mref(n, n) I + c_K (V/4) sum_j B_n(j)^T D_j B_n(j)
-// with B_n^T D B_n [c][d] = sum_{p,q} g_p g_q D[v(c, p)][v(d, q)], g = grad N_n
-// at point j and v(c, p) the Voigt index of du_c/dx_p.  Per point the 6 x 6
-// coefficients of the quadratic forms in (gx^2, gy^2, gz^2, gx gy, gy gz, gz gx)
-// are formed once and shared by the nodes.  A thread takes one element-member
+// The blocks by colours (more than 256 slots): the elements of one colour share
+// no node.  A thread takes one element-member
 // and one part of the nodes (the 4 corners, edges 01 12 20, or edges 03 13
 // 23), so it holds at most 4 blocks: FP64 register pressure sets the
 // occupancy here, and each part re-reads D (from L2).
-__device__ __forceinline__ constexpr int voigt_of(int c, int p)
-{
-    return c == p ? c : ((c + p == 1) ? 3 : ((c + p == 3) ? 4 : 5));
-}
-
-// adds w g^T C g (the 6 entries of the symmetric 3x3 block) for node n (a
-// compile-time index after unrolling) with g = grad N_n at barycentrics L
-__device__ __forceinline__ void diag_node_add(int n, const double L[4], const double gL[4][3], const double C[6][6],
-                                              double w, double acc[6])
-{
-    constexpr int E[6][2] = {{0, 1}, {1, 2}, {2, 0}, {0, 3}, {1, 3}, {2, 3}};
-    double g[3];
-    if (n < 4) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) g[a] = (4.0 * L[n] - 1.0) * gL[n][a];
-    } else {
-        const int ea = E[n - 4][0], eb = E[n - 4][1];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) g[a] = 4.0 * (L[ea] * gL[eb][a] + L[eb] * gL[ea][a]);
-    }
-    const double gg[6] = {g[0] * g[0], g[1] * g[1], g[2] * g[2], g[0] * g[1], g[1] * g[2], g[2] * g[0]};
-#pragma unroll
-    for (int cd = 0; cd < 6; ++cd) {
-        double a = 0.0;
-#pragma unroll
-        for (int pq = 0; pq < 6; ++pq) a += gg[pq] * C[cd][pq];
-        acc[cd] += w * a;
-    }
-}
-
 __global__ __launch_bounds__(256) void k_diag(DevMesh M, int MB, int nm, int e0, int e1,
                                              const double* __restrict__ D, const double* __restrict__ h,
                                              const double* __restrict__ mat, StepConst sc,
@@ -846,8 +812,6 @@ __global__ __launch_bounds__(256) void k_diag(DevMesh M, int MB, int nm, int e0,
     const double dt = sc.dt;
     const double sm = rho * vol * (4.0 / (dt * dt) + 2.0 * sc.ahat * he / dt);
     const double w = (1.0 + 2.0 * sc.bhat * he / dt) * vol * 0.25;
-    constexpr int PQ[6][2] = {{0, 0}, {1, 1}, {2, 2}, {0, 1}, {1, 2}, {2, 0}};
-    constexpr int CD[6][2] = {{0, 0}, {0, 1}, {0, 2}, {1, 1}, {1, 2}, {2, 2}};
     double blk[4][6];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -863,28 +827,20 @@ __global__ __launch_bounds__(256) void k_diag(DevMesh M, int MB, int nm, int e0,
             const uint32_t rs = (uint32_t)(EB * MB);
 #pragma unroll
             for (int k = 0; k < 21; ++k) d[k] = ld_u(Dj, (uint32_t)k * rs + (uint32_t)m);
-#pragma unroll
-            for (int cd = 0; cd < 6; ++cd)
-#pragma unroll
-                for (int pq = 0; pq < 6; ++pq) {
-                    const int c = CD[cd][0], dd = CD[cd][1], p = PQ[pq][0], q = PQ[pq][1];
-                    double v = d[sym6(voigt_of(c, p), voigt_of(dd, q))];
-                    if (p != q) v += d[sym6(voigt_of(c, q), voigt_of(dd, p))];
-                    C[cd][pq] = v;
-                }
+            diag_coef<0, 6>(d, C);
         }
         double L[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) L[i] = (i == j) ? QA_ : QB_;
         if (part == 0) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) diag_node_add(i, L, gL, C, w, blk[i]);
+            for (int i = 0; i < 4; ++i) diag_node_add<6>(i, L, gL, C, w, blk[i]);
         } else if (part == 1) {
 #pragma unroll
-            for (int i = 0; i < 3; ++i) diag_node_add(4 + i, L, gL, C, w, blk[i]);
+            for (int i = 0; i < 3; ++i) diag_node_add<6>(4 + i, L, gL, C, w, blk[i]);
         } else {
 #pragma unroll
-            for (int i = 0; i < 3; ++i) diag_node_add(7 + i, L, gL, C, w, blk[i]);
+            for (int i = 0; i < 3; ++i) diag_node_add<6>(7 + i, L, gL, C, w, blk[i]);
         }
     }
     const int nn = part == 0 ? 4 : 3, n0 = part == 0 ? 0 : 1 + 3 * part;
@@ -903,13 +859,8 @@ __global__ __launch_bounds__(256) void k_diag(DevMesh M, int MB, int nm, int e0,
     }
 }
 
-// Diagonal blocks of the inner operator (one D per element, the bfloat16
-// element mean): with D constant over the element the stiffness block of
-// node n is C : int grad N_n grad N_n^T dV, and that integral has a closed
-// form in the barycentric gradients g (int L_a^2 = V/10, int L_a L_b = V/20,
-// int L_a = V/4): corner a 0.6 V g_a g_a^T; edge (a, b)
-// 1.6 V (g_a g_a^T + g_b g_b^T) + 0.8 V (g_a g_b^T + g_b g_a^T).  One lane
-// per element-member of a colour (the colour's elements share no node).
+// The inner operator's blocks (one D per element) by colours, one lane per
+// element-member.
 __global__ __launch_bounds__(256) void k_diag_mean(DevMesh M, int MB, int nm, int e0, int e1,
                                                   const uint32_t* __restrict__ D16, const double* __restrict__ h,
                                                   const double* __restrict__ mat, StepConst sc,
@@ -935,9 +886,6 @@ __global__ __launch_bounds__(256) void k_diag_mean(DevMesh M, int MB, int nm, in
     const double dt = sc.dt;
     const double sm = rho * vol * (4.0 / (dt * dt) + 2.0 * sc.ahat * he / dt);
     const double sk = (1.0 + 2.0 * sc.bhat * he / dt) * vol;
-    constexpr int PQ[6][2] = {{0, 0}, {1, 1}, {2, 2}, {0, 1}, {1, 2}, {2, 0}};
-    constexpr int CD[6][2] = {{0, 0}, {0, 1}, {0, 2}, {1, 1}, {1, 2}, {2, 2}};
-    constexpr int E[6][2] = {{0, 1}, {1, 2}, {2, 0}, {0, 3}, {1, 3}, {2, 3}};
     const int EB = MB >= 64 ? 1 : 64 / MB;
     double C[6][6];
     {
@@ -948,31 +896,12 @@ __global__ __launch_bounds__(256) void k_diag_mean(DevMesh M, int MB, int nm, in
             d[2 * q] = (double)bf2f(wv & 0xFFFFu);
             d[2 * q + 1] = (double)bf2f(wv >> 16);
         }
-#pragma unroll
-        for (int cd = 0; cd < 6; ++cd)
-#pragma unroll
-            for (int pq = 0; pq < 6; ++pq) {
-                const int c = CD[cd][0], dd = CD[cd][1], p = PQ[pq][0], q = PQ[pq][1];
-                double v = d[sym6(voigt_of(c, p), voigt_of(dd, q))];
-                if (p != q) v += d[sym6(voigt_of(c, q), voigt_of(dd, p))];
-                C[cd][pq] = v;
-            }
+        diag_coef<0, 6>(d, C);
     }
 #pragma unroll
     for (int n = 0; n < 10; ++n) {
-        double G[6];  // int d_p N_n d_q N_n dV / V in the PQ order
-        if (n < 4) {
-#pragma unroll
-            for (int pq = 0; pq < 6; ++pq) G[pq] = 0.6 * gL[n][PQ[pq][0]] * gL[n][PQ[pq][1]];
-        } else {
-            const int a = E[n - 4][0], b = E[n - 4][1];
-#pragma unroll
-            for (int pq = 0; pq < 6; ++pq) {
-                const int p = PQ[pq][0], q = PQ[pq][1];
-                G[pq] = 1.6 * (gL[a][p] * gL[a][q] + gL[b][p] * gL[b][q]) +
-                        0.8 * (gL[a][p] * gL[b][q] + gL[b][p] * gL[a][q]);
-            }
-        }
+        double G[6];
+        mean_grad_products(n, gL, G);
         const long node = M.conn[n * ne + e];
         const double md = sm * mass_ref(n, n);
         double* dg = diag + node * 6 * MB;
@@ -1001,15 +930,11 @@ void launch_diag(hipStream_t s, const DevMesh& M, int MB, int nm, int e0, int e1
     if (n > 0) hipLaunchKernelGGL(k_diag, dim3(nblocks(n)), dim3(256), 0, s, M, MB, nm, e0, e1, D, h, mat, sc, diag);
 }
 
-__global__ void k_diag_dashpot(DevMesh M, int MB, int nm, const double* __restrict__ mat, double coef,
-                               double* __restrict__ diag)
+// the dashpot's part of the diagonal block of boundary node i
+__device__ __forceinline__ void dashpot_diag(const DevMesh& M, int MB, int m, long i, const double* __restrict__ mat,
+                                             double coef, double acc[6])
 {
-    const long t = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    const int m = (int)(t % MB);
-    const long i = t / MB;
-    if (i >= M.nbn || m >= nm) return;
-    const long node = M.bn_node[i];
-    double acc[6] = {0, 0, 0, 0, 0, 0};
+    for (int k = 0; k < 6; ++k) acc[k] = 0.0;
     for (int q = M.bn_ptr[i]; q < M.bn_ptr[i + 1]; ++q) {
         const int f = M.bn_face[q], a = M.bn_loc[q];
         const int l = M.f_layer[f];
@@ -1025,6 +950,18 @@ __global__ void k_diag_dashpot(DevMesh M, int MB, int nm, const double* __restri
         acc[4] += Maa * ((vp - vs) * n[1] * n[2]);
         acc[5] += Maa * (vs + (vp - vs) * n[2] * n[2]);
     }
+}
+
+__global__ void k_diag_dashpot(DevMesh M, int MB, int nm, const double* __restrict__ mat, double coef,
+                               double* __restrict__ diag)
+{
+    const long t = blockIdx.x * (long)blockDim.x + threadIdx.x;
+    const int m = (int)(t % MB);
+    const long i = t / MB;
+    if (i >= M.nbn || m >= nm) return;
+    const long node = M.bn_node[i];
+    double acc[6];
+    dashpot_diag(M, MB, m, i, mat, coef, acc);
     for (int k = 0; k < 6; ++k) diag[(node * 6 + k) * MB + m] += acc[k];
 }
 
@@ -1035,16 +972,10 @@ void launch_diag_dashpot(hipStream_t s, const DevMesh& M, int MB, int nm, const 
     if (n > 0) hipLaunchKernelGGL(k_diag_dashpot, dim3(nblocks(n)), dim3(256), 0, s, M, MB, nm, mat, coef, diag);
 }
 
-__global__ void k_invert_diag(int nn, int MB, int nm, const double* __restrict__ diag,
-                              double* __restrict__ pinv, float* __restrict__ pinv32)
+// pinv of node i: the inverse of its block a = [a0 a1 a2; a1 a3 a4; a2 a4 a5]
+__device__ __forceinline__ void invert_block(const double a[6], long i, int MB, int m, double* __restrict__ pinv,
+                                             float* __restrict__ pinv32)
 {
-    const long t = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    const int m = (int)(t % MB);
-    const long i = t / MB;
-    if (i >= nn || m >= nm) return;
-    double a[6];
-    for (int k = 0; k < 6; ++k) a[k] = diag[(i * 6 + k) * MB + m];
-    // a = [a0 a1 a2; a1 a3 a4; a2 a4 a5]
     const double c00 = a[3] * a[5] - a[4] * a[4];
     const double c01 = a[2] * a[4] - a[1] * a[5];
     const double c02 = a[1] * a[4] - a[2] * a[3];
@@ -1058,16 +989,80 @@ __global__ void k_invert_diag(int nn, int MB, int nm, const double* __restrict__
         inv[0] = c00 * r; inv[1] = c01 * r; inv[2] = c02 * r;
         inv[3] = c11 * r; inv[4] = c12 * r; inv[5] = c22 * r;
     }
+#pragma unroll
     for (int k = 0; k < 6; ++k) {
         pinv[(i * 6 + k) * MB + m] = inv[k];
         if (pinv32) pinv32[(i * 6 + k) * MB + m] = (float)inv[k];
     }
 }
 
+__global__ void k_invert_diag(int nn, int MB, int nm, const double* __restrict__ diag,
+                              double* __restrict__ pinv, float* __restrict__ pinv32)
+{
+    const long t = blockIdx.x * (long)blockDim.x + threadIdx.x;
+    const int m = (int)(t % MB);
+    const long i = t / MB;
+    if (i >= nn || m >= nm) return;
+    double a[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) a[k] = diag[(i * 6 + k) * MB + m];
+    invert_block(a, i, MB, m, pinv, pinv32);
+}
+
 void launch_invert_diag(hipStream_t s, int nn, int MB, int nm, const double* diag, double* pinv, float* pinv32)
 {
     long n = (long)nn * MB;
     if (n > 0) hipLaunchKernelGGL(k_invert_diag, dim3(nblocks(n)), dim3(256), 0, s, nn, MB, nm, diag, pinv, pinv32);
+}
+
+// Node sums of the rows of k_diag_slots: half 0 writes its three entries of the
+// diagonal blocks; half 1 has the other three in registers, adds the dashpot's
+// part at boundary nodes, writes them and the inverse.
+template <int HALF>
+__global__ __launch_bounds__(256) void k_diag_rows(DevMesh M, int MB, int nm, const double* __restrict__ rows,
+                                                  const double* __restrict__ mat, double coef,
+                                                  double* __restrict__ diag, double* __restrict__ pinv,
+                                                  float* __restrict__ pinv32)
+{
+    const long t = blockIdx.x * 256l + threadIdx.x;
+    const int m = (int)(t % MB);
+    const long nd = t / MB;
+    if (nd >= M.nn || m >= nm) return;
+    const long node = MB >= 64 ? (long)__builtin_amdgcn_readfirstlane((int)nd) : nd;
+    double* dg = diag + node * 6 * MB + m;
+    double s[3];
+    if constexpr (HALF == 0) {
+        node_rows<double>(M, node, rows, MB, m, false, s);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) dg[(size_t)c * MB] = s[c];
+    } else {
+        double a[6];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) a[c] = dg[(size_t)c * MB];
+        node_rows<double>(M, node, rows, MB, m, false, s);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) a[3 + c] = s[c];
+        const int i = M.bn_of_node[node];
+        if (i >= 0) {
+            double b[6];
+            dashpot_diag(M, MB, m, i, mat, coef, b);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) a[k] += b[k];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) dg[(size_t)c * MB] = a[c];
+        }
+#pragma unroll
+        for (int c = 3; c < 6; ++c) dg[(size_t)c * MB] = a[c];
+        invert_block(a, node, MB, m, pinv, pinv32);
+    }
+}
+
+void launch_diag_rows(hipStream_t s, const DevMesh& M, int MB, int nm, int half, const double* rows, const double* mat,
+                      double coef, double* diag, double* pinv, float* pinv32)
+{
+    const dim3 g(nblocks((long)M.nn * MB)), b(256);
+    if (half == 0) hipLaunchKernelGGL((k_diag_rows<0>), g, b, 0, s, M, MB, nm, rows, mat, coef, diag, pinv, pinv32);
+    else hipLaunchKernelGGL((k_diag_rows<1>), g, b, 0, s, M, MB, nm, rows, mat, coef, diag, pinv, pinv32);
 }
 
 // ---------------------------------------------------------------------------

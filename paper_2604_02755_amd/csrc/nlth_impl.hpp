@@ -147,6 +147,12 @@ void launch_diag(hipStream_t s, const DevMesh& M, int MB, int nm, int e0, int e1
 // the same from the bfloat16 element-mean D of the inner operator (closed-form integrals)
 void launch_diag_mean(hipStream_t s, const DevMesh& M, int MB, int nm, int e0, int e1, const uint32_t* D16,
                       const double* h, const double* mat, StepConst sc, double* diag);
+// the same by clusters, three of the six entries at a time, and their node sums
+// (half 1: with the dashpot's part and the inverse); D16 not NULL: element means
+void launch_diag_slots(hipStream_t s, const DevMesh& M, int MB, int nm, int half, const double* D64,
+                       const uint32_t* D16, const double* h, const double* mat, StepConst sc, double* rows);
+void launch_diag_rows(hipStream_t s, const DevMesh& M, int MB, int nm, int half, const double* rows, const double* mat,
+                      double coef, double* diag, double* pinv, float* pinv32);
 void launch_diag_dashpot(hipStream_t s, const DevMesh& M, int MB, int nm, const double* mat, int n_layers,
                          double coef, double* diag);
 void launch_invert_diag(hipStream_t s, int nn, int MB, int nm, const double* diag, double* pinv,

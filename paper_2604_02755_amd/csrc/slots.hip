@@ -188,18 +188,18 @@ __global__ __launch_bounds__(512) void k_op_slots(DevMesh M, int MB, int nm, int
         }
         __syncthreads();
         for (int lr = slot; act && lr < ncn; lr += NT >> LG) {
-            T s[3];
+            T s[3], xv[3] = {0, 0, 0};
+            if (partial) {  // (under way while the rows are summed)
+#pragma unroll
+                for (int cc = 0; cc < 3; ++cc)
+                    xv[cc] = STAGE ? xs[cc * XS + (lr << LG) + lane] : x1[((size_t)nds[lr] * 3 + cc) * MB + m];
+            }
             row_sums<T>(lists, lptr[lr], lptr[lr + 1], out, OS, LG, lane, s);
             T* rp = rows + ((size_t)r0 + lr) * 3 * MB + m;
 #pragma unroll
             for (int cc = 0; cc < 3; ++cc) {
                 rp[(size_t)cc * MB] = s[cc];
-                if (partial) {
-                    T xv;
-                    if constexpr (STAGE) xv = xs[cc * XS + (lr << LG) + lane];
-                    else xv = x1[((size_t)nds[lr] * 3 + cc) * MB + m];
-                    dot += (double)xv * (double)s[cc];
-                }
+                dot += (double)xv[cc] * (double)s[cc];
             }
         }
     }
@@ -299,6 +299,134 @@ void launch_ebe32_ctail(hipStream_t s, const DevMesh& M, int G, const int* tl, c
 {
     const float* none = nullptr;
     op_slots<float, 4, OP_A>(s, M, G, G, tl, cD, ch, cmat, sc, x, none, co, nullptr, dcoef, nullptr, partial, nblk);
+}
+
+// The 3x3 block-Jacobi diagonal blocks, three of their six entries (half 0: 00
+// 01 02, half 1: 11 12 22) at a time: the block's three values of a node take
+// the place of its three forces in the scheme above (one lane per
+// element-member, LDS, rows out, node sums by k_diag_rows), for ensembles of up to 256
+// slots.  DK 4: one bfloat16 D per element.  Bound by the FP64 D on many
+// members, which both halves read (all six entries at once would take 60 doubles
+// of LDS a lane and a rows buffer of twice the size).
+// Against one launch per element colour adding to the nodes:
+// DIAGFIG
+template <int DK, int LG>
+__global__ __launch_bounds__(256) void k_diag_slots(DevMesh M, int MB, int nm, int ncb, int half,
+                                                   const void* __restrict__ Dv, const double* __restrict__ h,
+                                                   const double* __restrict__ mat, StepConst sc,
+                                                   double* __restrict__ rows)
+{
+    using S = SlotShape<double, LG>;
+    constexpr int L = 1 << LG, OS = S::OS;
+    extern __shared__ __align__(16) char smem[];
+    const int t = threadIdx.x, NT = blockDim.x;
+    const int blk = (int)blockIdx.x, g = blk / ncb * L, cb = blk % ncb;
+    const int c = (cb % 8) * (ncb / 8) + cb / 8;  // XCD-contiguous clusters
+    if (c >= M.ncl) return;
+    double* out = (double*)smem;  // [33][OS], the last three rows zeros
+    uint2* lists = (uint2*)(out + 33 * OS);
+    uint16_t* lptr = (uint16_t*)(lists + M.cl_list_stride);
+    const int4 ch = M.cl_head[c];
+    const int e0 = ch.x, r0 = ch.y, nec = ch.z, ncn = ch.w;
+    const int slot = t >> LG, lane = t & (L - 1), m = g + lane;
+    const uint4* lsrc = (const uint4*)(M.cl_lists + (size_t)c * M.cl_list_stride);
+    for (int i = t; 2 * i < M.cl_list_stride; i += NT) ((uint4*)lists)[i] = lsrc[i];
+    for (int i = t; i < M.cl_node_stride; i += NT) lptr[i] = M.cl_lptr[(size_t)c * M.cl_node_stride + i];
+    for (int i = t; i < 3 * OS; i += NT) out[30 * OS + i] = 0.0;
+    const int e = e0 + slot;
+    if (slot < nec && m < nm) {
+        double gL[4][3];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) gL[k / 3][k % 3] = M.geo64[(size_t)k * M.ne + e];
+        const double vol = M.geo64[(size_t)12 * M.ne + e];
+        const double rho = matv(mat, M.layer[e], MAT_RHO, MB, m);
+        double he = 0.0;
+        if (sc.damping_mode == 0 && h) he = h[(size_t)e * MB + m];
+        else if (sc.damping_mode == 1) he = sc.h0;
+        const double dt = sc.dt;
+        const double sm = rho * vol * (4.0 / (dt * dt) + 2.0 * sc.ahat * he / dt);
+        const double sk = (1.0 + 2.0 * sc.bhat * he / dt) * vol;
+        const int EB = MB >= 64 ? 1 : 64 / MB;
+        double acc[10][3], C[3][6];
+#pragma unroll
+        for (int n = 0; n < 10; ++n) acc[n][0] = acc[n][1] = acc[n][2] = 0.0;
+        if constexpr (DK == 4) {
+            double d[22];
+#pragma unroll
+            for (int q = 0; q < 11; ++q) {
+                const uint32_t wv = ((const uint32_t*)Dv)[d16m_index(e, q, MB, EB, m)];
+                d[2 * q] = (double)bf2f(wv & 0xFFFFu);
+                d[2 * q + 1] = (double)bf2f(wv >> 16);
+            }
+            if (half) diag_coef<3, 3>(d, C);
+            else diag_coef<0, 3>(d, C);
+#pragma unroll
+            for (int n = 0; n < 10; ++n) {
+                double G[6];
+                mean_grad_products(n, gL, G);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    double a = 0.0;
+#pragma unroll
+                    for (int pq = 0; pq < 6; ++pq) a += G[pq] * C[k][pq];
+                    acc[n][k] = sk * a;
+                }
+            }
+        } else {
+#pragma unroll 1
+            for (int j = 0; j < 4; ++j) {
+                double d[21], lam[4];
+                const double* Dj = (const double*)Dv + d_index(e, j, 0, MB, EB, m);
+#pragma unroll
+                for (int k = 0; k < 21; ++k) d[k] = Dj[(size_t)k * EB * MB];
+                if (half) diag_coef<3, 3>(d, C);
+                else diag_coef<0, 3>(d, C);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) lam[i] = (i == j) ? QA_ : QB_;
+#pragma unroll
+                for (int n = 0; n < 10; ++n) diag_node_add<3>(n, lam, gL, C, 0.25 * sk, acc[n]);
+            }
+        }
+#pragma unroll
+        for (int n = 0; n < 10; ++n) {
+            const double md = sm * mass_ref(n, n);  // to 00, or 11 and 22
+            out[(3 * n) * OS + t] = acc[n][0] + md;
+            out[(3 * n + 1) * OS + t] = acc[n][1];
+            out[(3 * n + 2) * OS + t] = acc[n][2] + (half ? md : 0.0);
+        }
+    }
+    __syncthreads();
+    for (int lr = slot; m < nm && lr < ncn; lr += NT >> LG) {
+        double s[3];
+        row_sums<double>(lists, lptr[lr], lptr[lr + 1], out, OS, LG, lane, s);
+        double* rp = rows + ((size_t)r0 + lr) * 3 * MB + m;
+#pragma unroll
+        for (int cc = 0; cc < 3; ++cc) rp[(size_t)cc * MB] = s[cc];
+    }
+}
+
+void launch_diag_slots(hipStream_t s, const DevMesh& M, int MB, int nm, int half, const double* D64,
+                       const uint32_t* D16, const double* h, const double* mat, StepConst sc, double* rows)
+{
+    const int ncb = (M.ncl + 7) / 8 * 8;
+    // lanes of a block: the wide clusters' 64 elements with up to 4 members, the
+    // regular ones' 16 with 16 (30 doubles of LDS a lane, two blocks of 256 on a CU)
+    const int LG = MB >= 16 ? 4 : (MB >= 4 ? 2 : MB - 1);
+    const int NT = std::max(LG == 0 ? 128 : 256, ((M.cl_max_elems << LG) + 63) / 64 * 64);
+    const size_t tail = (size_t)M.cl_list_stride * 8 + 512;
+#define NLTH_DIAG(LGV)                                                                                               \
+    do {                                                                                                             \
+        const size_t lds = (size_t)33 * SlotShape<double, LGV>::OS * 8 + tail;                                       \
+        if (D16) hipLaunchKernelGGL((k_diag_slots<4, LGV>), dim3(ncb * (MB >> LGV)), dim3(NT), lds, s, M, MB, nm, ncb, half, (const void*)D16, h, mat, sc, rows); \
+        else hipLaunchKernelGGL((k_diag_slots<0, LGV>), dim3(ncb * (MB >> LGV)), dim3(NT), lds, s, M, MB, nm, ncb, half, (const void*)D64, h, mat, sc, rows); \
+    } while (0)
+    switch (LG) {
+    case 0: NLTH_DIAG(0); break;
+    case 1: NLTH_DIAG(1); break;
+    case 2: NLTH_DIAG(2); break;
+    default: NLTH_DIAG(4); break;
+    }
+#undef NLTH_DIAG
 }
 
 }  // namespace nlth
