@@ -1007,11 +1007,12 @@ void Ens::create(Ctx* c, const Mesh* m, const Problem& prob, int member_pad)
     NLTH_HIP(hipMemsetAsync(scal.p, 0, scal.bytes, s));
     double* dptr = scal.as<double>();
     cs.bb = dptr; cs.rr = dptr + MB; cs.rz = dptr + 2 * MB; cs.alpha = dptr + 3 * MB; cs.beta = dptr + 4 * MB;
-    cs.pAp = dptr + 5 * MB; cs.r0 = dptr + 6 * MB; cs.irr = dptr + 7 * MB; cs.irz = dptr + 8 * MB;
+    cs.pAp = dptr + 5 * MB; cs.rz_prev = dptr + 6 * MB; cs.irz = dptr + 8 * MB;
     cs.ialpha = dptr + 9 * MB; cs.ibeta = dptr + 10 * MB; cs.ir0 = dptr + 11 * MB;
     int* iptr = (int*)(dptr + 12 * MB);
     cs.active = iptr; cs.iters = iptr + MB; cs.status = iptr + 2 * MB; cs.inner_active = iptr + 3 * MB;
     cs.inner_iters = iptr + 4 * MB; cs.inner_total = iptr + 5 * MB; cs.inner_upd = iptr + 6 * MB;
+    cs.iters_prev = iptr + 7 * MB;
     cs.lz = lz.as<double>();
     NLTH_HIP(hipHostMalloc((void**)&h_mail, sizeof(int) * (5 * (size_t)MB + 1),
                            hipHostMallocMapped | hipHostMallocCoherent));
@@ -1566,6 +1567,51 @@ void Ens::cheb_solve()
     NLTH_HIP(hipGraphLaunch(g_cheb, s));
 }
 
+// A few-slot CG iteration after its operator (rows and the nblk partial sums of
+// p.Ap): the updates and their stages
+template <typename T>
+void Ens::iter_updates(int nblk, T* x, T* p, T* r, T* z, const T* pinv_t, const double* alpha, const double* beta,
+                       const int* act, double tol2, int maxit)
+{
+    const bool inner = sizeof(T) == 4;
+    double* pd = partial.as<double>();
+    StageIn st{};
+    const StageIn* fused = stage_sums(inner ? FIN_IN_ALPHA : FIN_ALPHA, pd, 1, nblk, tol2, maxit, st) ? &st : nullptr;
+    if (st.partial == pd) pd += (size_t)nblk * MB;  // what this launch reads stays while it writes its own
+    hipEvent_t t0 = nullptr;
+    if (inner) tstart(t0);
+    launch_rows_update<T>(s, UPD_PZ, mesh->dev(MB), MB, nm, 0, nullptr, (const T*)cbuf.p, r, z, pinv_t, nullptr, nullptr,
+                          alpha, act, pd, &nblk, fused);
+    if (inner) tstop(t0, &pc_gather32, (int64_t)mesh->nn * nm);
+    fused = stage_sums(inner ? FIN_IN_BETA : FIN_BETA, pd, 2, nblk, tol2, maxit, st) ? &st : nullptr;
+    launch_pz<T>(s, ndof, MB, nm, x, p, z, alpha, beta, cs.inner_upd, fused);
+}
+
+// A stage of a few-slot iteration: true if the next kernel's blocks form it
+// themselves, each from the sums in `st` (every block the same), false if it was
+// launched.  A stage of its own is a launch and its chain, 4.6 us, and where the
+// sums are many a fold of them before it, 4.8; formed in the next kernel it
+// makes that 1.2 to 3.5 us longer while each block reads few sums (12,288
+// elements, FP64, 1 slot: 50 us of kernels an iteration, 28 with both fused), 5
+// with 3,700 of them and 2,000 blocks (331,776 elements, 1 slot).  From 16 slots
+// on the sums are folded, and 16 lanes read what is left as fast as one.
+bool Ens::stage_sums(FinalizeStage stage, const double* pd, int nd, int nblk, double tol2, int maxit, StageIn& st)
+{
+    st = StageIn{nullptr, nblk, tol2, maxit, cs};
+    if ((long)nd * nblk * MB <= kFuseSums) {
+        st.partial = pd;
+        return true;
+    }
+    if (MB >= 16) {
+        st.nblk = kFoldSums / (nd * MB);
+        st.partial = fold;
+        launch_fold(s, nd, MB, pd, nblk, st.nblk, fold);
+        return true;
+    }
+    launch_finalize(s, stage, nd, MB, nm, pd, nblk, fold, nullptr, 0, cs, tol2, maxit);
+    return false;
+}
+
 // one inner FP32 PCG iteration (every launch reads its scalars on the device)
 void Ens::inner_iter()
 {
@@ -1583,11 +1629,9 @@ void Ens::inner_iter()
     if (scatter == 0) {
         op_rows32(ip.as<float>(), iact, &nblk);
         tstop(t0, &pc_ebe32, (int64_t)mesh->ne * nm);
-        fin(FIN_IN_ALPHA, 1, nblk, tol2, P.inner_maxit);
-        tstart(t0);
-        launch_rows_update<float>(s, UPD_PZ, mesh->dev(MB), MB, nm, 0, nullptr, (const float*)cbuf.p, ir.as<float>(),
-                                  iw.as<float>(), pinv32.as<float>(), nullptr, nullptr, cs.ialpha, iact, pd, &nblk);
-        tstop(t0, &pc_gather32, (int64_t)mesh->nn * nm);
+        iter_updates<float>(nblk, iz.as<float>(), ip.as<float>(), ir.as<float>(), iw.as<float>(), pinv32.as<float>(),
+                            cs.ialpha, cs.ibeta, iact, tol2, P.inner_maxit);
+        return;
     } else {
         if (scatter == 2) {
             op_rows32(ip.as<float>(), iact, nullptr);
@@ -1622,6 +1666,15 @@ void Ens::pcg_iter()
     const int* act = cs.active;
     const double tol2 = P.cg_tol * P.cg_tol;
     double* pd = partial.as<double>();
+    if (scatter == 0) {
+        hipEvent_t t0;
+        tstart(t0);
+        op_rows(OP_A, p.as<double>(), nullptr, act, 2.0 / P.dt, nullptr, &nblk);
+        tstop(t0, &pc_ebe64, (int64_t)mesh->ne * nm);
+        iter_updates<double>(nblk, x, p.as<double>(), r.as<double>(), z.as<double>(), pinv.as<double>(), cs.alpha,
+                             cs.beta, act, tol2, P.cg_maxit);
+        return;
+    }
     op_alpha(FIN_ALPHA, tol2, act);
     if (scatter != 1) {
         launch_rows_update<double>(s, UPD_PZ, mesh->dev(MB), MB, nm, 0, nullptr, cbuf.as<double>(), r.as<double>(),

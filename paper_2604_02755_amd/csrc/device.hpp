@@ -541,4 +541,41 @@ __device__ __forceinline__ void mean_grad_products(int n, const double gL[4][3],
     }
 }
 
+// Per-member sums of ND x nblk partial rows of MB <= 32 slots by a block of 256
+// threads (valid in threads t < MB), in a fixed order: every block of a launch
+// that forms them gets the same bits.  Eight loads of a thread in flight at a time.
+template <int ND>
+__device__ __forceinline__ void member_sums(const double* __restrict__ partial, int nblk, int MB, double* __restrict__ sh,
+                                            double S[ND])
+{
+    const int t = threadIdx.x, m = t % MB, rpb = 256 / MB;
+    double a[ND];
+#pragma unroll
+    for (int k = 0; k < ND; ++k) a[k] = 0.0;
+    for (int b = t / MB; b < nblk; b += 8 * rpb) {
+        double v[ND][8];
+#pragma unroll
+        for (int k = 0; k < ND; ++k)
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                v[k][q] = b + q * rpb < nblk ? partial[((size_t)k * nblk + b + q * rpb) * MB + m] : 0.0;
+#pragma unroll
+        for (int k = 0; k < ND; ++k)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) a[k] += v[k][q];
+    }
+#pragma unroll
+    for (int k = 0; k < ND; ++k) {
+        for (int o = 32; o >= MB; o >>= 1) a[k] += __shfl_xor(a[k], o);
+        if ((t & 63) < MB) sh[(k * 4 + (t >> 6)) * MB + (t & 63)] = a[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ND; ++k) {
+        S[k] = 0.0;
+        if (t < MB)
+            for (int w = 0; w < 4; ++w) S[k] += sh[(k * 4 + w) * MB + t];
+    }
+}
+
 }  // namespace nlth

@@ -457,34 +457,77 @@ template void launch_gather<float>(hipStream_t, const DevMesh&, int, int, const 
 // rows of the listed members, partials in the full layout.  Bound by HBM: per
 // DOF-member of the FP32 inner CG on 64 members the rows (2.7 per node) 11 B, r
 // read and written and z written 12 B, the inverse 8 B.
-template <typename T, int KIND, int G>
+// FUSED (few slots, few partial sums): every block forms the alpha stage from the
+// operator's partial sums itself, with its first node's loads under way, and
+// block 0 writes what stage_logic(FIN_ALPHA / FIN_IN_ALPHA) would; no thread reads
+// those (sg.partial is not this launch's own `partial`).
+template <typename T, int KIND, int G, bool FUSED>
 __global__ __launch_bounds__(256) void k_rows_update(DevMesh M, int MB, int nm, const int* __restrict__ tl,
                                                     const T* __restrict__ f, T* __restrict__ r, T* __restrict__ z,
                                                     const T* __restrict__ pinv, T* __restrict__ x,
                                                     const T* __restrict__ p, const double* __restrict__ alpha,
-                                                    const int* __restrict__ active, double* __restrict__ partial)
+                                                    const int* __restrict__ active, double* __restrict__ partial,
+                                                    StageIn sg)
 {
     const int W = G ? G : MB, t = threadIdx.x, k = t % W, slot = t / W;
     const int npb = 256 / W;
     const int m = !G ? k : (k < min(tl[0], W) ? tl[1 + k] : -1);
     const bool act = m >= 0 && m < nm && active[m];
     double d0 = 0.0, d1 = 0.0;
+    const long per = ((M.nn + gridDim.x - 1) / gridDim.x + npb - 1) / npb * npb;
+    const long n0 = (long)blockIdx.x * per, n1 = n0 + per < M.nn ? n0 + per : M.nn;
+    T q[3], R[3], P[6];
+    auto load = [&](long node) {
+        const size_t i = (size_t)node * 3 * W + k;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) R[c] = r[i + (size_t)c * W];
+        if (KIND == UPD_PZ) {
+            const T* pv = pinv + (size_t)node * 6 * W + k;
+#pragma unroll
+            for (int c = 0; c < 6; ++c) P[c] = pv[(size_t)c * W];
+        }
+        node_rows<T>(M, node, f, W, k, true, q);
+    };
+    T al = 0;
+    if constexpr (FUSED) {
+        constexpr bool INNER = sizeof(T) == 4;
+        const CgScalars& cs = sg.cs;
+        if (act && n0 + slot < n1) load(n0 + slot);
+        __shared__ double sum[4 * 32];
+        __shared__ double sa[32];
+        bool on = false;
+        double rz = 0.0, S[1];
+        if (t < MB && t < nm) {
+            on = active[t];
+            rz = INNER ? cs.irz[t] : cs.rz[t];
+        }
+        member_sums<1>(sg.partial, sg.nblk, MB, sum, S);
+        if (t < MB) {
+            const double a = on ? rz / S[0] : 0.0;
+            sa[t] = a;
+            if (blockIdx.x == 0 && t < nm) {
+                const int it = INNER ? cs.inner_iters[t] : cs.iters[t];
+                (INNER ? cs.ialpha : cs.alpha)[t] = a;
+                cs.inner_upd[t] = on;
+                cs.rz_prev[t] = rz;
+                cs.iters_prev[t] = it;
+                if (INNER) {
+                    if (on && it < kLanczosMax) cs.lz[(long)it * MB + t] = a;
+                } else {
+                    cs.pAp[t] = S[0];
+                }
+            }
+        }
+        __syncthreads();
+        al = (T)sa[k];
+    } else if (act) {
+        al = (T)alpha[m];
+    }
     if (act) {
-        const T al = (T)alpha[m];
-        const long per = ((M.nn + gridDim.x - 1) / gridDim.x + npb - 1) / npb * npb;
-        const long n0 = (long)blockIdx.x * per, n1 = n0 + per < M.nn ? n0 + per : M.nn;
         for (long nd = n0 + slot; nd < n1; nd += npb) {
             const long node = !G && MB >= 64 ? (long)__builtin_amdgcn_readfirstlane((int)nd) : nd;
-            T q[3];
+            if (!FUSED || nd != n0 + slot) load(node);
             const size_t i = (size_t)node * 3 * W + k;
-            T R[3] = {r[i], r[i + W], r[i + 2 * W]};
-            T P[6];
-            if (KIND == UPD_PZ) {
-                const T* pv = pinv + (size_t)node * 6 * W + k;
-#pragma unroll
-                for (int c = 0; c < 6; ++c) P[c] = pv[(size_t)c * W];
-            }
-            node_rows<T>(M, node, f, W, k, true, q);
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 R[c] -= al * q[c];
@@ -534,32 +577,37 @@ __global__ __launch_bounds__(256) void k_rows_update(DevMesh M, int MB, int nm, 
 template <typename T>
 void launch_rows_update(hipStream_t s, int kind, const DevMesh& M, int MB, int nm, int G, const int* tl, const T* rows,
                         T* r, T* z, const T* pinv, T* x, const T* p, const double* alpha, const int* active,
-                        double* partial, int* nblk)
+                        double* partial, int* nblk, const StageIn* fused)
 {
     const int g = gather_blocks(M.nn, G ? G : MB, kMaxPartialBlocks);
     *nblk = g;
-#define NLTH_UPD(KIND, GG)                                                                                          \
-    hipLaunchKernelGGL((k_rows_update<T, KIND, GG>), dim3(g), dim3(256), 0, s, M, MB, nm, tl, rows, r, z, pinv, x, p, \
-                       alpha, active, partial)
+    const StageIn sg = fused ? *fused : StageIn{};
+#define NLTH_UPD(KIND, GG, F)                                                                                        \
+    hipLaunchKernelGGL((k_rows_update<T, KIND, GG, F>), dim3(g), dim3(256), 0, s, M, MB, nm, tl, rows, r, z, pinv, x, \
+                       p, alpha, active, partial, sg)
+    if (fused) {
+        NLTH_UPD(UPD_PZ, 0, true);
+        return;
+    }
     if constexpr (sizeof(T) == 8) {
         if (kind == UPD_XR) {
-            if (G == 0) NLTH_UPD(UPD_XR, 0);
-            else if (G == 16) NLTH_UPD(UPD_XR, 16);
-            else NLTH_UPD(UPD_XR, 32);
+            if (G == 0) NLTH_UPD(UPD_XR, 0, false);
+            else if (G == 16) NLTH_UPD(UPD_XR, 16, false);
+            else NLTH_UPD(UPD_XR, 32, false);
             return;
         }
     }
-    if (G == 0) NLTH_UPD(UPD_PZ, 0);
-    else if (G == 16) NLTH_UPD(UPD_PZ, 16);
-    else NLTH_UPD(UPD_PZ, 32);
+    if (G == 0) NLTH_UPD(UPD_PZ, 0, false);
+    else if (G == 16) NLTH_UPD(UPD_PZ, 16, false);
+    else NLTH_UPD(UPD_PZ, 32, false);
 #undef NLTH_UPD
 }
 template void launch_rows_update<double>(hipStream_t, int, const DevMesh&, int, int, int, const int*, const double*,
                                          double*, double*, const double*, double*, const double*, const double*,
-                                         const int*, double*, int*);
+                                         const int*, double*, int*, const StageIn*);
 template void launch_rows_update<float>(hipStream_t, int, const DevMesh&, int, int, int, const int*, const float*,
                                         float*, float*, const float*, float*, const float*, const double*, const int*,
-                                        double*, int*);
+                                        double*, int*, const StageIn*);
 
 // threads per block of the element-by-element launches (a tuning knob; per
 // host thread so concurrent contexts do not interfere)

@@ -31,9 +31,35 @@ constexpr int kClusterElems = 16;         // most elements of an element cluster
 constexpr int kWideNodes = 240;           // the same of a wide cluster, which
 constexpr int kWideElems = 64;            // ensembles of up to
 constexpr int kWideSlots = 8;             // member slots use
+// most partial sums that each block of the next kernel reads itself, and how many
+// they are folded to beyond that with 16 and more slots
+constexpr int kFuseSums = 3072;
+constexpr int kFoldSums = 1024;
 constexpr int kFoldBlocks = 256;          // rows to which long partial sums are folded before the finalize
 // length (in MB-rows of doubles) of the partial-sum buffer, without the operator's rows
 constexpr int kPartialRows = 3 * kMaxPartialBlocks > kGatherBlocks ? 3 * kMaxPartialBlocks : kGatherBlocks;
+
+struct CgScalars {  // per member [MB] device arrays
+    double *bb, *rr, *rz, *alpha, *beta, *pAp;
+    int *active, *iters, *status, *stepping;  // stepping: member takes part in this step
+    int *inner_active, *inner_iters, *inner_total;
+    int* inner_upd;  // members whose alpha was formed this iteration (their x, p still update)
+    double* rz_prev;  // r.z and the iteration count before this iteration's beta stage
+    int* iters_prev;
+    double *irz, *ialpha, *ibeta, *ir0;
+    double* lz;  // inner CG coefficients: alpha_k at [k * MB + m], beta_k at [(kLanczosMax + k) * MB + m]
+};
+
+// input of a stage that an update kernel forms itself: the partial sums' rows, the
+// stage's limits and the scalars
+struct StageIn {
+    const double* partial;
+    int nblk;
+    double tol2;
+    int maxit;
+    CgScalars cs;
+};
+
 
 // Per-member material of one layer, member-innermost: mat[(l*MAT_N + field)*MB + m]
 enum MatField { MAT_RHO = 0, MAT_G0, MAT_KB, MAT_VS, MAT_VP, MAT_GREF, MAT_HMAX, MAT_BETA, MAT_N };
@@ -116,7 +142,7 @@ enum { UPD_PZ = 0, UPD_XR = 1 };
 template <typename T>
 void launch_rows_update(hipStream_t s, int kind, const DevMesh& M, int MB, int nm, int G, const int* tl, const T* rows,
                         T* r, T* z, const T* pinv, T* x, const T* p, const double* alpha, const int* active,
-                        double* partial, int* nblk);
+                        double* partial, int* nblk, const StageIn* fused = nullptr);
 // operator of `mode` for fewer than 64 member slots: cluster rows and (dcoef
 // != 0) the dashpot rows dcoef * C_abs x1 (+ 2 C_base vI) of the boundary
 // nodes, to `rows`; with partial the per-member block partials of x1 . y
@@ -220,15 +246,6 @@ template <typename T>
 void launch_dotsv(hipStream_t s, int nd, const T* a0, const T* b0, const T* a1, const T* b1, const T* a2,
                   const T* b2, long nrows, int MB, int nm, const int* flag, double* partial, int* nblk);
 
-struct CgScalars {  // per member [MB] device arrays
-    double *bb, *rr, *rz, *alpha, *beta, *pAp, *r0;
-    int *active, *iters, *status, *stepping;  // stepping: member takes part in this step
-    int *inner_active, *inner_iters, *inner_total;
-    int* inner_upd;  // members whose alpha was formed this iteration (their x, p still update)
-    double *irr, *irz, *ialpha, *ibeta, *ir0;
-    double* lz;  // inner CG coefficients: alpha_k at [k * MB + m], beta_k at [(kLanczosMax + k) * MB + m]
-};
-
 // inner CG iterations whose coefficients are kept for the spectrum estimate
 constexpr int kLanczosMax = 64;
 // law state per spring and integration point: 4 FP64 + one int32 of flags,
@@ -286,6 +303,7 @@ __device__ __forceinline__ void tail_partials(double acc[ND], int MB, int m, dou
         for (int j = 0; j < ND; ++j) partial[((size_t)j * nblk + boff + blockIdx.x) * MB + t] = pm[j][t];
 }
 
+void launch_fold(hipStream_t s, int nd, int MB, const double* partial, int nblk, int rows, double* fold);
 void launch_finalize(hipStream_t s, FinalizeStage st, int nd, int MB, int nm, const double* partial, int nblk,
                      double* fold, const int* tl, int G, CgScalars cs, double tol2, int maxit);
 
@@ -306,7 +324,7 @@ void launch_inner_update(hipStream_t s, int nn, int MB, int nm, float* ir, float
 // x += alpha p, then p = z + beta p, for the members of upd
 template <typename T>
 void launch_pz(hipStream_t s, long nrows, int MB, int nm, T* x, T* p, const T* z, const double* alpha,
-               const double* beta, const int* upd);
+               const double* beta, const int* upd, const StageIn* fused = nullptr);
 void launch_inner_out(hipStream_t s, long nrows, int MB, int nm, const float* iz, double* z, const double* Ap,
                       const double* r, const int* active, double* partial, int* nblk);
 void launch_zero_if_b0(hipStream_t s, long nrows, int MB, int nm, double* x, const double* bb, const int* stepping);

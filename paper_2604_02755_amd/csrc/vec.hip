@@ -11,7 +11,7 @@
 // depend on timing.
 #include <math.h>
 
-#include "nlth_impl.hpp"
+#include "device.hpp"
 
 namespace nlth {
 
@@ -501,29 +501,97 @@ void launch_inner_update(hipStream_t s, int nn, int MB, int nm, float* ir, float
     else hipLaunchKernelGGL((k_inner_update<1>), dim3(g), dim3(256), 0, s, nn, MB, nm, ir, w, iAp, pinv32, ialpha, iactive, partial);
 }
 
+// The beta stage by every block of the p update (few partial sums: a launch of
+// its own costs more than the sums, 5 us a stage against 2): S = (r.r, r.z) of
+// member t, for threads t < MB.  What block 0 writes here (convergence, counts,
+// r.z) the other blocks read from what the alpha stage left (inner_upd, rz_prev,
+// iters_prev).  Same logic as stage_logic(FIN_BETA / FIN_IN_BETA).
+template <bool INNER>
+__device__ __forceinline__ double fused_beta(const StageIn& st, int m, const double S[2], bool upd, double rz_prev,
+                                             int it, double ref, int MB, bool write)
+{
+    const CgScalars& cs = st.cs;
+    if (!upd) return 0.0;
+    ++it;
+    const bool conv = S[0] <= st.tol2 * ref, stop = conv || it >= st.maxit;
+    const double beta = stop ? 0.0 : S[1] / rz_prev;
+    if (write) {
+        if (INNER) {
+            cs.inner_iters[m] = it;
+            cs.inner_total[m] += 1;
+            if (stop) {
+                cs.inner_active[m] = 0;
+            } else {
+                cs.ibeta[m] = beta;
+                cs.irz[m] = S[1];
+                if (it <= kLanczosMax) cs.lz[(long)(kLanczosMax + it - 1) * MB + m] = beta;
+            }
+        } else {
+            cs.iters[m] = it;
+            cs.rr[m] = S[0];
+            if (stop) {
+                cs.active[m] = 0;
+                if (!conv) cs.status[m] = -5;
+            } else {
+                cs.beta[m] = beta;
+                cs.rz[m] = S[1];
+            }
+        }
+    }
+    return beta;
+}
+
 // CG: x += a p (with this iteration's p), then p = z + b p, for the members
 // whose alpha was formed this iteration (upd); a member that has just converged
-// takes its last x update, and its p is not used again
-template <typename T, int VEC>
+// takes its last x update, and its p is not used again.  FUSED: the block forms
+// the beta stage first (the first row's loads under way meanwhile).
+template <typename T, int VEC, bool FUSED>
 __global__ __launch_bounds__(256) void k_pz(long nrows, int MB, int nm, T* __restrict__ x,
                                            T* __restrict__ p, const T* __restrict__ z,
-                                                 const double* __restrict__ alpha, const double* __restrict__ beta,
-                                                 const int* __restrict__ upd)
+                                           const double* __restrict__ alpha, const double* __restrict__ beta,
+                                           const int* __restrict__ upd, StageIn sg)
 {
     const int QB = MB / VEC, rpb = 256 / QB;
     const int t = threadIdx.x, q = t % QB, m0 = q * VEC;
+    long row = (long)blockIdx.x * rpb + t / QB;
     bool act[4];
-    if (!member_mask(upd, m0, VEC, nm, act)) return;
+    const bool any = member_mask(upd, m0, VEC, nm, act);
+    if (!FUSED && !any) return;
     T al[VEC], be[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) {
         al[v] = act[v] ? (T)alpha[m0 + v] : (T)0;
-        be[v] = act[v] ? (T)beta[m0 + v] : (T)0;
+        be[v] = !FUSED && act[v] ? (T)beta[m0 + v] : (T)0;
     }
-    for (long row = (long)blockIdx.x * rpb + t / QB; row < nrows; row += (long)gridDim.x * rpb) {
+    Pk<T, VEC> X, P, Z;
+    if constexpr (FUSED) {
+        constexpr bool INNER = sizeof(T) == 4;
+        if (any && row < nrows) {
+            const long i = row * MB + m0;
+            X = ld<T, VEC>(x + i), P = ld<T, VEC>(p + i), Z = ld<T, VEC>(z + i);
+        }
+        __shared__ double sh[2 * 4 * 32];
+        __shared__ double sb[32];
+        bool u = false;
+        double rzp = 0.0, ref = 0.0;
+        int it = 0;
+        if (t < MB && t < nm) {
+            u = upd[t];
+            rzp = sg.cs.rz_prev[t];
+            ref = INNER ? sg.cs.ir0[t] : sg.cs.bb[t];
+            it = sg.cs.iters_prev[t];
+        }
+        double S[2];
+        member_sums<2>(sg.partial, sg.nblk, MB, sh, S);
+        if (t < MB) sb[t] = fused_beta<INNER>(sg, t, S, u, rzp, it, ref, MB, blockIdx.x == 0);
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) be[v] = act[v] ? (T)sb[m0 + v] : (T)0;
+        if (!any) return;
+    }
+    for (bool first = FUSED; row < nrows; row += (long)gridDim.x * rpb, first = false) {
         const long i = row * MB + m0;
-        Pk<T, VEC> X = ld<T, VEC>(x + i), P = ld<T, VEC>(p + i);
-        const Pk<T, VEC> Z = ld<T, VEC>(z + i);
+        if (!FUSED || !first) X = ld<T, VEC>(x + i), P = ld<T, VEC>(p + i), Z = ld<T, VEC>(z + i);
 #pragma unroll
         for (int v = 0; v < VEC; ++v)
             if (act[v]) {
@@ -537,17 +605,21 @@ __global__ __launch_bounds__(256) void k_pz(long nrows, int MB, int nm, T* __res
 
 template <typename T>
 void launch_pz(hipStream_t s, long nrows, int MB, int nm, T* x, T* p, const T* z, const double* alpha,
-               const double* beta, const int* upd)
+               const double* beta, const int* upd, const StageIn* fused)
 {
     const int VEC = vec_of(MB), QB = MB / VEC;
     const int g = grid_for(nrows, 256 / QB);
-    if (VEC == 4) hipLaunchKernelGGL((k_pz<T, 4>), dim3(g), dim3(256), 0, s, nrows, MB, nm, x, p, z, alpha, beta, upd);
-    else hipLaunchKernelGGL((k_pz<T, 1>), dim3(g), dim3(256), 0, s, nrows, MB, nm, x, p, z, alpha, beta, upd);
+    const StageIn sg = fused ? *fused : StageIn{};
+#define NLTH_PZ(V, F) \
+    hipLaunchKernelGGL((k_pz<T, V, F>), dim3(g), dim3(256), 0, s, nrows, MB, nm, x, p, z, alpha, beta, upd, sg)
+    if (VEC == 4) { if (fused) NLTH_PZ(4, true); else NLTH_PZ(4, false); }
+    else { if (fused) NLTH_PZ(1, true); else NLTH_PZ(1, false); }
+#undef NLTH_PZ
 }
 template void launch_pz<float>(hipStream_t, long, int, int, float*, float*, const float*, const double*, const double*,
-                               const int*);
+                               const int*, const StageIn*);
 template void launch_pz<double>(hipStream_t, long, int, int, double*, double*, const double*, const double*,
-                                const double*, const int*);
+                                const double*, const int*, const StageIn*);
 
 // preconditioner output z = iz (FP64) for outer-active members (0 for the
 // others, whose z is not used again in the step); partials (z.Ap, z.r)
@@ -1036,6 +1108,8 @@ __device__ void stage_logic(int stage, int m, int MB, const double S[3], CgScala
         cs.pAp[m] = S[0];
         cs.alpha[m] = cs.active[m] ? cs.rz[m] / S[0] : 0.0;
         cs.inner_upd[m] = cs.active[m];
+        cs.rz_prev[m] = cs.rz[m];
+        cs.iters_prev[m] = cs.iters[m];
         break;
     case FIN_BETA:  // S = (r.r, r.z)
         if (cs.active[m]) {
@@ -1085,6 +1159,8 @@ __device__ void stage_logic(int stage, int m, int MB, const double S[3], CgScala
     case FIN_IN_ALPHA:  // S = (ip.iAp)
         cs.ialpha[m] = cs.inner_active[m] ? cs.irz[m] / S[0] : 0.0;
         cs.inner_upd[m] = cs.inner_active[m];
+        cs.rz_prev[m] = cs.irz[m];
+        cs.iters_prev[m] = cs.inner_iters[m];
         if (cs.inner_active[m] && cs.inner_iters[m] < kLanczosMax)
             cs.lz[(long)cs.inner_iters[m] * MB + m] = cs.ialpha[m];
         break;
@@ -1129,49 +1205,68 @@ __global__ __launch_bounds__(256) void k_finalize(int stage, int nd, int MB, int
         for (int k = 0; k < min(tl[0], G); ++k)
             if (tl[1 + k] == m) col = k;
     }
-    __shared__ double sh[3][256];
+    __shared__ double sh[3][4];
     const int t = threadIdx.x;
+    double a[3] = {0.0, 0.0, 0.0};
+    for (int b = t; col >= 0 && b < nblk; b += 8 * 256)  // the loads of a group under way together
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            if (k >= nd) break;
+            double v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                v[q] = b + 256 * q < nblk ? partial[((long)k * nblk + b + 256 * q) * W + col] : 0.0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) a[k] += v[q];
+        }
+#pragma unroll
     for (int k = 0; k < 3; ++k) {
-        double a = 0.0;
-        if (k < nd)
-            for (int b = t; col >= 0 && b < nblk; b += 256) a += partial[((long)k * nblk + b) * W + col];
-        sh[k][t] = a;
+        for (int o = 32; o > 0; o >>= 1) a[k] += __shfl_xor(a[k], o);
+        if ((t & 63) == 0) sh[k][t >> 6] = a[k];
     }
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (t < s)
-            for (int k = 0; k < 3; ++k) sh[k][t] += sh[k][t + s];
-        __syncthreads();
-    }
     if (t == 0) {
-        double S[3] = {sh[0][0], sh[1][0], sh[2][0]};
+        double S[3];
+        for (int k = 0; k < 3; ++k) S[k] = (sh[k][0] + sh[k][1]) + (sh[k][2] + sh[k][3]);
         stage_logic(stage, m, MB, S, cs, tol2, maxit);
     }
 }
 
 // Sums of nd x nblk partial rows over runs of consecutive rows, coalesced:
-// fold[(k * kFoldBlocks + b) * MB + m].  One block per member reading a column
+// fold[(k * rows + b) * MB + m].  One block per member reading a column
 // of thousands of rows (8 bytes of every row) took 24 us at 16,384 rows of 64.
 __global__ __launch_bounds__(256) void k_fold(int MB, const double* __restrict__ partial, int nblk,
                                              double* __restrict__ fold)
 {
     const int k = blockIdx.y, t = threadIdx.x;
-    const int per = (nblk + kFoldBlocks - 1) / kFoldBlocks;
-    const int b0 = blockIdx.x * per, b1 = b0 + per < nblk ? b0 + per : nblk;
-    const double* p = partial + (size_t)k * nblk * MB;
+    const int per = (nblk + gridDim.x - 1) / gridDim.x;
+    const int b0 = blockIdx.x * per, n = min(per, nblk - b0);
+    const double* p = partial + ((size_t)k * nblk + b0) * MB;
+    double* out = fold + ((size_t)k * gridDim.x + blockIdx.x) * MB;
     __shared__ double sh[256];
+    if (MB <= 32) {
+        double S[1];
+        member_sums<1>(p, n, MB, sh, S);
+        if (t < MB) out[t] = S[0];
+        return;
+    }
     // thread t takes member t % MB of every (256 / MB)-th row (MB <= 256 here)
     const int m = t % MB, rl = t / MB, rpb = 256 / MB;
     double a = 0.0;
 #pragma unroll 4
-    for (int b = b0 + rl; b < b1; b += rpb) a += p[(size_t)b * MB + m];
+    for (int b = rl; b < n; b += rpb) a += p[(size_t)b * MB + m];
     sh[t] = a;
     __syncthreads();
     for (int s = 128; s >= MB; s >>= 1) {
         if (t < s) sh[t] += sh[t + s];
         __syncthreads();
     }
-    if (t < MB) fold[((size_t)k * kFoldBlocks + blockIdx.x) * MB + t] = sh[t];
+    if (t < MB) out[t] = sh[t];
+}
+
+void launch_fold(hipStream_t s, int nd, int MB, const double* partial, int nblk, int rows, double* fold)
+{
+    hipLaunchKernelGGL(k_fold, dim3(rows, nd), dim3(256), 0, s, MB, partial, nblk, fold);
 }
 
 void launch_finalize(hipStream_t s, FinalizeStage st, int nd, int MB, int nm, const double* partial, int nblk,
@@ -1180,8 +1275,8 @@ void launch_finalize(hipStream_t s, FinalizeStage st, int nd, int MB, int nm, co
     // the fold is a launch more (about 3 us): it pays once a column takes longer
     // than that to read
     const int W = tl ? G : MB;
-    if (nd > 0 && W <= 256 && nblk > (W >= 16 ? 512 : 2048)) {
-        hipLaunchKernelGGL(k_fold, dim3(kFoldBlocks, nd), dim3(256), 0, s, W, partial, nblk, fold);
+    if (nd > 0 && W <= 256 && nblk > (W >= 16 ? 512 : 8192)) {
+        launch_fold(s, nd, W, partial, nblk, kFoldBlocks, fold);
         partial = fold;
         nblk = kFoldBlocks;
     }

@@ -33,3 +33,50 @@ def test_slot_counts_match_oracle(nlth_mod, oracle_lib, members, precision, inne
         err = oracle_lib.rel_l2(out["vel"][m], ref["vel"])
         print("  member", m, "rel L2 vs oracle", err, flush=True)
         assert np.abs(ref["vel"]).max() > 0 and err < 1e-9
+
+
+@pytest.mark.parametrize("members,dims", [(1, (5, 3, 3)), (3, (8, 8, 8)), (8, (16, 16, 17)), (16, (10, 8, 8)),
+                                          (32, (10, 8, 8)), (70, (6, 5, 4))])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_iterations_match_the_colour_path(nlth_mod, members, dims, precision):
+    """The stages of a CG iteration formed inside the update kernels (few sums, and
+    folded sums from 16 slots on), launched (8 slots, 26,112 tets), and the
+    diagonal by clusters, against the colour path with its separate stages and one
+    diagonal launch per colour: as many iterations (one more or less where a
+    residual lies at the tolerance within rounding), the same velocities, and the
+    same member status when the iteration limit stops the solve."""
+    mesh = I.box_mesh(*dims, 1.0, I.two_layer(1.0), 2)
+    rng = np.random.default_rng(members)
+    acc = 40.0 * rng.standard_normal((members, 3, 3))
+    prob = I.make_problem(members, I.CFG0_LAYERS["vs"], I.CFG0_LAYERS["rho"], gamma_ref=rng.uniform(5e-4, 2e-3, members),
+                          n_springs=12, n_steps=3, input_acc=acc, cg_tol=1e-12, precision=precision)
+    ctx = nlth_mod.Context(0, use_torch_stream=False)
+    try:
+        mh = ctx.mesh(mesh)
+        for maxit in (2000, 2):
+            prob.cg_maxit = maxit
+            got = []
+            for scatter in (-1, 1):
+                print("stages case", members, dims, precision, maxit, scatter, flush=True)
+                ens = ctx.ensemble(mh, mesh, prob)
+                try:
+                    if scatter == 1:
+                        ens.set_tuning(scatter=1)
+                    try:
+                        ens.step(prob.n_steps)
+                    except nlth_mod.NlthError as e:
+                        assert maxit == 2 and e.code == nlth_mod.NLTH_ENOCONV
+                    got.append(ens.read())
+                finally:
+                    ens.close()
+            a, b = got
+            assert np.array_equal(a["status"], b["status"])
+            if maxit == 2:
+                assert np.all(a["status"] == nlth_mod.NLTH_ENOCONV) and np.array_equal(a["iters"][..., 0], b["iters"][..., 0])
+                continue
+            assert np.all(a["status"] == 0) and np.abs(b["vel"]).max() > 0
+            print("  iterations", a["iters"][0, :, 0], b["iters"][0, :, 0], flush=True)
+            assert np.abs(a["iters"][..., 0] - b["iters"][..., 0]).max() <= 1
+            assert np.linalg.norm(a["vel"] - b["vel"]) < 1e-9 * np.linalg.norm(b["vel"])
+    finally:
+        ctx.close()
