@@ -51,6 +51,8 @@ struct DevBuf {
     template <typename T> T* as() const { return (T*)p; }
 };
 
+constexpr size_t kSpecKeep = 64u << 20;
+
 struct Ctx;
 
 struct Mesh {
@@ -270,6 +272,7 @@ struct Ctx {
     bool own_stream = false;
     Budget budget;
     std::mutex mu;  // serialises API calls on the context
+    DevBuf spec_ws;  // workspace of the response spectra (under mu, up to kSpecKeep)
     int paging_sets = 2;  // member sets of a paged ensemble (1 or 2)
     std::string last_error;
     int log_level = 0;
