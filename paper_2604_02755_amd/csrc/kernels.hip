@@ -1401,9 +1401,18 @@ void launch_zero_member(hipStream_t s, double* p, long rows, int MB, int m)
 // (4 % faster again); 0: D accumulated in registers.
 // MEM: a reversal memory of `depth` > 1 points (inner loops close, as the
 // oracle's law with that depth); false: the three-rule law.
+// PARTS > 1 (many springs, few lanes): a block's PARTS wavefronts take the same 64
+// lanes and a share of the springs each; the first sums their D and damping.
+// The law is bound by issue (about 1,500 cycles of a SIMD a spring and wavefront:
+// two springs ahead or a third wavefront a SIMD change nothing), so this pays only
+// while SIMDs idle: 150 springs on 12,288 elements (768 wavefronts) 300 -> 249 us,
+// on 1,152 (72) 272 -> 70 with 8 parts,
+// on 331,776 elements 3.8 -> 5.0 ms.
 constexpr int kLawLdsSprings = 16;
-template <bool WAVE_ELEM, int LDS_NS, bool MEM>
-__global__ __launch_bounds__(256, LDS_NS > 0 ? 4 : 1) void k_law(DevMesh M, int MB, int nm, int e0, int ec, long ecp,
+constexpr long kLawPartLanes = 1l << 16;  // a wavefront a SIMD without parts
+constexpr long kLawManyParts = 1l << 14;
+template <bool WAVE_ELEM, int LDS_NS, bool MEM, int PARTS>
+__global__ __launch_bounds__(PARTS == 8 ? 512 : 256, LDS_NS > 0 ? 4 : 1) void k_law(DevMesh M, int MB, int nm, int e0, int ec, long ecp,
                                             const double* __restrict__ mat, const int* __restrict__ nonlinear,
                                             int ns, int depth, const double* __restrict__ dirs,
                                             const double* __restrict__ w, const double* __restrict__ du,
@@ -1411,11 +1420,13 @@ __global__ __launch_bounds__(256, LDS_NS > 0 ? 4 : 1) void k_law(DevMesh M, int 
                                             uint32_t* __restrict__ D16, double* __restrict__ h,
                                             const int* __restrict__ stepping, bool d16_mean)
 {
-    const long t = blockIdx.x * (long)blockDim.x + threadIdx.x;
+    const int part = PARTS > 1 ? (int)threadIdx.x >> 6 : 0;
+    const long t = PARTS > 1 ? blockIdx.x * 64l + (threadIdx.x & 63) : blockIdx.x * (long)blockDim.x + threadIdx.x;
     const int j = (int)(t & 3);
     const long q = t >> 2;
     const int m = (int)(q % MB);
     long el = q / MB;
+    // (lanes that leave here leave in every wavefront of the block)
     if (WAVE_ELEM) el = __builtin_amdgcn_readfirstlane((int)el);
     if (el >= ec || m >= nm) return;
     if (stepping && !stepping[m]) return;
@@ -1478,11 +1489,12 @@ __global__ __launch_bounds__(256, LDS_NS > 0 ? 4 : 1) void k_law(DevMesh M, int 
     for (int k = 0; k < 21; ++k) d[k] = 0;
     double hs = 0.0;
     // the next spring's state is loaded while this one is updated
-    long nidx = th.at(el, 0, j, m);
+    const int sp0 = part * ns / PARTS, sp1 = (part + 1) * ns / PARTS;
+    long nidx = th.at(el, sp0, j, m);
     double ngp = th.d[nidx], ngr = th.d[fn + nidx], ntr = th.d[2 * fn + nidx], nsm = th.d[3 * fn + nidx];
     int nfl = th.i[nidx];
 #pragma unroll 1
-    for (int sp = 0; sp < ns; ++sp) {
+    for (int sp = sp0; sp < sp1; ++sp) {
         const double* n = dirs + 6 * sp;
         const double dg = LDS_NS > 0 ? cgs[sp * 256 + threadIdx.x]
                                      : n[0] * ej[0] + n[1] * ej[1] + n[2] * ej[2] + n[3] * ej[3] + n[4] * ej[4] +
@@ -1491,7 +1503,7 @@ __global__ __launch_bounds__(256, LDS_NS > 0 ? 4 : 1) void k_law(DevMesh M, int 
         double gp = ngp, gr = ngr, tr = ntr, sm = nsm;
         int dir = (nfl & 3) - 1, skel = (nfl >> 2) & 1;
         int cnt = MEM ? nfl >> 3 : 0;  // older reversal points kept
-        if (sp + 1 < ns) {
+        if (sp + 1 < sp1) {
             nidx = th.at(el, sp + 1, j, m);
             ngp = th.d[nidx]; ngr = th.d[fn + nidx]; ntr = th.d[2 * fn + nidx]; nsm = th.d[3 * fn + nidx];
             nfl = th.i[nidx];
@@ -1603,6 +1615,23 @@ __global__ __launch_bounds__(256, LDS_NS > 0 ? 4 : 1) void k_law(DevMesh M, int 
                 for (int qq = r; qq < 6; ++qq) d[sym6(r, qq)] += c * n[r] * n[qq];
         }
     }
+    if constexpr (PARTS > 1) {
+        __shared__ double ps[PARTS - 1][22][64];
+        const int lane = threadIdx.x & 63;
+        if (part > 0) {
+#pragma unroll
+            for (int k = 0; k < 21; ++k) ps[part - 1][k][lane] = d[k];
+            ps[part - 1][21][lane] = hs;
+        }
+        __syncthreads();
+        if (part > 0) return;
+#pragma unroll
+        for (int p = 0; p < PARTS - 1; ++p) {
+#pragma unroll
+            for (int k = 0; k < 21; ++k) d[k] += ps[p][k][lane];
+            hs += ps[p][21][lane];
+        }
+    }
 #pragma unroll
     for (int r = 0; r < 3; ++r)
 #pragma unroll
@@ -1627,17 +1656,18 @@ __global__ __launch_bounds__(256, LDS_NS > 0 ? 4 : 1) void k_law(DevMesh M, int 
     if (j == 0) h[e * MB + m] = 0.25 * hsum;
 }
 
-template <int LDS_NS, bool MEM>
-static void law_dispatch(hipStream_t s, dim3 g, const DevMesh& M, int MB, int nm, int e0, int ec, long ecp,
+template <int LDS_NS, bool MEM, int PARTS>
+static void law_dispatch(hipStream_t s, long n, const DevMesh& M, int MB, int nm, int e0, int ec, long ecp,
                          const double* mat, const int* nonlinear, int ns, int depth, const double* dirs,
                          const double* w, const double* du, void* theta, double* D, float* D32, uint32_t* D16,
                          double* h, const int* stepping, bool d16_mean)
 {
+    const dim3 g(PARTS > 1 ? (unsigned)((n + 63) / 64) : nblocks(n));
     if (MB >= 16)
-        hipLaunchKernelGGL((k_law<true, LDS_NS, MEM>), g, dim3(256), 0, s, M, MB, nm, e0, ec, ecp, mat, nonlinear, ns,
+        hipLaunchKernelGGL((k_law<true, LDS_NS, MEM, PARTS>), g, dim3(PARTS > 1 ? 64 * PARTS : 256), 0, s, M, MB, nm, e0, ec, ecp, mat, nonlinear, ns,
                            depth, dirs, w, du, theta, D, D32, D16, h, stepping, d16_mean);
     else
-        hipLaunchKernelGGL((k_law<false, LDS_NS, MEM>), g, dim3(256), 0, s, M, MB, nm, e0, ec, ecp, mat, nonlinear, ns,
+        hipLaunchKernelGGL((k_law<false, LDS_NS, MEM, PARTS>), g, dim3(PARTS > 1 ? 64 * PARTS : 256), 0, s, M, MB, nm, e0, ec, ecp, mat, nonlinear, ns,
                            depth, dirs, w, du, theta, D, D32, D16, h, stepping, d16_mean);
 }
 
@@ -1647,20 +1677,20 @@ void launch_law(hipStream_t s, const DevMesh& M, int MB, int nm, int e0, int ec,
 {
     long n = (long)ec * MB * 4;
     if (n <= 0) return;
-    const dim3 g(nblocks(n));
     const bool small = ns <= kLawLdsSprings, mem = depth > 1;
-    if (small && !mem)
-        law_dispatch<kLawLdsSprings, false>(s, g, M, MB, nm, e0, ec, ecp, mat, nonlinear, ns, depth, dirs, w, du,
-                                            theta, D, D32, D16, h, stepping, d16_mean);
-    else if (small)
-        law_dispatch<kLawLdsSprings, true>(s, g, M, MB, nm, e0, ec, ecp, mat, nonlinear, ns, depth, dirs, w, du,
-                                           theta, D, D32, D16, h, stepping, d16_mean);
-    else if (!mem)
-        law_dispatch<0, false>(s, g, M, MB, nm, e0, ec, ecp, mat, nonlinear, ns, depth, dirs, w, du, theta, D, D32,
-                               D16, h, stepping, d16_mean);
-    else
-        law_dispatch<0, true>(s, g, M, MB, nm, e0, ec, ecp, mat, nonlinear, ns, depth, dirs, w, du, theta, D, D32,
-                              D16, h, stepping, d16_mean);
+    const int parts = n <= kLawManyParts ? 8 : (n <= kLawPartLanes ? 4 : 1);
+#define NLTH_LAW(LDS_NS, MEM, PARTS)                                                                                 \
+    law_dispatch<LDS_NS, MEM, PARTS>(s, n, M, MB, nm, e0, ec, ecp, mat, nonlinear, ns, depth, dirs, w, du, theta, D, \
+                                     D32, D16, h, stepping, d16_mean)
+    if (small && !mem) NLTH_LAW(kLawLdsSprings, false, 1);
+    else if (small) NLTH_LAW(kLawLdsSprings, true, 1);
+    else if (!mem && parts == 8) NLTH_LAW(0, false, 8);
+    else if (!mem && parts == 4) NLTH_LAW(0, false, 4);
+    else if (!mem) NLTH_LAW(0, false, 1);
+    else if (parts == 8) NLTH_LAW(0, true, 8);
+    else if (parts == 4) NLTH_LAW(0, true, 4);
+    else NLTH_LAW(0, true, 1);
+#undef NLTH_LAW
 }
 
 // ---------------------------------------------------------------------------

@@ -80,3 +80,31 @@ def test_iterations_match_the_colour_path(nlth_mod, members, dims, precision):
             assert np.linalg.norm(a["vel"] - b["vel"]) < 1e-9 * np.linalg.norm(b["vel"])
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("depth", [1, 3])
+@pytest.mark.parametrize("springs,dims,members", [(17, (5, 3, 3), 2), (150, (5, 3, 3), 1), (37, (8, 8, 8), 2),
+                                                  (150, (8, 6, 4), 16), (18, (8, 8, 8), 8)])
+def test_springs_in_parts_match_oracle(nlth_mod, oracle_lib, springs, dims, members, depth):
+    """The law with more springs than the LDS form takes: 8 wavefronts a block
+    sharing them (up to 16,384 element-point-members), 4 (up to 65,536), and none,
+    with spring counts that the parts do not divide."""
+    mesh = I.box_mesh(*dims, 1.0, I.two_layer(1.0), 2)
+    rng = np.random.default_rng(springs)
+    acc = 60.0 * rng.standard_normal((members, 5, 3))
+    prob = I.make_problem(members, I.CFG0_LAYERS["vs"], I.CFG0_LAYERS["rho"], gamma_ref=rng.uniform(2e-4, 5e-4, members),
+                          n_springs=150, n_steps=5, input_acc=acc, cg_tol=1e-12, masing_depth=depth)
+    pick = np.linspace(0, 149, springs).round().astype(int)
+    prob.dirs, prob.weights = np.ascontiguousarray(prob.dirs[pick]), np.full(springs, 5.0 / springs)
+    ctx = nlth_mod.Context(0, use_torch_stream=False)
+    try:
+        mh = ctx.mesh(mesh)
+        print("springs case", springs, dims, members, depth, flush=True)
+        out = ctx.solve(mh, mesh, prob)
+    finally:
+        ctx.close()
+    assert out["rc"] == 0
+    ref = oracle_lib.run(mesh, prob, member=members - 1)
+    err = oracle_lib.rel_l2(out["vel"][members - 1], ref["vel"])
+    print("  rel L2 vs oracle", err, flush=True)
+    assert np.abs(ref["vel"]).max() > 0 and err < 1e-9
