@@ -14,6 +14,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <climits>
 #include <chrono>
 #include <cstdio>
 #include <unordered_map>
@@ -1212,14 +1213,47 @@ int Ens::count_flags() const
     return n;
 }
 
-// any member still iterating?  (the flags copied to the host mailbox)
+// any member still iterating?  (the flags, and the iteration counts that follow
+// them in memory, copied to the host mailbox)
 int Ens::read_any_active(const int* flags)
 {
-    launch_copy_i32(s, flags, d_mail, nm);
+    launch_copy_i32(s, flags, d_mail, MB + nm);
+    return wait_any_active();
+}
+
+int Ens::wait_any_active()
+{
     NLTH_HIP(hipStreamSynchronize(s));
     for (int m = 0; m < nm; ++m)
         if (h_flags[m]) return 1;
     return 0;
+}
+
+// Iterations of kind 0 (inner) or 1 (FP64 PCG) until no member iterates, or
+// `limit`; returns the most that a member took.  A check of the flags is a round
+// trip to the host of 25 to 45 us, two iterations of a small mesh: the first check
+// comes when as many iterations have been issued as the last such solve took
+// (members that converge earlier are frozen, so this changes no result), in
+// graphs of 32, check_every and a few.
+int Ens::iterate(int kind, int guess, int limit)
+{
+    const int few = std::min(4, check_every);
+    int n = guess > 0 ? guess : check_every, done = 0;
+    for (;;) {
+        n = std::min(n, limit - done);
+        while (n > 0) {
+            int k = n >= 32 ? 32 : check_every;
+            if (n < k) k = std::min((n + few - 1) / few * few, limit - done);
+            run_iters(kind, k, n <= k);
+            n -= k;
+            done += k;
+        }
+        if (!wait_any_active() || done >= limit) break;
+        n = kind == 0 ? few : check_every;
+    }
+    int most = 0;
+    for (int m = 0; m < nm; ++m) most = std::max(most, h_flags[MB + m]);
+    return most;
 }
 
 // tl: the partials are rows of G lanes, the listed members'
@@ -1248,11 +1282,16 @@ void Ens::solve_pcg()
                      z.as<double>(), p.as<double>(), st, pd, &nblk);
     fin(FIN_START, 3, nblk, tol2, P.cg_maxit);
     launch_zero_if_b0(s, n, MB, nm, x, cs.bb, st);
+    if (MB < 64) {
+        if (pcg_guess == 0 && !read_any_active(act)) return;
+        pcg_guess = iterate(1, pcg_guess, INT_MAX);
+        return;
+    }
     if (!read_any_active(act)) return;
     for (;;) {
         if (!tail64_g) enter_tail64();  // with few members left: compact rows
-        run_iters(1, check_every);
-        if (!read_any_active(act)) break;
+        run_iters(1, check_every, true);
+        if (!wait_any_active()) break;
         if (tail64_g) tail_count = count_flags();
     }
     if (tail64_g) leave_tail64();
@@ -1381,13 +1420,7 @@ void Ens::inner_solve()
         launch_inner_start(s, mesh->nn, MB, nm, r.as<double>(), pinv32.as<float>(), ir.as<float>(), iz.as<float>(),
                            ip.as<float>(), iw.as<float>(), iAp.as<float>(), act, pd, &nblk);
     fin(FIN_IN_START, 2, nblk, tol2, P.inner_maxit);
-    int done_iters = 0;
-    while (done_iters < P.inner_maxit) {
-        const int chunk = std::min(check_every, P.inner_maxit - done_iters);
-        run_iters(0, chunk);
-        done_iters += chunk;
-        if (!read_any_active(iact)) break;
-    }
+    inner_guess = iterate(0, inner_guess, P.inner_maxit);
     // the listed members' result back to the full rows (the others are not
     // outer-active: the output step writes zero for them); with the outer
     // iteration on the compact rows it stays there
@@ -1716,22 +1749,26 @@ void Ens::clear_graphs()
 }
 
 // k iterations of kind 0 (inner) or 1 (FP64 PCG); a chunk of k iterations is
-// captured once into a hipGraph per (kind, compact-row width, k) and replayed
+// captured once into a hipGraph per (kind, compact-row width, k, check) and replayed
 // (the launches and their arguments are the same every chunk: scalars are
 // read on the device), which removes per-launch host overhead
-void Ens::run_iters(int kind, int k)
+void Ens::run_iters(int kind, int k, bool check)
 {
-    if (!use_graph || profile || k <= 0 || k > 64) {
+    auto issue = [&] {
         for (int i = 0; i < k; ++i) kind == 0 ? inner_iter() : pcg_iter();
+        if (check) launch_copy_i32(s, kind == 0 ? cs.inner_active : cs.active, d_mail, MB + nm);
+    };
+    if (!use_graph || profile || k <= 0 || k > 64) {
+        issue();
         return;
     }
     const int g = kind == 1 ? tail64_g : tail_g;
-    hipGraphExec_t& ge = g_chunks[(kind * 64 + g) * 128 + k];
+    hipGraphExec_t& ge = g_chunks[((kind * 64 + g) * 128 + k) * 2 + check];
     if (!ge) {
         hipGraph_t g = nullptr;
         NLTH_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
         try {
-            for (int i = 0; i < k; ++i) kind == 0 ? inner_iter() : pcg_iter();
+            issue();
         } catch (...) {
             (void)hipStreamEndCapture(s, &g);
             if (g) (void)hipGraphDestroy(g);
@@ -1743,7 +1780,7 @@ void Ens::run_iters(int kind, int k)
         if (e != hipSuccess) {
             ge = nullptr;
             use_graph = false;  // fall back to direct launches of the same kernels
-            for (int i = 0; i < k; ++i) kind == 0 ? inner_iter() : pcg_iter();
+            issue();
             return;
         }
     }

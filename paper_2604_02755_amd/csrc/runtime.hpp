@@ -237,7 +237,10 @@ struct Ens {
     int read_any_active(const int* flags);
     void inner_iter();
     void pcg_iter();
-    void run_iters(int kind, int k);
+    void run_iters(int kind, int k, bool check);  // check: with the flags' copy to the mailbox
+    int wait_any_active();
+    int iterate(int kind, int guess, int limit);
+    int pcg_guess = 0, inner_guess = 0;  // most iterations of a member in the last such solve
     bool use_graph = true;
     // captured CG chunks, by (kind, compact-row width, iterations); the Chebyshev solve
     std::map<int, hipGraphExec_t> g_chunks;
