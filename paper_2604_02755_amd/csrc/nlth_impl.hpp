@@ -63,6 +63,11 @@ struct StageIn {
 
 // Per-member material of one layer, member-innermost: mat[(l*MAT_N + field)*MB + m]
 enum MatField { MAT_RHO = 0, MAT_G0, MAT_KB, MAT_VS, MAT_VP, MAT_GREF, MAT_HMAX, MAT_BETA, MAT_N };
+// the table of one member, passed to the allocation-free application's kernel by value
+constexpr int kNoAllocMaxLayers = 32;
+struct LayerMat {
+    double v[kNoAllocMaxLayers * MAT_N];
+};
 
 struct DevMesh {
     int ne, nn;
@@ -155,7 +160,7 @@ void launch_op_slots32(hipStream_t s, const DevMesh& M, int MB, int nm, const fl
 // one member, D [ne][4][21] and h [ne] in input tet order (order: storage
 // position -> input tet): the operator of launch_op_slots64 on them
 void launch_op_input64(hipStream_t s, OpMode mode, const DevMesh& M, const int* order, const double* D,
-                       const double* h, const double* mat, StepConst sc, const double* x, double* rows, double dcoef);
+                       const double* h, const LayerMat& lm, StepConst sc, const double* x, double* rows, double dcoef);
 // the same for a multiple of 64 slots (up to 256), co the rows
 void launch_ebe_cluster64(hipStream_t s, OpMode mode, const DevMesh& M, int MB, int nm, const double* D,
                           const double* h, const double* mat, StepConst sc, const double* x1, const double* x2,

@@ -1,8 +1,8 @@
 // Allocation-free form of the diagnostic operator application, for callers
 // that cannot allocate device memory: code under HIP graph capture, tight
 // serving loops, harnesses that forbid hipMalloc.  The caller passes device
-// buffers for the inputs and the output; every intermediate (the material
-// table, the operator's rows) lives in one file-scope device array of
+// buffers for the inputs and the output; the intermediate (the operator's
+// rows) lives in one file-scope device array of
 // kScratchBytes that each device the library runs on holds until the process
 // ends.  Its device address comes from hipGetSymbolAddress, taken once per
 // device when a context is created on it (in host code the array's name is
@@ -21,7 +21,6 @@
 namespace nlth {
 
 constexpr size_t kScratchBytes = (size_t)64 << 20;  // per device
-constexpr int kNoAllocMaxLayers = 32;
 constexpr int kScratchDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -47,17 +46,6 @@ static char* scratch_of(int device)
 {
     std::lock_guard<std::mutex> g(g_scratch_mu);
     return (device >= 0 && device < kScratchDevices) ? (char*)g_scratch_ptr[device] : nullptr;
-}
-
-// per-layer material of member 0, passed by value (MB = 1 layout of the table)
-struct LayerMat {
-    int n;  // n_layers * MAT_N entries
-    double v[kNoAllocMaxLayers * MAT_N];
-};
-
-__global__ void k_noalloc_mat(LayerMat lm, double* __restrict__ mat)
-{
-    for (int t = threadIdx.x; t < lm.n; t += blockDim.x) mat[t] = lm.v[t];
 }
 
 void rayleigh_coefficients(double f_lo, double f_hi, double* a, double* b);
@@ -94,12 +82,10 @@ extern "C" int nlth_apply_operator_noalloc(nlth_ctx* ctx, const nlth_mesh* mesh,
             throw Error{NLTH_EINVAL, "problem: Rayleigh band needs 0 < f_lo < f_hi"};
         const int ne = mesh->ne, nn = mesh->nn;
         const long n3 = 3L * nn;
-        // scratch regions: the material table and the operator's rows (at most
-        // ten per element)
-        const size_t o_mat = 0;
-        const size_t o_rows = o_mat + round256((size_t)nl * MAT_N * 8);
-        // the capacity that the entry point states (D, h, two nodal vectors and
-        // ten rows per element): more than what the regions above take
+        // the scratch holds the operator's rows (at most ten per element); the
+        // capacity that the entry point states counts a material table, D, h, two
+        // nodal vectors and ten rows per element
+        const size_t o_rows = round256((size_t)nl * MAT_N * 8);
         const size_t ne_pad = ((size_t)ne + 63) / 64 * 64;
         const size_t need = o_rows + round256(ne_pad * 84 * 8) + round256(ne_pad * 8) + 2 * round256((size_t)n3 * 8) +
                             round256(ne_pad * 30 * 8);
@@ -112,7 +98,6 @@ extern "C" int nlth_apply_operator_noalloc(nlth_ctx* ctx, const nlth_mesh* mesh,
             throw Error{NLTH_EINVAL, buf};
         }
         LayerMat lm{};
-        lm.n = nl * MAT_N;
         for (int l = 0; l < nl; ++l) {
             const double rho = prob->rho[l], vs = prob->vs[l], nu = prob->nu[l], hm = prob->h_max[l];
             if (!(rho > 0 && vs > 0 && nu > -1.0 && nu < 0.5))
@@ -140,13 +125,11 @@ extern "C" int nlth_apply_operator_noalloc(nlth_ctx* ctx, const nlth_mesh* mesh,
         NLTH_HIP(hipSetDevice(ctx->device));
         char* base = scratch_of(ctx->device);
         if (!base) throw Error{NLTH_EDEVICE, "scratch address not set up on this device"};
-        double* mat = (double*)(base + o_mat);
         double* rows = (double*)(base + o_rows);
         hipStream_t s = ctx->stream;
         const DevMesh dm = mesh->dev_input();
         const double dc = which == NLTH_OP_A ? 2.0 / prob->dt : 0.0;
-        hipLaunchKernelGGL(k_noalloc_mat, dim3(1), dim3(256), 0, s, lm, mat);
-        launch_op_input64(s, (OpMode)which, dm, mesh->order_d.as<int>(), D_ip, h, mat, sc, x, rows, dc);
+        launch_op_input64(s, (OpMode)which, dm, mesh->order_d.as<int>(), D_ip, h, lm, sc, x, rows, dc);
         launch_gather<double>(s, dm, 1, 1, rows, dc != 0.0, nullptr, 0.0, y, nullptr, mesh->node_in.as<int>());
         NLTH_HIP(hipGetLastError());
         return NLTH_OK;

@@ -95,12 +95,13 @@ struct SlotShape {
 // shorter chain but 1.5 times the instructions: no faster on small meshes, 124
 // against 45 us (FP32, without the sums) at 8 slots.
 template <typename T, int DK, int MODE, int LG>
-__global__ __launch_bounds__(512) void k_op_slots(DevMesh M, int MB, int nm, int ncb, int nbb, const int* __restrict__ tl,
-                                                 const void* __restrict__ Dv, const int* __restrict__ order,
-                                                 const double* __restrict__ h, const double* __restrict__ mat,
-                                                 StepConst sc, const T* __restrict__ x1, const T* __restrict__ x2,
-                                                 T* __restrict__ rows, const int* __restrict__ active, double dcoef,
-                                                 const double* __restrict__ vI, double* __restrict__ partial)
+__device__ __forceinline__ void op_slots_block(const DevMesh& M, int MB, int nm, int ncb, int nbb,
+                                               const int* __restrict__ tl, const void* __restrict__ Dv,
+                                               const int* __restrict__ order, const double* __restrict__ h,
+                                               const double* __restrict__ mat, const StepConst& sc,
+                                               const T* __restrict__ x1, const T* __restrict__ x2, T* __restrict__ rows,
+                                               const int* __restrict__ active, double dcoef,
+                                               const double* __restrict__ vI, double* __restrict__ partial)
 {
     using S = SlotShape<T, LG>;
     constexpr int L = 1 << LG, OS = S::OS, XS = S::XS;
@@ -207,22 +208,59 @@ __global__ __launch_bounds__(512) void k_op_slots(DevMesh M, int MB, int nm, int
 }
 
 template <typename T, int DK, int MODE, int LG>
-static void op_launch(hipStream_t s, const DevMesh& M, int MB, int nm, const int* tl, const void* D, const int* order,
-                      const double* h, const double* mat, StepConst sc, const T* x1, const T* x2, T* rows,
-                      const int* active, double dcoef, const double* vI, double* partial, int* nblk)
+__global__ __launch_bounds__(512) void k_op_slots(DevMesh M, int MB, int nm, int ncb, int nbb, const int* __restrict__ tl,
+                                                 const void* __restrict__ Dv, const double* __restrict__ h,
+                                                 const double* __restrict__ mat, StepConst sc,
+                                                 const T* __restrict__ x1, const T* __restrict__ x2,
+                                                 T* __restrict__ rows, const int* __restrict__ active, double dcoef,
+                                                 const double* __restrict__ vI, double* __restrict__ partial)
+{
+    op_slots_block<T, DK, MODE, LG>(M, MB, nm, ncb, nbb, tl, Dv, nullptr, h, mat, sc, x1, x2, rows, active, dcoef, vI,
+                                    partial);
+}
+
+// One member, D and h in input order, the material table a kernel argument (a
+// launch that put it in memory first took 5 us of a call's 32 on 1,152 elements)
+template <int MODE>
+__global__ __launch_bounds__(512) void k_op_input64(DevMesh M, int ncb, int nbb, const double* __restrict__ D,
+                                                   const int* __restrict__ order, const double* __restrict__ h,
+                                                   LayerMat lm, StepConst sc, const double* __restrict__ x,
+                                                   double* __restrict__ rows, double dcoef)
+{
+    op_slots_block<double, 2, MODE, 0>(M, 1, 1, ncb, nbb, nullptr, D, order, h, lm.v, sc, x, nullptr, rows, nullptr,
+                                       dcoef, nullptr, nullptr);
+}
+
+// threads, blocks and LDS of a launch for MB slots
+struct SlotGrid {
+    int NT, ncb, nbb;
+    size_t lds;
+};
+template <typename T, int MODE, int LG>
+static SlotGrid slot_grid(const DevMesh& M, int MB, double dcoef)
 {
     using S = SlotShape<T, LG>;
-    const int NT = std::max(S::THREADS, ((M.cl_max_elems << LG) + 63) / 64 * 64);
-    const int ncb = (M.ncl + 7) / 8 * 8;
+    SlotGrid g;
+    g.NT = std::max(S::THREADS, ((M.cl_max_elems << LG) + 63) / 64 * 64);
+    g.ncb = (M.ncl + 7) / 8 * 8;
     // boundary nodes per block: up to 8 lanes of a wavefront share a node
-    const int parts = 64 / MB < 8 ? 64 / MB : 8, npb = NT / (MB * parts);
+    const int parts = 64 / MB < 8 ? 64 / MB : 8, npb = g.NT / (MB * parts);
     const long nb = dcoef != 0.0 ? ((long)M.nbn + npb - 1) / npb : 0;
-    const int nbb = (int)(nb < kDashpotBlocks ? nb : kDashpotBlocks);
-    if (nblk) *nblk = ncb + nbb;
-    size_t lds = ((size_t)33 * S::OS + (S::STAGE && MODE != OP_RHS ? 3 * S::XS : 0)) * sizeof(T);
-    lds += (size_t)M.cl_list_stride * 8 + 512 + (size_t)M.cl_node_stride * 4;
-    hipLaunchKernelGGL((k_op_slots<T, DK, MODE, LG>), dim3(ncb * (MB >> LG) + nbb), dim3(NT), lds, s, M, MB, nm, ncb,
-                       nbb, tl, D, order, h, mat, sc, x1, x2, rows, active, dcoef, vI, partial);
+    g.nbb = (int)(nb < kDashpotBlocks ? nb : kDashpotBlocks);
+    g.lds = ((size_t)33 * S::OS + (S::STAGE && MODE != OP_RHS ? 3 * S::XS : 0)) * sizeof(T);
+    g.lds += (size_t)M.cl_list_stride * 8 + 512 + (size_t)M.cl_node_stride * 4;
+    return g;
+}
+
+template <typename T, int DK, int MODE, int LG>
+static void op_launch(hipStream_t s, const DevMesh& M, int MB, int nm, const int* tl, const void* D, const double* h,
+                      const double* mat, StepConst sc, const T* x1, const T* x2, T* rows, const int* active,
+                      double dcoef, const double* vI, double* partial, int* nblk)
+{
+    const SlotGrid g = slot_grid<T, MODE, LG>(M, MB, dcoef);
+    if (nblk) *nblk = g.ncb + g.nbb;
+    hipLaunchKernelGGL((k_op_slots<T, DK, MODE, LG>), dim3(g.ncb * (MB >> LG) + g.nbb), dim3(g.NT), g.lds, s, M, MB, nm,
+                       g.ncb, g.nbb, tl, D, h, mat, sc, x1, x2, rows, active, dcoef, vI, partial);
 }
 
 template <typename T, int DK, int MODE>
@@ -231,7 +269,7 @@ static void op_slots(hipStream_t s, const DevMesh& M, int MB, int nm, const int*
                      double dcoef, const double* vI, double* partial, int* nblk)
 {
 #define NLTH_LG(LG) \
-    op_launch<T, DK, MODE, LG>(s, M, MB, nm, tl, D, nullptr, h, mat, sc, x1, x2, rows, active, dcoef, vI, partial, nblk)
+    op_launch<T, DK, MODE, LG>(s, M, MB, nm, tl, D, h, mat, sc, x1, x2, rows, active, dcoef, vI, partial, nblk)
     switch (MB) {
     case 1: NLTH_LG(0); break;
     case 2: NLTH_LG(1); break;
@@ -274,13 +312,14 @@ void launch_op_slots32(hipStream_t s, const DevMesh& M, int MB, int nm, const fl
 }
 
 void launch_op_input64(hipStream_t s, OpMode mode, const DevMesh& M, const int* order, const double* D,
-                       const double* h, const double* mat, StepConst sc, const double* x, double* rows, double dcoef)
+                       const double* h, const LayerMat& lm, StepConst sc, const double* x, double* rows, double dcoef)
 {
-    const double* none = nullptr;
+    const SlotGrid g = slot_grid<double, OP_A, 0>(M, 1, dcoef);
+    const dim3 nb(g.ncb + g.nbb), nt(g.NT);
     switch (mode) {
-    case OP_A: op_launch<double, 2, OP_A, 0>(s, M, 1, 1, nullptr, D, order, h, mat, sc, x, none, rows, nullptr, dcoef, nullptr, nullptr, nullptr); break;
-    case OP_K: op_launch<double, 2, OP_K, 0>(s, M, 1, 1, nullptr, D, order, h, mat, sc, x, none, rows, nullptr, dcoef, nullptr, nullptr, nullptr); break;
-    default: op_launch<double, 2, OP_M, 0>(s, M, 1, 1, nullptr, D, order, h, mat, sc, x, none, rows, nullptr, dcoef, nullptr, nullptr, nullptr); break;
+    case OP_A: hipLaunchKernelGGL((k_op_input64<OP_A>), nb, nt, g.lds, s, M, g.ncb, g.nbb, D, order, h, lm, sc, x, rows, dcoef); break;
+    case OP_K: hipLaunchKernelGGL((k_op_input64<OP_K>), nb, nt, g.lds, s, M, g.ncb, g.nbb, D, order, h, lm, sc, x, rows, dcoef); break;
+    default: hipLaunchKernelGGL((k_op_input64<OP_M>), nb, nt, g.lds, s, M, g.ncb, g.nbb, D, order, h, lm, sc, x, rows, dcoef); break;
     }
 }
 
