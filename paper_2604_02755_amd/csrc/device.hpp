@@ -355,6 +355,10 @@ __device__ __forceinline__ void element_forces(const T gL[4][3], T vol, T sm, T 
 #pragma unroll
                 for (int k = 0; k < 21; ++k)
                     d[k] = ld_u_nt(D, (uint32_t)(j * 21 + k) * rs + m);
+            } else if constexpr (DK == 2) {  // a row of 84 in LDS
+                const T* D = (const T*)Dp;
+#pragma unroll
+                for (int k = 0; k < 21; ++k) d[k] = D[j * 21 + k];
             } else {
                 const uint32_t* D = (const uint32_t*)Dp;
 #pragma unroll

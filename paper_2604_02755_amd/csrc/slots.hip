@@ -76,6 +76,10 @@ struct SlotShape {
     static constexpr int THREADS = LG == 0 ? 128 : (LG < 4 ? 64 << LG : 16 << LG);
 };
 
+// DK 2, doubles of a staged D row in LDS: 16 bytes more than the row, so the lanes'
+// reads spread over all banks
+constexpr int kInputRow = 86;
+
 // One block per element cluster, one lane per element-member: forces of all its
 // element-members to LDS, summed there per node row over the cluster's
 // incidence lists (a fixed order), the rows out for the gather.  Blocks after
@@ -106,6 +110,7 @@ __device__ __forceinline__ void op_slots_block(const DevMesh& M, int MB, int nm,
     using S = SlotShape<T, LG>;
     constexpr int L = 1 << LG, OS = S::OS, XS = S::XS;
     constexpr bool STAGE = S::STAGE && MODE != OP_RHS;
+    constexpr bool DIN = DK == 2 && MODE != OP_M;  // D rows staged where `out` comes later
     extern __shared__ __align__(16) char smem[];
     const int t = threadIdx.x, NT = blockDim.x;
     if (tl) nm = min(tl[0], MB);
@@ -121,7 +126,7 @@ __device__ __forceinline__ void op_slots_block(const DevMesh& M, int MB, int nm,
     }
     if (c < M.ncl) {
         T* out = (T*)smem;  // [33][OS], the last three rows zeros
-        T* xs = out + 33 * OS;  // [3][XS]
+        T* xs = out + (DIN ? S::ELEMS * kInputRow : 33 * OS);  // [3][XS]
         uint2* lists = (uint2*)(xs + (STAGE ? 3 * XS : 0));
         uint16_t* lptr = (uint16_t*)(lists + M.cl_list_stride);
         int* nds = (int*)(lptr + 256);
@@ -141,7 +146,32 @@ __device__ __forceinline__ void op_slots_block(const DevMesh& M, int MB, int nm,
         const uint4* lsrc = (const uint4*)(M.cl_lists + (size_t)c * M.cl_list_stride);
         for (int i = t; 2 * i < M.cl_list_stride; i += NT) ((uint4*)lists)[i] = lsrc[i];
         for (int i = t; i < M.cl_node_stride; i += NT) lptr[i] = M.cl_lptr[(size_t)c * M.cl_node_stride + i];
-        for (int i = t; i < 3 * OS; i += NT) out[30 * OS + i] = (T)0;
+        if constexpr (DIN) {
+            const double* Di = (const double*)Dv;
+            const bool wide = ((uintptr_t)Di & 15) == 0;  // (rows of 672 bytes)
+            constexpr int Q = 11;
+            for (int u0 = t; u0 < nec * 42; u0 += Q * NT) {
+                double v[Q][2];
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const int u = min(u0 + q * NT, nec * 42 - 1), r = u / 42;
+                    const double* p = Di + (size_t)order[e0 + r] * 84 + (u - 42 * r) * 2;
+                    if (wide) {
+                        const double2 w = *(const double2*)p;
+                        v[q][0] = w.x, v[q][1] = w.y;
+                    } else {
+                        v[q][0] = p[0], v[q][1] = p[1];
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const int u = u0 + q * NT, r = u / 42;
+                    if (u < nec * 42) *(double2*)((double*)smem + r * kInputRow + (u - 42 * r) * 2) = make_double2(v[q][0], v[q][1]);
+                }
+            }
+        } else {
+            for (int i = t; i < 3 * OS; i += NT) out[30 * OS + i] = (T)0;
+        }
         const bool act = m < nm && (!active || active[m]), on = slot < nec && act;
         const int e = e0 + (slot < nec ? slot : 0);
         const T* geo = geo_of<T>(M);
@@ -155,21 +185,20 @@ __device__ __forceinline__ void op_slots_block(const DevMesh& M, int MB, int nm,
         else if (sc.damping_mode == 1) he = sc.h0;
         T sm, sk, cv = 0;
         op_scales<T, MODE>(sc, rho, (double)vol, he, sm, sk, cv);
-        // D in blocks of 64 (element, member) pairs; DK 2: FP64 rows of an element
-        // contiguous, in input order
+        // D in blocks of 64 (element, member) pairs; DK 2: rows staged in LDS
         constexpr int W = DK == 4 ? 11 : (DK == 1 ? 44 : 84);
-        constexpr size_t B = DK == 0 || DK == 2 ? sizeof(T) : 4;
+        constexpr size_t B = DK == 0 ? sizeof(T) : 4;
         const size_t pe = (size_t)e * MB;
-        const char* Dp = DK == 2 ? (const char*)Dv + (size_t)order[e] * 84 * B
+        const char* Dp = DK == 2 ? smem + (size_t)slot * kInputRow * 8
                                  : (const char*)Dv + ((pe >> 6) * W * 64 + (pe & 63) + m) * B;
-        constexpr uint32_t rs = DK == 2 ? 1 : 64;
+        constexpr uint32_t rs = 64;
         T f[10][3];
         if constexpr (STAGE) {
             const uint4 lw = ((const uint4*)M.cl_lconn)[e];
             const uint32_t w[3] = {lw.x, lw.y, lw.z};
             __syncthreads();
             if (on)
-                element_forces<T, DK == 2 ? 0 : DK, MODE>(
+                element_forces<T, DK, MODE>(
                     gL, vol, sm, sk, cv, Dp, rs, 0u,
                     [&](int n, int cc, int) { return xs[cc * XS + (int)(((w[n / 4] >> (8 * (n % 4))) & 0xFFu) << LG) + lane]; },
                     f);
@@ -177,7 +206,7 @@ __device__ __forceinline__ void op_slots_block(const DevMesh& M, int MB, int nm,
             size_t nb[10];
 #pragma unroll
             for (int n = 0; n < 10; ++n) nb[n] = (size_t)M.conn[(size_t)n * M.ne + e] * 3 * MB + m;
-            element_forces<T, DK == 2 ? 0 : DK, MODE>(
+            element_forces<T, DK, MODE>(
                 gL, vol, sm, sk, cv, Dp, rs, 0u,
                 [&](int n, int cc, int v) { return (v ? x2 : x1)[nb[n] + (size_t)cc * MB]; }, f);
         }
@@ -186,6 +215,9 @@ __device__ __forceinline__ void op_slots_block(const DevMesh& M, int MB, int nm,
             for (int n = 0; n < 10; ++n)
 #pragma unroll
                 for (int cc = 0; cc < 3; ++cc) out[(3 * n + cc) * OS + t] = f[n][cc];
+            if (DIN)
+#pragma unroll
+                for (int cc = 0; cc < 3; ++cc) out[(30 + cc) * OS + t] = (T)0;
         }
         __syncthreads();
         for (int lr = slot; act && lr < ncn; lr += NT >> LG) {
@@ -220,7 +252,10 @@ __global__ __launch_bounds__(512) void k_op_slots(DevMesh M, int MB, int nm, int
 }
 
 // One member, D and h in input order, the material table a kernel argument (a
-// launch that put it in memory first took 5 us of a call's 32 on 1,152 elements)
+// launch that put it in memory first took 3 us of a call's 30 on 1,152 elements).
+// The block's D rows are staged in LDS, where `out` comes after them: a lane
+// reading its own row of 672 bytes fetched every line sixteen times past an L1 that
+// does not hold 64 rows (55,000 elements: 36.5 us, staged 25.0).
 template <int MODE>
 __global__ __launch_bounds__(512) void k_op_input64(DevMesh M, int ncb, int nbb, const double* __restrict__ D,
                                                    const int* __restrict__ order, const double* __restrict__ h,
@@ -236,7 +271,7 @@ struct SlotGrid {
     int NT, ncb, nbb;
     size_t lds;
 };
-template <typename T, int MODE, int LG>
+template <typename T, int MODE, int LG, bool DIN = false>
 static SlotGrid slot_grid(const DevMesh& M, int MB, double dcoef)
 {
     using S = SlotShape<T, LG>;
@@ -247,7 +282,7 @@ static SlotGrid slot_grid(const DevMesh& M, int MB, double dcoef)
     const int parts = 64 / MB < 8 ? 64 / MB : 8, npb = g.NT / (MB * parts);
     const long nb = dcoef != 0.0 ? ((long)M.nbn + npb - 1) / npb : 0;
     g.nbb = (int)(nb < kDashpotBlocks ? nb : kDashpotBlocks);
-    g.lds = ((size_t)33 * S::OS + (S::STAGE && MODE != OP_RHS ? 3 * S::XS : 0)) * sizeof(T);
+    g.lds = ((size_t)(DIN ? S::ELEMS * kInputRow : 33 * S::OS) + (S::STAGE && MODE != OP_RHS ? 3 * S::XS : 0)) * sizeof(T);
     g.lds += (size_t)M.cl_list_stride * 8 + 512 + (size_t)M.cl_node_stride * 4;
     return g;
 }
@@ -314,7 +349,8 @@ void launch_op_slots32(hipStream_t s, const DevMesh& M, int MB, int nm, const fl
 void launch_op_input64(hipStream_t s, OpMode mode, const DevMesh& M, const int* order, const double* D,
                        const double* h, const LayerMat& lm, StepConst sc, const double* x, double* rows, double dcoef)
 {
-    const SlotGrid g = slot_grid<double, OP_A, 0>(M, 1, dcoef);
+    SlotGrid g = mode == OP_M ? slot_grid<double, OP_A, 0>(M, 1, dcoef) : slot_grid<double, OP_A, 0, true>(M, 1, dcoef);
+    g.NT = 256;  // (threads that stage D: 128 took 28.6 us, 256 25)
     const dim3 nb(g.ncb + g.nbb), nt(g.NT);
     switch (mode) {
     case OP_A: hipLaunchKernelGGL((k_op_input64<OP_A>), nb, nt, g.lds, s, M, g.ncb, g.nbb, D, order, h, lm, sc, x, rows, dcoef); break;
