@@ -361,6 +361,9 @@ static void finish_clusters(int nn, const std::vector<int>& bn_node, ClusterList
     std::vector<int> fill(L.cn_ptr.begin(), L.cn_ptr.end() - 1);
     for (int r = 0; r < rows; ++r) L.cn_row[fill[L.node[r]]++] = r;
     for (size_t i = 0; i < bn_node.size(); ++i) L.cn_row[fill[bn_node[i]]++] = rows + (int)i;
+    for (size_t c = 0; c + 1 < L.noff.size(); ++c)
+        for (int r = L.noff[c]; r < L.noff[c + 1]; ++r)
+            if (L.cn_row[L.cn_ptr[L.node[r]]] == r) L.lptr[c * L.node_stride + r - L.noff[c]] |= kOwnerRow;
 }
 
 static void upload_clusters(Budget* b, const ClusterLists& L, Mesh::Clusters& C)
@@ -1600,24 +1603,71 @@ void Ens::cheb_solve()
     NLTH_HIP(hipGraphLaunch(g_cheb, s));
 }
 
-// A few-slot CG iteration after its operator (rows and the nblk partial sums of
-// p.Ap): the updates and their stages
+// k CG iterations with few slots (T double: the FP64 PCG, float: the inner CG):
+// operator, residual update, p update, with the stages in the updates where the
+// sums are few.  With 1 and 2 slots the p update joins the next iteration's operator
+// (p alternating with the operator's result vector, which these paths do not
+// use) and only the last iteration has a launch for it, while the operator's blocks
+// are at most two a CU and its time is a chain: 1,152 elements 8.5 + 4.1 -> 10.3 us,
+// 12,288 9.0 + 4.9 -> 12.0 (on 55,000 elements in FP32 the operator reads z and p
+// of 1.9 nodes a node and took longer than the two).
 template <typename T>
-void Ens::iter_updates(int nblk, T* x, T* p, T* r, T* z, const T* pinv_t, const double* alpha, const double* beta,
-                       const int* act, double tol2, int maxit)
+void Ens::few_slot_iters(int k)
 {
-    const bool inner = sizeof(T) == 4;
-    double* pd = partial.as<double>();
-    StageIn st{};
-    const StageIn* fused = stage_sums(inner ? FIN_IN_ALPHA : FIN_ALPHA, pd, 1, nblk, tol2, maxit, st) ? &st : nullptr;
-    if (st.partial == pd) pd += (size_t)nblk * MB;  // what this launch reads stays while it writes its own
-    hipEvent_t t0 = nullptr;
-    if (inner) tstart(t0);
-    launch_rows_update<T>(s, UPD_PZ, mesh->dev(MB), MB, nm, 0, nullptr, (const T*)cbuf.p, r, z, pinv_t, nullptr, nullptr,
-                          alpha, act, pd, &nblk, fused);
-    if (inner) tstop(t0, &pc_gather32, (int64_t)mesh->nn * nm);
-    fused = stage_sums(inner ? FIN_IN_BETA : FIN_BETA, pd, 2, nblk, tol2, maxit, st) ? &st : nullptr;
-    launch_pz<T>(s, ndof, MB, nm, x, p, z, alpha, beta, cs.inner_upd, fused);
+    constexpr bool inner = sizeof(T) == 4;
+    const DevMesh dm = mesh->dev(MB);
+    T *x, *p0, *p1, *r_, *z_;
+    const T* pinv_;
+    if constexpr (inner) {
+        x = iz.as<float>(), p0 = ip.as<float>(), p1 = iAp.as<float>(), r_ = ir.as<float>(), z_ = iw.as<float>();
+        pinv_ = pinv32.as<float>();
+    } else {
+        x = du.as<double>(), p0 = p.as<double>(), p1 = Ap.as<double>(), r_ = r.as<double>(), z_ = z.as<double>();
+        pinv_ = pinv.as<double>();
+    }
+    const int* act = inner ? cs.inner_active : cs.active;
+    const double *alpha = inner ? cs.ialpha : cs.alpha, *beta = inner ? cs.ibeta : cs.beta;
+    const double tol2 = inner ? P.inner_tol * P.inner_tol : P.cg_tol * P.cg_tol, dc = 2.0 / P.dt;
+    const int maxit = inner ? P.inner_maxit : P.cg_maxit;
+    double* const pd0 = partial.as<double>();
+    StageIn sb{};
+    bool lag = false;  // the p update is the operator's
+    T* pc = p0;
+    int nblk = 0;
+    for (int i = 0; i < k; ++i) {
+        hipEvent_t t0 = nullptr;
+        tstart(t0);
+        if (lag) {
+            T* pn = pc == p0 ? p1 : p0;
+            const PUpdate<T> pu{z_, pn, x, alpha, sb};
+            if constexpr (inner)
+                nblk = launch_op_p32(s, dm, MB, nm, D32.as<float>(), D16.as<uint32_t>(), d16_mean, h.as<double>(),
+                                     mat.as<double>(), sc, pc, (float*)cbuf.p, dc, pd0, pu);
+            else
+                nblk = launch_op_p64(s, dm, MB, nm, D64.as<double>(), h.as<double>(), mat.as<double>(), sc, pc,
+                                     cbuf.as<double>(), dc, pd0, pu);
+            pc = pn;
+        } else if constexpr (inner) {
+            op_rows32(pc, act, &nblk);
+        } else {
+            op_rows(OP_A, pc, nullptr, act, dc, nullptr, &nblk);
+        }
+        tstop(t0, inner ? &pc_ebe32 : &pc_ebe64, (int64_t)mesh->ne * nm);
+        const int op_blocks = nblk;
+        StageIn sa{};
+        const bool fa = stage_sums(inner ? FIN_IN_ALPHA : FIN_ALPHA, pd0, 1, nblk, tol2, maxit, sa);
+        const bool direct = sa.partial == pd0;  // what the next launch reads stays while it writes its own
+        double* pd = direct ? pd0 + (size_t)nblk * MB : pd0;
+        if (inner) tstart(t0);
+        launch_rows_update<T>(s, UPD_PZ, dm, MB, nm, 0, nullptr, (const T*)cbuf.p, r_, z_, pinv_, nullptr, nullptr, alpha,
+                              act, pd, &nblk, fa ? &sa : nullptr);
+        if (inner) tstop(t0, &pc_gather32, (int64_t)mesh->nn * nm);
+        const bool fb = stage_sums(inner ? FIN_IN_BETA : FIN_BETA, pd, 2, nblk, tol2, maxit, sb);
+        lag = MB <= 2 && op_blocks <= kLagBlocks && i + 1 < k && direct && sb.partial == pd;
+        if (lag) continue;
+        launch_pz<T>(s, ndof, MB, nm, x, p0, z_, alpha, beta, cs.inner_upd, fb ? &sb : nullptr, pc);
+        pc = p0;
+    }
 }
 
 // A stage of a few-slot iteration: true if the next kernel's blocks form it
@@ -1652,6 +1702,10 @@ void Ens::inner_iter()
         tail_iter();
         return;
     }
+    if (scatter == 0) {
+        few_slot_iters<float>(1);
+        return;
+    }
     const long n = ndof;
     int nblk;
     const int* iact = cs.inner_active;
@@ -1659,29 +1713,21 @@ void Ens::inner_iter()
     double* pd = partial.as<double>();
     hipEvent_t t0;
     tstart(t0);
-    if (scatter == 0) {
-        op_rows32(ip.as<float>(), iact, &nblk);
+    if (scatter == 2) {
+        op_rows32(ip.as<float>(), iact, nullptr);
         tstop(t0, &pc_ebe32, (int64_t)mesh->ne * nm);
-        iter_updates<float>(nblk, iz.as<float>(), ip.as<float>(), ir.as<float>(), iw.as<float>(), pinv32.as<float>(),
-                            cs.ialpha, cs.ibeta, iact, tol2, P.inner_maxit);
-        return;
+        tstart(t0);
+        launch_gather_dot(s, mesh->dev(MB), MB, nm, (const float*)cbuf.p, iAp.as<float>(), iact, ip.as<float>(), pd,
+                          &nblk);
+        tstop(t0, &pc_gather32, (int64_t)mesh->nn * nm);
     } else {
-        if (scatter == 2) {
-            op_rows32(ip.as<float>(), iact, nullptr);
-            tstop(t0, &pc_ebe32, (int64_t)mesh->ne * nm);
-            tstart(t0);
-            launch_gather_dot(s, mesh->dev(MB), MB, nm, (const float*)cbuf.p, iAp.as<float>(), iact, ip.as<float>(), pd,
-                              &nblk);
-            tstop(t0, &pc_gather32, (int64_t)mesh->nn * nm);
-        } else {
-            ebe32(ip.as<float>(), iAp.as<float>(), iact);
-            launch_dotsv<float>(s, 1, ip.as<float>(), iAp.as<float>(), nullptr, nullptr, nullptr, nullptr, ndof, MB,
-                                nm, iact, pd, &nblk);
-        }
-        fin(FIN_IN_ALPHA, 1, nblk, tol2, P.inner_maxit);
-        launch_inner_update(s, mesh->nn, MB, nm, ir.as<float>(), iw.as<float>(), iAp.as<float>(), pinv32.as<float>(),
-                            cs.ialpha, iact, pd, &nblk);
+        ebe32(ip.as<float>(), iAp.as<float>(), iact);
+        launch_dotsv<float>(s, 1, ip.as<float>(), iAp.as<float>(), nullptr, nullptr, nullptr, nullptr, ndof, MB,
+                            nm, iact, pd, &nblk);
     }
+    fin(FIN_IN_ALPHA, 1, nblk, tol2, P.inner_maxit);
+    launch_inner_update(s, mesh->nn, MB, nm, ir.as<float>(), iw.as<float>(), iAp.as<float>(), pinv32.as<float>(),
+                        cs.ialpha, iact, pd, &nblk);
     fin(FIN_IN_BETA, 2, nblk, tol2, P.inner_maxit);
     launch_pz<float>(s, n, MB, nm, iz.as<float>(), ip.as<float>(), iw.as<float>(), cs.ialpha, cs.ibeta, cs.inner_upd);
 }
@@ -1693,21 +1739,16 @@ void Ens::pcg_iter()
         tail64_iter();
         return;
     }
+    if (scatter == 0) {
+        few_slot_iters<double>(1);
+        return;
+    }
     const long n = ndof;
     int nblk;
     double* x = du.as<double>();
     const int* act = cs.active;
     const double tol2 = P.cg_tol * P.cg_tol;
     double* pd = partial.as<double>();
-    if (scatter == 0) {
-        hipEvent_t t0;
-        tstart(t0);
-        op_rows(OP_A, p.as<double>(), nullptr, act, 2.0 / P.dt, nullptr, &nblk);
-        tstop(t0, &pc_ebe64, (int64_t)mesh->ne * nm);
-        iter_updates<double>(nblk, x, p.as<double>(), r.as<double>(), z.as<double>(), pinv.as<double>(), cs.alpha,
-                             cs.beta, act, tol2, P.cg_maxit);
-        return;
-    }
     op_alpha(FIN_ALPHA, tol2, act);
     if (scatter != 1) {
         launch_rows_update<double>(s, UPD_PZ, mesh->dev(MB), MB, nm, 0, nullptr, cbuf.as<double>(), r.as<double>(),
@@ -1755,7 +1796,9 @@ void Ens::clear_graphs()
 void Ens::run_iters(int kind, int k, bool check)
 {
     auto issue = [&] {
-        for (int i = 0; i < k; ++i) kind == 0 ? inner_iter() : pcg_iter();
+        if (scatter == 0 && !tail_g) kind == 0 ? few_slot_iters<float>(k) : few_slot_iters<double>(k);
+        else
+            for (int i = 0; i < k; ++i) kind == 0 ? inner_iter() : pcg_iter();
         if (check) launch_copy_i32(s, kind == 0 ? cs.inner_active : cs.active, d_mail, MB + nm);
     };
     if (!use_graph || profile || k <= 0 || k > 64) {

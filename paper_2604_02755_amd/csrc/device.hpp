@@ -80,9 +80,10 @@ __device__ __forceinline__ T ld_u_nt(const T* base, uint32_t i)
 // member m: coef * sum over its faces of rho (Vp n n^T + Vs (I - n n^T)) int N_a N_b dA x_b,
 // plus, with vI, the incident-wave force 2 C_base v_I on base faces.  Only
 // every parts-th face of the node, from the part-th on (lanes share a node).
-template <typename T>
+// x(i): the nodal value at index i.
+template <typename XF>
 __device__ __forceinline__ void dashpot_at(const DevMesh& M, int MB, int m, int i, const double* __restrict__ mat,
-                                           double coef, const T* __restrict__ x, const double* __restrict__ vI,
+                                           double coef, XF x, const double* __restrict__ vI,
                                            double acc[3], int part = 0, int parts = 1)
 {
     for (int q = M.bn_ptr[i] + part; q < M.bn_ptr[i + 1]; q += parts) {
@@ -105,7 +106,7 @@ __device__ __forceinline__ void dashpot_at(const DevMesh& M, int MB, int m, int 
 #pragma unroll
         for (int b = 0; b < 6; ++b)
 #pragma unroll
-            for (int c = 0; c < 3; ++c) xb[b][c] = (double)x[(nb[b] * 3 + c) * MB + m];
+            for (int c = 0; c < 3; ++c) xb[b][c] = (double)x((size_t)((nb[b] * 3 + c) * MB + m));
         double X[3] = {0, 0, 0}, rs = 0;
 #pragma unroll
         for (int b = 0; b < 6; ++b) {
@@ -438,20 +439,19 @@ __device__ __forceinline__ void ebe_element(const DevMesh& M, int MB, int m, lon
 // face mesh has about six): the chain of dependent loads of a single lane
 // walking them was the longest of a small problem's operator (9.5 us of 45 us
 // per CG iteration with 360 elements).
-template <typename T>
+template <typename T, typename XF>
 __device__ __forceinline__ double boundary_rows(const DevMesh& M, int MB, int nm, const double* __restrict__ mat,
-                                                double coef, const T* __restrict__ x,
-                                                const double* __restrict__ vI, const int* __restrict__ active,
+                                                double coef, XF x, const double* __restrict__ vI, bool on,
                                                 T* __restrict__ rows, int blk, int nblk, int nthreads)
 {
     const int parts = MB >= 64 ? 1 : (64 / MB < 8 ? 64 / MB : 8);
     const int t = threadIdx.x, m = t % MB, q = t / MB, part = q % parts;
     const int npb = nthreads / (MB * parts);  // nodes per block pass
-    const bool act = m < nm && (!active || active[m]);
+    const bool act = m < nm && on;
     double dot = 0.0;
     for (long i = (long)blk * npb + q / parts; i < M.nbn; i += (long)nblk * npb) {
         double acc[3] = {0.0, 0.0, 0.0};
-        if (act) dashpot_at<T>(M, MB, m, (int)i, mat, coef, x, vI, acc, part, parts);
+        if (act) dashpot_at(M, MB, m, (int)i, mat, coef, x, vI, acc, part, parts);
         for (int o = MB; o < MB * parts; o <<= 1)  // the lanes of a node: a fixed tree
 #pragma unroll
             for (int c = 0; c < 3; ++c) acc[c] += __shfl_xor(acc[c], o);
@@ -461,7 +461,7 @@ __device__ __forceinline__ double boundary_rows(const DevMesh& M, int MB, int nm
             for (int c = 0; c < 3; ++c) {
                 const T v = (T)acc[c];
                 rows[((size_t)i * 3 + c) * MB + m] = v;
-                dot += (double)x[(node * 3 + c) * MB + m] * (double)v;
+                dot += (double)x((node * 3 + c) * MB + m) * (double)v;
             }
         }
     }
@@ -545,14 +545,15 @@ __device__ __forceinline__ void mean_grad_products(int n, const double gL[4][3],
     }
 }
 
-// Per-member sums of ND x nblk partial rows of MB <= 32 slots by a block of 256
+// Per-member sums of ND x nblk partial rows of MB <= 32 slots by a block of NT
 // threads (valid in threads t < MB), in a fixed order: every block of a launch
 // that forms them gets the same bits.  Eight loads of a thread in flight at a time.
-template <int ND>
+template <int ND, int NT = 256>
 __device__ __forceinline__ void member_sums(const double* __restrict__ partial, int nblk, int MB, double* __restrict__ sh,
                                             double S[ND])
 {
-    const int t = threadIdx.x, m = t % MB, rpb = 256 / MB;
+    constexpr int nw = NT / 64;
+    const int t = threadIdx.x, m = t % MB, rpb = NT / MB;
     double a[ND];
 #pragma unroll
     for (int k = 0; k < ND; ++k) a[k] = 0.0;
@@ -571,15 +572,74 @@ __device__ __forceinline__ void member_sums(const double* __restrict__ partial, 
 #pragma unroll
     for (int k = 0; k < ND; ++k) {
         for (int o = 32; o >= MB; o >>= 1) a[k] += __shfl_xor(a[k], o);
-        if ((t & 63) < MB) sh[(k * 4 + (t >> 6)) * MB + (t & 63)] = a[k];
+        if ((t & 63) < MB) sh[(k * nw + (t >> 6)) * MB + (t & 63)] = a[k];
     }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < ND; ++k) {
         S[k] = 0.0;
         if (t < MB)
-            for (int w = 0; w < 4; ++w) S[k] += sh[(k * 4 + w) * MB + t];
+            for (int w = 0; w < nw; ++w) S[k] += sh[(k * nw + w) * MB + t];
     }
 }
+
+// The beta stage by every block of the kernel that updates p (few partial sums: a launch of
+// its own costs more than the sums, 5 us a stage against 2): S = (r.r, r.z) of
+// member t, for threads t < MB.  What block 0 writes here (convergence, counts,
+// r.z) the other blocks read from what the alpha stage left (inner_upd, rz_prev,
+// iters_prev).  `on`: the member iterates on.  Same logic as stage_logic(FIN_BETA / FIN_IN_BETA).
+template <bool INNER>
+__device__ __forceinline__ double fused_beta(const StageIn& st, int m, const double S[2], bool upd, double rz_prev,
+                                             int it, double ref, int MB, bool write, bool& on)
+{
+    const CgScalars& cs = st.cs;
+    on = false;
+    if (!upd) return 0.0;
+    ++it;
+    const bool conv = S[0] <= st.tol2 * ref, stop = conv || it >= st.maxit;
+    const double beta = stop ? 0.0 : S[1] / rz_prev;
+    on = !stop;
+    if (write) {
+        if (INNER) {
+            cs.inner_iters[m] = it;
+            cs.inner_total[m] += 1;
+            if (stop) {
+                cs.inner_active[m] = 0;
+            } else {
+                cs.ibeta[m] = beta;
+                cs.irz[m] = S[1];
+                if (it <= kLanczosMax) cs.lz[(long)(kLanczosMax + it - 1) * MB + m] = beta;
+            }
+        } else {
+            cs.iters[m] = it;
+            cs.rr[m] = S[0];
+            if (stop) {
+                cs.active[m] = 0;
+                if (!conv) cs.status[m] = -5;
+            } else {
+                cs.beta[m] = beta;
+                cs.rz[m] = S[1];
+            }
+        }
+    }
+    return beta;
+}
+
+// the stage's inputs of member t, loaded ahead of its sums
+template <bool INNER>
+struct BetaState {
+    bool upd = false;
+    double rz_prev = 0.0, ref = 0.0;
+    int it = 0;
+    __device__ __forceinline__ BetaState(const CgScalars& cs, int MB, int nm)
+    {
+        const int t = threadIdx.x;
+        if (t >= MB || t >= nm) return;
+        upd = cs.inner_upd[t];
+        rz_prev = cs.rz_prev[t];
+        ref = INNER ? cs.ir0[t] : cs.bb[t];
+        it = cs.iters_prev[t];
+    }
+};
 
 }  // namespace nlth

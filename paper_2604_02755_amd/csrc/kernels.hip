@@ -180,8 +180,10 @@ __global__ __launch_bounds__(256) void k_ebe_cluster(DevMesh M, int MB, int nm, 
     const int gb = nb8 ? (gi / gs < nb8 ? gi / gs : nb8) : 0;  // boundary groups before this one
     if (nb8 && gi % gs == gs - 1 && gi / gs < nb8) {
         const int bb = gb * 8 + (blockIdx.x & 7);
-        const double d = boundary_rows<T>(M, MB, nm, mat, dcoef, x1, vI, active, co + (size_t)M.cl_rows * 3 * MB, bb,
-                                          nbb, 256);
+        const int mm = threadIdx.x % MB;
+        const double d = boundary_rows<T>(M, MB, nm, mat, dcoef, [&](size_t n) { return x1[n]; }, vI,
+                                          !active || (mm < nm && active[mm]), co + (size_t)M.cl_rows * 3 * MB, bb, nbb,
+                                          256);
         if (!partial) return;
         double* sh = (double*)ys;
         sh[threadIdx.x] = d;  // all of member t % MB
@@ -747,7 +749,7 @@ __global__ __launch_bounds__(256) void k_dashpot(DevMesh M, int MB, int nm, cons
     const long i = g / MB;
     if (i >= M.nbn || m >= nm || (active && !active[m])) return;
     double acc[3] = {0, 0, 0};
-    dashpot_at<T>(M, MB, m, (int)i, mat, coef, x, vI, acc);
+    dashpot_at(M, MB, m, (int)i, mat, coef, [&](size_t n) { return x[n]; }, vI, acc);
     const size_t yi = (size_t)M.bn_node[i] * 3 * MB + m;
 #pragma unroll
     for (int c = 0; c < 3; ++c) y[yi + (size_t)c * MB] += (T)acc[c];

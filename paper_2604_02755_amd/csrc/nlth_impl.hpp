@@ -30,7 +30,9 @@ constexpr int kClusterNodes = 48;         // most distinct nodes of an element c
 constexpr int kClusterElems = 16;         // most elements of an element cluster
 constexpr int kWideNodes = 240;           // the same of a wide cluster, which
 constexpr int kWideElems = 64;            // ensembles of up to
+constexpr uint16_t kOwnerRow = 0x8000;    // in cl_lptr: the row is its node's first
 constexpr int kWideSlots = 8;             // member slots use
+constexpr int kLagBlocks = 512;           // most operator blocks of an iteration whose p update joins the next operator
 // most partial sums that each block of the next kernel reads itself, and how many
 // they are folded to beyond that with 16 and more slots
 constexpr int kFuseSums = 3072;
@@ -58,6 +60,16 @@ struct StageIn {
     double tol2;
     int maxit;
     CgScalars cs;
+};
+
+// The p and x updates of an iteration made by the next one's operator (1 and 2
+// slots): with the beta stage from `sg`, p_new = z + beta p and x += alpha p
+template <typename T>
+struct PUpdate {
+    const T* z;
+    T *p_new, *x;
+    const double* alpha;
+    StageIn sg;
 };
 
 
@@ -157,6 +169,12 @@ void launch_op_slots64(hipStream_t s, OpMode mode, const DevMesh& M, int MB, int
 void launch_op_slots32(hipStream_t s, const DevMesh& M, int MB, int nm, const float* D32, const uint32_t* D16,
                        bool d16_mean, const double* h, const double* mat, StepConst sc, const float* x, float* rows,
                        const int* active, double dcoef, double* partial, int* nblk);
+// operator A on p_new of `pu` (x1: the old p), MB 1 or 2, p.Ap to partial
+int launch_op_p64(hipStream_t s, const DevMesh& M, int MB, int nm, const double* D, const double* h, const double* mat,
+                   StepConst sc, const double* p, double* rows, double dcoef, double* partial, const PUpdate<double>& pu);
+int launch_op_p32(hipStream_t s, const DevMesh& M, int MB, int nm, const float* D32, const uint32_t* D16,
+                   bool d16_mean, const double* h, const double* mat, StepConst sc, const float* p, float* rows,
+                   double dcoef, double* partial, const PUpdate<float>& pu);
 // one member, D [ne][4][21] and h [ne] in input tet order (order: storage
 // position -> input tet): the operator of launch_op_slots64 on them
 void launch_op_input64(hipStream_t s, OpMode mode, const DevMesh& M, const int* order, const double* D,
@@ -329,7 +347,7 @@ void launch_inner_update(hipStream_t s, int nn, int MB, int nm, float* ir, float
 // x += alpha p, then p = z + beta p, for the members of upd
 template <typename T>
 void launch_pz(hipStream_t s, long nrows, int MB, int nm, T* x, T* p, const T* z, const double* alpha,
-               const double* beta, const int* upd, const StageIn* fused = nullptr);
+               const double* beta, const int* upd, const StageIn* fused = nullptr, const T* p_in = nullptr);
 void launch_inner_out(hipStream_t s, long nrows, int MB, int nm, const float* iz, double* z, const double* Ap,
                       const double* r, const int* active, double* partial, int* nblk);
 void launch_zero_if_b0(hipStream_t s, long nrows, int MB, int nm, double* x, const double* bb, const int* stepping);

@@ -216,9 +216,7 @@ struct Ens {
     void op_rows(OpMode mode, const double* x1, const double* x2, const int* active, double dcoef, const double* vI,
                  int* nblk);
     void op_rows32(const float* x, const int* active, int* nblk);
-    template <typename T>
-    void iter_updates(int nblk, T* x, T* p, T* r, T* z, const T* pinv_t, const double* alpha, const double* beta,
-                      const int* act, double tol2, int maxit);
+    template <typename T> void few_slot_iters(int k);
     bool stage_sums(FinalizeStage stage, const double* pd, int nd, int nblk, double tol2, int maxit, StageIn& st);
     void op_alpha(FinalizeStage stage, double tol2, const int* active);
     void build_rhs();

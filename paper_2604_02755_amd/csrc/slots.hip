@@ -98,14 +98,18 @@ constexpr int kInputRow = 86;
 // 808 -> 675.  Four lanes per element-member, one per integration point, had a
 // shorter chain but 1.5 times the instructions: no faster on small meshes, 124
 // against 45 us (FP32, without the sums) at 8 slots.
-template <typename T, int DK, int MODE, int LG>
+// PF (1 and 2 slots): the p update of the CG iteration before joins the staging of
+// p: every block forms the beta stage and p_new of its own nodes, and the first
+// cluster of a node writes it with the x update (owner rows: kOwnerRow).
+template <typename T, int DK, int MODE, int LG, bool PF = false>
 __device__ __forceinline__ void op_slots_block(const DevMesh& M, int MB, int nm, int ncb, int nbb,
                                                const int* __restrict__ tl, const void* __restrict__ Dv,
                                                const int* __restrict__ order, const double* __restrict__ h,
                                                const double* __restrict__ mat, const StepConst& sc,
                                                const T* __restrict__ x1, const T* __restrict__ x2, T* __restrict__ rows,
                                                const int* __restrict__ active, double dcoef,
-                                               const double* __restrict__ vI, double* __restrict__ partial)
+                                               const double* __restrict__ vI, double* __restrict__ partial,
+                                               const PUpdate<T>* pu = nullptr)
 {
     using S = SlotShape<T, LG>;
     constexpr int L = 1 << LG, OS = S::OS, XS = S::XS;
@@ -118,9 +122,56 @@ __device__ __forceinline__ void op_slots_block(const DevMesh& M, int MB, int nm,
     const int blk = (int)blockIdx.x, g = blk / ncb * L, cb = blk % ncb;  // first member of the group; cluster block
     const int c = (cb % 8) * (ncb / 8) + cb / 8;                        // XCD-contiguous clusters
     const int ncl_blocks = ncb * (MB / L);
+    bool on_m = false;  // PF: this lane's member iterates
+    T be = 0, al = 0;
+    bool upd = false;
+    // PF: z, p and x of the rows that this thread stages, under way while the sums are formed
+    constexpr int RP = (S::NODES + (S::THREADS >> LG) - 1) / (S::THREADS >> LG);
+    T zr[PF ? RP : 1][3], pr[PF ? RP : 1][3], xr[PF ? RP : 1][3];
+    size_t ir[PF ? RP : 1];
+    bool own[PF ? RP : 1];
+    if constexpr (PF) {
+        constexpr bool INNER = sizeof(T) == 4;
+        __shared__ double ps[2 * S::THREADS / 64 * L];  // (the block has S::THREADS: at most 64 elements of L lanes)
+        __shared__ double pb[L];
+        __shared__ int pon[L];
+        const int mt = t & (L - 1);
+        if (blk < ncl_blocks && c < M.ncl) {
+            const int ncn = M.cl_head[c].w;
+#pragma unroll
+            for (int q = 0; q < RP; ++q) {
+                const int lr = (t >> LG) + q * (NT >> LG);
+                own[q] = false;
+                if (lr >= ncn) continue;
+                ir[q] = (size_t)M.cl_nodes[(size_t)c * M.cl_node_stride + lr] * 3 * MB + mt;
+                own[q] = M.cl_lptr[(size_t)c * M.cl_node_stride + lr] & kOwnerRow;
+#pragma unroll
+                for (int cc = 0; cc < 3; ++cc) {
+                    zr[q][cc] = pu->z[ir[q] + (size_t)cc * MB];
+                    pr[q][cc] = x1[ir[q] + (size_t)cc * MB];
+                    if (own[q]) xr[q][cc] = pu->x[ir[q] + (size_t)cc * MB];
+                }
+            }
+        }
+        const BetaState<INNER> bs(pu->sg.cs, MB, nm);
+        double S2[2];
+        member_sums<2, S::THREADS>(pu->sg.partial, pu->sg.nblk, MB, ps, S2);
+        if (t < MB) {
+            bool on;
+            pb[t] = fused_beta<INNER>(pu->sg, t, S2, bs.upd, bs.rz_prev, bs.it, bs.ref, MB, blk == 0, on);
+            pon[t] = (int)on | ((int)bs.upd << 1);
+        }
+        __syncthreads();
+        on_m = pon[mt] & 1;
+        upd = pon[mt] & 2;
+        be = (T)pb[mt];
+        al = upd ? (T)pu->alpha[mt] : (T)0;
+    }
+    auto lane_on = [&](int mm) { return PF ? on_m : mm < nm && (!active || active[mm]); };
     if (blk >= ncl_blocks) {
-        dot = boundary_rows<T>(M, MB, nm, mat, dcoef, x1, vI, active, rows + (size_t)M.cl_rows * 3 * MB,
-                               blk - ncl_blocks, nbb, NT);
+        dot = boundary_rows<T>(M, MB, nm, mat, dcoef,
+                               [&](size_t n) { return PF ? pu->z[n] + be * x1[n] : x1[n]; }, vI, lane_on(t % MB),
+                               rows + (size_t)M.cl_rows * 3 * MB, blk - ncl_blocks, nbb, NT);
         if (partial) slot_partials(dot, MB, (double*)smem, partial + (size_t)(ncb + blk - ncl_blocks) * MB);
         return;
     }
@@ -133,7 +184,22 @@ __device__ __forceinline__ void op_slots_block(const DevMesh& M, int MB, int nm,
         const int4 ch = M.cl_head[c];
         const int e0 = ch.x, r0 = ch.y, nec = ch.z, ncn = ch.w;
         const int slot = t >> LG, lane = t & (L - 1), m = g + lane;
-        if constexpr (STAGE) {
+        if constexpr (PF) {
+#pragma unroll
+            for (int q = 0; q < RP; ++q) {
+                const int lr = slot + q * (NT >> LG);
+                if (lr >= ncn) continue;
+#pragma unroll
+                for (int cc = 0; cc < 3; ++cc) {
+                    const T pn = zr[q][cc] + be * pr[q][cc];
+                    xs[cc * XS + (lr << LG) + lane] = pn;
+                    if (own[q] && upd) {
+                        pu->p_new[ir[q] + (size_t)cc * MB] = pn;
+                        pu->x[ir[q] + (size_t)cc * MB] = xr[q][cc] + al * pr[q][cc];
+                    }
+                }
+            }
+        } else if constexpr (STAGE) {
             // the member lanes of a row read its node's three values
             for (int lr = slot; lr < ncn; lr += NT >> LG) {
                 const size_t x0 = (size_t)M.cl_nodes[(size_t)c * M.cl_node_stride + lr] * 3 * MB + m;
@@ -145,7 +211,7 @@ __device__ __forceinline__ void op_slots_block(const DevMesh& M, int MB, int nm,
         }
         const uint4* lsrc = (const uint4*)(M.cl_lists + (size_t)c * M.cl_list_stride);
         for (int i = t; 2 * i < M.cl_list_stride; i += NT) ((uint4*)lists)[i] = lsrc[i];
-        for (int i = t; i < M.cl_node_stride; i += NT) lptr[i] = M.cl_lptr[(size_t)c * M.cl_node_stride + i];
+        for (int i = t; i < M.cl_node_stride; i += NT) lptr[i] = M.cl_lptr[(size_t)c * M.cl_node_stride + i] & ~kOwnerRow;
         if constexpr (DIN) {
             const double* Di = (const double*)Dv;
             const bool wide = ((uintptr_t)Di & 15) == 0;  // (rows of 672 bytes)
@@ -172,7 +238,7 @@ __device__ __forceinline__ void op_slots_block(const DevMesh& M, int MB, int nm,
         } else {
             for (int i = t; i < 3 * OS; i += NT) out[30 * OS + i] = (T)0;
         }
-        const bool act = m < nm && (!active || active[m]), on = slot < nec && act;
+        const bool act = m < nm && lane_on(m), on = slot < nec && act;
         const int e = e0 + (slot < nec ? slot : 0);
         const T* geo = geo_of<T>(M);
         T gL[4][3];
@@ -249,6 +315,16 @@ __global__ __launch_bounds__(512) void k_op_slots(DevMesh M, int MB, int nm, int
 {
     op_slots_block<T, DK, MODE, LG>(M, MB, nm, ncb, nbb, tl, Dv, nullptr, h, mat, sc, x1, x2, rows, active, dcoef, vI,
                                     partial);
+}
+
+template <typename T, int DK, int LG>
+__global__ __launch_bounds__(512) void k_op_p(DevMesh M, int MB, int nm, int ncb, int nbb, const void* __restrict__ Dv,
+                                             const double* __restrict__ h, const double* __restrict__ mat, StepConst sc,
+                                             const T* __restrict__ p, T* __restrict__ rows, double dcoef,
+                                             double* __restrict__ partial, PUpdate<T> pu)
+{
+    op_slots_block<T, DK, OP_A, LG, true>(M, MB, nm, ncb, nbb, nullptr, Dv, nullptr, h, mat, sc, p, nullptr, rows,
+                                          nullptr, dcoef, nullptr, partial, &pu);
 }
 
 // One member, D and h in input order, the material table a kernel argument (a
@@ -346,6 +422,37 @@ void launch_op_slots32(hipStream_t s, const DevMesh& M, int MB, int nm, const fl
         op_slots<float, 0, OP_A>(s, M, MB, nm, nullptr, D32, h, mat, sc, x, none, rows, active, dcoef, nullptr, partial, nblk);
 }
 
+template <typename T, int DK>
+static int op_p(hipStream_t s, const DevMesh& M, int MB, int nm, const void* D, const double* h, const double* mat,
+                 StepConst sc, const T* p, T* rows, double dcoef, double* partial, const PUpdate<T>& pu)
+{
+    if (MB == 1) {
+        const SlotGrid g = slot_grid<T, OP_A, 0>(M, 1, dcoef);
+        hipLaunchKernelGGL((k_op_p<T, DK, 0>), dim3(g.ncb + g.nbb), dim3(g.NT), g.lds, s, M, 1, nm, g.ncb, g.nbb, D, h,
+                           mat, sc, p, rows, dcoef, partial, pu);
+        return g.ncb + g.nbb;
+    }
+    const SlotGrid g = slot_grid<T, OP_A, 1>(M, 2, dcoef);
+    hipLaunchKernelGGL((k_op_p<T, DK, 1>), dim3(g.ncb + g.nbb), dim3(g.NT), g.lds, s, M, 2, nm, g.ncb, g.nbb, D, h, mat,
+                       sc, p, rows, dcoef, partial, pu);
+    return g.ncb + g.nbb;
+}
+
+int launch_op_p64(hipStream_t s, const DevMesh& M, int MB, int nm, const double* D, const double* h, const double* mat,
+                   StepConst sc, const double* p, double* rows, double dcoef, double* partial, const PUpdate<double>& pu)
+{
+    return op_p<double, 0>(s, M, MB, nm, D, h, mat, sc, p, rows, dcoef, partial, pu);
+}
+
+int launch_op_p32(hipStream_t s, const DevMesh& M, int MB, int nm, const float* D32, const uint32_t* D16,
+                   bool d16_mean, const double* h, const double* mat, StepConst sc, const float* p, float* rows,
+                   double dcoef, double* partial, const PUpdate<float>& pu)
+{
+    if (D16 && d16_mean) return op_p<float, 4>(s, M, MB, nm, D16, h, mat, sc, p, rows, dcoef, partial, pu);
+    if (D16) return op_p<float, 1>(s, M, MB, nm, D16, h, mat, sc, p, rows, dcoef, partial, pu);
+    return op_p<float, 0>(s, M, MB, nm, D32, h, mat, sc, p, rows, dcoef, partial, pu);
+}
+
 void launch_op_input64(hipStream_t s, OpMode mode, const DevMesh& M, const int* order, const double* D,
                        const double* h, const LayerMat& lm, StepConst sc, const double* x, double* rows, double dcoef)
 {
@@ -406,7 +513,7 @@ __global__ __launch_bounds__(256) void k_diag_slots(DevMesh M, int MB, int nm, i
     const int slot = t >> LG, lane = t & (L - 1), m = g + lane;
     const uint4* lsrc = (const uint4*)(M.cl_lists + (size_t)c * M.cl_list_stride);
     for (int i = t; 2 * i < M.cl_list_stride; i += NT) ((uint4*)lists)[i] = lsrc[i];
-    for (int i = t; i < M.cl_node_stride; i += NT) lptr[i] = M.cl_lptr[(size_t)c * M.cl_node_stride + i];
+    for (int i = t; i < M.cl_node_stride; i += NT) lptr[i] = M.cl_lptr[(size_t)c * M.cl_node_stride + i] & ~kOwnerRow;
     for (int i = t; i < 3 * OS; i += NT) out[30 * OS + i] = 0.0;
     const int e = e0 + slot;
     if (slot < nec && m < nm) {

@@ -501,53 +501,13 @@ void launch_inner_update(hipStream_t s, int nn, int MB, int nm, float* ir, float
     else hipLaunchKernelGGL((k_inner_update<1>), dim3(g), dim3(256), 0, s, nn, MB, nm, ir, w, iAp, pinv32, ialpha, iactive, partial);
 }
 
-// The beta stage by every block of the p update (few partial sums: a launch of
-// its own costs more than the sums, 5 us a stage against 2): S = (r.r, r.z) of
-// member t, for threads t < MB.  What block 0 writes here (convergence, counts,
-// r.z) the other blocks read from what the alpha stage left (inner_upd, rz_prev,
-// iters_prev).  Same logic as stage_logic(FIN_BETA / FIN_IN_BETA).
-template <bool INNER>
-__device__ __forceinline__ double fused_beta(const StageIn& st, int m, const double S[2], bool upd, double rz_prev,
-                                             int it, double ref, int MB, bool write)
-{
-    const CgScalars& cs = st.cs;
-    if (!upd) return 0.0;
-    ++it;
-    const bool conv = S[0] <= st.tol2 * ref, stop = conv || it >= st.maxit;
-    const double beta = stop ? 0.0 : S[1] / rz_prev;
-    if (write) {
-        if (INNER) {
-            cs.inner_iters[m] = it;
-            cs.inner_total[m] += 1;
-            if (stop) {
-                cs.inner_active[m] = 0;
-            } else {
-                cs.ibeta[m] = beta;
-                cs.irz[m] = S[1];
-                if (it <= kLanczosMax) cs.lz[(long)(kLanczosMax + it - 1) * MB + m] = beta;
-            }
-        } else {
-            cs.iters[m] = it;
-            cs.rr[m] = S[0];
-            if (stop) {
-                cs.active[m] = 0;
-                if (!conv) cs.status[m] = -5;
-            } else {
-                cs.beta[m] = beta;
-                cs.rz[m] = S[1];
-            }
-        }
-    }
-    return beta;
-}
-
 // CG: x += a p (with this iteration's p), then p = z + b p, for the members
 // whose alpha was formed this iteration (upd); a member that has just converged
 // takes its last x update, and its p is not used again.  FUSED: the block forms
 // the beta stage first (the first row's loads under way meanwhile).
 template <typename T, int VEC, bool FUSED>
 __global__ __launch_bounds__(256) void k_pz(long nrows, int MB, int nm, T* __restrict__ x,
-                                           T* __restrict__ p, const T* __restrict__ z,
+                                           const T* p_in, T* p, const T* __restrict__ z,
                                            const double* __restrict__ alpha, const double* __restrict__ beta,
                                            const int* __restrict__ upd, StageIn sg)
 {
@@ -568,22 +528,15 @@ __global__ __launch_bounds__(256) void k_pz(long nrows, int MB, int nm, T* __res
         constexpr bool INNER = sizeof(T) == 4;
         if (any && row < nrows) {
             const long i = row * MB + m0;
-            X = ld<T, VEC>(x + i), P = ld<T, VEC>(p + i), Z = ld<T, VEC>(z + i);
+            X = ld<T, VEC>(x + i), P = ld<T, VEC>(p_in + i), Z = ld<T, VEC>(z + i);
         }
         __shared__ double sh[2 * 4 * 32];
         __shared__ double sb[32];
-        bool u = false;
-        double rzp = 0.0, ref = 0.0;
-        int it = 0;
-        if (t < MB && t < nm) {
-            u = upd[t];
-            rzp = sg.cs.rz_prev[t];
-            ref = INNER ? sg.cs.ir0[t] : sg.cs.bb[t];
-            it = sg.cs.iters_prev[t];
-        }
+        const BetaState<INNER> bs(sg.cs, MB, nm);
         double S[2];
+        bool on;
         member_sums<2>(sg.partial, sg.nblk, MB, sh, S);
-        if (t < MB) sb[t] = fused_beta<INNER>(sg, t, S, u, rzp, it, ref, MB, blockIdx.x == 0);
+        if (t < MB) sb[t] = fused_beta<INNER>(sg, t, S, bs.upd, bs.rz_prev, bs.it, bs.ref, MB, blockIdx.x == 0, on);
         __syncthreads();
 #pragma unroll
         for (int v = 0; v < VEC; ++v) be[v] = act[v] ? (T)sb[m0 + v] : (T)0;
@@ -591,7 +544,7 @@ __global__ __launch_bounds__(256) void k_pz(long nrows, int MB, int nm, T* __res
     }
     for (bool first = FUSED; row < nrows; row += (long)gridDim.x * rpb, first = false) {
         const long i = row * MB + m0;
-        if (!FUSED || !first) X = ld<T, VEC>(x + i), P = ld<T, VEC>(p + i), Z = ld<T, VEC>(z + i);
+        if (!FUSED || !first) X = ld<T, VEC>(x + i), P = ld<T, VEC>(p_in + i), Z = ld<T, VEC>(z + i);
 #pragma unroll
         for (int v = 0; v < VEC; ++v)
             if (act[v]) {
@@ -605,21 +558,21 @@ __global__ __launch_bounds__(256) void k_pz(long nrows, int MB, int nm, T* __res
 
 template <typename T>
 void launch_pz(hipStream_t s, long nrows, int MB, int nm, T* x, T* p, const T* z, const double* alpha,
-               const double* beta, const int* upd, const StageIn* fused)
+               const double* beta, const int* upd, const StageIn* fused, const T* p_in)
 {
     const int VEC = vec_of(MB), QB = MB / VEC;
     const int g = grid_for(nrows, 256 / QB);
     const StageIn sg = fused ? *fused : StageIn{};
 #define NLTH_PZ(V, F) \
-    hipLaunchKernelGGL((k_pz<T, V, F>), dim3(g), dim3(256), 0, s, nrows, MB, nm, x, p, z, alpha, beta, upd, sg)
+    hipLaunchKernelGGL((k_pz<T, V, F>), dim3(g), dim3(256), 0, s, nrows, MB, nm, x, p_in ? p_in : p, p, z, alpha, beta, upd, sg)
     if (VEC == 4) { if (fused) NLTH_PZ(4, true); else NLTH_PZ(4, false); }
     else { if (fused) NLTH_PZ(1, true); else NLTH_PZ(1, false); }
 #undef NLTH_PZ
 }
 template void launch_pz<float>(hipStream_t, long, int, int, float*, float*, const float*, const double*, const double*,
-                               const int*, const StageIn*);
+                               const int*, const StageIn*, const float*);
 template void launch_pz<double>(hipStream_t, long, int, int, double*, double*, const double*, const double*,
-                                const double*, const int*, const StageIn*);
+                                const double*, const int*, const StageIn*, const double*);
 
 // preconditioner output z = iz (FP64) for outer-active members (0 for the
 // others, whose z is not used again in the step); partials (z.Ap, z.r)

@@ -35,7 +35,7 @@ def test_slot_counts_match_oracle(nlth_mod, oracle_lib, members, precision, inne
         assert np.abs(ref["vel"]).max() > 0 and err < 1e-9
 
 
-@pytest.mark.parametrize("members,dims", [(1, (5, 3, 3)), (3, (8, 8, 8)), (8, (16, 16, 17)), (16, (10, 8, 8)),
+@pytest.mark.parametrize("members,dims", [(1, (5, 3, 3)), (2, (9, 8, 7)), (3, (8, 8, 8)), (8, (16, 16, 17)), (16, (10, 8, 8)),
                                           (32, (10, 8, 8)), (70, (6, 5, 4))])
 @pytest.mark.parametrize("precision", [0, 1])
 def test_iterations_match_the_colour_path(nlth_mod, members, dims, precision):
