@@ -1027,6 +1027,7 @@ void Ens::create(Ctx* c, const Mesh* m, const Problem& prob, int member_pad)
     stepping.alloc(bg, (size_t)MB * 4);
     cs.stepping = stepping.as<int>();
     h_member_step.assign(MB, 0);
+    used.assign(MB, 0);
     h_stepping.assign(MB, 0);
     h_status.assign(MB, 0);
     {

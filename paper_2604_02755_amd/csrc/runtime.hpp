@@ -238,6 +238,7 @@ struct Ens {
     void run_iters(int kind, int k, bool check);  // check: with the flags' copy to the mailbox
     int wait_any_active();
     int iterate(int kind, int guess, int limit);
+    std::vector<char> used;  // serving: slots that a request has taken since the ensemble was created
     int pcg_guess = 0, inner_guess = 0;  // most iterations of a member in the last such solve
     bool use_graph = true;
     // captured CG chunks, by (kind, compact-row width, iterations); the Chebyshev solve

@@ -129,7 +129,10 @@ void Ens::reset_member(int m)
                              vI_all.as<double>() + (size_t)m * ns_steps * 3, P.dt);
     for (DevBuf* bb : {&u, &v, &a, &q, &du, &du2, &du3}) launch_zero_member(s, bb->as<double>(), ndof, MB, m);
     launch_fill(s, vmax.as<double>() + (size_t)m * std::max(1, mesh->nrecv), 0.0, std::max(1, mesh->nrecv));
-    launch_theta_reset_member(s, theta.p, ne_pad, P.ns, MB, m);
+    // (a slot's law state is as created until its first request steps: the reset is
+    // 560 us with 98,304 elements and 8 slots)
+    if (used[m]) launch_theta_reset_member(s, theta.p, ne_pad, P.ns, MB, m);
+    used[m] = 1;
     launch_law_init(s, dm, MB, nm, mat.as<double>(), P.nl, P.ns, dirs.as<double>(), w.as<double>(), D64.as<double>(),
                     D32.as<float>(), D16.as<uint32_t>(), h.as<double>(), m, d16_mean);
     int zero = 0;
