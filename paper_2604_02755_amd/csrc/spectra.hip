@@ -26,11 +26,13 @@ namespace nlth {
 // states at the parts' ends follow from these and the same update over a
 // part's length, and the part is run again from its state for the peaks.
 //
-// Bound by the chain of a step, which few wavefronts leave open: the samples are
-// loaded sixteen ahead (a load a step, waited for, took 477 cycles a step).
-// Kernel: 867 series of 1,500 samples, 40 periods (542 wavefronts), 298 -> 88 us
-// with one part, 83 with four; calls: 12 series of 2,000 samples, 20 periods,
-// 362 -> 84 us (16 parts; 103 with P = 1 in the larger cases and waited loads).
+// Bound by the chain of a step and by the vector loads: the samples are loaded
+// sixteen ahead (a load a step, waited for, took 477 cycles a step), and where a
+// wavefront's lanes cover at most four records (22 periods and more) they load
+// sixteen samples of each at once and read them back from LDS.  Kernel: 867 series
+// of 1,500 samples, 40 periods (542 wavefronts), 298 -> 88 us with one part, 83 with
+// four, 58 through LDS; calls: 12 series of 2,000 samples, 20 periods, 362 -> 84 us
+// (16 parts).
 constexpr int kSpecAhead = 16;
 
 struct Osc {
@@ -44,10 +46,13 @@ __device__ __forceinline__ Osc osc_step(double w, double h, double t)
 }
 
 // samples n0 .. n1 of record v from (y, xd) just before sample n0, whose
-// predecessors' velocity and offset are vp and op; PEAK: px, pv the largest |x|, |x'|
+// predecessors' velocity and offset are vp and op; PEAK: px, pv the largest |x|, |x'|.
+// tile (64 doubles of LDS of the wavefront, or NULL): the lane's record is the ts-th of
+// at most four of the wavefront, and the lane loads samples of record tv into it
 template <bool PEAK>
 __device__ __forceinline__ void osc_run(const double* __restrict__ v, int n0, int n1, const Osc& a, double scale,
-                                        double& x, double& xd, double& px, double& pv)
+                                        double& x, double& xd, double& px, double& pv, const double* __restrict__ tv,
+                                        double* tile, int ts)
 {
     // y = x + off; the offset of the last step is carried in `off`
     double vp = n0 > 0 ? v[n0 - 1] : 0.0, off = 0.0, y = x;
@@ -65,10 +70,28 @@ __device__ __forceinline__ void osc_run(const double* __restrict__ v, int n0, in
         }
     };
     const int last = n1 - 1;
+    int n = n0;
+    if (tile) {
+        // the lanes of at most four series: one load a tile, 16 samples of each
+        double nx = n0 < n1 ? tv[min(n0 + (int)(threadIdx.x & 15), last)] : 0.0;
+        for (; n + kSpecAhead <= n1; n += kSpecAhead) {
+            tile[threadIdx.x & 63] = nx;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            nx = tv[min(n + kSpecAhead + (int)(threadIdx.x & 15), last)];
+            double b[kSpecAhead];
+#pragma unroll
+            for (int k = 0; k < kSpecAhead; ++k) b[k] = tile[ts * kSpecAhead + k];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int k = 0; k < kSpecAhead; ++k) step(b[k]);
+        }
+        for (; n < n1; ++n) step(v[n]);
+        x = y - off;
+        return;
+    }
     double b[kSpecAhead];
 #pragma unroll
     for (int k = 0; k < kSpecAhead; ++k) b[k] = n0 < n1 ? v[min(n0 + k, last)] : 0.0;
-    int n = n0;
     for (; n + kSpecAhead <= n1; n += kSpecAhead) {
         double c[kSpecAhead];
 #pragma unroll
@@ -97,10 +120,16 @@ __global__ __launch_bounds__(64 * P) void k_response_spectra(const double* __res
     const double scale = 1.0 / (dt * w * w);
     const double* v = vel + (size_t)sr * nt;
     double x = 0.0, xd = 0.0, px = 0.0, pv = 0.0;
+    __shared__ double tiles[P][64];
+    const int sr0 = (int)(min(blockIdx.x * 64l, (long)ns * np - 1) / np);
+    const int srl = (int)(min(blockIdx.x * 64l + 63, (long)ns * np - 1) / np);
+    double* tile = srl - sr0 < 4 ? tiles[part] : nullptr;
+    const double* tv = vel + (size_t)min(sr0 + (lane >> 4), srl) * nt;
+    const int ts = sr - sr0;
     const int len = (nt + P - 1) / P, n0 = min(part * len, nt), n1 = min(n0 + len, nt);
     if constexpr (P > 1) {
         __shared__ double end[P][2][64], peak[P][2][64];
-        if (part < P - 1) osc_run<false>(v, n0, n1, a, scale, x, xd, px, pv);
+        if (part < P - 1) osc_run<false>(v, n0, n1, a, scale, x, xd, px, pv, tv, tile, ts);
         end[part][0][lane] = x;
         end[part][1][lane] = xd;
         __syncthreads();
@@ -111,7 +140,7 @@ __global__ __launch_bounds__(64 * P) void k_response_spectra(const double* __res
             xd = fma(l.a21, x, fma(l.a22, xd, end[c][1][lane]));
             x = x1;
         }
-        osc_run<true>(v, n0, n1, a, scale, x, xd, px, pv);
+        osc_run<true>(v, n0, n1, a, scale, x, xd, px, pv, tv, tile, ts);
         peak[part][0][lane] = px;
         peak[part][1][lane] = pv;
         __syncthreads();
@@ -121,7 +150,7 @@ __global__ __launch_bounds__(64 * P) void k_response_spectra(const double* __res
             pv = fmax(pv, peak[c][1][lane]);
         }
     } else {
-        osc_run<true>(v, n0, n1, a, scale, x, xd, px, pv);
+        osc_run<true>(v, n0, n1, a, scale, x, xd, px, pv, tv, tile, ts);
     }
     if (t < (long)ns * np) out[t] = kind == 0 ? pv : w * px;
 }
