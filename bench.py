@@ -542,7 +542,7 @@ def main():
                     "hbm_gbs_algorithmic": round(gbs, 1), "fp32_tflops": round(tfl, 2),
                     "fp32_nonpacked_peak": FP32_PEAK_TFLOPS / 2,
                     "fp32_nonpacked_frac": round(tfl / (FP32_PEAK_TFLOPS / 2), 4),
-                    "gather_kernel": "nlth::k_gather<float, true, true> (node sums of the cluster rows, dot fused)",
+                    "gather_kernel": "nlth::k_gather<float, true> (node sums of the cluster rows, dot fused)",
                     "gather_avg_launch_us": round(sp["ms_gather32"] / max(1, sp["n_gather32"]) * 1e3, 2),
                     "operator_avg_us": round((sp["ms_ebe32"] + sp["ms_gather32"]) / n_app * 1e3, 2)}
 

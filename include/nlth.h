@@ -269,9 +269,9 @@ int nlth_ens_stats(const nlth_ens* ens, nlth_stats* st);
  * shapes do not change results (converged members are frozen on the device);
  * the inner policy changes the iteration path only within the outer FP64
  * tolerance.  scatter picks how element forces reach the nodes (the default
- * depends on the member slots): per-element outputs summed per node in a
- * fixed order; clusters of consecutive elements summed in LDS in a fixed
- * order, then per node; or one launch per element colour adding into the
+ * depends on the member slots): clusters of consecutive elements summed in LDS in a
+ * fixed order, then per node, with lanes for elements and members (fewer than 64
+ * slots) or for 64 members of an element; or one launch per element colour adding into the
  * nodal vector.
  * Out-of-range fields (ebe_block not 0/64/128/256, check_every outside
  * 0..64, inner_maxit outside 0..100000, inner_tol outside [0, 1), cluster_blocks
@@ -289,8 +289,8 @@ typedef struct {
     int32_t use_graph;
     int32_t inner_maxit;
     double inner_tol;
-    int32_t scatter;           /* -1 keep; 0 element outputs + node gather (fewer than 64 member
-                                  slots); 1 one launch per colour; 2 element clusters + node gather
+    int32_t scatter;           /* -1 keep; 0 element clusters of few slots + node sums (fewer than 64
+                                  member slots); 1 one launch per colour; 2 element clusters + node gather
                                   (64..256 slots, a multiple of 64) */
     int32_t cluster_blocks;    /* 0 keep; 2, 3 or 4 co-resident FP32 cluster blocks per CU (default 3) */
     int32_t inner_method;      /* -1 keep; 0 inner CG (default); 1 Chebyshev iteration of degree

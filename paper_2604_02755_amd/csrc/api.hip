@@ -1609,8 +1609,8 @@ void Ens::cheb_solve()
 // sums are few.  With 1 and 2 slots the p update joins the next iteration's operator
 // (p alternating with the operator's result vector, which these paths do not
 // use) and only the last iteration has a launch for it, while the operator's blocks
-// are at most two a CU and its time is a chain: 1,152 elements 8.5 + 4.1 -> 10.3 us,
-// 12,288 9.0 + 4.9 -> 12.0 (on 55,000 elements in FP32 the operator reads z and p
+// are at most two a CU and its time is a chain: 360 elements 8.5 + 4.1 -> 10.3 us,
+// 12,288 9.0 + 4.9 -> 12.0 (on 98,304 elements in FP32 the operator reads z and p
 // of 1.9 nodes a node and took longer than the two).
 template <typename T>
 void Ens::few_slot_iters(int k)

@@ -1408,8 +1408,7 @@ void launch_zero_member(hipStream_t s, double* p, long rows, int MB, int m)
 // The law is bound by issue (about 1,500 cycles of a SIMD a spring and wavefront:
 // two springs ahead or a third wavefront a SIMD change nothing), so this pays only
 // while SIMDs idle: 150 springs on 12,288 elements (768 wavefronts) 300 -> 249 us,
-// on 1,152 (72) 272 -> 70 with 8 parts,
-// on 331,776 elements 3.8 -> 5.0 ms.
+// on 360 (23) 272 -> 70 with 8 parts, on 331,776 elements 3.8 -> 5.0 ms.
 constexpr int kLawLdsSprings = 16;
 constexpr long kLawPartLanes = 1l << 16;  // a wavefront a SIMD without parts
 constexpr long kLawManyParts = 1l << 14;

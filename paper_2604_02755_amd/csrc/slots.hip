@@ -328,10 +328,10 @@ __global__ __launch_bounds__(512) void k_op_p(DevMesh M, int MB, int nm, int ncb
 }
 
 // One member, D and h in input order, the material table a kernel argument (a
-// launch that put it in memory first took 3 us of a call's 30 on 1,152 elements).
+// launch that put it in memory first took 3 us of a call's 30 on 720 elements).
 // The block's D rows are staged in LDS, where `out` comes after them: a lane
 // reading its own row of 672 bytes fetched every line sixteen times past an L1 that
-// does not hold 64 rows (55,000 elements: 36.5 us, staged 25.0).
+// does not hold 64 rows (58,080 elements: 36.5 us, staged 25.0).
 template <int MODE>
 __global__ __launch_bounds__(512) void k_op_input64(DevMesh M, int ncb, int nbb, const double* __restrict__ D,
                                                    const int* __restrict__ order, const double* __restrict__ h,
@@ -490,8 +490,9 @@ void launch_ebe32_ctail(hipStream_t s, const DevMesh& M, int G, const int* tl, c
 // slots.  DK 4: one bfloat16 D per element.  Bound by the FP64 D on many
 // members, which both halves read (all six entries at once would take 60 doubles
 // of LDS a lane and a rows buffer of twice the size).
-// Against one launch per element colour adding to the nodes:
-// DIAGFIG
+// Against one launch per element colour adding to the nodes, with the fill, the
+// dashpot and the inversion: 12,288 elements, FP64, 1 slot 31 x 22 -> 36 us; 221,184
+// elements, element-mean D, 64 slots 33 x 129 us -> 2 x 1,330 and the node sums.
 template <int DK, int LG>
 __global__ __launch_bounds__(256) void k_diag_slots(DevMesh M, int MB, int nm, int ncb, int half,
                                                    const void* __restrict__ Dv, const double* __restrict__ h,
