@@ -26,6 +26,7 @@ enum OpMode { OP_A = 0, OP_K = 1, OP_M = 2, OP_RHS = 3 };
 constexpr int kMaxPartialBlocks = 2048;   // blocks of a fused vector kernel's partial sums
 constexpr int kGatherBlocks = 16384;      // blocks of a node gather with partial sums
 constexpr int kDashpotBlocks = 1024;      // most boundary blocks of an operator launch
+constexpr int kBoundaryAtEnd = 4096;      // cluster blocks up to which the boundary blocks come last
 constexpr int kClusterNodes = 48;         // most distinct nodes of an element cluster
 constexpr int kClusterElems = 16;         // most elements of an element cluster
 constexpr int kWideNodes = 240;           // the same of a wide cluster, which
