@@ -34,6 +34,7 @@ constexpr int kWideElems = 64;            // ensembles of up to
 constexpr uint16_t kOwnerRow = 0x8000;    // in cl_lptr: the row is its node's first
 constexpr int kWideSlots = 8;             // member slots use
 constexpr int kLagBlocks = 512;           // most operator blocks of an iteration whose p update joins the next operator
+constexpr int kLagThreads = 128;          // threads of those blocks: what sums the beta stage with 1 and 2 slots
 // most partial sums that each block of the next kernel reads itself, and how many
 // they are folded to beyond that with 16 and more slots
 constexpr int kFuseSums = 3072;

@@ -74,6 +74,7 @@ struct SlotShape {
     // (331,776 elements, FP32, 1 slot: 64 threads 39 us, 128 33, 256 46;
     // 98,304 elements, 16 slots: 192 threads 92 us, 256 86, 320 146)
     static constexpr int THREADS = LG == 0 ? 128 : (LG < 4 ? 64 << LG : 16 << LG);
+    static_assert(LG > 1 || (THREADS == kLagThreads && (ELEMS << LG) <= THREADS), "k_op_p and k_pz sum in one order");
 };
 
 // DK 2, doubles of a staged D row in LDS: 16 bytes more than the row, so the lanes'
@@ -155,7 +156,7 @@ __device__ __forceinline__ void op_slots_block(const DevMesh& M, int MB, int nm,
         }
         const BetaState<INNER> bs(pu->sg.cs, MB, nm);
         double S2[2];
-        member_sums<2, S::THREADS>(pu->sg.partial, pu->sg.nblk, MB, ps, S2);
+        member_sums<2, kLagThreads>(pu->sg.partial, pu->sg.nblk, MB, ps, S2);
         if (t < MB) {
             bool on;
             pb[t] = fused_beta<INNER>(pu->sg, t, S2, bs.upd, bs.rz_prev, bs.it, bs.ref, MB, blk == 0, on);
