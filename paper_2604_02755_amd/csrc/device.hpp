@@ -546,19 +546,20 @@ __device__ __forceinline__ void mean_grad_products(int n, const double gL[4][3],
 }
 
 // Per-member sums of ND x nblk partial rows of MB <= 32 slots by the first NT
-// threads of a block (valid in threads t < MB).  The order depends on NT and MB
+// threads of a block of TB (valid in threads t < MB).  The order depends on NT and MB
 // alone, so every kernel that forms the same stage with the same NT gets the same
 // bits.  Eight loads of a thread in flight at a time.
-template <int ND, int NT = 256>
+template <int ND, int NT = 256, int TB = NT>
 __device__ __forceinline__ void member_sums(const double* __restrict__ partial, int nblk, int MB, double* __restrict__ sh,
                                             double S[ND])
 {
     constexpr int nw = NT / 64;
     const int t = threadIdx.x, m = t % MB, rpb = NT / MB;
+    const bool sums = TB == NT || t < NT;
     double a[ND];
 #pragma unroll
     for (int k = 0; k < ND; ++k) a[k] = 0.0;
-    for (int b = t < NT ? t / MB : nblk; b < nblk; b += 8 * rpb) {
+    for (int b = sums ? t / MB : nblk; b < nblk; b += 8 * rpb) {
         double v[ND][8];
 #pragma unroll
         for (int k = 0; k < ND; ++k)
@@ -573,7 +574,7 @@ __device__ __forceinline__ void member_sums(const double* __restrict__ partial, 
 #pragma unroll
     for (int k = 0; k < ND; ++k) {
         for (int o = 32; o >= MB; o >>= 1) a[k] += __shfl_xor(a[k], o);
-        if (t < NT && (t & 63) < MB) sh[(k * nw + (t >> 6)) * MB + (t & 63)] = a[k];
+        if (sums && (t & 63) < MB) sh[(k * nw + (t >> 6)) * MB + (t & 63)] = a[k];
     }
     __syncthreads();
 #pragma unroll

@@ -537,7 +537,7 @@ __global__ __launch_bounds__(256) void k_pz(long nrows, int MB, int nm, T* __res
         bool on;
         // 1 and 2 slots: the order of the operator that forms this stage on the other
         // iterations of a chunk (k_op_p), so that results do not depend on where chunks end
-        member_sums<2, VEC == 1 ? kLagThreads : 256>(sg.partial, sg.nblk, MB, sh, S);
+        member_sums<2, VEC == 1 ? kLagThreads : 256, 256>(sg.partial, sg.nblk, MB, sh, S);
         if (t < MB) sb[t] = fused_beta<INNER>(sg, t, S, bs.upd, bs.rz_prev, bs.it, bs.ref, MB, blockIdx.x == 0, on);
         __syncthreads();
 #pragma unroll
