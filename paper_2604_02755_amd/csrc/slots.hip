@@ -277,6 +277,8 @@ __device__ __forceinline__ void op_slots_block(const DevMesh& M, int MB, int nm,
                 gL, vol, sm, sk, cv, Dp, rs, 0u,
                 [&](int n, int cc, int v) { return (v ? x2 : x1)[nb[n] + (size_t)cc * MB]; }, f);
         }
+        // the forces go where other lanes' D rows are
+        if constexpr (DIN) __syncthreads();
         if (on) {
 #pragma unroll
             for (int n = 0; n < 10; ++n)
