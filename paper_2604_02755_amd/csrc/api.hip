@@ -14,7 +14,6 @@
 #include <string.h>
 
 #include <algorithm>
-#include <climits>
 #include <chrono>
 #include <cstdio>
 #include <unordered_map>
@@ -1234,14 +1233,17 @@ int Ens::wait_any_active()
 }
 
 // Iterations of kind 0 (inner) or 1 (FP64 PCG) until no member iterates, or
-// `limit`; returns the most that a member took.  A check of the flags is a round
-// trip to the host of 25 to 45 us, two iterations of a small mesh: the first check
-// comes when as many iterations have been issued as the last such solve took
-// (members that converge earlier are frozen, so this changes no result), in
-// graphs of 32, check_every and a few.
-int Ens::iterate(int kind, int guess, int limit)
+// `limit`.  A check of the flags is a round trip to the host of 25 to 45 us, two
+// iterations of a small mesh: the first check comes when as many iterations have
+// been issued as the solve before took (members that converge earlier are frozen,
+// so this changes no result), in graphs of 32, check_every and a few.  At most
+// kGuessSlack more than the solve before that one took, and not what a member
+// took that stopped at the limit: a frozen iteration still costs its launches, and
+// one hard solve would make the next one as long.
+void Ens::iterate(int kind, Took& took, int limit)
 {
     const int few = std::min(4, check_every);
+    const int guess = took.before > 0 ? std::min(took.last, took.before + kGuessSlack) : took.last;
     int n = guess > 0 ? guess : check_every, done = 0;
     for (;;) {
         n = std::min(n, limit - done);
@@ -1256,8 +1258,9 @@ int Ens::iterate(int kind, int guess, int limit)
         n = kind == 0 ? few : check_every;
     }
     int most = 0;
-    for (int m = 0; m < nm; ++m) most = std::max(most, h_flags[MB + m]);
-    return most;
+    for (int m = 0; m < nm; ++m)
+        if (kind == 0 || h_flags[MB + m] < limit) most = std::max(most, h_flags[MB + m]);
+    took = Took{most, took.last};
 }
 
 // tl: the partials are rows of G lanes, the listed members'
@@ -1287,8 +1290,8 @@ void Ens::solve_pcg()
     fin(FIN_START, 3, nblk, tol2, P.cg_maxit);
     launch_zero_if_b0(s, n, MB, nm, x, cs.bb, st);
     if (MB < 64) {
-        if (pcg_guess == 0 && !read_any_active(act)) return;
-        pcg_guess = iterate(1, pcg_guess, INT_MAX);
+        if (pcg_took.last == 0 && !read_any_active(act)) return;
+        iterate(1, pcg_took, P.cg_maxit);
         return;
     }
     if (!read_any_active(act)) return;
@@ -1424,7 +1427,7 @@ void Ens::inner_solve()
         launch_inner_start(s, mesh->nn, MB, nm, r.as<double>(), pinv32.as<float>(), ir.as<float>(), iz.as<float>(),
                            ip.as<float>(), iw.as<float>(), iAp.as<float>(), act, pd, &nblk);
     fin(FIN_IN_START, 2, nblk, tol2, P.inner_maxit);
-    inner_guess = iterate(0, inner_guess, P.inner_maxit);
+    iterate(0, inner_took, P.inner_maxit);
     // the listed members' result back to the full rows (the others are not
     // outer-active: the output step writes zero for them); with the outer
     // iteration on the compact rows it stays there

@@ -237,9 +237,11 @@ struct Ens {
     void pcg_iter();
     void run_iters(int kind, int k, bool check);  // check: with the flags' copy to the mailbox
     int wait_any_active();
-    int iterate(int kind, int guess, int limit);
+    struct Took { int last = 0, before = 0; };  // most iterations of a member in the last two such solves
+    static constexpr int kGuessSlack = 32;
+    void iterate(int kind, Took& took, int limit);
     std::vector<char> used;  // serving: slots that a request has taken since the ensemble was created
-    int pcg_guess = 0, inner_guess = 0;  // most iterations of a member in the last such solve
+    Took pcg_took, inner_took;
     bool use_graph = true;
     // captured CG chunks, by (kind, compact-row width, iterations); the Chebyshev solve
     std::map<int, hipGraphExec_t> g_chunks;
