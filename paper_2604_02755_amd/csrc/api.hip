@@ -1239,11 +1239,16 @@ int Ens::wait_any_active()
 // so this changes no result), in graphs of 32, check_every and a few.  At most
 // kGuessSlack more than the solve before that one took, and not what a member
 // took that stopped at the limit: a frozen iteration still costs its launches, and
-// one hard solve would make the next one as long.
+// one hard solve would make the next one as long.  With 64 and more slots an
+// iteration is long against a check: the first one comes after check_every, the
+// next after a few each (inner solves to a tolerance, 64 members, 98,304 elements:
+// guessed 107.5 ms a step, so 106.9, every check_every 108.4; 720 elements 4.01, 4.01,
+// 4.44).
 void Ens::iterate(int kind, Took& took, int limit)
 {
     const int few = std::min(4, check_every);
-    const int guess = took.before > 0 ? std::min(took.last, took.before + kGuessSlack) : took.last;
+    int guess = took.before > 0 ? std::min(took.last, took.before + kGuessSlack) : took.last;
+    if (MB >= 64) guess = 0;
     int n = guess > 0 ? guess : check_every, done = 0;
     for (;;) {
         n = std::min(n, limit - done);
