@@ -777,6 +777,15 @@ static void rayleigh_fit(double fl, double fh, double* a, double* b)
 
 void rayleigh_coefficients(double f_lo, double f_hi, double* a, double* b) { rayleigh_fit(f_lo, f_hi, a, b); }
 
+// rows of an ensemble's partial-sum buffer, without the fold's: of the vector
+// kernels, or of the operator (a row per cluster and boundary block, the latter
+// rounded up to a multiple of 8)
+static size_t partial_rows(const Mesh& m, int MB)
+{
+    return std::max<size_t>(kPartialRows, MB <= 256 ? (size_t)m.clusters(MB).n + 16 + kDashpotBlocks : 0);
+}
+static size_t partial_bytes(const Mesh& m, int MB) { return (partial_rows(m, MB) + 3 * kFoldBlocks) * MB * 8; }
+
 int64_t ensemble_bytes(const Mesh& m, const Problem& p, int MB, bool paged)
 {
     const int64_t ndof = 3L * m.nn;
@@ -793,6 +802,7 @@ int64_t ensemble_bytes(const Mesh& m, const Problem& p, int MB, bool paged)
                  (p.inner_dtype == NLTH_INNER_FP32 ? 84 : (p.inner_dtype == NLTH_INNER_BF16_MEAN ? 11 : 44)) * MB;
     bytes += (int64_t)m.ne * MB * 8;                        // h
     if (MB <= 256) bytes += (m.clusters(MB).rows + m.nbn) * 3 * MB * 8;  // cluster and dashpot rows
+    bytes += (int64_t)partial_bytes(m, MB);
     bytes += (int64_t)p.n_steps * std::max(1, m.nrecv) * 3 * MB * 8;  // receiver history
     bytes += (int64_t)p.n_steps * 3 * MB * 8 * 2;           // acc, vI
     if (!paged) bytes += (int64_t)m.ne * 4 * p.ns * MB * theta_bytes(p.depth);
@@ -949,7 +959,10 @@ void Ens::create(Ctx* c, const Mesh* m, const Problem& prob, int member_pad)
         std::lock_guard<std::mutex> g(bg->mu);
         avail = bg->limit > 0 ? bg->limit - bg->used : INT64_MAX;
     }
-    const int64_t reserve = (int64_t)P.n_steps * std::max(1, m->nrecv) * 3 * MB * 8 * 2 + (64 << 20) + reserve_extra;
+    // what is allocated after it: the records, and 64 MiB for the rest, more where
+    // the partial sums would leave less than half of that
+    const int64_t rest = std::max<int64_t>(64 << 20, (int64_t)partial_bytes(*m, MB) + (32 << 20));
+    const int64_t reserve = (int64_t)P.n_steps * std::max(1, m->nrecv) * 3 * MB * 8 * 2 + rest + reserve_extra;
     paged = force_paged || (int64_t)state_bytes + reserve > avail;
     if (!paged) {
         theta.alloc(bg, state_bytes);
@@ -1000,11 +1013,8 @@ void Ens::create(Ctx* c, const Mesh* m, const Problem& prob, int member_pad)
     launch_fill(s, vmax.as<double>(), 0.0, (long)MB * std::max(1, m->nrecv));
     iters_dev.alloc(bg, (size_t)MB * ns_steps * 2 * 4);
     NLTH_HIP(hipMemsetAsync(iters_dev.p, 0, iters_dev.bytes, s));
-    // partial sums: of the vector kernels, or of the operator (a row per cluster
-    // and boundary block, the latter rounded up to a multiple of 8); then the fold
-    const size_t prows = std::max<size_t>(kPartialRows, MB <= 256 ? (size_t)m->clusters(MB).n + 16 + kDashpotBlocks : 0);
-    partial.alloc(bg, (prows + 3 * kFoldBlocks) * MB * 8);
-    fold = partial.as<double>() + prows * MB;
+    partial.alloc(bg, partial_bytes(*m, MB));
+    fold = partial.as<double>() + partial_rows(*m, MB) * MB;
     // CG scalars: 12 double arrays and 9 int arrays of MB
     scal.alloc(bg, (size_t)MB * (12 * 8 + 9 * 4) + 64);
     NLTH_HIP(hipMemsetAsync(scal.p, 0, scal.bytes, s));
