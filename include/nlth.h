@@ -352,7 +352,10 @@ int nlth_release(nlth_ctx* ctx, uint64_t ticket);
  * at rest and is advanced exactly step by step; out: [n_series][n_periods],
  * kind NLTH_SPEC_VELOCITY max_n |x'_n| (relative velocity) or
  * NLTH_SPEC_PSEUDO_VELOCITY w max_n |x_n|.  Host pointers, caller-owned,
- * read or written during the call (synchronous).  NLTH_EINVAL for NULL
+ * read or written during the call (synchronous).  The context keeps the
+ * call's device workspace (records, periods and spectra, up to 64 MiB) for the
+ * next one where hbm_budget holds it, and gives it back when it creates a mesh
+ * or an ensemble.  NLTH_EINVAL for NULL
  * pointers, empty sizes, dt <= 0, h outside [0, 1), a period <= 0 or an
  * unknown kind. */
 #define NLTH_SPEC_VELOCITY 0

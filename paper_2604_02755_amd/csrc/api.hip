@@ -866,6 +866,7 @@ void Ens::create(Ctx* c, const Mesh* m, const Problem& prob, int member_pad)
     ctx = c;
     mesh = m;
     P = prob;
+    c->spec_ws.release();
     if (P.nl <= m->max_layer) throw Error{NLTH_EINVAL, "problem: mesh uses a layer id >= n_layers"};
     nm = P.nm;
     MB = member_pad > 0 ? member_pad : pad_members(nm);
@@ -1363,6 +1364,7 @@ bool Ens::alloc_tail64()
         off[i] = tot;
         tot += (sz[i] + 255) / 256 * 256;
     }
+    ctx->spec_ws.release();
     try {
         tail64_mem.alloc(&ctx->budget, tot);
         if (!tlist.p) tlist.alloc(&ctx->budget, (size_t)(1 + MB) * 4);
@@ -1471,6 +1473,7 @@ void Ens::update_tail()
             off[i] = tot;
             tot += (sz[i] + 255) / 256 * 256;
         }
+        ctx->spec_ws.release();
         try {
             tail_mem.alloc(&ctx->budget, tot);
             tlist.alloc(&ctx->budget, (size_t)(1 + MB) * 4);
@@ -2250,6 +2253,7 @@ int nlth_mesh_create(nlth_ctx* ctx, const nlth_mesh_desc* d, nlth_mesh** out)
     *out = nullptr;
     std::lock_guard<std::mutex> g(ctx->mu);
     if (!ctx->host_only) NLTH_HIP(hipSetDevice(ctx->device));
+    ctx->spec_ws.release();
     std::unique_ptr<nlth_mesh> m(new nlth_mesh());
     build_mesh(ctx, d, *m);
     ctx->live_meshes++;
@@ -2304,6 +2308,7 @@ int nlth_ens_create(nlth_ctx* ctx, const nlth_mesh* mesh, const nlth_problem* pr
     if (ctx->host_only) throw Error{NLTH_EDEVICE, "host-only context cannot run solves"};
     std::lock_guard<std::mutex> g(ctx->mu);
     NLTH_HIP(hipSetDevice(ctx->device));
+    ctx->spec_ws.release();
     std::unique_ptr<nlth_ens> e(new nlth_ens());
     int64_t avail;
     {
@@ -2537,12 +2542,20 @@ int nlth_response_spectra(nlth_ctx* ctx, const double* vel, int32_t n_series, in
     NLTH_HIP(hipSetDevice(ctx->device));
     const size_t nv = (size_t)n_series * n_steps, no = (size_t)n_series * n_periods;
     // records, periods and spectra in one workspace, which the context keeps while
-    // it is small (allocating and freeing 10 MB takes 27 us of a call's 400)
+    // it is small and its budget holds it (allocating and freeing 10 MB takes 27 us
+    // of a call's 400); whatever allocates next on the context gives it back
     const size_t o1 = (nv * 8 + 255) / 256 * 256, o2 = o1 + ((size_t)n_periods * 8 + 255) / 256 * 256;
     const size_t need = o2 + no * 8;
     DevBuf own;
-    DevBuf& ws = need <= kSpecKeep ? ctx->spec_ws : own;
-    if (ws.bytes < need) ws.alloc(nullptr, need);
+    if (need <= kSpecKeep && ctx->spec_ws.bytes < need) {
+        try {
+            ctx->spec_ws.alloc(&ctx->budget, need);
+        } catch (const Error&) {  // (nothing held then)
+        }
+    }
+    const bool kept = ctx->spec_ws.bytes >= need;
+    if (!kept) own.alloc(nullptr, need);
+    const DevBuf& ws = kept ? ctx->spec_ws : own;
     double *dv = ws.as<double>(), *dp = (double*)((char*)ws.p + o1), *dout = (double*)((char*)ws.p + o2);
     hipStream_t s = ctx->stream;
     NLTH_HIP(hipMemcpyAsync(dv, vel, nv * 8, hipMemcpyHostToDevice, s));

@@ -51,7 +51,7 @@ struct DevBuf {
     template <typename T> T* as() const { return (T*)p; }
 };
 
-constexpr size_t kSpecKeep = 64u << 20;
+constexpr size_t kSpecKeep = 64u << 20;  // largest workspace of the response spectra that a context keeps
 
 struct Ctx;
 
@@ -276,7 +276,8 @@ struct Ctx {
     bool own_stream = false;
     Budget budget;
     std::mutex mu;  // serialises API calls on the context
-    DevBuf spec_ws;  // workspace of the response spectra (under mu, up to kSpecKeep)
+    DevBuf spec_ws;  // workspace of the response spectra, kept between calls (under mu): up to kSpecKeep, charged
+                     // to the budget, released before anything else is allocated
     int paging_sets = 2;  // member sets of a paged ensemble (1 or 2)
     std::string last_error;
     int log_level = 0;

@@ -35,3 +35,51 @@ def test_estimate_counts_the_partial_sums(nlth_mod):
     assert st["paged"] and st["member_sets"] == 2
     assert np.abs(ref["vel"]).max() > 0
     assert np.linalg.norm(out["vel"] - ref["vel"]) < 1e-7 * np.linalg.norm(ref["vel"])
+
+
+def test_spectra_workspace_stays_within_the_budget(nlth_mod):
+    """40 MB of records: served whatever the budget, kept afterwards only where the budget
+    holds them, and given back to an ensemble that needs the room to be resident."""
+    import torch
+    rng = np.random.default_rng(6)
+    vel, periods = rng.standard_normal((2500, 2000)).cumsum(axis=1), np.geomspace(0.1, 5.0, 8)
+    mesh = I.box_mesh(8, 8, 6, 1.0, I.two_layer(2.0), 4)
+    prob = I.make_problem(8, I.CFG0_LAYERS["vs"], I.CFG0_LAYERS["rho"], n_springs=12, n_steps=1)
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    ref, held = None, {}
+    for budget in (8 << 20, 0):
+        ctx = nlth_mod.Context(0, hbm_budget=budget, use_torch_stream=False)
+        try:
+            ctx.response_spectra(vel[:1], 1e-3, periods)  # (what the first kernel of its kind loads)
+            before = free()
+            print("spectra budget case", budget, flush=True)
+            got = ctx.response_spectra(vel, 1e-3, periods)
+            held[budget] = before - free()
+            ref = got if ref is None else ref
+            assert np.array_equal(got, ref) and np.abs(ref).max() > 0
+        finally:
+            ctx.close()
+    print("held", held, flush=True)
+    assert held[8 << 20] < 8 << 20
+    ctx = nlth_mod.Context(0, use_torch_stream=False)
+    try:
+        ens = ctx.ensemble(ctx.mesh(mesh), mesh, prob)
+        need = ens.stats()["device_bytes"]
+        ens.close()
+    finally:
+        ctx.close()
+    # the least that keeps the state resident: 64 MiB beside it
+    ctx = nlth_mod.Context(0, hbm_budget=need + (64 << 20), use_torch_stream=False)
+    try:
+        mh = ctx.mesh(mesh)
+        ctx.response_spectra(vel, 1e-3, periods)
+        ens = ctx.ensemble(mh, mesh, prob)
+        st = ens.stats()
+        ens.close()
+        assert not st["paged"] and st["device_bytes"] == need
+    finally:
+        ctx.close()
