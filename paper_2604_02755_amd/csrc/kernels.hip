@@ -149,8 +149,11 @@ __global__ __launch_bounds__(256) void k_ebe(DevMesh M, int MB, int nm, int e0, 
 // co[(row * 3 + c) * MB + m] (row = the cluster's first row + local node) and
 // a gather over the node -> rows lists finishes the sum.  nbb blocks spread
 // over the grid write the dashpot rows of the boundary nodes (first in the grid
-// they held every CU for 30 us; a kernel of their own took 57 us of 1.2 ms with
-// 221,184 elements and 64 members).  With partial, the per-member sums of x1 .
+// they held every CU for 30 us); FP32 launches of more cluster blocks than
+// kBoundaryApart leave them to a launch of their own (element-mean D, with and
+// apart, us: 24,576 blocks (221,184 elements, 64 members) 649 and 665; 32,768 (147,456,
+// 128 members) 862 and 850; 36,864 (442,368, 64) 1,107 and 1,085; 65,536 (786,432, 64)
+// 1,987 and 1,920, with D per point 2,868 and 2,805).  With partial, the per-member sums of x1 .
 // (operator x1) over a block's rows go to partial[block * MB + m] (nbb + clusters
 // rows), so the node sums need not read x for a dot product.
 // LDS of a cluster block: the node rows, padded so that NB blocks share a CU
@@ -310,6 +313,17 @@ static int cluster_bnd_blocks(const DevMesh& M, int MB, double dcoef)
     return (int)((n < kDashpotBlocks ? n : kDashpotBlocks) + 7) / 8 * 8;
 }
 
+// The dashpot rows as a launch of their own, a pass a block.
+template <typename T>
+__global__ __launch_bounds__(256) void k_boundary_rows(DevMesh M, int MB, int nm, const double* __restrict__ mat,
+                                                      double dcoef, const T* __restrict__ x,
+                                                      const int* __restrict__ active, T* __restrict__ rows)
+{
+    const int m = threadIdx.x % MB;
+    boundary_rows<T>(M, MB, nm, mat, dcoef, [&](size_t n) { return x[n]; }, nullptr, !active || (m < nm && active[m]),
+                     rows, blockIdx.x, gridDim.x, 256);
+}
+
 // blocks of the FP32 cluster launches per CU (a tuning knob, per host thread)
 static thread_local int t_cluster_blocks = 3;
 void set_cluster_blocks(int b) { t_cluster_blocks = (b == 2 || b == 3 || b == 4) ? b : 3; }
@@ -319,8 +333,15 @@ static void cluster_launch(hipStream_t s, const DevMesh& M, int MB, int nm, cons
                            const double* mat, StepConst sc, const T* x1, const T* x2, T* co, const int* active,
                            double dcoef, const double* vI, double* partial, int* nblk)
 {
-    const int ngroups = MB / 64, nbb = cluster_bnd_blocks(M, MB, dcoef);
+    const int ngroups = MB / 64;
     const long g = ((long)M.ncl * ngroups + 7) / 8 * 8;
+    int nbb = cluster_bnd_blocks(M, MB, dcoef);
+    if (sizeof(T) == 4 && nbb && !partial && g > kBoundaryApart) {
+        const int npb = 256 / MB;
+        hipLaunchKernelGGL((k_boundary_rows<T>), dim3((M.nbn + npb - 1) / npb), dim3(256), 0, s, M, MB, nm, mat, dcoef, x1,
+                           active, co + (size_t)M.cl_rows * 3 * MB);
+        nbb = 0;
+    }
     if (nblk) *nblk = nbb + M.ncl;
     hipLaunchKernelGGL((k_ebe_cluster<T, DK, MODE, NB>), dim3((unsigned)(nbb + g)), dim3(256), 0, s, M, MB, nm, ngroups,
                        nbb, D, h, mat, sc, x1, x2, co, active, dcoef, vI, partial);

@@ -27,6 +27,7 @@ constexpr int kMaxPartialBlocks = 2048;   // blocks of a fused vector kernel's p
 constexpr int kGatherBlocks = 16384;      // blocks of a node gather with partial sums
 constexpr int kDashpotBlocks = 1024;      // most boundary blocks of an operator launch
 constexpr int kBoundaryAtEnd = 4096;      // cluster blocks up to which the boundary blocks come last
+constexpr int kBoundaryApart = 28672;     // cluster blocks above which FP32 dashpot rows are a launch of their own
 constexpr int kClusterNodes = 48;         // most distinct nodes of an element cluster
 constexpr int kClusterElems = 16;         // most elements of an element cluster
 constexpr int kWideNodes = 240;           // the same of a wide cluster, which
