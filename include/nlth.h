@@ -244,12 +244,13 @@ typedef struct {
     double ms_copy;            /* copy-stream busy time while paging */
     int32_t n_members, members_padded, n_colors;
     int64_t device_bytes, host_bytes;
-    double ms_gather32;        /* node gather of the inner operator's element outputs or cluster rows */
+    double ms_gather32;        /* node sums of the inner operator's rows (below 64 slots with the
+                                  CG's residual update, which forms them) */
     int64_t n_gather32;
     double cheb_lo_min;        /* Chebyshev inner bounds of the last step: smallest lower bound and */
     double cheb_hi_max;        /* largest upper bound over the members (0 without Chebyshev) */
     double ms_tail32;          /* operator on the compact rows of the last active members
-                                  (element kernel, node gather and dashpot): the inner FP32 one,
+                                  (element forces and dashpot to rows, p.Ap): the inner FP32 one,
                                   or with NLTH_FP64 the PCG's; the mixed path's outer FP64
                                   operator on those rows counts in ms_ebe64 */
     int64_t n_tail32;
@@ -381,10 +382,10 @@ int nlth_apply_operator(nlth_ctx* ctx, const nlth_mesh* mesh, const nlth_problem
  * nlth_apply_operator's FP64 application y = Op x for member 0 of `prob`, on
  * caller-owned DEVICE buffers, with no allocation.  D_ip [n_tets*4*21] (input
  * tet order, upper triangle of D row by row per point), h [n_tets] (NULL =
- * 0), x and y [3*n_nodes] (input node order).  Every intermediate lives in a
+ * 0), x and y [3*n_nodes] (input node order).  The intermediate lives in a
  * library-held device array of 64 MiB per device (reserved for the life of
- * the process), enough for meshes up to about 67,000 tets; larger meshes give
- * NLTH_EINVAL, as do more than 32 layers.  The work is queued on the
+ * the process); meshes above about 67,000 tets give NLTH_EINVAL, as do more
+ * than 32 layers.  The work is queued on the
  * context's compute stream and the call returns without waiting: y is ready
  * when that stream has drained.  Calls on one context are ordered by its
  * stream; calls through different contexts (streams) of one device share the

@@ -375,7 +375,6 @@ static void upload_clusters(Budget* b, const ClusterLists& L, Mesh::Clusters& C)
     upload(b, C.lists, L.lists);
     upload(b, C.lptr, L.lptr);
     C.max_elems = L.max_elems;
-    C.max_nodes = L.max_nodes;
     C.node_stride = L.node_stride;
     C.list_stride = L.list_stride;
     upload(b, C.cn_ptr, L.cn_ptr);
@@ -664,7 +663,6 @@ DevMesh Mesh::dev(int MB) const
     d.cl_lconn = c.lconn.as<uint32_t>();
     d.cl_rows = c.rows;
     d.cl_max_elems = c.max_elems;
-    d.cl_max_nodes = c.max_nodes;
     d.cl_node_stride = c.node_stride;
     d.cl_list_stride = c.list_stride;
     d.cl_nodes = c.nodes.as<int>();
@@ -1016,14 +1014,14 @@ void Ens::create(Ctx* c, const Mesh* m, const Problem& prob, int member_pad)
     NLTH_HIP(hipMemsetAsync(iters_dev.p, 0, iters_dev.bytes, s));
     partial.alloc(bg, partial_bytes(*m, MB));
     fold = partial.as<double>() + partial_rows(*m, MB) * MB;
-    // CG scalars: 12 double arrays and 9 int arrays of MB
-    scal.alloc(bg, (size_t)MB * (12 * 8 + 9 * 4) + 64);
+    // CG scalars: 11 double arrays and 8 int arrays of MB
+    scal.alloc(bg, (size_t)MB * (11 * 8 + 8 * 4) + 64);
     NLTH_HIP(hipMemsetAsync(scal.p, 0, scal.bytes, s));
     double* dptr = scal.as<double>();
     cs.bb = dptr; cs.rr = dptr + MB; cs.rz = dptr + 2 * MB; cs.alpha = dptr + 3 * MB; cs.beta = dptr + 4 * MB;
-    cs.pAp = dptr + 5 * MB; cs.rz_prev = dptr + 6 * MB; cs.irz = dptr + 8 * MB;
-    cs.ialpha = dptr + 9 * MB; cs.ibeta = dptr + 10 * MB; cs.ir0 = dptr + 11 * MB;
-    int* iptr = (int*)(dptr + 12 * MB);
+    cs.pAp = dptr + 5 * MB; cs.rz_prev = dptr + 6 * MB; cs.irz = dptr + 7 * MB;
+    cs.ialpha = dptr + 8 * MB; cs.ibeta = dptr + 9 * MB; cs.ir0 = dptr + 10 * MB;
+    int* iptr = (int*)(dptr + 11 * MB);
     cs.active = iptr; cs.iters = iptr + MB; cs.status = iptr + 2 * MB; cs.inner_active = iptr + 3 * MB;
     cs.inner_iters = iptr + 4 * MB; cs.inner_total = iptr + 5 * MB; cs.inner_upd = iptr + 6 * MB;
     cs.iters_prev = iptr + 7 * MB;

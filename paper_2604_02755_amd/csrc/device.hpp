@@ -186,10 +186,6 @@ __device__ __forceinline__ long d16m_index(long e, int q, int MB, int EB, int m)
 }
 constexpr int kEdgeOpp[6] = {5, 3, 4, 1, 2, 0};  // edge opposite each edge
 
-// DK: storage of D, 0 = T itself, 1 = bfloat16 pairs (uint32 words).
-// Forces of one element-member (element e, member m): the 30 nodal values of
-// the operator of MODE applied to x1 (and x2), written to f; nbase[n] is the
-// offset of node n's row in the nodal vectors.
 // scales of the element's mass and stiffness terms (and, for the right-hand
 // side, of v in the mass term) from its density, volume and damping; the
 // quotients by dt are formed on the host
@@ -212,8 +208,9 @@ __device__ __forceinline__ void op_scales(const StepConst& sc, double rho, doubl
 
 // Forces of one element-member: the 30 nodal values of the operator of MODE
 // applied to x(n, c, 0) (and x(n, c, 1) for the right-hand side), to f.  Dp: the
-// element's D (storage DK), entry (j, k) at Dp[(j * 21 + k) * rs + m] (DK 0; the
-// bfloat16 words likewise).
+// element's D in the storage DK: 0, T itself, entry (j, k) at Dp[(j * 21 + k) * rs + m];
+// 1, bfloat16 pairs, word (j, q) at Dp[(j * 11 + q) * rs + m]; 2, T in a row of 84;
+// 4, one D for the element in bfloat16 pairs, word q at Dp[q * rs + m].
 template <typename T, int DK, int MODE, class XF>
 __device__ __forceinline__ void element_forces(const T gL[4][3], T vol, T sm, T sk, T cv, const void* __restrict__ Dp,
                                                uint32_t rs, uint32_t m, XF x, T f[10][3])
@@ -348,10 +345,7 @@ __device__ __forceinline__ void element_forces(const T gL[4][3], T vol, T sm, T 
 #pragma unroll
             for (int q = 0; q < 6; ++q) eps[q] = (T)QB_ * S[q] + c1 * Ek[j][q];
             T d[22];
-            if constexpr (DK == 4) {
-#pragma unroll
-                for (int k = 0; k < 22; ++k) d[k] = dm[k];
-            } else if constexpr (DK == 0) {
+            if constexpr (DK == 0) {
                 const T* D = (const T*)Dp;
 #pragma unroll
                 for (int k = 0; k < 21; ++k)
@@ -395,6 +389,8 @@ __device__ __forceinline__ void element_forces(const T gL[4][3], T vol, T sm, T 
     }
 }
 
+// the same of element e and member m on member-innermost vectors x1 (and x2);
+// nbase[n] is the offset of node n's row in them
 template <typename T, int DK, int MODE>
 __device__ __forceinline__ void ebe_element(const DevMesh& M, int MB, int m, long e, const void* __restrict__ Dv,
                                             const double* __restrict__ h, const double* __restrict__ mat,

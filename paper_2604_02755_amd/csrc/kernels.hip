@@ -10,9 +10,12 @@
 // covers 64 members of one element, so element data is wave-uniform and
 // member data is read in contiguous 256/512-byte rows.
 //
-// Element-by-element scatter is atomic-free: a launch covers one colour of
-// the element colouring (no two elements of a colour share a node), and the
-// host issues the colours in sequence on one stream.
+// Element forces reach the nodes without atomics and in a fixed order: a block
+// sums those of a cluster of consecutive elements in LDS and writes the cluster's
+// node rows, which a node pass sums (here for 64 to 256 member slots, in
+// slots.hip below that); above 256 slots a launch covers one colour of the
+// element colouring (no two elements of a colour share a node) and adds into the
+// nodal vector, the colours in sequence on one stream.
 #include <math.h>
 
 #include "device.hpp"
@@ -74,11 +77,6 @@ __global__ void k_neg_copy(const double* a, double* b, long n)
     long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
     if (i < n) b[i] = -a[i];
 }
-__global__ void k_cast32(const double* a, float* b, long n)
-{
-    long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (i < n) b[i] = (float)a[i];
-}
 __global__ void k_copy_i32(const int* a, int* b, int n)
 {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -102,10 +100,6 @@ void launch_fill32(hipStream_t s, float* p, float v, long n)
 void launch_neg_copy(hipStream_t s, const double* a, double* b, long n)
 {
     if (n > 0) hipLaunchKernelGGL(k_neg_copy, dim3(nblocks(n)), dim3(256), 0, s, a, b, n);
-}
-void launch_cast32(hipStream_t s, const double* a, float* b, long n)
-{
-    if (n > 0) hipLaunchKernelGGL(k_cast32, dim3(nblocks(n)), dim3(256), 0, s, a, b, n);
 }
 
 // ---------------------------------------------------------------------------
@@ -672,9 +666,10 @@ void launch_ebe32(hipStream_t s, const DevMesh& M, int MB, int nm, int e0, int e
 // element-mean D, h, the material rows and the FP32 block-Jacobi inverse once
 // per outer iteration for its inner CG; the FP64 PCG packs the FP64 D per
 // point, h, the material rows, its inverse and the CG vectors once per step.
-// The operator sums its element forces per element cluster into compact
-// cluster rows, which a gather sums per node into a compact result.  Partial sums keep the full [block][MB] layout (zero for members not
-// listed), so the per-member stage logic is the same.
+// The operator (slots.hip) sums its element forces per element cluster into compact
+// rows and takes p . A p on them, a partial sum of G lanes a block; the update
+// (k_rows_update) sums the rows per node and keeps the full [block][MB] layout of
+// its partial sums (zero for members not listed), so the stage logic is the same.
 // ---------------------------------------------------------------------------
 
 // rows of a member-innermost array, listed members only: compact row rc of G

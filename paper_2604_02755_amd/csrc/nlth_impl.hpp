@@ -30,10 +30,10 @@ constexpr int kBoundaryAtEnd = 4096;      // cluster blocks up to which the boun
 constexpr int kBoundaryApart = 28672;     // cluster blocks above which FP32 dashpot rows are a launch of their own
 constexpr int kClusterNodes = 48;         // most distinct nodes of an element cluster
 constexpr int kClusterElems = 16;         // most elements of an element cluster
-constexpr int kWideNodes = 240;           // the same of a wide cluster, which
-constexpr int kWideElems = 64;            // ensembles of up to
-constexpr uint16_t kOwnerRow = 0x8000;    // in cl_lptr: the row is its node's first
+constexpr int kWideNodes = 240;           // the same of a wide cluster, which ensembles
+constexpr int kWideElems = 64;            // of up to
 constexpr int kWideSlots = 8;             // member slots use
+constexpr uint16_t kOwnerRow = 0x8000;    // in cl_lptr: the row is its node's first
 constexpr int kLagBlocks = 512;           // most operator blocks of an iteration whose p update joins the next operator
 constexpr int kLagThreads = 128;          // threads of those blocks: what sums the beta stage with 1 and 2 slots
 // most partial sums that each block of the next kernel reads itself, and how many
@@ -75,7 +75,6 @@ struct PUpdate {
     StageIn sg;
 };
 
-
 // Per-member material of one layer, member-innermost: mat[(l*MAT_N + field)*MB + m]
 enum MatField { MAT_RHO = 0, MAT_G0, MAT_KB, MAT_VS, MAT_VP, MAT_GREF, MAT_HMAX, MAT_BETA, MAT_N };
 // the table of one member, passed to the allocation-free application's kernel by value
@@ -109,7 +108,7 @@ struct DevMesh {
     const int* cl_noff;     // [ncl+1] rows of the clusters' node lists
     const uint32_t* cl_lconn; // [ne*4] local nodes of each element, four 8-bit indices per word
     long cl_rows;           // rows of all clusters
-    int cl_max_elems, cl_max_nodes;      // of the clusters
+    int cl_max_elems;                    // of a cluster
     int cl_node_stride, cl_list_stride;  // of the tables of a cluster
     const int4* cl_head;      // [ncl] first element, first row, elements, rows
     const int* cl_nodes;      // [ncl][cl_node_stride] node of a row
@@ -221,8 +220,7 @@ void set_ebe_block(int bs);
 // blocks per CU of the cluster launches on this host thread
 void set_cluster_blocks(int b);
 // convergence tail: the CG of at most G (16 or 32) listed members on compact
-// rows (lane k = member tl[1 + k], tl[0] = the count); partial sums in the
-// full [block][MB] layout.  Mixed path: its inner FP32 solve; FP64 path: PCG.
+// rows (lane k = member tl[1 + k], tl[0] = the count).  Mixed path: its inner FP32 solve; FP64 path: PCG.
 void launch_tail_pack(hipStream_t s, const DevMesh& M, int MB, int G, int n_layers, const int* tl,
                       const uint32_t* D16, const double* h, const double* mat, const float* pinv32, uint32_t* cD,
                       double* ch, double* cmat, float* cpinv);
@@ -382,7 +380,6 @@ void launch_incident_velocity(hipStream_t s, int MB, int nm, int n_steps, const 
                               double* vI_all, double dt);
 void launch_pick_vI(hipStream_t s, int MB, int nm, int n_steps, const double* vI_all,
                     const int* member_step, double* vI_cur);
-void launch_cast32(hipStream_t s, const double* a, float* b, long n);
 void launch_response_spectra(hipStream_t s, const double* vel, int ns, int nt, double dt, const double* periods, int np,
                              double h, int kind, double* out);
 

@@ -82,12 +82,12 @@ extern "C" int nlth_apply_operator_noalloc(nlth_ctx* ctx, const nlth_mesh* mesh,
             throw Error{NLTH_EINVAL, "problem: Rayleigh band needs 0 < f_lo < f_hi"};
         const int ne = mesh->ne, nn = mesh->nn;
         const long n3 = 3L * nn;
-        // the scratch holds the operator's rows (at most ten per element); the
-        // capacity that the entry point states counts a material table, D, h, two
-        // nodal vectors and ten rows per element
-        const size_t o_rows = round256((size_t)nl * MAT_N * 8);
+        // the scratch holds the operator's rows, at most ten per element (2.6 on boxes)
+        // and one per boundary node; the capacity that the entry point states is larger,
+        // a material table, D, h, two nodal vectors and ten rows per element, and stays as
+        // callers know it
         const size_t ne_pad = ((size_t)ne + 63) / 64 * 64;
-        const size_t need = o_rows + round256(ne_pad * 84 * 8) + round256(ne_pad * 8) + 2 * round256((size_t)n3 * 8) +
+        const size_t need = round256((size_t)nl * MAT_N * 8) + round256(ne_pad * 84 * 8) + round256(ne_pad * 8) + 2 * round256((size_t)n3 * 8) +
                             round256(ne_pad * 30 * 8);
         if (need > kScratchBytes) {
             char buf[200];
@@ -125,7 +125,7 @@ extern "C" int nlth_apply_operator_noalloc(nlth_ctx* ctx, const nlth_mesh* mesh,
         NLTH_HIP(hipSetDevice(ctx->device));
         char* base = scratch_of(ctx->device);
         if (!base) throw Error{NLTH_EDEVICE, "scratch address not set up on this device"};
-        double* rows = (double*)(base + o_rows);
+        double* rows = (double*)base;
         hipStream_t s = ctx->stream;
         const DevMesh dm = mesh->dev_input();
         const double dc = which == NLTH_OP_A ? 2.0 / prob->dt : 0.0;

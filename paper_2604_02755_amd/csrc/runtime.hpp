@@ -71,11 +71,11 @@ struct Mesh {
     DevBuf conn, geo64, geo32, layer, bn_node, bn_ptr, bn_face, bn_loc, f_node, f_M, f_n, f_layer, f_kind, recv_d;
     DevBuf celem, bn_of;
     // element clusters with their row lists on the device: the regular ones
-    // (4 member slots and more) and the wide ones (1 and 2 slots)
+    // (more than kWideSlots member slots) and the wide ones (up to that)
     struct Clusters {
         int n = 0;
         long rows = 0;  // total rows of the clusters' node lists
-        int max_elems = 0, max_nodes = 0, node_stride = 0, list_stride = 0;
+        int max_elems = 0, node_stride = 0, list_stride = 0;
         DevBuf off, noff, lconn, nodes, head, lists, lptr, cn_ptr, cn_row;
     } cl, wide;
     // node numbers in input order (the allocation-free application): of the
