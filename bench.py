@@ -85,7 +85,7 @@ def step_roofline(value: float, n_outer: float, n_inner: float, n_springs: int, 
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("kernels.hip", "vec.hip"):
+    for f in ("kernels.hip", "vec.hip", "device.hpp", "nlth_impl.hpp"):
         with open(os.path.join(ROOT, "paper_2604_02755_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
