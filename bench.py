@@ -530,8 +530,10 @@ def main():
                     "kernel": ("nlth::k_ebe_cluster<float, %d, 0, %d> (inner operator: element forces summed per "
                                "cluster in LDS)" % ({0: 1, 1: 0, 2: 4}[prob.inner_dtype], cb))
                               if sp["members_padded"] >= 64 else
-                              "nlth::k_ebe<float, 1, 0, false, 1> (inner operator: element forces)",
-                    "timing": f"HIP events around each launch on the compute stream, profiled window of "
+                              "nlth::k_op_slots<float, %d, 0, ...> (inner operator: element forces summed per "
+                              "cluster in LDS, dashpot rows and p.Ap)" % {0: 1, 1: 0, 2: 4}[prob.inner_dtype],
+                    "timing": f"HIP events around each application on the compute stream (on large meshes of 64 "
+                              f"slots and more with the dashpot rows' own launch), profiled window of "
                               f"{args.profile_steps} steps after the timed steps (steps {n_total + 1}-"
                               f"{n_total + args.profile_steps})",
                     "launches": int(n_app), "avg_launch_us": round(ms / n_app * 1e3, 2),
