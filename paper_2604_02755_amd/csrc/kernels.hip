@@ -1796,38 +1796,51 @@ void launch_receivers(hipStream_t s, int nrecv, const int* recv, int MB, int nm,
 }
 
 // Incident velocity by the trapezoid rule from the incident acceleration (zero at
-// t = 0): one block per member, whose 64 threads of a component sum a run of
-// samples each, then run again from the sum of the runs before (a thread a
-// component, sample after sample: 379 us for 2,048 samples; this 12).
-constexpr int kVelRuns = 64;
-__global__ __launch_bounds__(3 * kVelRuns) void k_incident_velocity(int ns, const double* __restrict__ acc,
-                                                                   double* __restrict__ vI, double dt)
+// t = 0): one block per member, a wavefront a component, samples added one after
+// another (sums of runs of the record made a velocity depend on the record's
+// length).  Bound by that chain of FP64 additions: the lanes load the next 64 samples
+// while the terms of 64 are added in registers, from LDS and back (2,048 samples:
+// a load a step took 379 us, terms by lane reads 50; this 44).
+__global__ __launch_bounds__(192) void k_incident_velocity(int ns, const double* __restrict__ acc,
+                                                          double* __restrict__ vI, double dt)
 {
-    const int c = threadIdx.x / kVelRuns, run = threadIdx.x % kVelRuns, len = (ns + kVelRuns - 1) / kVelRuns;
-    const int n0 = min(run * len, ns), n1 = min(n0 + len, ns);
+    const int c = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const size_t base = (size_t)blockIdx.x * ns * 3 + c;
-    __shared__ double sums[3][kVelRuns];
-    double v = 0.0;
-    for (int pass = 0; pass < 2; ++pass) {
-        double ap = n0 > 0 ? acc[base + (size_t)(n0 - 1) * 3] : 0.0;
-#pragma unroll 8
-        for (int n = n0; n < n1; ++n) {
-            const double an = acc[base + (size_t)n * 3];
-            v += 0.5 * dt * (ap + an);
-            ap = an;
-            if (pass) vI[base + (size_t)n * 3] = v;
+    __shared__ __align__(16) double tiles[3][64];
+    double* tile = tiles[c];  // of the wavefront
+    auto fence = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
+    double v = 0.0, ap, an;
+    auto load = [&](int n) {  // past the end any sample: its sum is not stored
+        n = min(n, ns - 1);
+        ap = acc[base + (size_t)max(n - 1, 0) * 3];
+        an = acc[base + (size_t)n * 3];
+    };
+    load(lane);
+    for (int n = lane; n - lane < ns; n += 64) {
+        tile[lane] = (n > 0 ? ap : 0.0) + an;
+        load(n + 64);
+        fence();
+        double x[64];
+#pragma unroll
+        for (int k = 0; k < 64; ++k) x[k] = tile[k];
+#pragma unroll
+        for (int k = 0; k < 64; ++k) {
+            v += 0.5 * dt * x[k];
+            x[k] = v;
         }
-        if (pass) break;
-        sums[c][run] = v;
-        __syncthreads();
-        v = 0.0;
-        for (int r = 0; r < run; ++r) v += sums[c][r];
+        fence();
+        if (lane == 0)
+#pragma unroll
+            for (int k = 0; k < 64; ++k) tile[k] = x[k];
+        fence();
+        if (n < ns) vI[base + (size_t)n * 3] = tile[lane];
+        fence();
     }
 }
 
 void launch_incident_velocity(hipStream_t s, int, int nm, int ns, const double* acc, double* vI, double dt)
 {
-    hipLaunchKernelGGL(k_incident_velocity, dim3(nm), dim3(3 * kVelRuns), 0, s, ns, acc, vI, dt);
+    hipLaunchKernelGGL(k_incident_velocity, dim3(nm), dim3(192), 0, s, ns, acc, vI, dt);
 }
 
 // incident velocity of each member at its current step, member-innermost [3][MB]

@@ -334,7 +334,8 @@ __global__ __launch_bounds__(512) void k_op_p(DevMesh M, int MB, int nm, int ncb
 // launch that put it in memory first took 3 us of a call's 30 on 720 elements).
 // The block's D rows are staged in LDS, where `out` comes after them: a lane
 // reading its own row of 672 bytes fetched every line sixteen times past an L1 that
-// does not hold 64 rows (58,080 elements: 36.5 us, staged 25.0).
+// does not hold 64 rows (58,080 elements, D in the last-level cache: 36.5 us, staged
+// 25.0).
 template <int MODE>
 __global__ __launch_bounds__(512) void k_op_input64(DevMesh M, int ncb, int nbb, const double* __restrict__ D,
                                                    const int* __restrict__ order, const double* __restrict__ h,
