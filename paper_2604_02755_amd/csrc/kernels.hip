@@ -1701,7 +1701,9 @@ void launch_law(hipStream_t s, const DevMesh& M, int MB, int nm, int e0, int ec,
     long n = (long)ec * MB * 4;
     if (n <= 0) return;
     const bool small = ns <= kLawLdsSprings, mem = depth > 1;
-    const int parts = n <= kLawManyParts ? 8 : (n <= kLawPartLanes ? 4 : 1);
+    // by the whole mesh, not the chunk: a paged run sums the springs as the resident one
+    const long all = (long)M.ne * MB * 4;
+    const int parts = all <= kLawManyParts ? 8 : (all <= kLawPartLanes ? 4 : 1);
 #define NLTH_LAW(LDS_NS, MEM, PARTS)                                                                                 \
     law_dispatch<LDS_NS, MEM, PARTS>(s, n, M, MB, nm, e0, ec, ecp, mat, nonlinear, ns, depth, dirs, w, du, theta, D, \
                                      D32, D16, h, stepping, d16_mean)
