@@ -352,7 +352,9 @@ int nlth_release(nlth_ctx* ctx, uint64_t ticket);
  * seconds) the oscillator x'' + 2 h w x' + w^2 x = -a_g, w = 2 pi / T, starts
  * at rest and is advanced exactly step by step; out: [n_series][n_periods],
  * kind NLTH_SPEC_VELOCITY max_n |x'_n| (relative velocity) or
- * NLTH_SPEC_PSEUDO_VELOCITY w max_n |x_n|.  Host pointers, caller-owned,
+ * NLTH_SPEC_PSEUDO_VELOCITY w max_n |x_n|.  Records are cut into more parts the
+ * fewer records and periods a call has, which can change a spectrum's last
+ * bits.  Host pointers, caller-owned,
  * read or written during the call (synchronous).  The context keeps the
  * call's device workspace (records, periods and spectra, up to 64 MiB) for the
  * next one where hbm_budget holds it, and gives it back when it creates a mesh
